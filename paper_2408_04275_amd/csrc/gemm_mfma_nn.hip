@@ -1,0 +1,8 @@
+// Input-gradient products of the bf16 GEMM in the tile shapes smaller than 256 x 256.
+#include "gemm_mfma.h"
+
+namespace mmt {
+namespace gemm_detail {
+hipError_t launch_nn(int shape, const GemmP &p, hipStream_t st) { return launch_tile_shape<true, false>(shape, p, st); }
+}  // namespace gemm_detail
+}  // namespace mmt

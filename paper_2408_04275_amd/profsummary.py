@@ -19,7 +19,7 @@ import sys
 
 def short_name(name: str) -> str:
     name = re.sub(r"^void\s+", "", name.strip())
-    name = name.replace("(anonymous namespace)::", "").replace("mmt::", "")
+    name = name.replace("(anonymous namespace)::", "").replace("mmt::", "").replace("gemm_detail::", "")
     name = re.sub(r"\(.*$", "", name)                       # drop the parameter list
     return name.strip()
 
