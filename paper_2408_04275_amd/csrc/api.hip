@@ -177,12 +177,11 @@ void carve_bwd(Bump &b, const Dims &D, size_t T, BwdWs &w) {
 hipError_t gemm(int dtype, const GemmArgs &g, hipStream_t st);
 
 
-// bf16 storage runs on the matrix cores; fp32 storage on the vector ALUs
 hipError_t attn_fwd(int dtype, const AttnArgs &a, hipStream_t st) {
-    return dtype == DT_BF16 ? attn_mfma_fwd(a, st) : attn_simple_fwd(dtype, a, st);
+    return dtype == DT_BF16 ? attn_mfma_fwd(a, st) : attn_f32_supported(a) ? attn_f32_fwd(a, st) : attn_simple_fwd(a, st);
 }
 hipError_t attn_bwd(int dtype, const AttnArgs &a, hipStream_t st) {
-    return dtype == DT_BF16 ? attn_mfma_bwd(a, st) : attn_simple_bwd(dtype, a, st);
+    return dtype == DT_BF16 ? attn_mfma_bwd(a, st) : attn_f32_supported(a) ? attn_f32_bwd(a, st) : attn_simple_bwd(a, st);
 }
 
 GemmArgs f32out(GemmArgs g, bool on) { g.c_f32 = on; return g; }
@@ -263,6 +262,7 @@ hipError_t gemm(int dtype, const GemmArgs &g, hipStream_t st) {
         probed.clock_probe = g_gemm_clock;
         return gemm_mfma(probed, st);
     }
+    if (dtype == DT_F32 && gemm_f32_supported(g)) return gemm_f32(g, st);
     return gemm_simple(dtype, g, st);
 }
 
@@ -438,7 +438,8 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     if (G.w_o) HIP_TRY(wgrad(D.dtype, splittable(f32out(mk(GEMM_TN, D.H, D.nq, T, w.d_y1, D.H, c.o, D.nq, G.w_o, D.nq, nullptr, nullptr, accum), g32), w.split_ws, w.split_bytes), later, st));
     AttnArgs a = mk_attn(D, batch, c);
     a.d_o = w.d_o; a.d_qkv = w.d_qkv; a.Dsum = w.Dsum;
-    const bool fused_unrotate = !enc && D.dtype == DT_BF16 && (D.d == 64 || D.d == 128);       // the matrix-core kernels rotate dQ, dK back themselves
+    // the matrix-core kernels rotate dQ, dK back themselves
+    const bool fused_unrotate = !enc && (D.dtype == DT_BF16 ? D.d == 64 || D.d == 128 : attn_f32_supported(a));
     if (fused_unrotate) a.rope_cs = c.rope_cs;
     {
         ProfScope ps(MMTRAIN_PROF_ATTN_BWD, st);

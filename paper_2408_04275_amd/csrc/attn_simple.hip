@@ -1,4 +1,4 @@
-// Segment-masked attention on the vector ALUs, fp32 arithmetic: the fp32 storage path.
+// Segment-masked attention on the vector ALUs, fp32 storage: packs beyond the matrix-instruction kernels' 32-bit byte offsets.
 // One wavefront owns one (token, head); the head dimension is spread over the 64 lanes and
 // keys are visited one by one with an online softmax.  Masking is by construction: the key
 // loop runs over exactly the allowed keys of the token's own segment.
@@ -134,23 +134,24 @@ __global__ __launch_bounds__(256) void attn_simple_dkv_kernel(AttnArgs a) {
     }
 }
 
-hipError_t attn_simple_fwd(int dtype, const AttnArgs &a, hipStream_t st) {
+hipError_t attn_simple_fwd(const AttnArgs &a, hipStream_t st) {
     if (a.T == 0) return hipSuccess;
     const int grid = ceil_div((long)a.T * a.nh, 4);
-#define L(TT, EE) attn_simple_fwd_kernel<TT, EE><<<grid, 256, 0, st>>>(a)
-    if (dtype == DT_F32) { if (a.d == 64) L(float, 1); else L(float, 2); }
-    else { if (a.d == 64) L(bf16_t, 1); else L(bf16_t, 2); }
-#undef L
+    if (a.d == 64) attn_simple_fwd_kernel<float, 1><<<grid, 256, 0, st>>>(a);
+    else attn_simple_fwd_kernel<float, 2><<<grid, 256, 0, st>>>(a);
     return hipGetLastError();
 }
 
-hipError_t attn_simple_bwd(int dtype, const AttnArgs &a, hipStream_t st) {
+hipError_t attn_simple_bwd(const AttnArgs &a, hipStream_t st) {
     if (a.T == 0) return hipSuccess;
     const int gq = ceil_div((long)a.T * a.nh, 4), gk = ceil_div((long)a.T * a.nkv, 4);
-#define L(TT, EE) attn_simple_dq_kernel<TT, EE><<<gq, 256, 0, st>>>(a); attn_simple_dkv_kernel<TT, EE><<<gk, 256, 0, st>>>(a)
-    if (dtype == DT_F32) { if (a.d == 64) { L(float, 1); } else { L(float, 2); } }
-    else { if (a.d == 64) { L(bf16_t, 1); } else { L(bf16_t, 2); } }
-#undef L
+    if (a.d == 64) {
+        attn_simple_dq_kernel<float, 1><<<gq, 256, 0, st>>>(a);
+        attn_simple_dkv_kernel<float, 1><<<gk, 256, 0, st>>>(a);
+    } else {
+        attn_simple_dq_kernel<float, 2><<<gq, 256, 0, st>>>(a);
+        attn_simple_dkv_kernel<float, 2><<<gk, 256, 0, st>>>(a);
+    }
     return hipGetLastError();
 }
 

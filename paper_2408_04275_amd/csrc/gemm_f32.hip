@@ -1,0 +1,211 @@
+// fp32 GEMM on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 products, fp32 accumulation) for the fp32 storage path.
+//
+//   C[M,N] (+)= opA(A) . opB(B) (+ bias[N]) (+ residual[M,N])
+//
+// The fp32 layers are small (512 x 768 x 256), so what bounds a product is latency and how many compute units take part, not
+// the matrix cores' rate.  A workgroup owns a 32 x 32 tile of C and its eight wavefronts take every eighth 16-deep block of K
+// each: eight times the loads in flight and an eighth of the serial chain (four wavefronts with twice the look-ahead take 0 to
+// 15 % longer).  Large products run in 64 x 64 tiles with four wavefronts.  The partial tiles are added through LDS in a fixed
+// order.  512 x 768 x 256: 47.6 -> 7.3 us against the vector-ALU kernel; 512 x 256 x 1376: 257 -> 11.9 us.
+//
+// No operand goes through LDS: a fragment of the MFMA is 16 rows x 4 k, lane l holding row l & 15, k = l >> 4, and which k of
+// a block an MFMA takes is free as long as both operands agree.  MFMA j of a block takes k = 4 (l >> 4) + j:
+//   * K-contiguous operand: a lane's four k of a row are 16 contiguous bytes, one load for the block's four MFMAs;
+//   * K-strided operand: a lane loads 2 or 4 neighbouring rows of one k, one load per MFMA; fragment f then holds the rows
+//     (fragments) x (l & 15) + f, which only the epilogue has to know.
+// Rows and k outside the matrix read as zero (the buffer descriptor's bounds check).
+#include "kernels.h"
+
+namespace mmt {
+
+namespace {
+
+struct GemmF32 {
+    int M, N, K;
+    const float *A; int lda;
+    const float *B; int ldb;
+    float *C; int ldc;
+    const float *bias, *residual;
+    int accumulate;
+};
+
+constexpr uint32_t OOB = 0xfffffff0u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)(uint32_t)bytes, 0x00020000);
+}
+
+// One operand's fragments of a 16-deep K block: v[f][j] = fragment f's element for MFMA j.
+template <int TB, bool KC>
+struct Operand {
+    __amdgpu_buffer_rsrc_t rs;
+    uint32_t off[KC ? TB : 4], step;
+    int kq, K;
+    __device__ __forceinline__ void init(const float *X, int ld, int row0, int nrows, int K_) {
+        const int r = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
+        K = K_;
+        kq = 4 * q;
+        if constexpr (KC) {
+            rs = rsrc(X, ((size_t)(nrows - 1) * ld + K_) * 4);
+            step = 64;
+#pragma unroll
+            for (int f = 0; f < TB; ++f) off[f] = (uint32_t)(((size_t)(row0 + 16 * f + r) * ld + kq) * 4);
+        } else {
+            rs = rsrc(X, ((size_t)(K_ - 1) * ld + nrows) * 4);
+            step = (uint32_t)ld * 64u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) off[j] = (uint32_t)(((size_t)(kq + j) * ld + row0 + TB * r) * 4);
+        }
+    }
+    __device__ __forceinline__ void load(int kb, float (&v)[TB][4]) const {
+        const uint32_t base = (uint32_t)kb * step;
+        if constexpr (KC) {
+#pragma unroll
+            for (int f = 0; f < TB; ++f) {
+                const uint32_t o = kb * 16 + kq < K ? off[f] + base : OOB;
+                const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)o, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[f][j] = __uint_as_float(w[j]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t o = kb * 16 + kq + j < K ? off[j] + base : OOB;
+                if constexpr (TB == 4) {
+                    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)o, 0, 0);
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) v[f][j] = __uint_as_float(w[f]);
+                } else {
+                    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)o, 0, 0);
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) v[f][j] = __uint_as_float(w[f]);
+                }
+            }
+        }
+    }
+};
+
+// AHEAD: K blocks of a wavefront in flight while one is multiplied
+template <int TB, int NW, int AHEAD, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmF32 p) {
+    constexpr int TILE = 16 * TB, PITCH = TILE + 4;
+    __shared__ __attribute__((aligned(16))) float red[NW / 2][TILE][PITCH];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, q = lane >> 4;
+    const int n0 = blockIdx.x * TILE, m0 = blockIdx.y * TILE;
+    Operand<TB, A_KC> la;
+    Operand<TB, B_KC> lb;
+    la.init(p.A, p.lda, m0, p.M, p.K);
+    lb.init(p.B, p.ldb, n0, p.N, p.K);
+
+    f32x4 acc[TB][TB];
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // blocks wave, wave + NW, ... of K; those beyond the end read as zero
+    const int nkb = (p.K + 15) / 16;
+    float a[AHEAD][TB][4], b[AHEAD][TB][4];
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) { la.load(wave + NW * s, a[s]); lb.load(wave + NW * s, b[s]); }
+    for (int kb = wave; kb < nkb; kb += NW * AHEAD) {
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) {
+            // operands swapped: a lane holds four neighbouring columns of one row of C
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int fa = 0; fa < TB; ++fa)
+#pragma unroll
+                    for (int fb = 0; fb < TB; ++fb)
+                        acc[fa][fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[s][fb][j], a[s][fa][j], acc[fa][fb], 0, 0, 0);
+            la.load(kb + NW * (s + AHEAD), a[s]);
+            lb.load(kb + NW * (s + AHEAD), b[s]);
+        }
+    }
+
+    // sum of the wavefronts' partial tiles: the upper half is added to the lower until two are left, those in the epilogue
+    auto row_of = [&](int fa) { return A_KC ? 16 * fa + r : TB * r + fa; };
+    auto put = [&](float (&t)[TILE][PITCH]) {
+#pragma unroll
+        for (int fa = 0; fa < TB; ++fa)
+#pragma unroll
+            for (int fb = 0; fb < TB; ++fb) {
+                if constexpr (B_KC) *reinterpret_cast<f32x4 *>(&t[row_of(fa)][16 * fb + 4 * q]) = acc[fa][fb];
+                else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t[row_of(fa)][TB * (4 * q + e) + fb] = acc[fa][fb][e];
+                }
+            }
+    };
+    if (wave >= NW / 2) put(red[wave - NW / 2]);
+    __syncthreads();
+#pragma unroll
+    for (int left = NW / 2; left >= 2; left /= 2) {
+        if (wave < left) {
+            const int from = left == NW / 2 ? wave : wave + left;
+#pragma unroll
+            for (int fa = 0; fa < TB; ++fa)
+#pragma unroll
+                for (int fb = 0; fb < TB; ++fb) {
+                    if constexpr (B_KC) acc[fa][fb] += *reinterpret_cast<const f32x4 *>(&red[from][row_of(fa)][16 * fb + 4 * q]);
+                    else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[fa][fb][e] += red[from][row_of(fa)][TB * (4 * q + e) + fb];
+                    }
+                }
+            if (left == 2 || wave >= left / 2) put(red[wave]);      // slot `wave` has been read by this wavefront alone
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < (TILE * TILE + 256 * NW - 1) / (256 * NW); ++i) {
+        const int c = threadIdx.x + 64 * NW * i, row = c / (TILE / 4), col = c % (TILE / 4) * 4;
+        const int m = m0 + row, n = n0 + col;
+        if (row >= TILE || m >= p.M || n >= p.N) continue;        // N is a multiple of 4
+        f32x4 v = *reinterpret_cast<const f32x4 *>(&red[0][row][col]) + *reinterpret_cast<const f32x4 *>(&red[1][row][col]);
+        const size_t o = (size_t)m * p.ldc + n;
+        if (p.bias) v += *reinterpret_cast<const f32x4 *>(p.bias + n);
+        if (p.residual) v += *reinterpret_cast<const f32x4 *>(p.residual + o);
+        if (p.accumulate) v += *reinterpret_cast<const f32x4 *>(p.C + o);
+        *reinterpret_cast<f32x4 *>(p.C + o) = v;
+    }
+}
+
+template <bool A_KC, bool B_KC>
+hipError_t launch(const GemmF32 &p, hipStream_t st) {
+    // 64 x 64 tiles read half the operand bytes; they pay once there are enough of them (2048^3: 233 -> 150 us; 1024 x 2560 x
+    // 512, 640 tiles: 43.5 -> 37.9; at 264 tiles both take 20 us; 512 x 256 x 688, 32 tiles: 7.0 -> 19.2)
+    if ((long)ceil_div(p.M, 64) * ceil_div(p.N, 64) >= 384)
+        gemm_f32_kernel<4, 4, 2, A_KC, B_KC><<<dim3(ceil_div(p.N, 64), ceil_div(p.M, 64)), 256, 0, st>>>(p);
+    else
+        gemm_f32_kernel<2, 8, 2, A_KC, B_KC><<<dim3(ceil_div(p.N, 32), ceil_div(p.M, 32)), 512, 0, st>>>(p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// 16-byte accesses throughout: leading dimensions, N, and whatever index is contiguous in an operand multiples of 4, all
+// pointers 16-byte aligned, 32-bit byte offsets
+bool gemm_f32_supported(const GemmArgs &g) {
+    if (g.M <= 0 || g.N <= 0 || g.K <= 0) return false;
+    if ((g.lda | g.ldb | g.ldc | g.N) & 3) return false;
+    const bool a_kc = g.layout != GEMM_TN, b_kc = g.layout == GEMM_NT;
+    if ((a_kc || b_kc) && (g.K & 3)) return false;
+    if (!a_kc && (g.M & 3)) return false;
+    const size_t rows_a = a_kc ? g.M : g.K, rows_b = b_kc ? g.N : g.K;
+    if ((rows_a + 256) * (size_t)g.lda * 4 >= 0xfff00000ull || (rows_b + 256) * (size_t)g.ldb * 4 >= 0xfff00000ull) return false;
+    const uintptr_t bits = (uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.residual;
+    return (bits & 15) == 0 && ceil_div(g.M, 32) <= 65535;
+}
+
+hipError_t gemm_f32(const GemmArgs &g, hipStream_t st) {
+    const GemmF32 p = {g.M, g.N, g.K, (const float *)g.A, g.lda, (const float *)g.B, g.ldb, (float *)g.C, g.ldc,
+                       (const float *)g.bias, (const float *)g.residual, g.accumulate ? 1 : 0};
+    switch (g.layout) {
+        case GEMM_NT: return launch<true, true>(p, st);
+        case GEMM_NN: return launch<true, false>(p, st);
+        default: return launch<false, false>(p, st);
+    }
+}
+
+}  // namespace mmt

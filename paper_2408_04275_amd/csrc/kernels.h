@@ -27,8 +27,11 @@ struct GemmArgs {
     unsigned long long *clock_probe = nullptr;
 };
 
-// gemm_simple.hip: any dtype, any shape, LDS-tiled FMA kernel (the fp32 path).
+// gemm_simple.hip: any dtype, any shape, LDS-tiled FMA kernel (what the matrix-core kernels do not take).
 hipError_t gemm_simple(int dtype, const GemmArgs &g, hipStream_t st);
+// gemm_f32.hip: fp32 storage on the fp32 matrix instruction.  `supported` checks alignment requirements.
+bool gemm_f32_supported(const GemmArgs &g);
+hipError_t gemm_f32(const GemmArgs &g, hipStream_t st);
 // gemm_mfma.hip: bf16 MFMA kernel.  `supported` checks alignment requirements.
 bool gemm_mfma_supported(const GemmArgs &g);
 hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st);
@@ -76,9 +79,13 @@ int pipeline_1f1b(const double *fwd, const double *bwd, int p, int l, const int3
                   double *intervals /* [l] or null */);
 int inter_reorder(const double *fwd, const double *bwd, int p, int l, const double *sizes /* [l] or null */, int32_t *order,
                   double *intervals_seen /* [l] or null */, int32_t *n_seen /* or null */);
-// attn_simple.hip: fp32 arithmetic on the vector ALUs, any storage dtype
-hipError_t attn_simple_fwd(int dtype, const AttnArgs &a, hipStream_t st);
-hipError_t attn_simple_bwd(int dtype, const AttnArgs &a, hipStream_t st);
+// attn_simple.hip: fp32 storage on the vector ALUs, any size
+hipError_t attn_simple_fwd(const AttnArgs &a, hipStream_t st);
+hipError_t attn_simple_bwd(const AttnArgs &a, hipStream_t st);
+// attn_f32.hip: fp32 storage on the fp32 matrix instruction (backward: dQ and dK are rotated back if rope_cs is given)
+bool attn_f32_supported(const AttnArgs &a);
+hipError_t attn_f32_fwd(const AttnArgs &a, hipStream_t st);
+hipError_t attn_f32_bwd(const AttnArgs &a, hipStream_t st);
 // attn_mfma.hip: bf16 storage, matrix cores
 hipError_t attn_mfma_fwd(const AttnArgs &a, hipStream_t st);
 hipError_t attn_mfma_bwd(const AttnArgs &a, hipStream_t st);
