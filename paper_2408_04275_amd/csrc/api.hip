@@ -134,9 +134,9 @@ void carve_ctx(Bump &b, const Dims &D, size_t T, Ctx &c) {
     c.m = b.take_elems(T * D.F, D.dtype);
 }
 
-// Scratch that lets an M x N gradient GEMM be cut along K in both ways the bf16 kernel knows: few output tiles
-// (gemm_mfma_splits: up to 256 / tiles products of M x N, 32 at most), or a partly filled last round of tiles
-// (gemm_mfma_tail_splits: never more than 256 blocks of 256 x 256).
+// What mmtrain_gemm_workspace_bytes answers: the scratch of a partly filled last round cut along K (gemm_mfma_tail_splits: never
+// more than 256 blocks of 256 x 256), and for few output tiles, which smaller tile shapes serve without scratch, the size
+// callers have been given for a cut of theirs.
 size_t gemm_scratch_bytes(size_t M, size_t N) {
     const size_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
     if (tiles > 128) return tiles % 256 && tiles % 256 <= 128 ? size_t(256) * 256 * 256 * 4 : 0;

@@ -20,7 +20,7 @@
 //   * operands whose contraction index is the row index in memory (B of NN, A and B of TN) are kept as
 //     tile[64 k][rows] (512 bytes per k for 256 rows) and the fragments are formed by the transposing LDS read
 //     ds_read_b64_tr_b16; 32-byte chunks are XOR-swizzled with k & 3 against bank conflicts.
-// Out-of-range rows and k are zero-filled by the buffer descriptor's bounds check.
+// k out of range is zero-filled by the buffer descriptor's bounds check; rows out of range meet only outputs that are not stored.
 //
 // Epilogue.  Accumulators go through a per-wavefront fp32 LDS staging area so that C,
 // residual and bias are accessed as full 16-byte row-major vectors; bias / residual / previous
@@ -69,12 +69,11 @@ struct GemmP {
     int c_f32;                 // C holds fp32 (weight gradients into fp32 main-gradient buffers)
     int tiles_m, tiles_n;
     // split K (fp32 output only): the K range is cut into `splits` chunks of k_chunk (a multiple of 64); chunk s of
-    // every tile is a work item of its own and writes the partial product to C + s * split_stride (fp32 elements)
+    // every tile is a work item of its own
     int splits, k_chunk;
-    long split_stride;
-    // A launch covers tiles [tile_begin, tile_begin + tile_count) of the tile order.  With `compact` (fp32 output)
-    // the partial product of chunk s of the launch's tile j is a dense 256 x 256 block at
-    // C + (s * tile_count + j) * 65536 instead of a window of an M x N matrix.
+    // A launch covers tiles [tile_begin, tile_begin + tile_count) of the tile order.  With `compact` (fp32 output, 256 x 256
+    // tiles) the partial product of chunk s of the launch's tile j is a dense block at C + (s * tile_count + j) * 65536
+    // instead of a window of an M x N matrix.
     int tile_begin, tile_count, compact;
     unsigned long long *clock_probe;       // see GemmArgs
 };
@@ -154,7 +153,6 @@ struct LoaderKC {
     int kc0, K, slab0;            // unit column (elements) this lane fetches; first slab's LDS offset
     // Rows beyond the matrix read as zero on the fast path too: their offset lies at or beyond the descriptor's size
     // whatever k is added.
-    static constexpr bool full = true;
     __device__ __forceinline__ void init(const bf16_t *X, int ld, int row0, int nrows, int K_) {
         rs = make_rsrc(X, ((size_t)(nrows - 1) * ld + K_) * 2);
         const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -198,43 +196,37 @@ struct LoaderKC {
 typedef __attribute__((ext_vector_type(4))) short shortx4;
 typedef __attribute__((ext_vector_type(8))) short shortx8;
 typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
+// Columns beyond the matrix need no mask: what the copy finds there (the next k-row, or zero beyond the end) meets only
+// outputs that are not stored.
 template <int NB>                                  // 32 NB rows; NB = 2, 4 or 8
 struct LoaderKS {
     static_assert(NB == 2 || NB == 4 || NB == 8, "a copy covers whole k-rows");
     static constexpr int ITEM_LDS = 1024, KPI = 16 / NB;      // LDS bytes and k-rows per item
     __amdgpu_buffer_rsrc_t rs;
     rawx4 rsv;
-    uint32_t vo[NB];                 // fast path: this lane's byte offset for item i, without k0
-    __device__ __forceinline__ uint32_t step_soff(int k0) const { return (uint32_t)k0 * k_step; }
-    uint32_t off_e, off_o, k_step;   // byte offset of this lane's 16 bytes for items 0 and 1 (k0 = 0); bytes per k
+    uint32_t vo[NB], k_step;         // this lane's byte offset for item i, without k0; bytes per k
     int slab0;
-    bool full;                       // all rows of the tile exist
+    __device__ __forceinline__ uint32_t step_soff(int k0) const { return (uint32_t)k0 * k_step; }
     __device__ __forceinline__ void init(const bf16_t *X, int ld, int row0, int nrows, int K_) {
         rs = make_rsrc(X, ((size_t)(K_ - 1) * ld + nrows) * 2);
         const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
         const int pos = lane & (4 * NB - 1), kh = lane / (4 * NB);          // 16-byte position in the k-row; which of the item's k-rows
-        const int n_e = (((pos >> 1) ^ (kh & 3)) << 4) + (pos & 1) * 8;
-        const int n_o = (((pos >> 1) ^ ((KPI + kh) & 3)) << 4) + (pos & 1) * 8;
         k_step = (uint32_t)ld * 2u;
-        off_e = row0 + n_e < nrows ? (uint32_t)(((size_t)(w * 16 + kh) * ld + row0 + n_e) * 2) : OOB;
-        off_o = row0 + n_o < nrows ? (uint32_t)(((size_t)(w * 16 + KPI + kh) * ld + row0 + n_o) * 2) : OOB;
-        full = row0 + 32 * NB <= nrows;
         slab0 = __builtin_amdgcn_readfirstlane(w * NB * 1024);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) { vo[i] = ((i & 1) ? off_o : off_e) + (uint32_t)(KPI * (i & ~1)) * k_step; asm volatile("" : "+v"(vo[i])); }
+        for (int i = 0; i < NB; ++i) {
+            const int k = KPI * i + kh, n = (((pos >> 1) ^ (k & 3)) << 4) + (pos & 1) * 8;
+            vo[i] = (uint32_t)(((size_t)(w * 16 + k) * ld + row0 + n) * 2);
+            asm volatile("" : "+v"(vo[i]));
+        }
         rsv = raw_rsrc(X, ((size_t)(K_ - 1) * ld + nrows) * 2);
     }
-    // FAST: as for the K-contiguous loader, and all rows of the tile exist.
+    // k beyond the matrix reads as zero either way; FAST: as for the K-contiguous loader
     template <bool FAST>
     __device__ __forceinline__ void copy_one(uint8_t *tile, int k0, int i) const {
-        const uint32_t base = (i & 1) ? off_o : off_e;
         lds_void *dst = (lds_void *)(tile + slab0 + i * ITEM_LDS);
-        if (FAST) {
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, (int)vo[i], __builtin_amdgcn_readfirstlane(k0 * (int)k_step), 0, 0);
-        } else {
-            const uint32_t off = base == OOB ? OOB : base + (uint32_t)(k0 + KPI * (i & ~1)) * k_step;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, (int)off, 0, 0, 0);
-        }
+        if (FAST) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, (int)vo[i], __builtin_amdgcn_readfirstlane(k0 * (int)k_step), 0, 0);
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, (int)(vo[i] + (uint32_t)k0 * k_step), 0, 0, 0);
     }
     template <bool FAST>
     __device__ __forceinline__ void copy_all(uint8_t *tile, int k0) const {
@@ -470,8 +462,7 @@ void gemm_mfma_kernel(const ARG arg) {
     typedef std::make_integer_sequence<int, Sched::NG> Groups;
     typedef std::make_integer_sequence<int, Sched::NF> Frags;
     constexpr int B0 = (AHEAD + 1) * TS::A_BYTES;                  // LDS offset of the first B slot
-    const bool rows_ok = la.full && lb.full;
-    if (rows_ok && nk_whole >= AHEAD) {
+    if (nk_whole >= AHEAD) {
 #pragma unroll
         for (int j = 0; j < AHEAD; ++j) {
             la.template copy_all<true>(smem + j * TS::A_BYTES, j * BK);
@@ -490,7 +481,7 @@ void gemm_mfma_kernel(const ARG arg) {
 
     // LDS offsets of the slots of A(kt), A(kt+1), A(kt+AHEAD) and of B(kt), which is B(kt+AHEAD)'s as well, and B(kt+1)
     int oa = 0, oa1 = TS::A_BYTES, oad = AHEAD * TS::A_BYTES, ob = B0, ob1 = B0 + (AHEAD > 1 ? TS::B_BYTES : 0);
-    // COPY: 2 = tile kt + AHEAD is whole (fast copies), 1 = it may reach beyond the matrix, 0 = there is no such tile
+    // COPY: 2 = tile kt + AHEAD is whole (fast copies), 1 = it reaches beyond K, 0 = there is no such tile
     auto step = [&](auto COPY_, int kt) {
         constexpr int COPY = decltype(COPY_)::value;
         const int k2 = (kt + AHEAD) * BK;
@@ -557,7 +548,7 @@ void gemm_mfma_kernel(const ARG arg) {
         ob = ob1;
         ob1 = AHEAD == 2 ? lastb : ob1 + TS::B_BYTES == TS::RING_BYTES ? B0 : ob1 + TS::B_BYTES;
     };
-    const int nk_fast = rows_ok ? max(nk_whole - AHEAD, 0) : 0, nk_copy = max(nk - AHEAD, 0);
+    const int nk_fast = max(nk_whole - AHEAD, 0), nk_copy = max(nk - AHEAD, 0);
     int kt = 0;
     for (; kt < nk_fast; ++kt) step(std::integral_constant<int, 2>{}, kt);
     for (; kt < nk_copy; ++kt) step(std::integral_constant<int, 1>{}, kt);
@@ -646,7 +637,7 @@ void gemm_mfma_kernel(const ARG arg) {
                     // fp32 output (never together with bias or residual): previous contents are read here
                     float *cf = reinterpret_cast<float *>(p.C) +
                                 (p.compact ? ((size_t)(chunk * p.tile_count + tl) << 16) + (size_t)(gm - m0) * 256 + (gn - n0)
-                                           : (size_t)chunk * p.split_stride + off);
+                                           : off);
                     if (p.accumulate) {
                         const float4 c0 = *reinterpret_cast<const float4 *>(cf), c1 = *reinterpret_cast<const float4 *>(cf + 4);
                         v[0] += c0.x; v[1] += c0.y; v[2] += c0.z; v[3] += c0.w;
@@ -716,9 +707,9 @@ hipError_t launch(const GemmP &p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Tile shapes of the forward and input-gradient products, largest first (choose_tile in gemm_mfma.hip).  AHEAD is as deep as
-// LDS allows with the number of workgroups per compute unit that hides a small tile's barrier waits: a 64 x 64 step is 128
-// cycles of MFMA against several hundred of memory latency.
+// Tile shapes smaller than 256 x 256 (choose_tile in gemm_mfma.hip).  AHEAD is as deep as LDS allows with the number of
+// workgroups per compute unit that hides a small tile's barrier waits: a 64 x 64 step is 128 cycles of MFMA against several
+// hundred of memory latency.  The first three need a K-contiguous A.
 typedef TileShape<7, 8, 2> Tile224;
 typedef TileShape<6, 8, 2> Tile192;
 typedef TileShape<5, 8, 2> Tile160;
@@ -727,32 +718,34 @@ typedef TileShape<6, 4, 3> Tile192x128;
 typedef TileShape<4, 4, 4> Tile128;
 typedef TileShape<2, 4, 3> Tile64x128;
 typedef TileShape<2, 2, 4> Tile64;
-enum { N_TILE_SHAPES = 9 };
+enum { TILE_256, TILE_224, TILE_192, TILE_160, TILE_256x128, TILE_192x128, TILE_128, TILE_64x128, TILE_64, N_TILE_SHAPES };
 
+// the launch of a forward or input-gradient product in tiles of shape TS
 template <bool A_KC, bool B_KC, class TS>
 hipError_t launch_tile(GemmP p, hipStream_t st) {
     p.tiles_m = ceil_div(p.M, TS::BM); p.tiles_n = ceil_div(p.N, TS::BN);
     p.tile_count = p.tiles_m * p.tiles_n;
     return p.residual || p.accumulate ? launch<A_KC, B_KC, true, false, TS>(p, st) : launch<A_KC, B_KC, false, false, TS>(p, st);
 }
-// tile shape 1 .. N_TILE_SHAPES - 1 of the list above
 template <bool A_KC, bool B_KC>
 hipError_t launch_tile_shape(int shape, const GemmP &p, hipStream_t st) {
     switch (shape) {
-        case 1: return launch_tile<A_KC, B_KC, Tile224>(p, st);
-        case 2: return launch_tile<A_KC, B_KC, Tile192>(p, st);
-        case 3: return launch_tile<A_KC, B_KC, Tile160>(p, st);
-        case 4: return launch_tile<A_KC, B_KC, Tile256x128>(p, st);
-        case 5: return launch_tile<A_KC, B_KC, Tile192x128>(p, st);
-        case 6: return launch_tile<A_KC, B_KC, Tile128>(p, st);
-        case 7: return launch_tile<A_KC, B_KC, Tile64x128>(p, st);
-        case 8: return launch_tile<A_KC, B_KC, Tile64>(p, st);
+        case TILE_224: return launch_tile<A_KC, B_KC, Tile224>(p, st);
+        case TILE_192: return launch_tile<A_KC, B_KC, Tile192>(p, st);
+        case TILE_160: return launch_tile<A_KC, B_KC, Tile160>(p, st);
+        case TILE_256x128: return launch_tile<A_KC, B_KC, Tile256x128>(p, st);
+        case TILE_192x128: return launch_tile<A_KC, B_KC, Tile192x128>(p, st);
+        case TILE_128: return launch_tile<A_KC, B_KC, Tile128>(p, st);
+        case TILE_64x128: return launch_tile<A_KC, B_KC, Tile64x128>(p, st);
+        case TILE_64: return launch_tile<A_KC, B_KC, Tile64>(p, st);
         default: return hipErrorInvalidValue;
     }
 }
-// gemm_mfma_nt.hip / gemm_mfma_nn.hip
+// gemm_mfma_nt.hip / gemm_mfma_nn.hip: one product in one of the smaller shapes
 hipError_t launch_nt(int shape, const GemmP &p, hipStream_t st);
 hipError_t launch_nn(int shape, const GemmP &p, hipStream_t st);
+// gemm_mfma_tn.hip: up to MAX_GROUP weight gradients in one launch, all in the same tile shape (a single one: n = 1)
+hipError_t launch_tn(int shape, const GemmP *p, int n, hipStream_t st);
 
 }  // namespace gemm_detail
 }  // namespace mmt

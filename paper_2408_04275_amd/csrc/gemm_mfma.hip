@@ -1,5 +1,5 @@
-// Host side of the bf16 GEMM (kernel: gemm_mfma.h): which tile shape, K-cuts of gradients with few tiles or a partly
-// filled last round, and the weight-gradient kernels.
+// Host side of the bf16 GEMM (kernel: gemm_mfma.h): which tile shape, the K-cut of a gradient's partly filled last round, and
+// the 256 x 256 kernels.
 #include "gemm_mfma.h"
 #include <cmath>
 
@@ -9,43 +9,11 @@ using namespace gemm_detail;
 
 namespace {
 
-constexpr int TILE = 256;              // the tile every K-cut and every weight gradient works with
+constexpr int TILE = 256;              // the largest tile, and the one the K-cut works with
 
-template <bool HAS_ADD, bool OUT_F32>
-hipError_t launch_group_tn(const GemmGroup &g, hipStream_t st) {
-    static std::atomic<bool> configured{false};
-    auto kern = gemm_mfma_kernel<false, false, HAS_ADD, OUT_F32, Tile256, GemmGroup>;
-    hipError_t e = allow_lds(configured, reinterpret_cast<const void *>(kern), Tile256::SMEM);
-    if (e != hipSuccess) return e;
-    int n_cu = 0;
-    e = compute_units(n_cu);
-    if (e != hipSuccess) return e;
-    const int items = g.first[MAX_GROUP];
-    if (items <= 0) return hipSuccess;
-    kern<<<items < n_cu ? items : n_cu, 256, Tile256::SMEM, st>>>(g);
-    return hipGetLastError();
-}
-
-// C (+)= sum over the K chunks of the fp32 partial products; C is bf16 or fp32.  4 elements per thread.
-template <typename TC>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, int splits, long stride, int M, int N,
-                                                            TC *__restrict__ C, int ldc, int accumulate) {
-    const long idx = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (idx >= (long)M * N) return;
-    const int m = (int)(idx / N), n = (int)(idx % N);                 // N is a multiple of 8
-    f32x4 v = *reinterpret_cast<const f32x4 *>(part + idx);
-    for (int sp = 1; sp < splits; ++sp) v += *reinterpret_cast<const f32x4 *>(part + sp * stride + idx);
-    TC *c = C + (long)m * ldc + n;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        float r = v[e];
-        if (accumulate) r += Elem<TC>::load(c + e);
-        Elem<TC>::store(c + e, r);
-    }
-}
-
-// The same for the dense 256 x 256 partial blocks of the tiles [tile_begin, tile_begin + tile_count) of the tile
-// order: block (s * tile_count + j) belongs to chunk s of tile tile_begin + j.  64 workgroups per tile.
+// C (+)= sum over the K chunks of the fp32 partial products; C is bf16 or fp32.  4 elements per thread.  The partial products
+// are dense 256 x 256 blocks of the tiles [tile_begin, tile_begin + tile_count) of the tile order: block
+// (s * tile_count + j) belongs to chunk s of tile tile_begin + j.  64 workgroups per tile.
 template <typename TC>
 __global__ __launch_bounds__(256) void tail_reduce_kernel(const float *__restrict__ part, int splits, int tile_begin, int tile_count,
                                                           int tiles_m, int tiles_n, int M, int N, TC *__restrict__ C, int ldc,
@@ -79,7 +47,7 @@ GemmP params(const GemmArgs &g) {
     p.c_f32 = g.c_f32 ? 1 : 0;
     p.tiles_m = ceil_div(g.M, TILE);
     p.tiles_n = ceil_div(g.N, TILE);
-    p.splits = 1; p.k_chunk = g.K; p.split_stride = 0;
+    p.splits = 1; p.k_chunk = g.K;
     p.tile_begin = 0; p.tile_count = p.tiles_m * p.tiles_n; p.compact = 0;
     p.clock_probe = g.clock_probe;
     return p;
@@ -108,21 +76,6 @@ bool gemm_mfma_supported(const GemmArgs &g) {
     return (bits & 15) == 0;
 }
 
-// How many K chunks for a weight-gradient GEMM: enough to give every compute unit a work item when the
-// output has few tiles (a ViT-sized layer: 16 to 64 tiles against 256 compute units, K = all tokens of the
-// pack), chunks of at least 512, and the partial products must fit the scratch buffer.
-int gemm_mfma_splits(const GemmArgs &g) {
-    if (g.layout != GEMM_TN || !g.split_ws || g.bias || g.residual) return 1;
-    const long tiles = (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE);
-    if (tiles > 128) return 1;
-    long s = 256 / tiles;
-    s = s < g.K / 512 ? s : g.K / 512;
-    const long fit = (long)(g.split_ws_bytes / ((size_t)g.M * g.N * 4));
-    s = s < fit ? s : fit;
-    s = s < 32 ? s : 32;
-    return s >= 2 ? (int)s : 1;
-}
-
 // The last, partly filled round of a large GEMM.  With one workgroup per compute unit the tiles are worked off in
 // rounds of n_cu; when the last round holds at most half that many tiles, each of them is cut along K into
 // n_cu / tiles chunks so that the round takes a fraction of a full one.  Returns the number of chunks (1: do not
@@ -148,97 +101,85 @@ int gemm_mfma_tail_splits(const GemmArgs &g, int n_cu, int &tail_tiles) {
 }
 
 // Weight-gradient products whose outputs have few tiles (at most 128: a narrow layer), run together: every tile of every
-// product is one work item with the whole contraction, so nothing is cut along K, nothing goes through scratch and one
-// launch fills the chip that each product alone would leave mostly idle.
+// product is one work item with the whole contraction, so nothing goes through scratch and one launch fills the chip that
+// each product alone would leave mostly idle.
 bool gemm_mfma_few_tiles(const GemmArgs &g) {
     return g.layout == GEMM_TN && !g.bias && !g.residual && gemm_mfma_supported(g) &&
            (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE) <= 128;
 }
 
-hipError_t gemm_mfma_group(const GemmArgs *gs, int n, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    if (n > MAX_GROUP) return hipErrorInvalidValue;
-    GemmGroup grp = {};
-    int total = 0;
-    for (int i = 0; i < n; ++i) {
-        if (!gemm_mfma_few_tiles(gs[i]) || gs[i].accumulate != gs[0].accumulate || gs[i].c_f32 != gs[0].c_f32)
-            return hipErrorInvalidValue;
-        grp.p[i] = params(gs[i]);
-        grp.first[i] = total;
-        total += grp.p[i].tile_count;
-    }
-    for (int i = n; i <= MAX_GROUP; ++i) grp.first[i] = total;
-    for (int i = n; i < MAX_GROUP; ++i) grp.p[i] = grp.p[0];
-    grp.n = n;
-    if (gs[0].c_f32) return launch_group_tn<false, true>(grp, st);
-    return gs[0].accumulate ? launch_group_tn<true, false>(grp, st) : launch_group_tn<false, false>(grp, st);
-}
+// Tile shape of a product, or of a group of products of one layout and contraction.  The 256 x 256 tile does the most
+// arithmetic per byte fetched, but a product with few of them leaves most compute units idle (one image of 576 patches through
+// a 1024 x 1024 linear: 12 tiles) and one with a few more than a whole number of rounds runs a nearly empty last one.  The rule
+// is the time each shape needs: every compute unit works off ceil(tiles / compute units) tiles one after the other, a tile
+// costs a start and epilogue plus so much per 64-deep K step, and a step gets slower as the chip fills (clock, L2).  The
+// constants (us) are least-squares fits to 150 random shapes each for the forward and input-gradient products (250 - 12000
+// rows, widths 1024 - 22016; nine tile shapes) and for the weight gradients (512 - 5120 square to oblong, K = 250 - 12000; five
+// shapes, A and B both strided): the shape the rule picks is 0.03 % / 0.07 % slower than the best of them on average, 2 % / 7 %
+// at worst.  Against 256 x 256 throughout it measured 65.9 -> 13.5 us on the 576 x 1024 x 4096 forward product (64 x 64 tiles),
+// 22.6 -> 14.8 us on 2304 x 3072 x 1024 (256 x 128), 72.2 -> 65.6 us on 9536 x 1024 x 4096 (160 x 256), and 58.3 -> 25.8 us on
+// the 4096 x 1024 x 2880 weight gradient, which was cut along K before (128 x 128); products of whole rounds of large tiles stay
+// where they were.
+struct TileCost { int shape, bm, bn; double tile, step; };
+constexpr TileCost COST_ROWS[] = {                     // K-contiguous A
+    {TILE_256, 256, 256, 4.13, 0.958}, {TILE_224, 224, 256, 2.92, 0.866}, {TILE_192, 192, 256, 2.19, 0.778},
+    {TILE_160, 160, 256, 1.37, 0.694}, {TILE_256x128, 256, 128, 1.15, 0.575}, {TILE_192x128, 192, 128, 1.01, 0.462},
+    {TILE_128, 128, 128, 0.77, 0.348}, {TILE_64x128, 64, 128, 0.0, 0.223}, {TILE_64, 64, 64, 0.0, 0.142}};
+constexpr TileCost COST_WGRAD[] = {
+    {TILE_256, 256, 256, 4.05, 1.044}, {TILE_256x128, 256, 128, 2.10, 0.618}, {TILE_128, 128, 128, 1.49, 0.389},
+    {TILE_64x128, 64, 128, 0.10, 0.254}, {TILE_64, 64, 64, 0.0, 0.176}};
 
-// Tile shape of a forward or input-gradient product.  The 256 x 256 tile does the most arithmetic per byte fetched, but a
-// product with few of them leaves most compute units idle (one image of 576 patches through a 1024 x 1024 linear: 12 tiles)
-// and one with a few more than a whole number of rounds runs a nearly empty last one.  The rule is the time each shape
-// needs: every compute unit works off ceil(tiles / compute units) tiles one after the other, a tile costs a start and
-// epilogue plus so much per 64-deep K step, and a step gets slower as the chip fills (clock, L2).  The constants (us) are a
-// least-squares fit to 150 random shapes (250 - 12000 rows, widths 1024 - 22016, both layouts) timed in all nine tile shapes:
-// the shape the rule picks is 0.03 % slower than the best of the nine on average, 2 % at worst.  Against 256 x 256 throughout
-// it measured 65.9 -> 13.5 us on 576 x 1024 x 4096 (64 x 64 tiles), 22.6 -> 14.8 us on 2304 x 3072 x 1024 (256 x 128),
-// 72.2 -> 65.6 us on 9536 x 1024 x 4096 (160 x 256); products of whole rounds of large tiles stay where they were.
-struct TileCost { int bm, bn; double tile, step; };
-constexpr TileCost TILE_COST[N_TILE_SHAPES] = {
-    {256, 256, 4.13, 0.958}, {224, 256, 2.92, 0.866}, {192, 256, 2.19, 0.778}, {160, 256, 1.37, 0.694}, {256, 128, 1.15, 0.575},
-    {192, 128, 1.01, 0.462}, {128, 128, 0.77, 0.348}, {64, 128, 0.0, 0.223}, {64, 64, 0.0, 0.142}};
-
-int choose_tile(int M, int N, int K, int n_cu) {
-    int best = 0;
+template <int N>
+int choose_tile(const TileCost (&table)[N], double launch, double rounds_power, double load, const GemmArgs *gs, int n, int n_cu) {
+    int best = TILE_256;
     double best_us = 0.;
-    for (int s = 0; s < N_TILE_SHAPES; ++s) {
-        const TileCost &t = TILE_COST[s];
-        const long tiles = (long)ceil_div(M, t.bm) * ceil_div(N, t.bn);
+    for (const TileCost &t : table) {
+        long tiles = 0;
+        for (int i = 0; i < n; ++i) tiles += (long)ceil_div(gs[i].M, t.bm) * ceil_div(gs[i].N, t.bn);
         const double share = (double)tiles / n_cu, fill = share < 1. ? share * share : 1.;
-        const double us = 3.4 + pow(ceil(share), 1.042) * (t.tile + ceil_div(K, BK) * t.step * (1. + 0.276 * fill));
+        const double us = launch + pow(ceil(share), rounds_power) * (t.tile + ceil_div(gs[0].K, BK) * t.step * (1. + load * fill));
         // a smaller tile moves more bytes per product: only for a gain beyond the fit's error
-        if (s == 0 || us < best_us * (best == 0 ? 0.98 : 1.)) { best = s; best_us = us; }
+        if (t.shape == TILE_256 || us < best_us * (best == TILE_256 ? 0.98 : 1.)) { best = t.shape; best_us = us; }
     }
     return best;
 }
+int choose_tile(const GemmArgs *gs, int n, int n_cu) {
+    return gs[0].layout == GEMM_TN ? choose_tile(COST_WGRAD, 3.7, 1.079, 0.105, gs, n, n_cu)
+                                   : choose_tile(COST_ROWS, 3.4, 1.042, 0.276, gs, n, n_cu);
+}
+
+hipError_t gemm_mfma_group(const GemmArgs *gs, int n, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    if (n > MAX_GROUP) return hipErrorInvalidValue;
+    GemmP p[MAX_GROUP];
+    for (int i = 0; i < n; ++i) {
+        if (!gemm_mfma_few_tiles(gs[i]) || gs[i].K != gs[0].K || gs[i].accumulate != gs[0].accumulate || gs[i].c_f32 != gs[0].c_f32)
+            return hipErrorInvalidValue;
+        p[i] = params(gs[i]);
+    }
+    int n_cu = 0;
+    hipError_t e = compute_units(n_cu);
+    if (e != hipSuccess) return e;
+    return launch_tn(choose_tile(gs, n, n_cu), p, n, st);
+}
 
 hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st) {
-    const int splits = gemm_mfma_splits(g);
-    if (splits > 1) {
-        GemmP p = params(g);
-        p.C = (bf16_t *)g.split_ws; p.ldc = g.N;
-        p.accumulate = 0; p.c_f32 = 1;
-        p.k_chunk = ceil_div(ceil_div(g.K, splits), BK) * BK;
-        p.splits = ceil_div(g.K, p.k_chunk);                          // no empty chunk
-        p.split_stride = (long)g.M * g.N;
-        hipError_t e = launch_partials(g.layout, p, st);
-        if (e != hipSuccess) return e;
-        const long quads = ((long)g.M * g.N + 3) / 4;
-        if (g.c_f32)
-            splitk_reduce_kernel<float><<<ceil_div(quads, 256), 256, 0, st>>>((const float *)g.split_ws, p.splits, p.split_stride,
-                                                                            g.M, g.N, (float *)g.C, g.ldc, g.accumulate ? 1 : 0);
-        else
-            splitk_reduce_kernel<bf16_t><<<ceil_div(quads, 256), 256, 0, st>>>((const float *)g.split_ws, p.splits, p.split_stride,
-                                                                             g.M, g.N, (bf16_t *)g.C, g.ldc, g.accumulate ? 1 : 0);
-        return hipGetLastError();
-    }
     GemmP p = params(g);
     int n_cu = 0, tail_tiles = 0;
     hipError_t e = compute_units(n_cu);
     if (e != hipSuccess) return e;
     const int tail_s = gemm_mfma_tail_splits(g, n_cu, tail_tiles);
-    p.tile_count -= tail_tiles;                                       // the full rounds
-    if (g.c_f32) e = launch<false, false, false, true, Tile256>(p, st);
-    else {
-        const int shape = tail_tiles == 0 && g.layout != GEMM_TN ? choose_tile(g.M, g.N, g.K, n_cu) : 0;
-        if (shape) return g.layout == GEMM_NT ? launch_nt(shape, p, st) : launch_nn(shape, p, st);
-        const bool add = p.residual || p.accumulate;
-        switch (g.layout) {
-            case GEMM_NT: e = add ? launch<true, true, true, false, Tile256>(p, st) : launch<true, true, false, false, Tile256>(p, st); break;
-            case GEMM_NN: e = add ? launch<true, false, true, false, Tile256>(p, st) : launch<true, false, false, false, Tile256>(p, st); break;
-            default: e = add ? launch<false, false, true, false, Tile256>(p, st) : launch<false, false, false, false, Tile256>(p, st); break;
-        }
+    if (tail_tiles == 0) {
+        const int shape = choose_tile(&g, 1, n_cu);
+        if (shape != TILE_256)
+            return g.layout == GEMM_NT ? launch_nt(shape, p, st) : g.layout == GEMM_NN ? launch_nn(shape, p, st) : launch_tn(shape, &p, 1, st);
     }
+    p.tile_count -= tail_tiles;                                       // the full rounds
+    const bool add = p.residual || p.accumulate;
+    if (g.c_f32) e = launch<false, false, false, true, Tile256>(p, st);
+    else if (g.layout == GEMM_NT) e = add ? launch<true, true, true, false, Tile256>(p, st) : launch<true, true, false, false, Tile256>(p, st);
+    else if (g.layout == GEMM_NN) e = add ? launch<true, false, true, false, Tile256>(p, st) : launch<true, false, false, false, Tile256>(p, st);
+    else e = add ? launch<false, false, true, false, Tile256>(p, st) : launch<false, false, false, false, Tile256>(p, st);
     if (e != hipSuccess || tail_tiles == 0) return e;
     GemmP t = params(g);
     t.C = (bf16_t *)g.split_ws; t.accumulate = 0; t.c_f32 = 1;

@@ -19,7 +19,7 @@ struct GemmArgs {
     const void *residual;       // [M, ldc] or null
     bool accumulate;            // C += result
     bool c_f32 = false;         // C is fp32 whatever the operands' dtype (bias / residual are not combined with it)
-    // optional scratch for split-K (TN on the matrix cores only): fp32 partial products, 256-byte aligned
+    // optional scratch for the fp32 partial products of a last round cut along K (NN and TN, bf16), 256-byte aligned
     void *split_ws = nullptr;
     size_t split_ws_bytes = 0;
     // measurement aid (matrix-core kernel only): when not null, device uint64[4]; the first workgroup stores the
@@ -36,7 +36,7 @@ hipError_t gemm_f32(const GemmArgs &g, hipStream_t st);
 bool gemm_mfma_supported(const GemmArgs &g);
 hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st);
 // Weight gradients with few output tiles (gemm_mfma_few_tiles: transposed-A layout, no bias / residual, at most 128 tiles of
-// 256 x 256) computed together in one launch, none of them cut along K; up to 4, all with the same accumulate / c_f32.
+// 256 x 256) computed together in one launch; up to 4, all with the same K and accumulate / c_f32.
 bool gemm_mfma_few_tiles(const GemmArgs &g);
 hipError_t gemm_mfma_group(const GemmArgs *gs, int n, hipStream_t st);
 

@@ -18,3 +18,14 @@ SHAPES = [(9, 40, 24, "64x64"), (65, 136, 712, "64x64"), (129, 72, 256, "64x64")
 def test_gemm_tile_shape(layout, M, N, K, tile):
     gemm_case(mm.BF16, layout, M, N, K, seed=21)
     gemm_case(mm.BF16, layout, M, N, K, bias=True, residual=True, accumulate=K > 500, seed=22)
+
+
+# weight gradients: one row or column of 8 past a tile edge, K (the tokens) with every kind of remainder
+WGRAD_SHAPES = [(8, 8, 1, "64x64"), (72, 136, 67, "64x64"), (520, 1032, 583, "64x64"), (1032, 2312, 321, "64x128"), (1544, 1288, 1411, "128x128"),
+                (2056, 1928, 1411, "256x128")]
+
+
+@pytest.mark.parametrize("M,N,K,tile", WGRAD_SHAPES)
+def test_weight_gradient_tile_shape(M, N, K, tile):
+    gemm_case(mm.BF16, mm.GEMM_TN, M, N, K, seed=23)
+    gemm_case(mm.BF16, mm.GEMM_TN, M, N, K, accumulate=True, seed=24)
