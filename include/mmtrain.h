@@ -259,7 +259,10 @@ MMTRAIN_API int mmtrain_gemm(int32_t dtype, int32_t layout, int32_t M, int32_t N
                  const void *bias, const void *residual, uint32_t flags,
                  void *workspace, size_t workspace_bytes, void *hip_stream);
 
-/* Bytes of workspace for the two attention operators below. */
+/* Bytes of workspace for the two attention operators below.  Beyond the per-token tables (the first
+ * total_tokens * (12 + 4 n_heads) bytes or so, all that is required) it has room for the fp32 partial sums that
+ * backward shares out when a group's query heads are worked off by several workgroups; with a smaller
+ * workspace they are not. */
 MMTRAIN_API size_t mmtrain_attn_workspace_bytes(int32_t total_tokens, int32_t n_segments, int32_t n_heads);
 
 /* Segment-masked attention forward over packed qkv[T, (nh + 2 nkv) d] (q heads | k heads |
@@ -276,8 +279,8 @@ MMTRAIN_API int mmtrain_attn_bwd(const mmtrain_layer_desc *desc, const mmtrain_b
 
 /* mmtrain_attn_bwd for callers that cannot allocate device memory or pass a workspace: code under HIP graph
  * capture, tight serving or training loops, harnesses that forbid hipMalloc.  Same arguments, results and
- * kernels as mmtrain_attn_bwd without the workspace: the scratch (per-token segment tables and the per-head
- * row sums D that the dQ kernel hands to the dK/dV kernel) is a fixed array of MMTRAIN_NOALLOC_SCRATCH_BYTES
+ * kernels as mmtrain_attn_bwd without the workspace: the scratch (per-token segment tables, the per-head
+ * row sums D that the dQ kernel hands to the dK/dV kernel, partial sums of dK and dV) is a fixed array of MMTRAIN_NOALLOC_SCRATCH_BYTES
  * inside the library, one copy on every GPU the library runs on, held until the process ends.  The call
  * allocates nothing and frees nothing, on the device or through any library.
  *   Limits: total_tokens <= MMTRAIN_NOALLOC_MAX_TOKENS and total_tokens * n_heads <=
@@ -288,7 +291,7 @@ MMTRAIN_API int mmtrain_attn_bwd(const mmtrain_layer_desc *desc, const mmtrain_b
  *   The first call on a device looks the array's address up (a host-side query, no allocation). */
 #define MMTRAIN_NOALLOC_MAX_TOKENS 16384
 #define MMTRAIN_NOALLOC_MAX_HEAD_TOKENS (64 * 16384)
-#define MMTRAIN_NOALLOC_SCRATCH_BYTES (16384 * 4 + 16384 * 8 + 64 * 16384 * 4 + 4 * 256)
+#define MMTRAIN_NOALLOC_SCRATCH_BYTES (16384 * 4 + 16384 * 8 + 64 * 16384 * 4 + 4 * 256 + 96 * 1024 * 1024)
 MMTRAIN_API int mmtrain_attn_bwd_noalloc(const mmtrain_layer_desc *desc, const mmtrain_batch *batch, const void *qkv,
                                          const void *o, const float *lse, const void *d_o, void *d_qkv,
                                          void *hip_stream);

@@ -45,6 +45,7 @@ struct BwdWs {
     float *Dsum, *part_g, *part_b, *part_c, *part_din, *part_dres;      // partial sums of the second normalisation's backward pass and of fc1's bias
     float *part_g1, *part_b1, *part_c2;                                 // ... of the first normalisation's and of the QKV bias (all reduced at the end of the pass)
     void *split_ws; size_t split_bytes;     // fp32 partial products of split weight-gradient GEMMs
+    float *dkv_part; size_t dkv_part_bytes; // fp32 partial sums of dK and dV (grouped heads)
 };
 
 int check_desc(const mmtrain_layer_desc *desc, Dims &D) {
@@ -172,6 +173,9 @@ void carve_bwd(Bump &b, const Dims &D, size_t T, BwdWs &w) {
     }
     w.split_bytes = sb;
     w.split_ws = sb ? (void *)b.take<float>(sb / 4) : nullptr;
+    const int parts = D.dtype == DT_BF16 && T ? attn_dkv_parts((int)T, D.nh, D.nkv, D.d) : 1;
+    w.dkv_part_bytes = parts > 1 ? parts * attn_dkv_part_bytes((int)T, D.nkv, D.d) : 0;
+    w.dkv_part = parts > 1 ? b.take<float>(w.dkv_part_bytes / 4) : nullptr;
 }
 
 hipError_t gemm(int dtype, const GemmArgs &g, hipStream_t st);
@@ -438,6 +442,7 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     if (G.w_o) HIP_TRY(wgrad(D.dtype, splittable(f32out(mk(GEMM_TN, D.H, D.nq, T, w.d_y1, D.H, c.o, D.nq, G.w_o, D.nq, nullptr, nullptr, accum), g32), w.split_ws, w.split_bytes), later, st));
     AttnArgs a = mk_attn(D, batch, c);
     a.d_o = w.d_o; a.d_qkv = w.d_qkv; a.Dsum = w.Dsum;
+    a.dkv_part = w.dkv_part; a.dkv_part_bytes = w.dkv_part_bytes;
     // the matrix-core kernels rotate dQ, dK back themselves
     const bool fused_unrotate = !enc && (D.dtype == DT_BF16 ? D.d == 64 || D.d == 128 : attn_f32_supported(a));
     if (fused_unrotate) a.rope_cs = c.rope_cs;
@@ -627,13 +632,19 @@ size_t mmtrain_gemm_workspace_bytes(int32_t layout, int32_t M, int32_t N) {
     return gemm_scratch_bytes((size_t)M, (size_t)N);
 }
 
-size_t mmtrain_attn_workspace_bytes(int32_t total_tokens, int32_t n_segments, int32_t n_heads) {
-    if (total_tokens < 0 || n_segments < 0 || n_heads <= 0) return 0;
+static size_t attn_scratch_bytes(int32_t total_tokens, int32_t n_heads) {
     Bump b = {nullptr, 0};
     b.take<int>((size_t)total_tokens);
     b.take<int2>((size_t)total_tokens);
     b.take<float>((size_t)total_tokens * n_heads);
     return ((b.off + 255) & ~size_t(255)) + 256;
+}
+
+size_t mmtrain_attn_workspace_bytes(int32_t total_tokens, int32_t n_segments, int32_t n_heads) {
+    if (total_tokens < 0 || n_segments < 0 || n_heads <= 0) return 0;
+    // The grouping is not known here: room for the partial sums of any (shares x key/value heads <= n_heads, 128 features)
+    const size_t any = n_heads > 1 ? (size_t)total_tokens * n_heads * 2 * 128 * 4 : 0;
+    return attn_scratch_bytes(total_tokens, n_heads) + (any < DKV_PART_BYTES_MAX ? any : DKV_PART_BYTES_MAX);
 }
 
 // `tensors`: the call's device tensors, all required and 16-byte aligned (checked before anything is enqueued)
@@ -648,8 +659,8 @@ static int attn_common(const mmtrain_layer_desc *desc, const mmtrain_batch *batc
         if (!p) return MMTRAIN_ERR_INVALID_ARG;
     if (misaligned(tensors)) return MMTRAIN_ERR_INVALID_ARG;
     if ((uintptr_t)workspace & 255) return MMTRAIN_ERR_INVALID_ARG;
-    if (!workspace || workspace_bytes < mmtrain_attn_workspace_bytes(T, batch->n_segments, D.nh))
-        return MMTRAIN_ERR_WORKSPACE;
+    const size_t scratch = attn_scratch_bytes(T, D.nh);      // required; what the workspace has beyond it may hold partial sums
+    if (!workspace || workspace_bytes < scratch) return MMTRAIN_ERR_WORKSPACE;
     Bump b = {(uint8_t *)workspace, 0};
     int *tok_seg = b.take<int>((size_t)T);
     int2 *tok_info = b.take<int2>((size_t)T);
@@ -658,6 +669,7 @@ static int attn_common(const mmtrain_layer_desc *desc, const mmtrain_batch *batc
     a.T = T; a.S = batch->n_segments; a.nh = D.nh; a.nkv = D.nkv; a.d = D.d; a.scale = D.scale;
     a.cu = batch->cu_seqlens_dev; a.modes = batch->seg_mask_dev; a.default_mode = batch->mask_mode;
     a.tok_seg = tok_seg; a.tok_info = tok_info; a.ld_qkv = D.nqkv; a.Dsum = Dsum;
+    if (workspace_bytes > scratch) { a.dkv_part = reinterpret_cast<float *>((uint8_t *)workspace + scratch); a.dkv_part_bytes = workspace_bytes - scratch; }
     a.cu_busy = g_attn_busy;
     attn_tile_order(batch->cu_seqlens_host, batch->seg_mask_host, batch->mask_mode, batch->n_segments, T, a);
     HIP_TRY(prep_tokens(batch->cu_seqlens_dev, batch->seg_mask_dev, batch->mask_mode, batch->n_segments, T, tok_seg, tok_info,
@@ -728,7 +740,7 @@ int mmtrain_attn_bwd_noalloc(const mmtrain_layer_desc *desc, const mmtrain_batch
     if ((rc = check_batch(batch))) return rc;
     if (batch->total_tokens > MMTRAIN_NOALLOC_MAX_TOKENS ||
         (int64_t)batch->total_tokens * D.nh > MMTRAIN_NOALLOC_MAX_HEAD_TOKENS ||
-        mmtrain_attn_workspace_bytes(batch->total_tokens, batch->n_segments, D.nh) > MMTRAIN_NOALLOC_SCRATCH_BYTES)
+        attn_scratch_bytes(batch->total_tokens, D.nh) > MMTRAIN_NOALLOC_SCRATCH_BYTES)
         return MMTRAIN_ERR_TOO_LARGE;
     if (batch->total_tokens == 0) return MMTRAIN_OK;
     if (!qkv || !o || !lse || !d_o || !d_qkv) return MMTRAIN_ERR_INVALID_ARG;

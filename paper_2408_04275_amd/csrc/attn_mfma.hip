@@ -366,6 +366,80 @@ __device__ __forceinline__ void store_rows(uint8_t *stage, const f32x16 (&acc)[C
     }
 }
 
+// The same rows as fp32, unscaled, for partial sums: every row of the tensor has ld floats, all D features are stored.
+template <int D>
+constexpr int STAGE32_BYTES = 32 * (4 * D + 16);
+template <int D, int CB>
+__device__ __forceinline__ void store_rows_f32(uint8_t *stage, const f32x16 (&acc)[CB], float *dst, long ld, int rows_valid, int dh) {
+    constexpr int RS = 4 * D + 16, LPR = D / 4, RPI = 64 / LPR;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq)
+            *reinterpret_cast<f32x4 *>(stage + l32 * RS + (32 * c + 8 * gq + 4 * half) * 4) =
+                f32x4{acc[c][4 * gq], acc[c][4 * gq + 1], acc[c][4 * gq + 2], acc[c][4 * gq + 3]};
+    const int r0 = lane / LPR, cb = (lane % LPR) * 16;
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+        const int r = i * RPI + r0;
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(stage + r * RS + cb);
+        if (r < rows_valid && cb / 4 < dh) *reinterpret_cast<f32x4 *>(dst + (long)r * ld + cb / 4) = v;
+    }
+}
+
+// End of both dK/dV kernels: a wavefront's 32 keys' dV and dK (unscaled) as rows of d_qkv, or, where the query heads of a
+// group are shared out over several workgroups, as this workgroup's fp32 partial sums.
+template <int D, int CB>
+__device__ __forceinline__ void store_dkv(const AttnArgs &a, uint8_t *smem, int wave, int half, int g, int key0, int key, bool valid,
+                                          f32x16 (&dk)[CB], f32x16 (&dv)[CB]) {
+    const int dh = a.d, nk = a.nkv * dh, rows = a.T - key0;
+    if (a.dkv_parts > 1) {
+        float *out = a.dkv_part + ((size_t)blockIdx.z * a.T + key0) * 2 * nk + g * dh;
+        uint8_t *stage = smem + wave * STAGE32_BYTES<D>;
+        store_rows_f32<D, CB>(stage, dk, out, 2 * nk, rows, dh);
+        store_rows_f32<D, CB>(stage, dv, out + nk, 2 * nk, rows, dh);
+        return;
+    }
+    bf16_t *okp = (bf16_t *)a.d_qkv + (long)key0 * a.ld_qkv + a.nh * dh + g * dh;
+    uint8_t *stage = smem + wave * STAGE_BYTES<D>;
+    store_rows<D, CB>(stage, dv, 1.f, okp + nk, a.ld_qkv, rows, dh);
+    if (valid && a.rope_cs) unrotate<CB>(dk, a.rope_cs + (long)key * (D / 2), half);
+    store_rows<D, CB>(stage, dk, a.scale, okp, a.ld_qkv, rows, dh);
+}
+
+// The partial sums of the workgroups that share a group's query heads, added in order: dK scaled and rotated back, dV, as bf16
+// rows of d_qkv.  A thread owns four features below d / 2 and the four they are rotated with.
+__global__ __launch_bounds__(256) void dkv_reduce_kernel(AttnArgs a) {
+    const int dh = a.d, nk = a.nkv * dh, quads = dh / 8, per_row = 2 * a.nkv * quads;
+    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (long)a.T * per_row) return;
+    const int t = (int)(idx / per_row), r = (int)(idx % per_row), head = r / quads, f = r % quads * 4;
+    const bool is_k = head < a.nkv;
+    const size_t stride = (size_t)a.T * 2 * nk;
+    const float *p = a.dkv_part + (size_t)t * 2 * nk + head * dh + f;
+    f32x4 lo = *reinterpret_cast<const f32x4 *>(p), hi = *reinterpret_cast<const f32x4 *>(p + dh / 2);
+    for (int i = 1; i < a.dkv_parts; ++i) {
+        lo += *reinterpret_cast<const f32x4 *>(p + i * stride);
+        hi += *reinterpret_cast<const f32x4 *>(p + i * stride + dh / 2);
+    }
+    if (is_k) {
+        if (a.rope_cs) {
+            const float2 *cs = a.rope_cs + (size_t)t * (dh / 2) + f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x = lo[e], y = hi[e];
+                lo[e] = x * cs[e].x + y * cs[e].y;
+                hi[e] = y * cs[e].x - x * cs[e].y;
+            }
+        }
+        lo *= a.scale; hi *= a.scale;
+    }
+    bf16_t *out = (bf16_t *)a.d_qkv + (size_t)t * a.ld_qkv + a.nh * dh + head * dh + f;      // k heads, then v heads
+    *reinterpret_cast<uint2 *>(out) = make_uint2(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]));
+    *reinterpret_cast<uint2 *>(out + dh / 2) = make_uint2(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]));
+}
+
 // ------------------------------------------------------------------------------------------
 // backward: dQ (and -D, D = rowsum(dO * O)).  Same roles as the forward kernel: 8 wavefronts x 32 queries.
 // ------------------------------------------------------------------------------------------
@@ -720,8 +794,11 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     add_busy(a.cu_busy ? a.cu_busy + 2048 : nullptr, false);
 
-    // grid: x = key/value head, y = position in the dispatch order of the key tiles (heaviest first)
-    const int g = blockIdx.x, group = a.nh / a.nkv;
+    // grid: x = key/value head, y = position in the dispatch order of the key tiles (heaviest first), z = this workgroup's share
+    // of the group's query heads
+    const int g = blockIdx.x, group_heads = a.nh / a.nkv;
+    const int h_first = g * group_heads + blockIdx.z * group_heads / a.dkv_parts;
+    const int group = g * group_heads + (blockIdx.z + 1) * group_heads / a.dkv_parts - h_first;
     const int k0 = (a.use_order ? a.order_k[blockIdx.y] : blockIdx.y) * BQ;
     // the wavefront's index as a scalar: what is derived from it (copy destinations, buffer descriptors) stays uniform
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
@@ -780,7 +857,7 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
     // A wavefront skips the steps none of whose queries sees any of its keys; the scores behind such a gap are
     // computed on their own.
     const int tiles_per_head = (qend - qbeg + BT2 - 1) / BT2, n_steps = group * tiles_per_head;
-    auto head_of = [&](int step) { return g * group + step / tiles_per_head; };
+    auto head_of = [&](int step) { return h_first + step / tiles_per_head; };
     auto qt_of = [&](int step) { return qbeg + (step % tiles_per_head) * BT2; };
     const unsigned span = (unsigned)(me.hi - me.lo);
 
@@ -955,13 +1032,7 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
     }
 done:
     lds_barrier();                                     // the tiles are done with: LDS now stages the output rows
-    {
-        bf16_t *okp = (bf16_t *)a.d_qkv + (long)(k0 + wave * 32) * ld + nq + g * dh;
-        uint8_t *stage = smem + wave * STAGE_BYTES<D>;
-        store_rows<D, CB>(stage, dv, 1.f, okp + nk, ld, T - (k0 + wave * 32), dh);
-        if (valid && a.rope_cs) unrotate<CB>(dk, a.rope_cs + (long)key * (D / 2), half);
-        store_rows<D, CB>(stage, dk, a.scale, okp, ld, T - (k0 + wave * 32), dh);
-    }
+    store_dkv<D, CB>(a, smem, wave, half, g, k0 + wave * 32, key, valid, dk, dv);
     add_busy(a.cu_busy ? a.cu_busy + 2048 : nullptr, true);
 }
 
@@ -978,8 +1049,11 @@ __global__ __launch_bounds__(256) void attn_dkv_plain_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     add_busy(a.cu_busy ? a.cu_busy + 2048 : nullptr, false);
 
-    // grid: x = key/value head, y = position in the dispatch order of the key tiles (heaviest first)
-    const int g = blockIdx.x, group = a.nh / a.nkv;
+    // grid: x = key/value head, y = position in the dispatch order of the key tiles (heaviest first), z = this workgroup's share
+    // of the group's query heads
+    const int g = blockIdx.x, group_heads = a.nh / a.nkv;
+    const int h_first = g * group_heads + blockIdx.z * group_heads / a.dkv_parts;
+    const int group = g * group_heads + (blockIdx.z + 1) * group_heads / a.dkv_parts - h_first;
     const int k0 = (a.use_order ? a.order_k[blockIdx.y] : blockIdx.y) * BQ;
     // the wavefront's index as a scalar: what is derived from it (copy destinations, buffer descriptors) stays uniform
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
@@ -1038,7 +1112,7 @@ __global__ __launch_bounds__(256) void attn_dkv_plain_kernel(AttnArgs a) {
         uint8_t *stage_k = smem + 2 * SLOT + wave * 2 * ROWS32_BYTES<D>, *stage_v = stage_k + ROWS32_BYTES<D>;
         cp_kv.issue(rs_q, stage_k, k0 + wave * 32, ld, nq + g * dh);
         cp_kv.issue(rs_q, stage_v, k0 + wave * 32, ld, nq + nk + g * dh);
-        copy_tile(smem, g * group, qbeg);
+        copy_tile(smem, h_first, qbeg);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -1055,7 +1129,7 @@ __global__ __launch_bounds__(256) void attn_dkv_plain_kernel(AttnArgs a) {
         lds_barrier();                                               // ... and everyone is done with the other slot
         if (step + 1 < n_steps) {
             const int nh2 = (step + 1) / tiles_per_head, nqt = qbeg + ((step + 1) % tiles_per_head) * BT2;
-            copy_tile(smem + (slot ^ 1) * SLOT, g * group + nh2, nqt);
+            copy_tile(smem + (slot ^ 1) * SLOT, h_first + nh2, nqt);
         }
         (void)hh;
         auto block = [&](auto B_) {
@@ -1144,13 +1218,7 @@ __global__ __launch_bounds__(256) void attn_dkv_plain_kernel(AttnArgs a) {
     }
 done:
     lds_barrier();                                     // the tiles are done with: LDS now stages the output rows
-    {
-        bf16_t *okp = (bf16_t *)a.d_qkv + (long)(k0 + wave * 32) * ld + nq + g * dh;
-        uint8_t *stage = smem + wave * STAGE_BYTES<D>;
-        store_rows<D, CB>(stage, dv, 1.f, okp + nk, ld, T - (k0 + wave * 32), dh);
-        if (valid && a.rope_cs) unrotate<CB>(dk, a.rope_cs + (long)key * (D / 2), half);
-        store_rows<D, CB>(stage, dk, a.scale, okp, ld, T - (k0 + wave * 32), dh);
-    }
+    store_dkv<D, CB>(a, smem, wave, half, g, k0 + wave * 32, key, valid, dk, dv);
     add_busy(a.cu_busy ? a.cu_busy + 2048 : nullptr, true);
 }
 
@@ -1184,6 +1252,7 @@ hipError_t launch_bwd(const AttnArgs &a, hipStream_t st) {
     static std::atomic<bool> configured{false};     // set once; concurrent first calls repeat the same idempotent set-up
     constexpr bool PIPELINED = D > 64;                  // see attn_dkv_plain_kernel
     constexpr int DKV_SLOT = 2 * BT2 * D * 2 + 2 * BT2 * 4;
+    static_assert(4 * STAGE32_BYTES<D> <= 2 * DKV_SLOT + 2 * DKV_STAGE_BYTES<D>, "room for the staged fp32 rows");
     const int smem_dq = std::max(DQ_LDS_BYTES<D>, 8 * STAGE_BYTES<D>), smem_dkv = PIPELINED ? 3 * DKV_SLOT + DKV_STAGE_BYTES<D> : 2 * DKV_SLOT + 2 * DKV_STAGE_BYTES<D>;
     if (!configured.load(std::memory_order_acquire)) {
         hipError_t e = set_smem(attn_dq_kernel<D>, smem_dq);
@@ -1194,8 +1263,10 @@ hipError_t launch_bwd(const AttnArgs &a, hipStream_t st) {
         configured.store(true, std::memory_order_release);
     }
     attn_dq_kernel<D><<<dim3(a.nh, ceil_div(a.T, FQ)), 512, smem_dq, st>>>(a);
-    if constexpr (PIPELINED) attn_dkv_kernel<D><<<dim3(a.nkv, ceil_div(a.T, BQ)), 256, smem_dkv, st>>>(a);
-    else attn_dkv_plain_kernel<D><<<dim3(a.nkv, ceil_div(a.T, BQ)), 256, smem_dkv, st>>>(a);
+    const dim3 grid(a.nkv, ceil_div(a.T, BQ), a.dkv_parts);
+    if constexpr (PIPELINED) attn_dkv_kernel<D><<<grid, 256, smem_dkv, st>>>(a);
+    else attn_dkv_plain_kernel<D><<<grid, 256, smem_dkv, st>>>(a);
+    if (a.dkv_parts > 1) dkv_reduce_kernel<<<ceil_div((long)a.T * 2 * a.nkv * (a.d / 8), 256), 256, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -1207,9 +1278,29 @@ hipError_t attn_mfma_fwd(const AttnArgs &a, hipStream_t st) {
     return a.d <= 64 ? launch_fwd<64>(a, st) : launch_fwd<128>(a, st);
 }
 
-hipError_t attn_mfma_bwd(const AttnArgs &a, hipStream_t st) {
-    if (a.T == 0) return hipSuccess;
-    if ((size_t)a.T * a.ld_qkv * 2 >= MAX_TENSOR_BYTES) return hipErrorInvalidValue;
+// Workgroups that share a group's query heads in the dK/dV kernels.  One workgroup per 128 keys and key/value head walks all
+// heads of the group one after the other: 64 query on 8 key/value heads over 2047 tokens are 128 workgroups for 256 compute
+// units, each with a chain of up to 96 steps.  Shared out, each writes fp32 partial sums (dkv_reduce_kernel adds them in order),
+// which costs 16 bytes per key, head and feature pair.  Only divisors of the group, so that the shares are equal (8 heads over 3
+// workgroups: 8 % slower than over 2), and as many as give two workgroups per compute unit, one at a time (128-wide heads), or
+// six, two at a time.  dQ + dK/dV in us, 64 / 8 heads of 128, before -> after: 500 tokens 151 -> 61 (8 workgroups per group), 1031
+// 204 -> 97 (4), 2047 260 -> 161 (4), 4096 411 -> 314 (2), 6000 625 -> 507 (2), where one and a half rounds become three; at 8192
+// tokens (512 workgroups as they are) two would gain 4 to 8 % for 134 MB of scratch, at 12000 nothing.  16 / 2 heads of 64, 2047
+// tokens: 199 -> 58 (8).
+int attn_dkv_parts(int T, int nh, int nkv, int d) {
+    const long group = nh / nkv, workgroups = (long)nkv * ceil_div(T, BQ), most = d <= 64 ? 1536 : workgroups <= 384 ? std::max(512l, 2 * workgroups) : 0;
+    int parts = 1;
+    for (long p = 2; p <= group; ++p)
+        if (group % p == 0 && p * workgroups <= most && p * attn_dkv_part_bytes(T, nkv, d) <= DKV_PART_BYTES_MAX) parts = (int)p;
+    return parts;
+}
+
+hipError_t attn_mfma_bwd(const AttnArgs &args, hipStream_t st) {
+    if (args.T == 0) return hipSuccess;
+    if ((size_t)args.T * args.ld_qkv * 2 >= MAX_TENSOR_BYTES) return hipErrorInvalidValue;
+    AttnArgs a = args;
+    a.dkv_parts = attn_dkv_parts(a.T, a.nh, a.nkv, a.d);
+    if (a.dkv_parts > 1 && a.dkv_part_bytes < a.dkv_parts * attn_dkv_part_bytes(a.T, a.nkv, a.d)) a.dkv_parts = 1;
     return a.d <= 64 ? launch_bwd<64>(a, st) : launch_bwd<128>(a, st);
 }
 

@@ -61,6 +61,9 @@ struct AttnArgs {
     // MFMA path, backward: when not null, the [T, d/2] (cos, sin) table of the rotary embedding; dQ and dK are
     // then rotated back in the kernels' epilogues (otherwise the caller does it afterwards)
     const float2 *rope_cs;
+    // MFMA path, backward, grouped heads: scratch for fp32 partial sums of dK and dV (may be null), [parts][T][2 nkv d]
+    float *dkv_part; size_t dkv_part_bytes;
+    int dkv_parts;              // workgroups that share a group's query heads; set by attn_mfma_bwd
     // MFMA path: dispatch order of the query tiles (256 queries: forward, dQ) and of the key tiles (128
     // keys: dK/dV), heaviest first; use_order = 0 means index order (more tiles than the tables hold)
     int use_order;
@@ -89,6 +92,12 @@ hipError_t attn_f32_bwd(const AttnArgs &a, hipStream_t st);
 // attn_mfma.hip: bf16 storage, matrix cores
 hipError_t attn_mfma_fwd(const AttnArgs &a, hipStream_t st);
 hipError_t attn_mfma_bwd(const AttnArgs &a, hipStream_t st);
+
+// Backward, grouped heads: workgroups that share the query heads of a group (1: none), each with an fp32 partial result of
+// attn_dkv_part_bytes; parts * that never exceeds DKV_PART_BYTES_MAX.
+constexpr size_t DKV_PART_BYTES_MAX = size_t(96) << 20;
+inline size_t attn_dkv_part_bytes(int T, int nkv, int d) { return (size_t)T * 2 * nkv * d * 4; }
+int attn_dkv_parts(int T, int nh, int nkv, int d);
 
 // elementwise.hip
 hipError_t prep_tokens(const int *cu, const uint8_t *modes, int default_mode, int S, int T, int *tok_seg,
