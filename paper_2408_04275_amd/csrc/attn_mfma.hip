@@ -30,9 +30,11 @@
 // under the current block's softmax, whole 64-query steps skipped per wavefront), for 64-wide heads a plain one
 // that leaves room for two workgroups per compute unit.
 //
-// Head dimensions: the kernels are instantiated for 64 and 128 features; a head of another width (a
-// multiple of 16, e.g. 80) uses the next instantiation with the missing features read as zero and never
-// stored.
+// Head dimensions: tiles in LDS are 64 or 128 features wide; a head of another width (a multiple of 16, e.g. 80) uses the
+// next wider ones with the missing features read as zero and never stored.  Template parameters: D the tiles' width, KS the
+// 16-feature slices that scores are contracted over, CB the 32-feature blocks of a result; heads of up to 80 and 96
+// features have kernels that leave the zero slices and blocks out (80: 5 of 8 and 3 of 4, 11 MFMAs per 32 x 32 block
+// instead of 16 forward, 16 of 24 in dQ, 22 of 32 in dK/dV).
 #include "kernels.h"
 #include <atomic>
 #include <algorithm>
@@ -255,7 +257,15 @@ __device__ __forceinline__ bf16x8 join(shortx4 lo, shortx4 hi) {
 // The transposing reads are written as assembly because the compiler makes the builtin wait for every
 // direct-to-LDS copy in flight; their results may be used only after this wait, which names them.
 #define TR_WAIT4(x) "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])
+#define TR_WAIT3(x) "+v"(x[0]), "+v"(x[1]), "+v"(x[2])
 #define TR_WAIT2(x) "+v"(x[0]), "+v"(x[1])
+// four arrays of CB transposing reads each have landed
+template <int CB, int N>
+__device__ __forceinline__ void tr_wait(shortx4 (&a)[N], shortx4 (&b)[N], shortx4 (&c)[N], shortx4 (&d)[N]) {
+    if constexpr (CB == 4) asm volatile("s_waitcnt lgkmcnt(0)" : TR_WAIT4(a), TR_WAIT4(b), TR_WAIT4(c), TR_WAIT4(d));
+    else if constexpr (CB == 3) asm volatile("s_waitcnt lgkmcnt(0)" : TR_WAIT3(a), TR_WAIT3(b), TR_WAIT3(c), TR_WAIT3(d));
+    else asm volatile("s_waitcnt lgkmcnt(0)" : TR_WAIT2(a), TR_WAIT2(b), TR_WAIT2(c), TR_WAIT2(d));
+}
 
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for(F &&f) {
@@ -283,10 +293,10 @@ __device__ __forceinline__ void lds_wait(V &x) {
 // Issue order of the section: the log-sum-exps and the D values of the first four queries, PF score fragments;
 // then per softmax element e (a chunk): [the fragment of score MFMA e / PER_M + PF] [one transposing read]
 // [log-sum-exps and D values of the next four queries, every fourth element].
-template <int NM, int PER_M, int PF, int PER_R>
+template <int NM, int PER_M, int PF, int NR, int PER_R>
 struct LdsSched {
     static constexpr bool has_frag(int e) { return e % PER_M == 0 && e / PER_M + PF < NM; }
-    static constexpr bool has_tr(int e) { return e % PER_R == 0; }
+    static constexpr bool has_tr(int e) { return e % PER_R == 0 && e / PER_R < NR; }
     static constexpr int in_chunk(int e) { return (has_frag(e) ? 1 : 0) + (has_tr(e) ? 1 : 0) + ((e & 3) == 0 && (e >> 2) < 3 ? 2 : 0); }
     static constexpr int before(int e) {                 // operations issued before the waits of chunk e
         int n = PF + 2;
@@ -302,11 +312,11 @@ struct LdsSched {
 };
 // 128-wide head (16 score MFMAs, one per element, five fragments ahead, a transposing read per element): in front of
 // element 0 seven operations are out; fragment 0 was the third, the first D values the second of them
-static_assert(LdsSched<16, 1, 5, 1>::before(0) == 7 && LdsSched<16, 1, 5, 1>::allowed_frag(0) == 4 &&
-              LdsSched<16, 1, 5, 1>::allowed_d(0) == 5, "issue order of the pipelined section, start");
+static_assert(LdsSched<16, 1, 5, 16, 1>::before(0) == 7 && LdsSched<16, 1, 5, 16, 1>::allowed_frag(0) == 4 &&
+              LdsSched<16, 1, 5, 16, 1>::allowed_d(0) == 5, "issue order of the pipelined section, start");
 // element 0 adds a fragment, a transposing read and two reads for queries 8 .. 11; fragment 1 was the fourth operation
-static_assert(LdsSched<16, 1, 5, 1>::before(1) == 11 && LdsSched<16, 1, 5, 1>::allowed_frag(1) == 7 &&
-              LdsSched<16, 1, 5, 1>::idx_d(1) == 10 && LdsSched<16, 1, 5, 1>::allowed_d(4) == LdsSched<16, 1, 5, 1>::before(4) - 11,
+static_assert(LdsSched<16, 1, 5, 16, 1>::before(1) == 11 && LdsSched<16, 1, 5, 16, 1>::allowed_frag(1) == 7 &&
+              LdsSched<16, 1, 5, 16, 1>::idx_d(1) == 10 && LdsSched<16, 1, 5, 16, 1>::allowed_d(4) == LdsSched<16, 1, 5, 16, 1>::before(4) - 11,
               "issue order of the pipelined section, first element");
 
 // Inverse rotary embedding of a gradient held in accumulator layout (the backward pass of the rotation that
@@ -404,7 +414,8 @@ __device__ __forceinline__ void store_dkv(const AttnArgs &a, uint8_t *smem, int 
     bf16_t *okp = (bf16_t *)a.d_qkv + (long)key0 * a.ld_qkv + a.nh * dh + g * dh;
     uint8_t *stage = smem + wave * STAGE_BYTES<D>;
     store_rows<D, CB>(stage, dv, 1.f, okp + nk, a.ld_qkv, rows, dh);
-    if (valid && a.rope_cs) unrotate<CB>(dk, a.rope_cs + (long)key * (D / 2), half);
+    if constexpr (CB == D / 32)
+        if (valid && a.rope_cs) unrotate<CB>(dk, a.rope_cs + (long)key * (D / 2), half);
     store_rows<D, CB>(stage, dk, a.scale, okp, a.ld_qkv, rows, dh);
 }
 
@@ -443,9 +454,8 @@ __global__ __launch_bounds__(256) void dkv_reduce_kernel(AttnArgs a) {
 // ------------------------------------------------------------------------------------------
 // backward: dQ (and -D, D = rowsum(dO * O)).  Same roles as the forward kernel: 8 wavefronts x 32 queries.
 // ------------------------------------------------------------------------------------------
-template <int D>
+template <int D, int KS, int CB>
 __global__ __launch_bounds__(512) void attn_dq_kernel(AttnArgs a) {
-    constexpr int KS = D / 16, CB = D / 32;
     constexpr int TILE = BT2 * D * 2, SLOT = 2 * TILE;             // K tile, then V tile
     constexpr int COPIES = BT2 * D * 2 / 1024 / 4;                 // per wavefront (4 wavefronts per tile)
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -563,13 +573,13 @@ __global__ __launch_bounds__(512) void attn_dq_kernel(AttnArgs a) {
             t2[0] = tr.template read<b, 1, 0, 0>(tile); t3[0] = tr.template read<b, 1, 0, 1>(tile);
             t0[1] = tr.template read<b, 0, 1, 0>(tile); t1[1] = tr.template read<b, 0, 1, 1>(tile);
             t2[1] = tr.template read<b, 1, 1, 0>(tile); t3[1] = tr.template read<b, 1, 1, 1>(tile);
-            if (CB > 2) {
+            if constexpr (CB > 2) {
                 t0[2] = tr.template read<b, 0, 2, 0>(tile); t1[2] = tr.template read<b, 0, 2, 1>(tile);
                 t2[2] = tr.template read<b, 1, 2, 0>(tile); t3[2] = tr.template read<b, 1, 2, 1>(tile);
+            }
+            if constexpr (CB > 3) {
                 t0[3] = tr.template read<b, 0, 3, 0>(tile); t1[3] = tr.template read<b, 0, 3, 1>(tile);
                 t2[3] = tr.template read<b, 1, 3, 0>(tile); t3[3] = tr.template read<b, 1, 3, 1>(tile);
-            } else {
-                t0[2] = t0[3] = t1[2] = t1[3] = t2[2] = t2[3] = t3[2] = t3[3] = shortx4{0, 0, 0, 0};
             }
             const bool inside = kb >= w_lo_max && kb + 32 <= w_hi_min;
             const unsigned span = (unsigned)(me.hi - me.lo);
@@ -586,7 +596,7 @@ __global__ __launch_bounds__(512) void attn_dq_kernel(AttnArgs a) {
             };
             if (inside) softmax(std::false_type{});
             else softmax(std::true_type{});
-            asm volatile("s_waitcnt lgkmcnt(0)" : TR_WAIT4(t0), TR_WAIT4(t1), TR_WAIT4(t2), TR_WAIT4(t3));
+            tr_wait<CB>(t0, t1, t2, t3);
             const bf16x8 ds0 = pack8(ds), ds1 = pack8(ds + 8);
 #pragma unroll
             for (int c = 0; c < CB; ++c) {
@@ -598,7 +608,8 @@ __global__ __launch_bounds__(512) void attn_dq_kernel(AttnArgs a) {
         block(std::integral_constant<int, 1>{});
     }
     lds_barrier();                                     // the tiles are done with: LDS now stages the output rows
-    if (valid && a.rope_cs) unrotate<CB>(dq, a.rope_cs + (long)q * (D / 2), half);
+    if constexpr (CB == D / 32)                        // (narrower heads are rotated back by a pass of their own)
+        if (valid && a.rope_cs) unrotate<CB>(dq, a.rope_cs + (long)q * (D / 2), half);
     store_rows<D, CB>(smem + wave * STAGE_BYTES<D>, dq, a.scale, (bf16_t *)a.d_qkv + (long)(q0 + wave * 32) * ld + head * dh, ld,
                       T - (q0 + wave * 32), dh);
     add_busy(a.cu_busy ? a.cu_busy + 1024 : nullptr, true);
@@ -629,10 +640,9 @@ constexpr float LAZY_LOG2 = 8.f;
 // dQ^T = K^T . dS^T above.  One barrier per step: after it every wavefront has finished the previous step, so the slot
 // that step used may be refilled.
 // ------------------------------------------------------------------------------------------
-template <int D, int WAVES>
+template <int D, int KS, int CB, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 2) void attn_fwd_kernel(AttnArgs a) {
     constexpr int FQW = WAVES * 32;                                // queries per workgroup
-    constexpr int KS = D / 16, CB = D / 32;
     constexpr int TILE = BT2 * D * 2, SLOT = 2 * TILE;             // K tile, then V tile
     constexpr int COPIES = BT2 * D * 2 / 1024 / 4;                 // per wavefront and tile (four wavefronts copy a tile)
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -748,13 +758,13 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fwd_kernel(AttnArgs a) {
             t2[0] = tr.template read<b, 1, 0, 0>(tv); t3[0] = tr.template read<b, 1, 0, 1>(tv);
             t0[1] = tr.template read<b, 0, 1, 0>(tv); t1[1] = tr.template read<b, 0, 1, 1>(tv);
             t2[1] = tr.template read<b, 1, 1, 0>(tv); t3[1] = tr.template read<b, 1, 1, 1>(tv);
-            if (CB > 2) {
+            if constexpr (CB > 2) {
                 t0[2] = tr.template read<b, 0, 2, 0>(tv); t1[2] = tr.template read<b, 0, 2, 1>(tv);
                 t2[2] = tr.template read<b, 1, 2, 0>(tv); t3[2] = tr.template read<b, 1, 2, 1>(tv);
+            }
+            if constexpr (CB > 3) {
                 t0[3] = tr.template read<b, 0, 3, 0>(tv); t1[3] = tr.template read<b, 0, 3, 1>(tv);
                 t2[3] = tr.template read<b, 1, 3, 0>(tv); t3[3] = tr.template read<b, 1, 3, 1>(tv);
-            } else {
-                t0[2] = t0[3] = t1[2] = t1[3] = t2[2] = t2[3] = t3[2] = t3[3] = shortx4{0, 0, 0, 0};
             }
             float p[16];
 #pragma unroll
@@ -762,7 +772,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fwd_kernel(AttnArgs a) {
                 p[i] = __builtin_amdgcn_exp2f(fmaf(s[b][i], sl2, -msc));
                 l_run += p[i];
             }
-            asm volatile("s_waitcnt lgkmcnt(0)" : TR_WAIT4(t0), TR_WAIT4(t1), TR_WAIT4(t2), TR_WAIT4(t3));
+            tr_wait<CB>(t0, t1, t2, t3);
             const bf16x8 p0 = pack8(p), p1 = pack8(p + 8);
 #pragma unroll
             for (int c = 0; c < CB; ++c) {
@@ -786,9 +796,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fwd_kernel(AttnArgs a) {
 // backward: dK, dV.  One key per lane (4 wavefronts x 32 keys); loop over the query heads of the group and
 // over the 64-query tiles that can see the workgroup's keys.
 // ------------------------------------------------------------------------------------------
-template <int D>
+template <int D, int KS, int CB>
 __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
-    constexpr int KS = D / 16, CB = D / 32;
     constexpr int TILE = BT2 * D * 2, SLOT = 2 * TILE + 2 * BT2 * 4;   // Q tile, dO tile, lse[64], D[64]
     constexpr int COPIES = BT2 * D * 2 / 1024 / 4;                     // per wavefront and tile
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -864,21 +873,22 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
     // LDS addresses, shared by all blocks.  A fragment of the score MFMAs: row 32 bn + l32 of a tile, 16-byte unit
     // (2 ks + half) ^ swz_unit(row), and swz_unit(32 + l32) = swz_unit(l32) ^ 4, so block 1 finds slice ks where block 0
     // finds slice ks ^ 2, 32 rows further on.
-    uint32_t f0[KS];
+    constexpr int KD = D / 16;                          // (the address of slice ks ^ 2 may lie beyond the slices in use)
+    uint32_t f0[KD];
 #pragma unroll
-    for (int k = 0; k < KS; ++k)
+    for (int k = 0; k < KD; ++k)
         f0[k] = (uint32_t)(uintptr_t)(lds_void *)smem + (l32 * (D / 8) + ((2 * k + half) ^ swz_unit<D>(l32))) * 16;
     const uint32_t l0 = (uint32_t)(uintptr_t)(lds_void *)smem + 2 * TILE + half * 16;
-    uint32_t fcur[KS], fnxt[KS], trc[8], lcur = 0;    // ... of the current step's tile, of the next step's
+    uint32_t fcur[KD], fnxt[KD], trc[8], lcur = 0;    // ... of the current step's tile, of the next step's
     int qt_cur = 0;
     int mbase = 0;                                      // first query of this lane's quads minus the first that sees its key
     f32x16 sc[2], dpc[2];                               // scores and dP of a step's two blocks
 
-    auto score_frag = [&](const uint32_t (&fa)[KS], auto BN_, auto J_) -> bf16x8 {
+    auto score_frag = [&](const uint32_t (&fa)[KD], auto BN_, auto J_) -> bf16x8 {
         constexpr int bn = decltype(BN_)::value, j = decltype(J_)::value, ks = j >> 1;
         return *(lds_bf16x8 *)(uintptr_t)(fa[ks ^ (2 * bn)] + ((j & 1) * TILE + bn * 64 * D));
     };
-    auto issue_frag = [&](bf16x8 &dst, const uint32_t (&fa)[KS], auto BN_, auto J_) {
+    auto issue_frag = [&](bf16x8 &dst, const uint32_t (&fa)[KD], auto BN_, auto J_) {
         constexpr int bn = decltype(BN_)::value, j = decltype(J_)::value, ks = j >> 1;
         lds_read16<(j & 1) * TILE + bn * 64 * D>(dst, fa[ks ^ (2 * bn)]);
     };
@@ -900,13 +910,13 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
         constexpr int b = decltype(B_)::value;
         constexpr int NM = 2 * KS, PER_M = 16 / NM, PF = NM > 8 ? 5 : 3;          // score MFMAs, softmax elements per MFMA, fragments in flight
         constexpr int NR = 4 * CB, PER_R = 16 / NR;                  // transposing reads of the block's first 16 queries
-        const uint32_t (&fa)[KS] = b == 0 ? fcur : fnxt;
+        const uint32_t (&fa)[KD] = b == 0 ? fcur : fnxt;
         constexpr std::integral_constant<int, b ^ 1> BN{};
         shortx4 o0[CB], o1[CB], q0f[CB], q1f[CB], o2[CB], o3[CB], q2f[CB], q3f[CB];
         uint32_t pp[8], dd[8];
         auto fused = [&](auto MASK_) {
             constexpr bool MASK = decltype(MASK_)::value;
-            using Sched = LdsSched<NM, PER_M, PF, PER_R>;
+            using Sched = LdsSched<NM, PER_M, PF, NR, PER_R>;
             bf16x8 fr[NM];
             f32x4 l4[4], d4[4];
             lds_read16<b * 128>(l4[0], lcur);
@@ -917,7 +927,7 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
             static_for<0, 16>([&](auto E_) {
                 constexpr int e = decltype(E_)::value, gq = e >> 2, el = e & 3;
                 if constexpr (el == 0) { lds_wait<Sched::allowed_d(e)>(l4[gq]); lds_wait<Sched::allowed_d(e)>(d4[gq]); }
-                if constexpr (e % PER_M == 0) {
+                if constexpr (e % PER_M == 0 && e / PER_M < NM) {
                     constexpr int j = e / PER_M;
                     lds_wait<Sched::allowed_frag(e)>(fr[j]);
                     // (the vector ALU reads these results no earlier than the next block's softmax, behind this block's
@@ -928,7 +938,7 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
                     else mfma_v(dpc[b ^ 1], fr[j], vf[j >> 1]);
                     if constexpr (j + PF < NM) issue_frag(fr[j + PF], fa, BN, std::integral_constant<int, j + PF>{});
                 }
-                if constexpr (e % PER_R == 0) {                      // read r: feature block r / 4; dO or Q; first or second quad
+                if constexpr (Sched::has_tr(e)) {                    // read r: feature block r / 4; dO or Q; first or second quad
                     constexpr int r = e / PER_R, c = r >> 2;
                     if constexpr ((r & 3) == 0) o0[c] = TrReader<D>::template read_at<b, 0, c, 0, TILE>(trc);
                     if constexpr ((r & 3) == 1) o1[c] = TrReader<D>::template read_at<b, 0, c, 1, TILE>(trc);
@@ -954,8 +964,7 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
             const uint4 v = make_uint4(w[0], w[1], w[2], w[3]);
             return *reinterpret_cast<const bf16x8 *>(&v);
         };
-        if constexpr (CB > 2) asm volatile("s_waitcnt lgkmcnt(0)" : TR_WAIT4(o0), TR_WAIT4(o1), TR_WAIT4(q0f), TR_WAIT4(q1f));
-        else asm volatile("s_waitcnt lgkmcnt(0)" : TR_WAIT2(o0), TR_WAIT2(o1), TR_WAIT2(q0f), TR_WAIT2(q1f));
+        tr_wait<CB>(o0, o1, q0f, q1f);
         static_for<0, CB>([&](auto C_) {                             // in flight during the next 2 CB MFMAs
             constexpr int c = decltype(C_)::value;
             o2[c] = TrReader<D>::template read_at<b, 1, c, 0, TILE>(trc); o3[c] = TrReader<D>::template read_at<b, 1, c, 1, TILE>(trc);
@@ -969,8 +978,7 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
                 dk[c] = MFMA(join(q0f[c], q1f[c]), dsf, dk[c]);
             }
         }
-        if constexpr (CB > 2) asm volatile("s_waitcnt lgkmcnt(0)" : TR_WAIT4(o2), TR_WAIT4(o3), TR_WAIT4(q2f), TR_WAIT4(q3f));
-        else asm volatile("s_waitcnt lgkmcnt(0)" : TR_WAIT2(o2), TR_WAIT2(o3), TR_WAIT2(q2f), TR_WAIT2(q3f));
+        tr_wait<CB>(o2, o3, q2f, q3f);
         {
             const bf16x8 pf = frag4(pp + 4), dsf = frag4(dd + 4);
 #pragma unroll
@@ -1012,7 +1020,7 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
         const bool act = qt < w_hi_max && qt + BT2 > w_lo_min;
         if (act) {
 #pragma unroll
-            for (int k = 0; k < KS; ++k) { fcur[k] = f0[k] + slot * SLOT; fnxt[k] = f0[k] + nslot * SLOT; }
+            for (int k = 0; k < KD; ++k) { fcur[k] = f0[k] + slot * SLOT; fnxt[k] = f0[k] + nslot * SLOT; }
 #pragma unroll
             for (int x = 0; x < 8; ++x) trc[x] = tr.off[x] + slot * SLOT;
             lcur = l0 + slot * SLOT;
@@ -1233,21 +1241,21 @@ hipError_t set_smem(K kern, int bytes) {
 template <int D>
 constexpr int FWD_WAVES = D <= 64 ? 4 : 8;
 
-template <int D>
+template <int D, int KS, int CB>
 hipError_t launch_fwd(const AttnArgs &a, hipStream_t st) {
     static std::atomic<bool> configured{false};     // set once; concurrent first calls repeat the same idempotent set-up
     constexpr int W = FWD_WAVES<D>;
     const int smem = std::max(2 * 2 * BT2 * D * 2 + (W == 4 ? 0 : W * ROWS32_BYTES<D>), W * STAGE_BYTES<D>);
     if (!configured.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_fwd_kernel<D, W>, smem);
+        hipError_t e = set_smem(attn_fwd_kernel<D, KS, CB, W>, smem);
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
     }
-    attn_fwd_kernel<D, W><<<dim3(a.nh, ceil_div(a.T, FQ) * (FQ / (W * 32))), W * 64, smem, st>>>(a);
+    attn_fwd_kernel<D, KS, CB, W><<<dim3(a.nh, ceil_div(a.T, FQ) * (FQ / (W * 32))), W * 64, smem, st>>>(a);
     return hipGetLastError();
 }
 
-template <int D>
+template <int D, int KS, int CB>
 hipError_t launch_bwd(const AttnArgs &a, hipStream_t st) {
     static std::atomic<bool> configured{false};     // set once; concurrent first calls repeat the same idempotent set-up
     constexpr bool PIPELINED = D > 64;                  // see attn_dkv_plain_kernel
@@ -1255,16 +1263,16 @@ hipError_t launch_bwd(const AttnArgs &a, hipStream_t st) {
     static_assert(4 * STAGE32_BYTES<D> <= 2 * DKV_SLOT + 2 * DKV_STAGE_BYTES<D>, "room for the staged fp32 rows");
     const int smem_dq = std::max(DQ_LDS_BYTES<D>, 8 * STAGE_BYTES<D>), smem_dkv = PIPELINED ? 3 * DKV_SLOT + DKV_STAGE_BYTES<D> : 2 * DKV_SLOT + 2 * DKV_STAGE_BYTES<D>;
     if (!configured.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_dq_kernel<D>, smem_dq);
+        hipError_t e = set_smem(attn_dq_kernel<D, KS, CB>, smem_dq);
         if (e != hipSuccess) return e;
-        if constexpr (PIPELINED) e = set_smem(attn_dkv_kernel<D>, smem_dkv);
+        if constexpr (PIPELINED) e = set_smem(attn_dkv_kernel<D, KS, CB>, smem_dkv);
         else e = set_smem(attn_dkv_plain_kernel<D>, smem_dkv);
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
     }
-    attn_dq_kernel<D><<<dim3(a.nh, ceil_div(a.T, FQ)), 512, smem_dq, st>>>(a);
+    attn_dq_kernel<D, KS, CB><<<dim3(a.nh, ceil_div(a.T, FQ)), 512, smem_dq, st>>>(a);
     const dim3 grid(a.nkv, ceil_div(a.T, BQ), a.dkv_parts);
-    if constexpr (PIPELINED) attn_dkv_kernel<D><<<grid, 256, smem_dkv, st>>>(a);
+    if constexpr (PIPELINED) attn_dkv_kernel<D, KS, CB><<<grid, 256, smem_dkv, st>>>(a);
     else attn_dkv_plain_kernel<D><<<grid, 256, smem_dkv, st>>>(a);
     if (a.dkv_parts > 1) dkv_reduce_kernel<<<ceil_div((long)a.T * 2 * a.nkv * (a.d / 8), 256), 256, 0, st>>>(a);
     return hipGetLastError();
@@ -1275,7 +1283,8 @@ hipError_t launch_bwd(const AttnArgs &a, hipStream_t st) {
 hipError_t attn_mfma_fwd(const AttnArgs &a, hipStream_t st) {
     if (a.T == 0) return hipSuccess;
     if ((size_t)a.T * a.ld_qkv * 2 >= MAX_TENSOR_BYTES) return hipErrorInvalidValue;
-    return a.d <= 64 ? launch_fwd<64>(a, st) : launch_fwd<128>(a, st);
+    return a.d <= 64 ? launch_fwd<64, 4, 2>(a, st) : a.d <= 80 ? launch_fwd<128, 5, 3>(a, st) : a.d <= 96 ? launch_fwd<128, 6, 3>(a, st)
+                                                                                             : launch_fwd<128, 8, 4>(a, st);
 }
 
 // Workgroups that share a group's query heads in the dK/dV kernels.  One workgroup per 128 keys and key/value head walks all
@@ -1301,7 +1310,8 @@ hipError_t attn_mfma_bwd(const AttnArgs &args, hipStream_t st) {
     AttnArgs a = args;
     a.dkv_parts = attn_dkv_parts(a.T, a.nh, a.nkv, a.d);
     if (a.dkv_parts > 1 && a.dkv_part_bytes < a.dkv_parts * attn_dkv_part_bytes(a.T, a.nkv, a.d)) a.dkv_parts = 1;
-    return a.d <= 64 ? launch_bwd<64>(a, st) : launch_bwd<128>(a, st);
+    return a.d <= 64 ? launch_bwd<64, 4, 2>(a, st) : a.d <= 80 ? launch_bwd<128, 5, 3>(a, st) : a.d <= 96 ? launch_bwd<128, 6, 3>(a, st)
+                                                                                             : launch_bwd<128, 8, 4>(a, st);
 }
 
 }  // namespace mmt

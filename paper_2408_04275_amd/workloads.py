@@ -273,7 +273,9 @@ def hardware_flops(shape: LayerShape, cu: np.ndarray, modes: np.ndarray) -> Dict
     (wider heads)."""
     cu = np.asarray(cu, dtype=np.int64)
     T = int(cu[-1])
-    d_pad = 64 if shape.head_dim <= 64 else 128
+    d = shape.head_dim
+    # features of the products contracted over the head (scores, dP) and of those whose rows are the head's features
+    d_in, d_out = (64, 64) if d <= 64 else (80, 96) if d <= 80 else (96, 96) if d <= 96 else (128, 128)
     seg = np.repeat(np.arange(len(cu) - 1), np.diff(cu))
     start, end = cu[seg], cu[seg + 1]
     bidir = np.asarray(modes)[seg] == BIDIR
@@ -289,7 +291,7 @@ def hardware_flops(shape: LayerShape, cu: np.ndarray, modes: np.ndarray) -> Dict
             for kb in range(kbeg, kend + (-(kend - kbeg)) % 64, 32):
                 blocks_q += kb < hi and kb + 32 > lo
     blocks_k = 0                                                  # ... by the dK/dV kernel
-    per_step = d_pad > 64
+    per_step = d > 64
     for k0 in range(0, T, 128):
         qbeg, qend = int(k_lo[k0]), int(k_hi[min(k0 + 128, T) - 1])
         for w0 in range(k0, min(k0 + 128, T), 32):
@@ -303,7 +305,7 @@ def hardware_flops(shape: LayerShape, cu: np.ndarray, modes: np.ndarray) -> Dict
     pairs_q, pairs_k = 1024.0 * blocks_q, 1024.0 * blocks_k
     nh = shape.n_heads
     m = model_flops(shape, cu, modes)
-    attn_fwd = 4.0 * d_pad * nh * pairs_q
-    attn_bwd = 6.0 * d_pad * nh * pairs_q + 8.0 * d_pad * nh * pairs_k
+    attn_fwd = 2.0 * (d_in + d_out) * nh * pairs_q
+    attn_bwd = (4.0 * d_in + 2.0 * d_out) * nh * pairs_q + 4.0 * (d_in + d_out) * nh * pairs_k
     return {"gemm_fwd_bwd": 3.0 * m["gemm_fwd"], "attn_fwd": attn_fwd, "attn_bwd": attn_bwd,
             "fwd_bwd": 3.0 * m["gemm_fwd"] + attn_fwd + attn_bwd}
