@@ -2,7 +2,7 @@
 // forward and backward, for packed variable-length segments.
 //
 // Tiling is on the GLOBAL token index, not per segment: a workgroup owns a run of consecutive queries
-// (256 in the forward and dQ kernels, one query per lane of 8 wavefronts; both lane halves of a wavefront
+// (256 or 128 in the forward and dQ kernels, one query per lane of 8 or 4 wavefronts; both lane halves of a wavefront
 // mirror the same 32 queries) or keys (128 in the dK/dV kernel).  Every query carries its own key range
 // [lo, hi) = [segment start, causal ? q + 1 : segment end), so a tile may straddle any number of
 // segment boundaries and a pack of many short segments still fills whole tiles.  The key loop of
@@ -148,7 +148,7 @@ __device__ __forceinline__ RowInfo key_range(const int2 *info, int k, int T) {
 // ------------------------------------------------------------------------------------------
 // shared pieces
 // ------------------------------------------------------------------------------------------
-constexpr int FQ = 256;         // queries per workgroup of the forward and dQ kernels (8 wavefronts x 32)
+constexpr int FQ = 256;         // queries per tile of the dispatch order of the forward and dQ kernels (8 wavefronts x 32)
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((ext_vector_type(4))) uint32_t rawx4;
@@ -351,8 +351,10 @@ template <int D>
 constexpr int ROWS32_BYTES = 32 * D * 2;              // 32 rows of one operand, staged in the tile layout
 template <int D>
 constexpr int DKV_STAGE_BYTES = 4 * ROWS32_BYTES<D>;  // the pipelined dK/dV kernel's K rows, behind its three slots
-template <int D>
-constexpr int DQ_LDS_BYTES = 2 * BT2 * D * 2 + 8 * 2 * ROWS32_BYTES<D>;   // the dQ kernel: first slot, then Q and dO rows of 8 wavefronts
+// the dQ kernel: first slot, then the Q and dO rows of 8 wavefronts (the second slot lies there later), or two slots, the second
+// of which holds the rows of one operand at a time of 4 wavefronts
+template <int D, int WAVES>
+constexpr int DQ_LDS_BYTES = WAVES == 8 ? 2 * BT2 * D * 2 + 8 * 2 * ROWS32_BYTES<D> : 2 * 2 * BT2 * D * 2;
 template <int D, int CB>
 __device__ __forceinline__ void store_rows(uint8_t *stage, const f32x16 (&acc)[CB], float scale, bf16_t *dst, long ld,
                                            int rows_valid, int dh) {
@@ -452,18 +454,21 @@ __global__ __launch_bounds__(256) void dkv_reduce_kernel(AttnArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// backward: dQ (and -D, D = rowsum(dO * O)).  Same roles as the forward kernel: 8 wavefronts x 32 queries.
+// backward: dQ (and -D, D = rowsum(dO * O)).  Same roles as the forward kernel: 8 or 4 wavefronts x 32 queries.
 // ------------------------------------------------------------------------------------------
-template <int D, int KS, int CB>
-__global__ __launch_bounds__(512) void attn_dq_kernel(AttnArgs a) {
+template <int D, int KS, int CB, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 2) void attn_dq_kernel(AttnArgs a) {
+    constexpr int FQW = WAVES * 32;                                // queries per workgroup
     constexpr int TILE = BT2 * D * 2, SLOT = 2 * TILE;             // K tile, then V tile
     constexpr int COPIES = BT2 * D * 2 / 1024 / 4;                 // per wavefront (4 wavefronts per tile)
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    add_busy(a.cu_busy ? a.cu_busy + 1024 : nullptr, false);
-
     // grid: x = head, y = position in the dispatch order of the query tiles (heaviest first)
     const int head = blockIdx.x, g = head / (a.nh / a.nkv);
-    const int q0 = (a.use_order ? a.order_q[blockIdx.y] : blockIdx.y) * FQ;
+    // (of FQ-query tiles: the workgroups of one tile, two with four wavefronts each, follow each other)
+    constexpr int PER_TILE = FQ / FQW;
+    const int q0 = (a.use_order ? a.order_q[blockIdx.y / PER_TILE] * PER_TILE + blockIdx.y % PER_TILE : blockIdx.y) * FQW;
+    if (q0 >= a.T) return;                                         // second half of a last tile that the pack only half fills
+    add_busy(a.cu_busy ? a.cu_busy + 1024 : nullptr, false);
     // the wavefront's index as a scalar: what is derived from it (copy destinations, buffer descriptors) stays uniform
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
     const int T = a.T;
@@ -477,17 +482,17 @@ __global__ __launch_bounds__(512) void attn_dq_kernel(AttnArgs a) {
     const bool valid = q < T;
     const WaveBounds wb = wave_bounds(me, q0 + wave * 32, T);
     const int w_lo_min = wb.lo_min, w_lo_max = wb.lo_max, w_hi_max = wb.hi_max, w_hi_min = wb.hi_min;
-    const RowInfo first = query_range(a.tok_info, q0, T), last = query_range(a.tok_info, min(q0 + FQ, T) - 1, T);
+    const RowInfo first = query_range(a.tok_info, q0, T), last = query_range(a.tok_info, min(q0 + FQW, T) - 1, T);
     const int kbeg = first.lo, kend = last.hi;
 
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(qkv), 0, (int)(uint32_t)((size_t)T * ld * 2), 0x00020000);
-    // wavefronts 4..7 copy the K tile, wavefronts 0..3 the V tile
+    // eight wavefronts: 4..7 copy the K tile, 0..3 the V tile; four wavefronts: each copies its quarter of both
     RowCopier<D, COPIES> cp;
     cp.init((wave & 3) * COPIES, ld, dh);
     auto copy_kv = [&](uint8_t *slot, int kt) {
-        if (wave >= 4) cp.issue(rs, slot, kt, ld, nq + g * dh);
-        else cp.issue(rs, slot + TILE, kt, ld, nq + nk + g * dh);
+        if (WAVES == 4 || wave >= 4) cp.issue(rs, slot, kt, ld, nq + g * dh);
+        if (WAVES == 4 || wave < 4) cp.issue(rs, slot + TILE, kt, ld, nq + nk + g * dh);
     };
     TrReader<D> tr;
     tr.init((uint32_t)(uintptr_t)(lds_void *)smem);
@@ -507,17 +512,31 @@ __global__ __launch_bounds__(512) void attn_dq_kernel(AttnArgs a) {
         RowCopier<D, ROWS32_BYTES<D> / 1024> cp_q, cp_o;
         cp_q.init(0, ld, dh);
         cp_o.init(0, nq, dh);
-        uint8_t *st_q = smem + SLOT + wave * 2 * ROWS32_BYTES<D>, *st_do = st_q + ROWS32_BYTES<D>;
-        cp_q.issue(rs, st_q, q0 + wave * 32, ld, head * dh);
-        cp_o.issue(rs_do, st_do, q0 + wave * 32, nq, head * dh);
-        copy_kv(smem, kbeg);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        uint8_t *st_q = smem + SLOT + wave * (WAVES == 8 ? 2 : 1) * ROWS32_BYTES<D>;
+        if constexpr (WAVES == 8) {
+            uint8_t *st_do = st_q + ROWS32_BYTES<D>;
+            cp_q.issue(rs, st_q, q0 + wave * 32, ld, head * dh);
+            cp_o.issue(rs_do, st_do, q0 + wave * 32, nq, head * dh);
+            copy_kv(smem, kbeg);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            qf[ks] = frag_k<D>(st_q, l32, ks, half);
-            dof[ks] = frag_k<D>(st_do, l32, ks, half);
+            for (int ks = 0; ks < KS; ++ks) {
+                qf[ks] = frag_k<D>(st_q, l32, ks, half);
+                dof[ks] = frag_k<D>(st_do, l32, ks, half);
+            }
+        } else {                                                     // one operand after the other in the same place
+            cp_q.issue(rs, st_q, q0 + wave * 32, ld, head * dh);
+            copy_kv(smem, kbeg);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) qf[ks] = frag_k<D>(st_q, l32, ks, half);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            cp_o.issue(rs_do, st_q, q0 + wave * 32, nq, head * dh);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) dof[ks] = frag_k<D>(st_q, l32, ks, half);
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // Q has been read: O may take its place
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // read: O may take the place
         cp_o.issue(rs_o, st_q, q0 + wave * 32, nq, head * dh);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
@@ -634,7 +653,7 @@ constexpr float LAZY_LOG2 = 8.f;
 // forward.  WAVES wavefronts x 32 queries per workgroup, two wavefronts per SIMD either way (so that one can run its
 // softmax on the vector ALUs while the other occupies the matrix core): 8 wavefronts = 256 queries, one workgroup per
 // compute unit (every K / V tile is fetched once for 256 queries), or 4 wavefronts = 128 queries, two workgroups per
-// compute unit (less masked work on short segments; used for 64-wide heads).  The keys are walked 64 at a time through
+// compute unit (see four_waves).  The keys are walked 64 at a time through
 // two LDS slots of {K tile, V tile}, both copied global -> LDS directly in their memory order (wavefronts 4..7 copy K,
 // 0..3 copy V).  O^T = V^T . P^T takes V^T from the row-major tile by the transposing LDS read, the same scheme as
 // dQ^T = K^T . dS^T above.  One barrier per step: after it every wavefront has finished the previous step, so the slot
@@ -1235,16 +1254,23 @@ hipError_t set_smem(K kern, int bytes) {
     return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// Wavefronts per workgroup of the forward kernel: four for 64-wide heads (packs of ViT-sized segments: 0.068 -> 0.054 ms
-// on the encoder workload), eight for 128-wide heads (no difference there within 2 %, and half the K / V tile traffic).
-// The dQ kernel, which has the same structure, gains nothing from four (0.182 -> 0.185 ms backward on that workload).
+// Wavefronts per workgroup of the forward and dQ kernels: four (128 queries, two workgroups per compute unit) or eight (256, one).
+// Four split the pack more finely: more compute units at work on short packs, less masked work on short segments, a smaller
+// last round.  Eight fetch every K / V tile half as often, which tells where query tiles walk many keys and there are tiles
+// enough for both.  64-wide heads always take four (encoder packs: forward 0.068 -> 0.054 ms; dQ + dK/dV 144 -> 131 us on 3000
+// bidirectional tokens, 136 -> 136 us on 8192).  Wider ones, forward / backward us with eight -> four: 1031 causal tokens of 32
+// heads in 4 segments 29 / 65 -> 25 / 63, 3000 in one long document 88 / 270 -> 79 / 263, 8192 in segments of 700
+// 114 / 396 -> 111 / 398; but 8192 in one long document (60 steps of 64 keys per tile on average) 478 / 1593 -> 497 / 1621, and
+// 4111 (30 steps, 544 workgroups) 137 / 449 -> 143 / 456.
 template <int D>
-constexpr int FWD_WAVES = D <= 64 ? 4 : 8;
+bool four_waves(const AttnArgs &a) {
+    const long tiles = ceil_div(a.T, FQ);
+    return D <= 64 || tiles * a.nh < 512 || (a.q_steps > 0 && a.q_steps <= 14 * tiles);
+}
 
-template <int D, int KS, int CB>
+template <int D, int KS, int CB, int W>
 hipError_t launch_fwd(const AttnArgs &a, hipStream_t st) {
     static std::atomic<bool> configured{false};     // set once; concurrent first calls repeat the same idempotent set-up
-    constexpr int W = FWD_WAVES<D>;
     const int smem = std::max(2 * 2 * BT2 * D * 2 + (W == 4 ? 0 : W * ROWS32_BYTES<D>), W * STAGE_BYTES<D>);
     if (!configured.load(std::memory_order_acquire)) {
         hipError_t e = set_smem(attn_fwd_kernel<D, KS, CB, W>, smem);
@@ -1254,23 +1280,43 @@ hipError_t launch_fwd(const AttnArgs &a, hipStream_t st) {
     attn_fwd_kernel<D, KS, CB, W><<<dim3(a.nh, ceil_div(a.T, FQ) * (FQ / (W * 32))), W * 64, smem, st>>>(a);
     return hipGetLastError();
 }
+template <int D, int KS, int CB, int W>
+hipError_t launch_dq(const AttnArgs &a, hipStream_t st) {
+    static std::atomic<bool> configured{false};
+    const int smem = std::max(DQ_LDS_BYTES<D, W>, W * STAGE_BYTES<D>);
+    if (!configured.load(std::memory_order_acquire)) {
+        hipError_t e = set_smem(attn_dq_kernel<D, KS, CB, W>, smem);
+        if (e != hipSuccess) return e;
+        configured.store(true, std::memory_order_release);
+    }
+    attn_dq_kernel<D, KS, CB, W><<<dim3(a.nh, ceil_div(a.T, FQ) * (FQ / (W * 32))), W * 64, smem, st>>>(a);
+    return hipGetLastError();
+}
+
+template <int D, int KS, int CB>
+hipError_t launch_fwd(const AttnArgs &a, hipStream_t st) {
+    if constexpr (D > 64)
+        if (!four_waves<D>(a)) return launch_fwd<D, KS, CB, 8>(a, st);
+    return launch_fwd<D, KS, CB, 4>(a, st);
+}
 
 template <int D, int KS, int CB>
 hipError_t launch_bwd(const AttnArgs &a, hipStream_t st) {
-    static std::atomic<bool> configured{false};     // set once; concurrent first calls repeat the same idempotent set-up
+    static std::atomic<bool> configured{false};
     constexpr bool PIPELINED = D > 64;                  // see attn_dkv_plain_kernel
     constexpr int DKV_SLOT = 2 * BT2 * D * 2 + 2 * BT2 * 4;
     static_assert(4 * STAGE32_BYTES<D> <= 2 * DKV_SLOT + 2 * DKV_STAGE_BYTES<D>, "room for the staged fp32 rows");
-    const int smem_dq = std::max(DQ_LDS_BYTES<D>, 8 * STAGE_BYTES<D>), smem_dkv = PIPELINED ? 3 * DKV_SLOT + DKV_STAGE_BYTES<D> : 2 * DKV_SLOT + 2 * DKV_STAGE_BYTES<D>;
+    const int smem_dkv = PIPELINED ? 3 * DKV_SLOT + DKV_STAGE_BYTES<D> : 2 * DKV_SLOT + 2 * DKV_STAGE_BYTES<D>;
+    hipError_t e;
     if (!configured.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_dq_kernel<D, KS, CB>, smem_dq);
-        if (e != hipSuccess) return e;
         if constexpr (PIPELINED) e = set_smem(attn_dkv_kernel<D, KS, CB>, smem_dkv);
         else e = set_smem(attn_dkv_plain_kernel<D>, smem_dkv);
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
     }
-    attn_dq_kernel<D, KS, CB><<<dim3(a.nh, ceil_div(a.T, FQ)), 512, smem_dq, st>>>(a);
+    if (four_waves<D>(a)) e = launch_dq<D, KS, CB, 4>(a, st);
+    else if constexpr (D > 64) e = launch_dq<D, KS, CB, 8>(a, st);
+    if (e != hipSuccess) return e;
     const dim3 grid(a.nkv, ceil_div(a.T, BQ), a.dkv_parts);
     if constexpr (PIPELINED) attn_dkv_kernel<D, KS, CB><<<grid, 256, smem_dkv, st>>>(a);
     else attn_dkv_plain_kernel<D><<<grid, 256, smem_dkv, st>>>(a);

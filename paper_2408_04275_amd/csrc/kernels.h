@@ -67,6 +67,7 @@ struct AttnArgs {
     // MFMA path: dispatch order of the query tiles (256 queries: forward, dQ) and of the key tiles (128
     // keys: dK/dV), heaviest first; use_order = 0 means index order (more tiles than the tables hold)
     int use_order;
+    int q_steps;                // 64-key steps of all query tiles together (0: not counted, use_order = 0)
     uint8_t order_q[64];
     uint8_t order_k[128];
     // MFMA path, measurement aid: when not null, device [3][1024] counters; every workgroup adds its run time

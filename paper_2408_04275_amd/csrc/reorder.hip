@@ -54,7 +54,7 @@ int intra_reorder(const double *sizes, int n, int m, int32_t *order, int32_t *gr
 namespace {
 struct TileOrderCache {
     uint64_t key = 0;
-    int S = -1, T = -1, default_mode = -1, use_order = 0;
+    int S = -1, T = -1, default_mode = -1, q_steps = 0;
     uint8_t order_q[sizeof(AttnArgs::order_q)], order_k[sizeof(AttnArgs::order_k)];
 };
 thread_local TileOrderCache g_tile_order;
@@ -81,7 +81,7 @@ void order_desc(const int *w, int n, uint8_t *idx) {
 void attn_tile_order(const int32_t *cu, const uint8_t *modes, int default_mode, int S, int T, AttnArgs &a) {
     constexpr int FQ = 256, BK = 128, MAXQ = (int)sizeof(a.order_q), MAXK = (int)sizeof(a.order_k);
     const int nq = (T + FQ - 1) / FQ, nk = (T + BK - 1) / BK;
-    a.use_order = 0;
+    a.use_order = a.q_steps = 0;
     if (nq > MAXQ || nk > MAXK || T == 0) return;              // more tiles than the tables hold: index order
     TileOrderCache &c = g_tile_order;
     const uint64_t key = pack_hash(cu, modes, S);
@@ -103,11 +103,14 @@ void attn_tile_order(const int32_t *cu, const uint8_t *modes, int default_mode, 
         }
         order_desc(wq, nq, c.order_q);
         order_desc(wk, nk, c.order_k);
-        c.key = key; c.S = S; c.T = T; c.default_mode = default_mode; c.use_order = 1;
+        c.q_steps = 0;
+        for (int i = 0; i < nq; ++i) c.q_steps += wq[i];
+        c.key = key; c.S = S; c.T = T; c.default_mode = default_mode;
     }
     for (int i = 0; i < nq; ++i) a.order_q[i] = c.order_q[i];
     for (int i = 0; i < nk; ++i) a.order_k[i] = c.order_k[i];
     a.use_order = 1;
+    a.q_steps = c.q_steps;
 }
 
 }  // namespace mmt

@@ -266,7 +266,8 @@ def hardware_flops(shape: LayerShape, cu: np.ndarray, modes: np.ndarray) -> Dict
     the masked part of every 32 x 32 block that is not skipped as a whole (diagonal and segment-boundary blocks),
     the recomputation of the scores in both backward kernels (dQ kernel: scores, dP, dQ = 6 d per pair;
     dK/dV kernel: scores, dP, dV, dK = 8 d per pair) and the zero padding of head dimensions that are not 64 or 128.
-    The block rules restate the kernels' launch geometry: forward and dQ: 256 queries per workgroup walk the
+    The block rules restate the kernels' launch geometry: forward and dQ: 256 queries per workgroup (128 in the form for
+    narrow heads and short packs, whose blocks start elsewhere but number about as many) walk the
     keys [first query's first key, last query's last key) in 64-key steps, and a wavefront (32 queries) runs a 32-key
     block unless the block lies outside [its first query's first key, its last query's last key); dK/dV: 128 keys per
     workgroup, 32 per wavefront, walk the queries in 64-query steps, skipping per block (64-wide heads) or per step
