@@ -64,6 +64,8 @@ __device__ __forceinline__ void load_raw8(const bf16_t *p, Raw8<bf16_t> &r) {
 __device__ __forceinline__ void load_raw8(const float *p, Raw8<float> &r) {
     r.a = *reinterpret_cast<const float4 *>(p); r.b = *reinterpret_cast<const float4 *>(p + 4);
 }
+__device__ __forceinline__ Raw8<bf16_t> load_plain8(const bf16_t *p) { return {*reinterpret_cast<const uint4 *>(p)}; }
+__device__ __forceinline__ Raw8<float> load_plain8(const float *p) { return {*reinterpret_cast<const float4 *>(p), *reinterpret_cast<const float4 *>(p + 4)}; }
 __device__ __forceinline__ void unpack8(const Raw8<bf16_t> &r, float (&v)[8]) {
     const uint32_t w[4] = {r.a.x, r.a.y, r.a.z, r.a.w};
 #pragma unroll
@@ -119,51 +121,9 @@ hipError_t prep_tokens(const int *cu, const uint8_t *modes, int default_mode, in
 }
 
 // ---- normalisation forward -----------------------------------------------------------
-// One workgroup per row.  RMSNorm: out = x * rsqrt(mean(x^2) + eps) * g.
+// RMSNorm: out = x * rsqrt(mean(x^2) + eps) * g.
 // LayerNorm: out = (x - mean) * rsqrt(var_biased + eps) * g + b (variance about the mean, two passes).
-template <typename T, bool LN>
-__global__ __launch_bounds__(256) void norm_fwd_kernel(const T *__restrict__ x, const T *__restrict__ g,
-                                                       const T *__restrict__ b, T *__restrict__ out,
-                                                       float *__restrict__ mean, float *__restrict__ rstd,
-                                                       int H, float eps) {
-    __shared__ float red[4];
-    const size_t row = blockIdx.x;
-    const T *xr = x + row * H;
-    float v[8];
-    float mu = 0.f;
-    if (LN) {
-        float s = 0.f;
-        for (int c = threadIdx.x * 8; c < H; c += 2048) {
-            load8(xr + c, v);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s += v[j];
-        }
-        mu = block_sum<4>(s, red) / H;
-    }
-    float ss = 0.f;
-    for (int c = threadIdx.x * 8; c < H; c += 2048) {
-        load8(xr + c, v);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ss += (v[j] - mu) * (v[j] - mu);
-    }
-    const float r = 1.0f / sqrtf(block_sum<4>(ss, red) / H + eps);
-    if (threadIdx.x == 0) {
-        rstd[row] = r;
-        if (LN) mean[row] = mu;
-    }
-    float gv[8], bv[8];
-    for (int c = threadIdx.x * 8; c < H; c += 2048) {
-        load8(xr + c, v);
-        load8(g + c, gv);
-        if (LN) load8(b + c, bv);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (v[j] - mu) * r * gv[j] + (LN ? bv[j] : 0.f);
-        store8(out + row * H + c, v);
-    }
-}
-
-// The same for rows of at most 256 * 8 * MAXC elements, a workgroup walking rows blockIdx.x, blockIdx.x + gridDim.x, ...:
-// the row stays in registers between the statistics and the scaling (one read of x), the gain and bias are fetched once
+// Rows of at most 256 * 8 * MAXC elements, a workgroup walking rows blockIdx.x, blockIdx.x + gridDim.x, ...: the row stays in registers between the statistics and the scaling (one read of x), the gain and bias are fetched once
 // per workgroup, and the next row is requested before the current one is reduced, so that a workgroup always has a
 // row in flight (with one short-lived workgroup per row the kernel reached 5.5 TB/s).
 template <typename T, bool LN, int MAXC>
@@ -226,33 +186,113 @@ __global__ __launch_bounds__(256) void norm_fwd_rows_kernel(const T *__restrict_
     }
 }
 
-// One launch of norm_fwd_rows_kernel: exactly as many workgroups as the device keeps resident at once (a grid one
-// workgroup per compute unit larger runs a second, nearly empty round: 22.9 -> 26.9 us at the 7B shape).
+// The same for rows of at most 512 * MAXC elements (MAXC <= 4), one wavefront per row: a 1024-wide row gives only half of a
+// workgroup's threads a chunk of 8, and its sums are a few cross-lane steps without a barrier.  9536 rows of 1024: 15.4 -> 10.4 us.
 template <typename T, bool LN, int MAXC>
+__global__ __launch_bounds__(256) void norm_fwd_wave_kernel(const T *__restrict__ x, const T *__restrict__ g,
+                                                            const T *__restrict__ b, T *__restrict__ out,
+                                                            float *__restrict__ mean, float *__restrict__ rstd,
+                                                            int nrows, int H, float eps) {
+    const int lane = threadIdx.x & 63, step = gridDim.x * 4;
+    int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    float gv[MAXC][8], bv[LN ? MAXC : 1][8];
+    Raw8<T> nxt[MAXC];
+    auto request = [&](int r) {
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            const int c = (lane + i * 64) * 8;
+            if (c < H && r < nrows) nxt[i] = load_plain8(x + (size_t)r * H + c);
+        }
+    };
+    request(row);
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+        const int c = (lane + i * 64) * 8;
+        if (c < H) {
+            load8(g + c, gv[i]);
+            if (LN) load8(b + c, bv[i]);
+        }
+    }
+    for (; row < nrows; row += step) {
+        float cur[MAXC][8];
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            if ((lane + i * 64) * 8 < H) unpack8(nxt[i], cur[i]);
+            else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) cur[i][j] = 0.f;
+            }
+        }
+        request(row + step);
+        float mu = 0.f;
+        if (LN) {
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < MAXC; ++i)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) s += cur[i][j];
+            mu = wave_sum(s) / H;
+        }
+        float ss = 0.f;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i)
+            if ((lane + i * 64) * 8 < H) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) ss += (cur[i][j] - mu) * (cur[i][j] - mu);
+            }
+        const float r = 1.0f / sqrtf(wave_sum(ss) / H + eps);
+        if (lane == 0) {
+            rstd[row] = r;
+            if (LN) mean[row] = mu;
+        }
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            const int c = (lane + i * 64) * 8;
+            if (c < H) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) cur[i][j] = (cur[i][j] - mu) * r * gv[i][j] + (LN ? bv[i][j] : 0.f);
+                store8(out + (size_t)row * H + c, cur[i]);
+            }
+        }
+    }
+}
+
+// One launch of norm_fwd_rows_kernel or norm_fwd_wave_kernel: exactly as many workgroups as the device keeps resident at once (a grid one
+// workgroup per compute unit larger runs a second, nearly empty round: 22.9 -> 26.9 us at the 7B shape).
+template <typename K>
+hipError_t resident_workgroups(std::atomic<int> &cached, K kern, int &grid) {
+    grid = cached.load(std::memory_order_relaxed);
+    if (grid) return hipSuccess;
+    int dev = 0, cus = 0, per_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0);
+    if (e != hipSuccess) return e;
+    grid = (cus > 0 ? cus : 256) * (per_cu > 0 ? per_cu : 4);
+    cached.store(grid, std::memory_order_relaxed);
+    return hipSuccess;
+}
+// WAVES_ROWS: a wavefront per row (four per workgroup), otherwise a workgroup per row
+template <typename T, bool LN, int MAXC, bool WAVE_ROWS>
 hipError_t launch_norm_fwd_rows(const void *x, const void *g, const void *b, void *out, float *mean, float *rstd, int nrows,
                                 int H, float eps, hipStream_t st) {
     static std::atomic<int> resident{0};
-    int grid = resident.load(std::memory_order_relaxed);
-    if (grid == 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, norm_fwd_rows_kernel<T, LN, MAXC>, 256, 0);
-        if (e != hipSuccess) return e;
-        grid = (cus > 0 ? cus : 256) * (per_cu > 0 ? per_cu : 4);
-        resident.store(grid, std::memory_order_relaxed);
-    }
-    if (nrows < grid) grid = nrows;
-    norm_fwd_rows_kernel<T, LN, MAXC><<<grid, 256, 0, st>>>((const T *)x, (const T *)g, (const T *)b, (T *)out, mean, rstd, nrows, H, eps);
+    auto kern = WAVE_ROWS ? norm_fwd_wave_kernel<T, LN, MAXC> : norm_fwd_rows_kernel<T, LN, MAXC>;
+    int grid = 0;
+    hipError_t e = resident_workgroups(resident, kern, grid);
+    if (e != hipSuccess) return e;
+    const int all = WAVE_ROWS ? ceil_div(nrows, 4) : nrows;
+    kern<<<all < grid ? all : grid, 256, 0, st>>>((const T *)x, (const T *)g, (const T *)b, (T *)out, mean, rstd, nrows, H, eps);
     return hipGetLastError();
 }
 
 hipError_t norm_fwd(int dtype, bool layernorm, const void *x, const void *g, const void *b, void *out,
                     float *mean, float *rstd, int T, int H, float eps, hipStream_t st) {
     if (T == 0) return hipSuccess;
-#define R(TT, LNV, MC) return launch_norm_fwd_rows<TT, LNV, MC>(x, g, b, out, mean, rstd, T, H, eps, st)
-#define L(TT, LNV) do { if (H % 8 == 0 && H <= 2048) R(TT, LNV, 1); else if (H % 8 == 0 && H <= 4096) R(TT, LNV, 2); else if (H % 8 == 0 && H <= 8192) R(TT, LNV, 4); \
-                        else norm_fwd_kernel<TT, LNV><<<T, 256, 0, st>>>((const TT *)x, (const TT *)g, (const TT *)b, (TT *)out, mean, rstd, H, eps); } while (0)
+    if (H % 8 || H > 8192) return hipErrorInvalidValue;
+#define R(TT, LNV, MC, WR) return launch_norm_fwd_rows<TT, LNV, MC, WR>(x, g, b, out, mean, rstd, T, H, eps, st)
+#define L(TT, LNV) do { if (H <= 512) R(TT, LNV, 1, true); else if (H <= 1024) R(TT, LNV, 2, true); else if (H <= 1536) R(TT, LNV, 3, true); \
+                        else if (H <= 2048) R(TT, LNV, 4, true); else if (H <= 4096) R(TT, LNV, 2, false); else R(TT, LNV, 4, false); } while (0)
     if (dtype == DT_F32) { if (layernorm) L(float, true); else L(float, false); }
     else { if (layernorm) L(bf16_t, true); else L(bf16_t, false); }
 #undef L
@@ -271,10 +311,15 @@ constexpr int NORM_BWD_MAXC = 4;          // column chunks of 8 per thread: H <=
                                           // built for 1 and 2 chunks: fewer registers per thread, more rows in flight)
 constexpr int NORM_BWD_GRID = 512;
 
-// narrow rows leave registers for more resident workgroups: twice the grid
+// Rows up to this width take a wavefront each (wider ones need more registers than leave room for two wavefronts per SIMD:
+// 4111 rows of 1280 15.4 -> 22.5 us)
+constexpr int NORM_BWD_WAVE_H = 1024;
+
+// up to 4096 there are registers for more resident workgroups: twice the grid; narrow rows: four rows per workgroup at a time
 int norm_bwd_blocks(int T, int H) {
-    const int grid = H <= 4096 ? 2 * NORM_BWD_GRID : NORM_BWD_GRID;
-    return T < grid ? (T > 0 ? T : 1) : grid;
+    const int grid = H > NORM_BWD_WAVE_H && H <= 4096 ? 2 * NORM_BWD_GRID : NORM_BWD_GRID;
+    const int all = H <= NORM_BWD_WAVE_H ? ceil_div(T, 4) : T;
+    return all < grid ? (all > 0 ? all : 1) : grid;
 }
 
 template <typename T, bool LN, int NORM_BWD_MAXC, bool COLS>
@@ -367,6 +412,101 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(const T *__restrict__ d_o
     }
 }
 
+// The same for rows of at most 512 * MAXC elements, one wavefront per row (as in norm_fwd_wave_kernel): no barrier per row, all
+// lanes at work on a 1024-wide row, and half the partial rows (or fewer).  9536 rows of 1024, with / without the column sums:
+// 25.1 -> 20.1 / 23.0 -> 18.1 us, and their reduction 17.2 -> 12.0.
+template <typename T, bool LN, int MAXC, bool COLS>
+__global__ __launch_bounds__(256) void norm_bwd_wave_kernel(const T *__restrict__ d_out, const T *__restrict__ x,
+                                                            const T *__restrict__ g, const float *__restrict__ mean,
+                                                            const float *__restrict__ rstd, const T *__restrict__ d_res,
+                                                            T *__restrict__ d_in, float *__restrict__ part_g,
+                                                            float *__restrict__ part_b, float *__restrict__ part_din,
+                                                            float *__restrict__ part_dres, int nrows, int H) {
+    __shared__ __attribute__((aligned(16))) float red[4][512 * MAXC];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = gridDim.x * 4;
+    float gv[MAXC][8], ag[MAXC][8], ab[LN ? MAXC : 1][8];
+    float ad[COLS ? MAXC : 1][8], ae[COLS ? MAXC : 1][8];
+    Raw8<T> pd[MAXC], px[MAXC], pr[MAXC];
+    auto request = [&](int row) {
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            const int c = (lane + i * 64) * 8;
+            if (c < H && row < nrows) {
+                load_raw8(d_out + (size_t)row * H + c, pd[i]);
+                load_raw8(x + (size_t)row * H + c, px[i]);
+                load_raw8(d_res + (size_t)row * H + c, pr[i]);
+            }
+        }
+    };
+    int row = blockIdx.x * 4 + wave;
+    request(row);
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+        const int c = (lane + i * 64) * 8;
+        if (c < H) load8(g + c, gv[i]);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            ag[i][j] = 0.f;
+            if (LN) ab[i][j] = 0.f;
+            if (COLS) { ad[i][j] = 0.f; ae[i][j] = 0.f; }
+        }
+    }
+    for (; row < nrows; row += step) {
+        const float r = rstd[row], mu = LN ? mean[row] : 0.f;
+        float dv[MAXC][8], xh[MAXC][8], rv[MAXC][8], s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i)
+            if ((lane + i * 64) * 8 < H) { unpack8(pd[i], dv[i]); unpack8(px[i], xh[i]); unpack8(pr[i], rv[i]); }
+        request(row + step);
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i)
+            if ((lane + i * 64) * 8 < H) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    xh[i][j] = (xh[i][j] - mu) * r;
+                    ag[i][j] += dv[i][j] * xh[i][j];
+                    if (LN) ab[i][j] += dv[i][j];
+                    dv[i][j] *= gv[i][j];          // ghat
+                    s0 += dv[i][j];
+                    s1 += dv[i][j] * xh[i][j];
+                }
+            }
+        s1 = wave_sum(s1) / H;
+        s0 = LN ? wave_sum(s0) / H : 0.f;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            const int c = (lane + i * 64) * 8;
+            if (c < H) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    if (COLS) ae[i][j] += rv[i][j];
+                    rv[i][j] += r * (dv[i][j] - s0 - xh[i][j] * s1);
+                    if (COLS) ad[i][j] += rv[i][j];
+                }
+                store8(d_in + (size_t)row * H + c, rv[i]);
+            }
+        }
+    }
+    // the four wavefronts' column sums, added in order, as one partial row
+    auto flush = [&](const float (&v)[MAXC][8], float *part) {
+        if (!part) return;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i)
+            if ((lane + i * 64) * 8 < H) store8(&red[wave][(lane + i * 64) * 8], v[i]);
+        __syncthreads();
+        for (int c = threadIdx.x * 4; c < H; c += 1024) {
+            f32x4 s = *reinterpret_cast<const f32x4 *>(&red[0][c]);
+#pragma unroll
+            for (int w = 1; w < 4; ++w) s += *reinterpret_cast<const f32x4 *>(&red[w][c]);
+            *reinterpret_cast<f32x4 *>(part + (size_t)blockIdx.x * H + c) = s;
+        }
+    };
+    flush(ag, part_g);
+    if constexpr (LN) flush(ab, part_b);
+    if constexpr (COLS) { flush(ad, part_din); flush(ae, part_dres); }
+}
+
 hipError_t norm_bwd(int dtype, bool layernorm, const void *d_out, const void *x, const void *g,
                     const float *mean, const float *rstd, const void *d_res, void *d_in, float *part_g,
                     float *part_b, float *part_din, float *part_dres, int T, int H, hipStream_t st) {
@@ -376,11 +516,16 @@ hipError_t norm_bwd(int dtype, bool layernorm, const void *d_out, const void *x,
     const bool cols = part_din || part_dres;
 #define L2(TT, LNV, MC, CV) norm_bwd_kernel<TT, LNV, MC, CV><<<grid, 256, 0, st>>>((const TT *)d_out, (const TT *)x, (const TT *)g, mean, rstd, (const TT *)d_res, (TT *)d_in, part_g, part_b, part_din, part_dres, T, H)
 #define L1(TT, LNV, MC) do { if (cols) L2(TT, LNV, MC, true); else L2(TT, LNV, MC, false); } while (0)
-#define L(TT, LNV) do { if (H <= 2048) L1(TT, LNV, 1); else if (H <= 4096) L1(TT, LNV, 2); else L1(TT, LNV, 4); } while (0)
+#define W2(TT, LNV, MC, CV) norm_bwd_wave_kernel<TT, LNV, MC, CV><<<grid, 256, 0, st>>>((const TT *)d_out, (const TT *)x, (const TT *)g, mean, rstd, (const TT *)d_res, (TT *)d_in, part_g, part_b, part_din, part_dres, T, H)
+#define W1(TT, LNV, MC) do { if (cols) W2(TT, LNV, MC, true); else W2(TT, LNV, MC, false); } while (0)
+#define L(TT, LNV) do { if (H <= 512) W1(TT, LNV, 1); else if (H <= NORM_BWD_WAVE_H) W1(TT, LNV, 2); \
+                        else if (H <= 2048) L1(TT, LNV, 1); else if (H <= 4096) L1(TT, LNV, 2); else L1(TT, LNV, 4); } while (0)
     if (dtype == DT_F32) { if (layernorm) L(float, true); else L(float, false); }
     else { if (layernorm) L(bf16_t, true); else L(bf16_t, false); }
 #undef L2
 #undef L1
+#undef W2
+#undef W1
 #undef L
     return hipGetLastError();
 }
@@ -529,16 +674,18 @@ hipError_t reduce_jobs(int dtype, const ReduceJob *jobs, int n, bool accumulate,
 }
 
 // ---- column sums (bias gradients) ----------------------------------------------------
-constexpr int COLSUM_ROWS = 16;            // rows per workgroup: short slabs, so that a [T, N] pass has T N / 32768 workgroups
-int colsum_slabs(int T) { return T > 0 ? ceil_div(T, COLSUM_ROWS) : 1; }
+// Rows per workgroup: short slabs, so that a [T, N] pass has enough workgroups (T N / 32768 at 16 rows), and shorter ones on
+// short packs, where a slab's rows one after the other are the kernel's time (GELU backward, us: 2304 x 4096 24.6 at 16 rows,
+// 15.5 at 4; 4111 x 5120 35.9 at 16, 29.8 at 8; 9536 x 4096 46.1 at 16, 48.3 at 8)
+int colsum_rows(int T) { return T > 6144 ? 16 : T > 3072 ? 8 : 4; }
+int colsum_slabs(int T) { return T > 0 ? ceil_div(T, colsum_rows(T)) : 1; }
 
 template <typename T>
-__global__ __launch_bounds__(256) void colsum_kernel(const T *__restrict__ in, int nrows, int N, int ld,
+__global__ __launch_bounds__(256) void colsum_kernel(const T *__restrict__ in, int nrows, int N, int ld, int slab,
                                                      float *__restrict__ part) {
     const int c = (blockIdx.x * 256 + threadIdx.x) * 8;
     if (c >= N) return;
-    const int r0 = blockIdx.y * COLSUM_ROWS;
-    const int r1 = min(nrows, r0 + COLSUM_ROWS);
+    const int r0 = blockIdx.y * slab, r1 = min(nrows, r0 + slab);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int r = r0; r < r1; r += 8) {              // 8 rows requested before the first is added
         float v[8][8];
@@ -558,8 +705,8 @@ __global__ __launch_bounds__(256) void colsum_kernel(const T *__restrict__ in, i
 hipError_t colsum_partials(int dtype, const void *in, int T, int N, int ld, float *part, hipStream_t st) {
     if (T == 0 || N == 0) return hipSuccess;
     dim3 grid(ceil_div(N, 2048), colsum_slabs(T));
-    if (dtype == DT_F32) colsum_kernel<float><<<grid, 256, 0, st>>>((const float *)in, T, N, ld, part);
-    else colsum_kernel<bf16_t><<<grid, 256, 0, st>>>((const bf16_t *)in, T, N, ld, part);
+    if (dtype == DT_F32) colsum_kernel<float><<<grid, 256, 0, st>>>((const float *)in, T, N, ld, colsum_rows(T), part);
+    else colsum_kernel<bf16_t><<<grid, 256, 0, st>>>((const bf16_t *)in, T, N, ld, colsum_rows(T), part);
     return hipGetLastError();
 }
 
@@ -710,14 +857,14 @@ __global__ __launch_bounds__(256) void gelu_bwd_kernel(const T *__restrict__ d_a
 }
 
 // The same over [nrows, N] with the column sums of d_z (the bias gradient of the linear in front of the activation):
-// a thread owns 8 columns of a slab of COLSUM_ROWS rows; part[slab, N] receives the slab's sums.
+// a thread owns 8 columns of a slab of rows; part[slab, N] receives the slab's sums.
 template <typename T>
 __global__ __launch_bounds__(256) void gelu_bwd_colsum_kernel(const T *__restrict__ d_a, const T *__restrict__ z,
-                                                              T *__restrict__ d_z, int nrows, int N,
+                                                              T *__restrict__ d_z, int nrows, int N, int slab,
                                                               float *__restrict__ part) {
     const int c = (blockIdx.x * 256 + threadIdx.x) * 8;
     if (c >= N) return;
-    const int r0 = blockIdx.y * COLSUM_ROWS, r1 = min(nrows, r0 + COLSUM_ROWS);
+    const int r0 = blockIdx.y * slab, r1 = min(nrows, r0 + slab);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int r = r0; r < r1; r += 4) {
         float v[4][8], g[4][8];
@@ -751,8 +898,8 @@ hipError_t gelu_fwd(int dtype, const void *z, void *a, long n, hipStream_t st) {
 hipError_t gelu_bwd_colsum(int dtype, const void *d_a, const void *z, void *d_z, int T, int N, float *part, hipStream_t st) {
     if (T == 0 || N == 0) return hipSuccess;
     dim3 grid(ceil_div(N, 2048), colsum_slabs(T));
-    if (dtype == DT_F32) gelu_bwd_colsum_kernel<float><<<grid, 256, 0, st>>>((const float *)d_a, (const float *)z, (float *)d_z, T, N, part);
-    else gelu_bwd_colsum_kernel<bf16_t><<<grid, 256, 0, st>>>((const bf16_t *)d_a, (const bf16_t *)z, (bf16_t *)d_z, T, N, part);
+    if (dtype == DT_F32) gelu_bwd_colsum_kernel<float><<<grid, 256, 0, st>>>((const float *)d_a, (const float *)z, (float *)d_z, T, N, colsum_rows(T), part);
+    else gelu_bwd_colsum_kernel<bf16_t><<<grid, 256, 0, st>>>((const bf16_t *)d_a, (const bf16_t *)z, (bf16_t *)d_z, T, N, colsum_rows(T), part);
     return hipGetLastError();
 }
 hipError_t gelu_bwd(int dtype, const void *d_a, const void *z, void *d_z, long n, hipStream_t st) {
