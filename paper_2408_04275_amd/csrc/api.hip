@@ -271,22 +271,22 @@ hipError_t gemm(int dtype, const GemmArgs &g, hipStream_t st) {
 }
 
 // Weight-gradient GEMMs of a backward pass whose outputs have few tiles are not launched where they stand but
-// collected and run together at the end of the pass (gemm_mfma_group): their operands all live until then.
+// collected and run together at the end of the pass (gemm_mfma_group, gemm_f32_group): their operands all live until then.
 struct DeferredWgrads {
     GemmArgs g[4];
     int n = 0;
 };
 hipError_t wgrad(int dtype, const GemmArgs &g, DeferredWgrads &later, hipStream_t st) {
-    if (dtype == DT_BF16 && later.n < 4 && gemm_mfma_few_tiles(g)) {
+    if (later.n < 4 && (dtype == DT_BF16 ? gemm_mfma_few_tiles(g) : gemm_f32_few_tiles(g))) {
         later.g[later.n++] = g;
         return hipSuccess;
     }
     return gemm(dtype, g, st);
 }
-hipError_t run_deferred(const DeferredWgrads &later, hipStream_t st) {
+hipError_t run_deferred(int dtype, const DeferredWgrads &later, hipStream_t st) {
     if (later.n == 0) return hipSuccess;
     ProfScope ps(MMTRAIN_PROF_GEMM_TN, st);
-    return gemm_mfma_group(later.g, later.n, st);
+    return dtype == DT_BF16 ? gemm_mfma_group(later.g, later.n, st) : gemm_f32_group(later.g, later.n, st);
 }
 
 }  // namespace
@@ -346,10 +346,10 @@ int mmtrain_layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     Ctx c;
     carve_ctx(b, D, (size_t)T, c);
 
-    HIP_TRY(prep_tokens(batch->cu_seqlens_dev, batch->seg_mask_dev, batch->mask_mode, batch->n_segments, T, c.tok_seg,
-                        c.tok_info, D.d, D.rope_base, c.rope_cs, st));
+    const TokenPrep prep = {batch->cu_seqlens_dev, batch->seg_mask_dev, batch->mask_mode, batch->n_segments, T, c.tok_seg, c.tok_info,
+                            D.d, D.rope_base, c.rope_cs};
     // attention block
-    HIP_TRY_TIMED(MMTRAIN_PROF_NORM_FWD, st, norm_fwd(D.dtype, enc, x, W->norm1_w, W->norm1_b, c.h1, c.mean1, c.rstd1, T, D.H, D.eps, st));
+    HIP_TRY_TIMED(MMTRAIN_PROF_NORM_FWD, st, norm_fwd(D.dtype, enc, x, W->norm1_w, W->norm1_b, c.h1, c.mean1, c.rstd1, T, D.H, D.eps, &prep, st));
     HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.nqkv, D.H, c.h1, D.H, W->w_qkv, D.H, c.qkv, D.nqkv, W->b_qkv), st));
     if (!enc) HIP_TRY_TIMED(MMTRAIN_PROF_ROPE, st, rope_inplace(D.dtype, c.qkv, D.nqkv, T, D.nh + D.nkv, D.d, c.rope_cs, false, st));
     AttnArgs a = mk_attn(D, batch, c);
@@ -359,7 +359,7 @@ int mmtrain_layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     }
     HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.H, D.nq, c.o, D.nq, W->w_o, D.nq, c.y1, D.H, W->b_o, x), st));
     // MLP block
-    HIP_TRY_TIMED(MMTRAIN_PROF_NORM_FWD, st, norm_fwd(D.dtype, enc, c.y1, W->norm2_w, W->norm2_b, c.h2, c.mean2, c.rstd2, T, D.H, D.eps, st));
+    HIP_TRY_TIMED(MMTRAIN_PROF_NORM_FWD, st, norm_fwd(D.dtype, enc, c.y1, W->norm2_w, W->norm2_b, c.h2, c.mean2, c.rstd2, T, D.H, D.eps, nullptr, st));
     HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.F1, D.H, c.h2, D.H, W->w_fc1, D.H, c.pre, D.F1, W->b_fc1), st));
     if (enc) HIP_TRY_TIMED(MMTRAIN_PROF_ACT_FWD, st, gelu_fwd(D.dtype, c.pre, c.m, (long)T * D.F, st));
     else HIP_TRY_TIMED(MMTRAIN_PROF_ACT_FWD, st, swiglu_fwd(D.dtype, c.pre, c.m, T, D.F, st));
@@ -463,7 +463,7 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     reduce_later(w.part_g1, G.norm1_w, nb, D.H);
     if (enc) reduce_later(w.part_b1, G.norm1_b, nb, D.H);
     HIP_TRY(reduce_jobs(gdt, jobs, n_jobs, accum, st));
-    HIP_TRY(run_deferred(later, st));
+    HIP_TRY(run_deferred(D.dtype, later, st));
     return MMTRAIN_OK;
 }
 
@@ -672,8 +672,8 @@ static int attn_common(const mmtrain_layer_desc *desc, const mmtrain_batch *batc
     if (workspace_bytes > scratch) { a.dkv_part = reinterpret_cast<float *>((uint8_t *)workspace + scratch); a.dkv_part_bytes = workspace_bytes - scratch; }
     a.cu_busy = g_attn_busy;
     attn_tile_order(batch->cu_seqlens_host, batch->seg_mask_host, batch->mask_mode, batch->n_segments, T, a);
-    HIP_TRY(prep_tokens(batch->cu_seqlens_dev, batch->seg_mask_dev, batch->mask_mode, batch->n_segments, T, tok_seg, tok_info,
-                        D.d, 0.f, nullptr, st));
+    HIP_TRY(prep_tokens({batch->cu_seqlens_dev, batch->seg_mask_dev, batch->mask_mode, batch->n_segments, T, tok_seg, tok_info, D.d, 0.f,
+                         nullptr}, st));
     return MMTRAIN_OK;
 }
 

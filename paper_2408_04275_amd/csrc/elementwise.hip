@@ -89,48 +89,60 @@ __device__ __forceinline__ int find_segment(const int *__restrict__ cu, int S, i
     return lo;
 }
 
-__global__ void tok_seg_kernel(const int *__restrict__ cu, const uint8_t *__restrict__ modes, int default_mode,
-                               int S, int T, int *__restrict__ tok_seg, int2 *__restrict__ tok_info) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    const int s = find_segment(cu, S, t);
-    tok_seg[t] = s;
-    const int mode = modes ? modes[s] : default_mode;
-    tok_info[t] = make_int2(cu[s], cu[s + 1] | (mode == MASK_BIDIR ? (1 << 30) : 0));
+__device__ __forceinline__ void token_entry(const TokenPrep &p, int t) {
+    if (t >= p.T) return;
+    const int s = find_segment(p.cu, p.S, t);
+    p.tok_seg[t] = s;
+    const int mode = p.modes ? p.modes[s] : p.default_mode;
+    p.tok_info[t] = make_int2(p.cu[s], p.cu[s + 1] | (mode == MASK_BIDIR ? (1 << 30) : 0));
 }
 
 // rope_cs[t, i] = (cos, sin)(pos(t) * base^(-2i/d)), pos(t) = t - cu[seg(t)]; evaluated in double
 // so that the fp32 table is correctly rounded for any position.
-__global__ void rope_table_kernel(const int *__restrict__ cu, int S, int T, int d, float rope_base,
-                                  float2 *__restrict__ rope_cs) {
-    const int half = d >> 1;
-    const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (long)T * half) return;
+__device__ __forceinline__ void rope_entry(const TokenPrep &p, long idx) {
+    const int half = p.d >> 1;
+    if (idx >= (long)p.T * half) return;
     const int t = (int)(idx / half), i = (int)(idx % half);
-    const double pos = (double)(t - cu[find_segment(cu, S, t)]);
-    const double phi = pos * exp(-2.0 * i / d * log((double)rope_base));
-    rope_cs[idx] = make_float2((float)cos(phi), (float)sin(phi));
+    const double pos = (double)(t - p.cu[find_segment(p.cu, p.S, t)]);
+    const double phi = pos * exp(-2.0 * i / p.d * log((double)p.rope_base));
+    p.rope_cs[idx] = make_float2((float)cos(phi), (float)sin(phi));
 }
 
-hipError_t prep_tokens(const int *cu, const uint8_t *modes, int default_mode, int S, int T, int *tok_seg,
-                       int2 *tok_info, int d, float rope_base, float2 *rope_cs, hipStream_t st) {
-    if (T == 0) return hipSuccess;
-    tok_seg_kernel<<<ceil_div(T, 256), 256, 0, st>>>(cu, modes, default_mode, S, T, tok_seg, tok_info);
-    if (rope_cs) rope_table_kernel<<<ceil_div((long)T * (d / 2), 256), 256, 0, st>>>(cu, S, T, d, rope_base, rope_cs);
+// Workgroup b of the bookkeeping: 256 tokens each, then 256 entries of the rotary table each.
+static int token_prep_blocks(const TokenPrep &p) {
+    return ceil_div(p.T, 256) + (p.rope_cs ? ceil_div((long)p.T * (p.d / 2), 256) : 0);
+}
+__device__ __forceinline__ void token_prep(const TokenPrep &p, int b) {
+    const int tok_blocks = (p.T + 255) / 256;
+    if (b < tok_blocks) token_entry(p, b * 256 + threadIdx.x);
+    else rope_entry(p, (long)(b - tok_blocks) * 256 + threadIdx.x);
+}
+
+__global__ __launch_bounds__(256) void token_prep_kernel(TokenPrep p) { token_prep(p, blockIdx.x); }
+
+hipError_t prep_tokens(const TokenPrep &p, hipStream_t st) {
+    if (p.T == 0) return hipSuccess;
+    token_prep_kernel<<<token_prep_blocks(p), 256, 0, st>>>(p);
     return hipGetLastError();
 }
 
 // ---- normalisation forward -----------------------------------------------------------
 // RMSNorm: out = x * rsqrt(mean(x^2) + eps) * g.
 // LayerNorm: out = (x - mean) * rsqrt(var_biased + eps) * g + b (variance about the mean, two passes).
-// Rows of at most 256 * 8 * MAXC elements, a workgroup walking rows blockIdx.x, blockIdx.x + gridDim.x, ...: the row stays in registers between the statistics and the scaling (one read of x), the gain and bias are fetched once
-// per workgroup, and the next row is requested before the current one is reduced, so that a workgroup always has a
-// row in flight (with one short-lived workgroup per row the kernel reached 5.5 TB/s).
+// The first prep_blocks workgroups do a layer's token bookkeeping instead, which the kernels after this one need: in launches
+// of their own the two tables cost a small pack 2 x 4.7 us.
+//
+// Rows of at most 256 * 8 * MAXC elements, a workgroup walking every `blocks`-th row: the row stays in registers between the
+// statistics and the scaling (one read of x), the gain and bias are fetched once per workgroup, and the next row is requested
+// before the current one is reduced, so that a workgroup always has a row in flight (with one short-lived workgroup per row the
+// kernel reached 5.5 TB/s).
 template <typename T, bool LN, int MAXC>
 __global__ __launch_bounds__(256) void norm_fwd_rows_kernel(const T *__restrict__ x, const T *__restrict__ g,
                                                             const T *__restrict__ b, T *__restrict__ out,
                                                             float *__restrict__ mean, float *__restrict__ rstd,
-                                                            int nrows, int H, float eps) {
+                                                            int nrows, int H, float eps, TokenPrep prep, int prep_blocks) {
+    if ((int)blockIdx.x < prep_blocks) return token_prep(prep, blockIdx.x);
+    const unsigned block = blockIdx.x - prep_blocks, blocks = gridDim.x - prep_blocks;
     __shared__ float red[4];
     float gv[MAXC][8], bv[LN ? MAXC : 1][8], cur[MAXC][8], nxt[MAXC][8];
 #pragma unroll
@@ -139,11 +151,11 @@ __global__ __launch_bounds__(256) void norm_fwd_rows_kernel(const T *__restrict_
         if (c < H) {
             load8(g + c, gv[i]);
             if (LN) load8(b + c, bv[i]);
-            if (blockIdx.x < nrows) load8(x + (size_t)blockIdx.x * H + c, cur[i]);
+            if (block < nrows) load8(x + (size_t)block * H + c, cur[i]);
         }
     }
-    for (size_t row = blockIdx.x; row < (size_t)nrows; row += gridDim.x) {
-        const size_t next = row + gridDim.x;
+    for (size_t row = block; row < (size_t)nrows; row += blocks) {
+        const size_t next = row + blocks;
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {
             const int c = (threadIdx.x + i * 256) * 8;
@@ -192,9 +204,10 @@ template <typename T, bool LN, int MAXC>
 __global__ __launch_bounds__(256) void norm_fwd_wave_kernel(const T *__restrict__ x, const T *__restrict__ g,
                                                             const T *__restrict__ b, T *__restrict__ out,
                                                             float *__restrict__ mean, float *__restrict__ rstd,
-                                                            int nrows, int H, float eps) {
-    const int lane = threadIdx.x & 63, step = gridDim.x * 4;
-    int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                            int nrows, int H, float eps, TokenPrep prep, int prep_blocks) {
+    if ((int)blockIdx.x < prep_blocks) return token_prep(prep, blockIdx.x);
+    const int lane = threadIdx.x & 63, step = (gridDim.x - prep_blocks) * 4;
+    int row = (blockIdx.x - prep_blocks) * 4 + (threadIdx.x >> 6);
     float gv[MAXC][8], bv[LN ? MAXC : 1][8];
     Raw8<T> nxt[MAXC];
     auto request = [&](int r) {
@@ -272,25 +285,29 @@ hipError_t resident_workgroups(std::atomic<int> &cached, K kern, int &grid) {
     cached.store(grid, std::memory_order_relaxed);
     return hipSuccess;
 }
-// WAVES_ROWS: a wavefront per row (four per workgroup), otherwise a workgroup per row
+// WAVE_ROWS: a wavefront per row (four per workgroup), otherwise a workgroup per row
 template <typename T, bool LN, int MAXC, bool WAVE_ROWS>
 hipError_t launch_norm_fwd_rows(const void *x, const void *g, const void *b, void *out, float *mean, float *rstd, int nrows,
-                                int H, float eps, hipStream_t st) {
+                                int H, float eps, const TokenPrep *prep, hipStream_t st) {
     static std::atomic<int> resident{0};
-    auto kern = WAVE_ROWS ? norm_fwd_wave_kernel<T, LN, MAXC> : norm_fwd_rows_kernel<T, LN, MAXC>;
+    auto kern = [] {
+        if constexpr (WAVE_ROWS) return norm_fwd_wave_kernel<T, LN, MAXC>;
+        else return norm_fwd_rows_kernel<T, LN, MAXC>;
+    }();
     int grid = 0;
     hipError_t e = resident_workgroups(resident, kern, grid);
     if (e != hipSuccess) return e;
-    const int all = WAVE_ROWS ? ceil_div(nrows, 4) : nrows;
-    kern<<<all < grid ? all : grid, 256, 0, st>>>((const T *)x, (const T *)g, (const T *)b, (T *)out, mean, rstd, nrows, H, eps);
+    const int all = WAVE_ROWS ? ceil_div(nrows, 4) : nrows, prep_blocks = prep ? token_prep_blocks(*prep) : 0;
+    kern<<<prep_blocks + (all < grid ? all : grid), 256, 0, st>>>((const T *)x, (const T *)g, (const T *)b, (T *)out, mean, rstd, nrows, H,
+                                                                  eps, prep ? *prep : TokenPrep{}, prep_blocks);
     return hipGetLastError();
 }
 
 hipError_t norm_fwd(int dtype, bool layernorm, const void *x, const void *g, const void *b, void *out,
-                    float *mean, float *rstd, int T, int H, float eps, hipStream_t st) {
+                    float *mean, float *rstd, int T, int H, float eps, const TokenPrep *prep, hipStream_t st) {
     if (T == 0) return hipSuccess;
     if (H % 8 || H > 8192) return hipErrorInvalidValue;
-#define R(TT, LNV, MC, WR) return launch_norm_fwd_rows<TT, LNV, MC, WR>(x, g, b, out, mean, rstd, T, H, eps, st)
+#define R(TT, LNV, MC, WR) return launch_norm_fwd_rows<TT, LNV, MC, WR>(x, g, b, out, mean, rstd, T, H, eps, prep, st)
 #define L(TT, LNV) do { if (H <= 512) R(TT, LNV, 1, true); else if (H <= 1024) R(TT, LNV, 2, true); else if (H <= 1536) R(TT, LNV, 3, true); \
                         else if (H <= 2048) R(TT, LNV, 4, true); else if (H <= 4096) R(TT, LNV, 2, false); else R(TT, LNV, 4, false); } while (0)
     if (dtype == DT_F32) { if (layernorm) L(float, true); else L(float, false); }

@@ -32,6 +32,9 @@ hipError_t gemm_simple(int dtype, const GemmArgs &g, hipStream_t st);
 // gemm_f32.hip: fp32 storage on the fp32 matrix instruction.  `supported` checks alignment requirements.
 bool gemm_f32_supported(const GemmArgs &g);
 hipError_t gemm_f32(const GemmArgs &g, hipStream_t st);
+// ... weight gradients with few tiles of 64 x 64 (below 384), up to 4 in one launch
+bool gemm_f32_few_tiles(const GemmArgs &g);
+hipError_t gemm_f32_group(const GemmArgs *gs, int n, hipStream_t st);
 // gemm_mfma.hip: bf16 MFMA kernel.  `supported` checks alignment requirements.
 bool gemm_mfma_supported(const GemmArgs &g);
 hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st);
@@ -101,11 +104,21 @@ inline size_t attn_dkv_part_bytes(int T, int nkv, int d) { return (size_t)T * 2 
 int attn_dkv_parts(int T, int nh, int nkv, int d);
 
 // elementwise.hip
-hipError_t prep_tokens(const int *cu, const uint8_t *modes, int default_mode, int S, int T, int *tok_seg,
-                       int2 *tok_info, int d, float rope_base, float2 *rope_cs /* [T, d/2] or null */,
-                       hipStream_t st);
+// Token bookkeeping of a pack: tok_seg, tok_info (see AttnArgs) and, if rope_cs is not null, the [T, d/2] rotary table.
+struct TokenPrep {
+    const int *cu;              // device [S+1]
+    const uint8_t *modes;       // device [S] or null
+    int default_mode, S, T;
+    int *tok_seg;
+    int2 *tok_info;
+    int d;
+    float rope_base;
+    float2 *rope_cs;
+};
+hipError_t prep_tokens(const TokenPrep &p, hipStream_t st);
+// prep: when not null, the same launch does that bookkeeping
 hipError_t norm_fwd(int dtype, bool layernorm, const void *x, const void *g, const void *b, void *out,
-                    float *mean, float *rstd, int T, int H, float eps, hipStream_t st);
+                    float *mean, float *rstd, int T, int H, float eps, const TokenPrep *prep, hipStream_t st);
 // d_in = norm_bwd(d_out) + d_res;  gain/bias gradient partial sums go to part_g/part_b, the column sums of d_in
 // and of d_res to part_din / part_dres ([norm_bwd_blocks(T, H), H] fp32 each; null = skip).
 int norm_bwd_blocks(int T, int H);
