@@ -250,9 +250,11 @@ typedef enum {
  * workspace (device memory, 256-byte aligned, caller-owned, may be NULL with 0 bytes) is
  * scratch for fp32 partial products.  With it, a bf16 NN or TN product without bias or
  * residual may be cut along K where that fills the chip better: the partly filled last
- * round of tiles of a large product.  mmtrain_gemm_workspace_bytes() returns a size that
- * allows every such cut; a smaller workspace only restricts them, and the result does not
- * depend on timing (the partial products are added in a fixed order). */
+ * round of tiles of a large product, and all of an NN product with few tiles and a very
+ * long K.  mmtrain_gemm_workspace_bytes() returns a size that allows the former (0 for NN with
+ * few tiles: the latter takes chunks * M * N * 4 bytes where a caller has them, at most 8
+ * chunks); a smaller workspace only restricts the cuts, and the result does not depend on
+ * timing (the partial products are added in a fixed order). */
 MMTRAIN_API size_t mmtrain_gemm_workspace_bytes(int32_t layout, int32_t M, int32_t N);
 MMTRAIN_API int mmtrain_gemm(int32_t dtype, int32_t layout, int32_t M, int32_t N, int32_t K,
                  const void *A, int32_t lda, const void *B, int32_t ldb, void *C, int32_t ldc,

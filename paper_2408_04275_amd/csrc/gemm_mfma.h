@@ -69,7 +69,7 @@ struct GemmP {
     int c_f32;                 // C holds fp32 (weight gradients into fp32 main-gradient buffers)
     int tiles_m, tiles_n;
     // split K (fp32 output only): the K range is cut into `splits` chunks of k_chunk (a multiple of 64); chunk s of
-    // every tile is a work item of its own
+    // every tile is a work item of its own, its partial product goes to the s-th M x ldc matrix from C on
     int splits, k_chunk;
     // A launch covers tiles [tile_begin, tile_begin + tile_count) of the tile order.  With `compact` (fp32 output, 256 x 256
     // tiles) the partial product of chunk s of the launch's tile j is a dense block at C + (s * tile_count + j) * 65536
@@ -637,7 +637,7 @@ void gemm_mfma_kernel(const ARG arg) {
                     // fp32 output (never together with bias or residual): previous contents are read here
                     float *cf = reinterpret_cast<float *>(p.C) +
                                 (p.compact ? ((size_t)(chunk * p.tile_count + tl) << 16) + (size_t)(gm - m0) * 256 + (gn - n0)
-                                           : off);
+                                           : off + (size_t)chunk * p.M * p.ldc);
                     if (p.accumulate) {
                         const float4 c0 = *reinterpret_cast<const float4 *>(cf), c1 = *reinterpret_cast<const float4 *>(cf + 4);
                         v[0] += c0.x; v[1] += c0.y; v[2] += c0.z; v[3] += c0.w;

@@ -35,6 +35,29 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const float *__restric
     }
 }
 
+// C (+)= sum over the K chunks of the M x N fp32 partial products, dense and one after the other (N a multiple of 8).
+// Streams (splits * 4 + 2) bytes per element; 8 elements per thread, rows on the grid's y.
+__global__ __launch_bounds__(256) void sum_chunks_kernel(const float *__restrict__ part, int splits, int M, int N, bf16_t *__restrict__ C,
+                                                         int ldc, int accumulate) {
+    const int n = (blockIdx.x * 256 + threadIdx.x) * 8;
+    if (n >= N) return;
+    const size_t plane = (size_t)M * N;
+    for (int m = blockIdx.y; m < M; m += gridDim.y) {
+        const float *src = part + (size_t)m * N + n;
+        f32x4 a = *reinterpret_cast<const f32x4 *>(src), b = *reinterpret_cast<const f32x4 *>(src + 4);
+        for (int s = 1; s < splits; ++s) {
+            a += *reinterpret_cast<const f32x4 *>(src + s * plane);
+            b += *reinterpret_cast<const f32x4 *>(src + s * plane + 4);
+        }
+        bf16_t *c = C + (size_t)m * ldc + n;
+        if (accumulate)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { a[e] += bf16_to_f32(c[e]); b[e] += bf16_to_f32(c[4 + e]); }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { Elem<bf16_t>::store(c + e, a[e]); Elem<bf16_t>::store(c + 4 + e, b[e]); }
+    }
+}
+
 GemmP params(const GemmArgs &g) {
     GemmP p;
     p.M = g.M; p.N = g.N; p.K = g.K;
@@ -130,9 +153,9 @@ constexpr TileCost COST_WGRAD[] = {
     {TILE_64x128, 64, 128, 0.10, 0.254}, {TILE_64, 64, 64, 0.0, 0.176}};
 
 template <int N>
-int choose_tile(const TileCost (&table)[N], double launch, double rounds_power, double load, const GemmArgs *gs, int n, int n_cu) {
+int choose_tile(const TileCost (&table)[N], double launch, double rounds_power, double load, const GemmArgs *gs, int n, int n_cu,
+                double &best_us) {
     int best = TILE_256;
-    double best_us = 0.;
     for (const TileCost &t : table) {
         long tiles = 0;
         for (int i = 0; i < n; ++i) tiles += (long)ceil_div(gs[i].M, t.bm) * ceil_div(gs[i].N, t.bn);
@@ -143,9 +166,31 @@ int choose_tile(const TileCost (&table)[N], double launch, double rounds_power, 
     }
     return best;
 }
-int choose_tile(const GemmArgs *gs, int n, int n_cu) {
-    return gs[0].layout == GEMM_TN ? choose_tile(COST_WGRAD, 3.7, 1.079, 0.105, gs, n, n_cu)
-                                   : choose_tile(COST_ROWS, 3.4, 1.042, 0.276, gs, n, n_cu);
+int choose_tile(const GemmArgs *gs, int n, int n_cu, double &us) {
+    return gs[0].layout == GEMM_TN ? choose_tile(COST_WGRAD, 3.7, 1.079, 0.105, gs, n, n_cu, us)
+                                   : choose_tile(COST_ROWS, 3.4, 1.042, 0.276, gs, n, n_cu, us);
+}
+
+// An input gradient (NN) with few tiles and a very long K, cut along K as a whole: `splits` chunks of 256 x 256 tiles through
+// scratch, and a kernel that adds them up.  The smaller tile shapes fill the chip too, but at half or a quarter of the
+// arithmetic per byte on every K step; the cut pays for its scratch traffic and second launch once, so it wins where K is long.
+// The rule compares choose_tile's estimate with the same model for K / splits, plus the reduction (its launch and 0.345 us per
+// MB), and asks for 5 % as both are fits.  Measured with operands that come from HBM (larger than the memory-side cache holds
+// from call to call), tile shape -> cut: 1031 x 4096 x 22016 (the gate / up input gradient of a short pack) 233 -> 177 us in
+// three chunks, 300 x 4096 x 22016 154 -> 78 in eight, 1031 x 1280 x 22016 136 -> 70 in eight; at the rule's edge, 2304 x 1024 x
+// 11008, 69 -> 70.  Up to K = 8192 the tile shapes are ahead.
+int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
+    if (g.layout != GEMM_NN || g.bias || g.residual || !g.split_ws) return 1;
+    const long tiles = (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE);
+    const size_t plane = (size_t)g.M * g.N * 4;
+    best_us *= 0.95;
+    int best = 1;
+    for (int s = 2; s <= 8 && s * tiles <= n_cu && s * 512 <= g.K && s * plane <= g.split_ws_bytes; ++s) {
+        const double fill = (double)(s * tiles) / n_cu;
+        const double us = 3.4 + 4.13 + ceil_div(ceil_div(g.K, BK), s) * 0.958 * (1. + 0.276 * fill * fill) + 3.4 + 0.345e-6 * plane * (s + 0.5);
+        if (us < best_us) { best = s; best_us = us; }
+    }
+    return best;
 }
 
 hipError_t gemm_mfma_group(const GemmArgs *gs, int n, hipStream_t st) {
@@ -160,7 +205,8 @@ hipError_t gemm_mfma_group(const GemmArgs *gs, int n, hipStream_t st) {
     int n_cu = 0;
     hipError_t e = compute_units(n_cu);
     if (e != hipSuccess) return e;
-    return launch_tn(choose_tile(gs, n, n_cu), p, n, st);
+    double us;
+    return launch_tn(choose_tile(gs, n, n_cu, us), p, n, st);
 }
 
 hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st) {
@@ -170,7 +216,18 @@ hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st) {
     if (e != hipSuccess) return e;
     const int tail_s = gemm_mfma_tail_splits(g, n_cu, tail_tiles);
     if (tail_tiles == 0) {
-        const int shape = choose_tile(&g, 1, n_cu);
+        double us;
+        const int shape = choose_tile(&g, 1, n_cu, us);
+        const int s = few_tile_splits(g, n_cu, us);
+        if (s > 1) {
+            p.k_chunk = ceil_div(ceil_div(g.K, s), BK) * BK;
+            p.splits = ceil_div(g.K, p.k_chunk);
+            p.C = (bf16_t *)g.split_ws; p.ldc = g.N; p.accumulate = 0; p.c_f32 = 1;
+            if ((e = launch_partials(g.layout, p, st)) != hipSuccess) return e;
+            sum_chunks_kernel<<<dim3(ceil_div(g.N, 2048), g.M < 4096 ? g.M : 4096), 256, 0, st>>>((const float *)g.split_ws, p.splits, g.M, g.N,
+                                                                                                   (bf16_t *)g.C, g.ldc, g.accumulate ? 1 : 0);
+            return hipGetLastError();
+        }
         if (shape != TILE_256)
             return g.layout == GEMM_NT ? launch_nt(shape, p, st) : g.layout == GEMM_NN ? launch_nn(shape, p, st) : launch_tn(shape, &p, 1, st);
     }

@@ -29,3 +29,11 @@ WGRAD_SHAPES = [(8, 8, 1, "64x64"), (72, 136, 67, "64x64"), (520, 1032, 583, "64
 def test_weight_gradient_tile_shape(M, N, K, tile):
     gemm_case(mm.BF16, mm.GEMM_TN, M, N, K, seed=23)
     gemm_case(mm.BF16, mm.GEMM_TN, M, N, K, accumulate=True, seed=24)
+
+
+# few tiles and a long K: with scratch an input gradient is cut along K (8, 5 and 7 chunks; K with a remainder, the last chunk shorter,
+# rows and columns past a tile edge); scratch for one chunk only leaves it whole
+@pytest.mark.parametrize("M,N,K,chunks", [(257, 4104, 25608, 8), (520, 4096, 22016, 5), (2304, 1032, 22024, 7), (257, 4104, 25608, 1)])
+def test_input_gradient_cut_along_k(M, N, K, chunks, monkeypatch):
+    monkeypatch.setattr(mm, "mmtrain_gemm_workspace_bytes", lambda layout, m, n: chunks * m * n * 4)
+    gemm_case(mm.BF16, mm.GEMM_NN, M, N, K, accumulate=chunks == 5, seed=25, workspace=True)
