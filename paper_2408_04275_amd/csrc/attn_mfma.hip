@@ -355,6 +355,9 @@ constexpr int DKV_STAGE_BYTES = 4 * ROWS32_BYTES<D>;  // the pipelined dK/dV ker
 // of which holds the rows of one operand at a time of 4 wavefronts
 template <int D, int WAVES>
 constexpr int DQ_LDS_BYTES = WAVES == 8 ? 2 * BT2 * D * 2 + 8 * 2 * ROWS32_BYTES<D> : 2 * 2 * BT2 * D * 2;
+// the plain dK/dV kernel: two slots of a Q tile, a dO tile and their log-sum-exps and D values, and the K and V rows of 4 wavefronts
+template <int D>
+constexpr int DKV_PLAIN_LDS = 2 * (2 * BT2 * D * 2 + 2 * BT2 * 4) + 2 * DKV_STAGE_BYTES<D>;
 template <int D, int CB>
 __device__ __forceinline__ void store_rows(uint8_t *stage, const f32x16 (&acc)[CB], float scale, bf16_t *dst, long ld,
                                            int rows_valid, int dh) {
@@ -398,6 +401,32 @@ __device__ __forceinline__ void store_rows_f32(uint8_t *stage, const f32x16 (&ac
         const f32x4 v = *reinterpret_cast<const f32x4 *>(stage + r * RS + cb);
         if (r < rows_valid && cb / 4 < dh) *reinterpret_cast<f32x4 *>(dst + (long)r * ld + cb / 4) = v;
     }
+}
+
+// Two wavefronts of a workgroup that share a row block (PARTS = 2): the second leaves its N values per lane in LDS, the first
+// picks them up after the barrier in between.  box: XCHG_BYTES<N> bytes that belong to the pair.
+template <int N>
+constexpr int XCHG_BYTES = (N + 3) / 4 * 1024;
+template <int CB>
+__device__ __forceinline__ void put_acc(uint8_t *box, const f32x16 (&acc)[CB]) {
+    f32x4 *p = reinterpret_cast<f32x4 *>(box) + (threadIdx.x & 63);
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[(4 * c + i) * 64] = f32x4{acc[c][4 * i], acc[c][4 * i + 1], acc[c][4 * i + 2], acc[c][4 * i + 3]};
+}
+// acc = acc * w_own + what the other wavefront put * w_other
+template <int CB>
+__device__ __forceinline__ void merge_acc(const uint8_t *box, f32x16 (&acc)[CB], float w_own, float w_other) {
+    const f32x4 *p = reinterpret_cast<const f32x4 *>(box) + (threadIdx.x & 63);
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x4 v = p[(4 * c + i) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[c][4 * i + e] = acc[c][4 * i + e] * w_own + v[e] * w_other;
+        }
 }
 
 // End of both dK/dV kernels: a wavefront's 32 keys' dV and dK (unscaled) as rows of d_qkv, or, where the query heads of a
@@ -454,14 +483,15 @@ __global__ __launch_bounds__(256) void dkv_reduce_kernel(AttnArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// backward: dQ (and -D, D = rowsum(dO * O)).  Same roles as the forward kernel: 8 or 4 wavefronts x 32 queries.
+// backward: dQ (and -D, D = rowsum(dO * O)).  Same roles as the forward kernel: 8 or 4 wavefronts x 32 queries, or two groups of 4.
 // ------------------------------------------------------------------------------------------
-template <int D, int KS, int CB, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 2) void attn_dq_kernel(AttnArgs a) {
+template <int D, int KS, int CB, int WAVES, int PARTS>
+__global__ __launch_bounds__(WAVES * PARTS * 64, 2) void attn_dq_kernel(AttnArgs a) {
+    static_assert(PARTS == 1 || WAVES == 4, "the key range is shared by two groups of four wavefronts");
     constexpr int FQW = WAVES * 32;                                // queries per workgroup
     constexpr int TILE = BT2 * D * 2, SLOT = 2 * TILE;             // K tile, then V tile
     constexpr int COPIES = BT2 * D * 2 / 1024 / 4;                 // per wavefront (4 wavefronts per tile)
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_all[];
     // grid: x = head, y = position in the dispatch order of the query tiles (heaviest first)
     const int head = blockIdx.x, g = head / (a.nh / a.nkv);
     // (of FQ-query tiles: the workgroups of one tile, two with four wavefronts each, follow each other)
@@ -470,7 +500,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_dq_kernel(AttnArgs a) {
     if (q0 >= a.T) return;                                         // second half of a last tile that the pack only half fills
     add_busy(a.cu_busy ? a.cu_busy + 1024 : nullptr, false);
     // the wavefront's index as a scalar: what is derived from it (copy destinations, buffer descriptors) stays uniform
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
+    const int part = PARTS == 1 ? 0 : wv / WAVES, wave = PARTS == 1 ? wv : wv % WAVES;
+    uint8_t *const smem = smem_all + part * 2 * SLOT;
     const int T = a.T;
     const bf16_t *qkv = (const bf16_t *)a.qkv;
     const long ld = a.ld_qkv;
@@ -517,7 +549,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_dq_kernel(AttnArgs a) {
             uint8_t *st_do = st_q + ROWS32_BYTES<D>;
             cp_q.issue(rs, st_q, q0 + wave * 32, ld, head * dh);
             cp_o.issue(rs_do, st_do, q0 + wave * 32, nq, head * dh);
-            copy_kv(smem, kbeg);
+            if (part == 0 || kbeg + BT2 < kend) copy_kv(smem, kbeg + part * BT2);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
@@ -526,7 +558,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_dq_kernel(AttnArgs a) {
             }
         } else {                                                     // one operand after the other in the same place
             cp_q.issue(rs, st_q, q0 + wave * 32, ld, head * dh);
-            copy_kv(smem, kbeg);
+            if (part == 0 || kbeg + BT2 < kend) copy_kv(smem, kbeg + part * BT2);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) qf[ks] = frag_k<D>(st_q, l32, ks, half);
@@ -555,7 +587,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_dq_kernel(AttnArgs a) {
     float lse2 = 0.f;                                  // log-sum-exp in log2 units
     if (valid) {
         lse2 = a.lse[(long)head * T + q] * LOG2E;
-        if (half == 0) a.Dsum[(long)head * T + q] = -Dq;                // the dK/dV kernels add it
+        if (half == 0 && part == 0) a.Dsum[(long)head * T + q] = -Dq;                // the dK/dV kernels add it
     }
     // With 64-wide heads dP - D comes out of the matrix core: the dP product of every block starts from -D instead of
     // from zero (a lane holds keys of ONE query, so the 16 accumulator registers of a lane all start from that query's
@@ -570,11 +602,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_dq_kernel(AttnArgs a) {
     const float sl2 = a.scale * LOG2E;
 
     int slot = 0;
-    for (int kt = kbeg; kt < kend; kt += BT2, slot ^= 1) {
+    for (int kt = kbeg + part * BT2; kt - part * BT2 < kend; kt += PARTS * BT2, slot ^= 1) {
         const uint8_t *sK = smem + slot * SLOT, *sV = sK + TILE;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this step's tiles have landed
         lds_barrier();                                               // ... and everyone is done with the other slot
-        if (kt + BT2 < kend) copy_kv(smem + (slot ^ 1) * SLOT, kt + BT2);
+        if (kt + PARTS * BT2 < kend) copy_kv(smem + (slot ^ 1) * SLOT, kt + PARTS * BT2);
         auto block = [&](auto B_) {
             constexpr int b = decltype(B_)::value;
             const int kb = kt + 32 * b;
@@ -627,9 +659,18 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_dq_kernel(AttnArgs a) {
         block(std::integral_constant<int, 1>{});
     }
     lds_barrier();                                     // the tiles are done with: LDS now stages the output rows
+    uint8_t *stage = smem_all + wave * STAGE_BYTES<D>;
+    if constexpr (PARTS == 2) {
+        uint8_t *box = smem_all + wave * XCHG_BYTES<16 * CB>;
+        stage += WAVES * XCHG_BYTES<16 * CB>;
+        if (part == 1) put_acc(box, dq);
+        lds_barrier();
+        if (part == 1) return;
+        merge_acc(box, dq, 1.f, 1.f);
+    }
     if constexpr (CB == D / 32)                        // (narrower heads are rotated back by a pass of their own)
         if (valid && a.rope_cs) unrotate<CB>(dq, a.rope_cs + (long)q * (D / 2), half);
-    store_rows<D, CB>(smem + wave * STAGE_BYTES<D>, dq, a.scale, (bf16_t *)a.d_qkv + (long)(q0 + wave * 32) * ld + head * dh, ld,
+    store_rows<D, CB>(stage, dq, a.scale, (bf16_t *)a.d_qkv + (long)(q0 + wave * 32) * ld + head * dh, ld,
                       T - (q0 + wave * 32), dh);
     add_busy(a.cu_busy ? a.cu_busy + 1024 : nullptr, true);
 }
@@ -653,18 +694,20 @@ constexpr float LAZY_LOG2 = 8.f;
 // forward.  WAVES wavefronts x 32 queries per workgroup, two wavefronts per SIMD either way (so that one can run its
 // softmax on the vector ALUs while the other occupies the matrix core): 8 wavefronts = 256 queries, one workgroup per
 // compute unit (every K / V tile is fetched once for 256 queries), or 4 wavefronts = 128 queries, two workgroups per
-// compute unit (see four_waves).  The keys are walked 64 at a time through
+// compute unit (see four_waves).  PARTS = 2: two groups of 4 wavefronts with the same 128 queries, the keys of every other step and
+// LDS slots each (see two_parts).  The keys are walked 64 at a time through
 // two LDS slots of {K tile, V tile}, both copied global -> LDS directly in their memory order (wavefronts 4..7 copy K,
 // 0..3 copy V).  O^T = V^T . P^T takes V^T from the row-major tile by the transposing LDS read, the same scheme as
 // dQ^T = K^T . dS^T above.  One barrier per step: after it every wavefront has finished the previous step, so the slot
 // that step used may be refilled.
 // ------------------------------------------------------------------------------------------
-template <int D, int KS, int CB, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 2) void attn_fwd_kernel(AttnArgs a) {
+template <int D, int KS, int CB, int WAVES, int PARTS>
+__global__ __launch_bounds__(WAVES * PARTS * 64, 2) void attn_fwd_kernel(AttnArgs a) {
+    static_assert(PARTS == 1 || WAVES == 4, "the key range is shared by two groups of four wavefronts");
     constexpr int FQW = WAVES * 32;                                // queries per workgroup
     constexpr int TILE = BT2 * D * 2, SLOT = 2 * TILE;             // K tile, then V tile
     constexpr int COPIES = BT2 * D * 2 / 1024 / 4;                 // per wavefront and tile (four wavefronts copy a tile)
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_all[];
     const int head = blockIdx.x, g = head / (a.nh / a.nkv);
     // the dispatch order is kept per FQ-query tile; the workgroups of one tile (two, with four wavefronts each) follow each other
     constexpr int PER_TILE = FQ / FQW;
@@ -672,7 +715,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fwd_kernel(AttnArgs a) {
     if (q0 >= a.T) return;                                         // second half of a last tile that the pack only half fills
     add_busy(a.cu_busy, false);
     // the wavefront's index as a scalar: what is derived from it (copy destinations, buffer descriptors) stays uniform
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
+    const int part = PARTS == 1 ? 0 : wv / WAVES, wave = PARTS == 1 ? wv : wv % WAVES;
+    uint8_t *const smem = smem_all + part * 2 * SLOT;
     const int T = a.T;
     const bf16_t *qkv = (const bf16_t *)a.qkv;
     const long ld = a.ld_qkv;
@@ -713,17 +758,17 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fwd_kernel(AttnArgs a) {
         cp_q.init(0, ld, dh);
         uint8_t *st_q = smem + (WAVES == 4 ? SLOT : 2 * SLOT) + wave * ROWS32_BYTES<D>;
         cp_q.issue(rs, st_q, q0 + wave * 32, ld, head * dh);
-        copy_kv(smem, kbeg);
+        if (part == 0 || kbeg + BT2 < kend) copy_kv(smem, kbeg + part * BT2);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[ks] = frag_k<D>(st_q, l32, ks, half);
     }
     int slot = 0;
-    for (int kt = kbeg; kt < kend; kt += BT2, slot ^= 1) {
+    for (int kt = kbeg + part * BT2; kt - part * BT2 < kend; kt += PARTS * BT2, slot ^= 1) {
         const uint8_t *sK = smem + slot * SLOT;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this step's tiles have landed
         lds_barrier();                                               // ... and everyone is done with the other slot
-        if (kt + BT2 < kend) copy_kv(smem + (slot ^ 1) * SLOT, kt + BT2);
+        if (kt + PARTS * BT2 < kend) copy_kv(smem + (slot ^ 1) * SLOT, kt + PARTS * BT2);
         bool act[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b) act[b] = (kt + 32 * b < w_hi_max) && (kt + 32 * b + 32 > w_lo_min);
@@ -803,9 +848,27 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fwd_kernel(AttnArgs a) {
         block(std::integral_constant<int, 1>{});
     }
 
-    const float l_tot = sum_across_halves(l_run);
     lds_barrier();                                     // the tiles are done with: LDS now stages the output rows
-    store_rows<D, CB>(smem + wave * STAGE_BYTES<D>, oacc, valid ? 1.f / l_tot : 0.f, (bf16_t *)a.o + (long)(q0 + wave * 32) * nq + head * dh,
+    uint8_t *stage = smem_all + wave * STAGE_BYTES<D>;
+    if constexpr (PARTS == 2) {                        // two partial softmaxes over disjoint keys become one
+        uint8_t *box = smem_all + wave * XCHG_BYTES<16 * CB + 2>;
+        float2 *ml = reinterpret_cast<float2 *>(box + 16 * CB * 256) + lane;
+        stage += WAVES * XCHG_BYTES<16 * CB + 2>;
+        if (part == 1) {
+            put_acc(box, oacc);
+            *ml = make_float2(m_run, l_run);
+        }
+        lds_barrier();
+        if (part == 1) return;
+        const float m1 = ml->x, m = fmaxf(m_run, m1);
+        const float w0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m) * sl2);
+        const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m1 - m) * sl2);
+        merge_acc(box, oacc, w0, w1);
+        l_run = l_run * w0 + ml->y * w1;
+        m_run = m;
+    }
+    const float l_tot = sum_across_halves(l_run);
+    store_rows<D, CB>(stage, oacc, valid ? 1.f / l_tot : 0.f, (bf16_t *)a.o + (long)(q0 + wave * 32) * nq + head * dh,
                       nq, T - (q0 + wave * 32), dh);
     if (valid && half == 0) a.lse[(long)head * T + q] = (m_run * sl2 + __builtin_amdgcn_logf(l_tot)) * LN2;
     add_busy(a.cu_busy, true);
@@ -1066,14 +1129,15 @@ done:
 // ------------------------------------------------------------------------------------------
 // backward: dK, dV, the plain form: a block's scores, its softmax and its products one after the other, two LDS
 // slots.  Used for the 64-wide head, where it fits 256 registers, so that two workgroups share a compute unit
-// and overlap each other's phases; the pipelined kernel above needs more registers than that at any width.
+// and overlap each other's phases; the pipelined kernel above needs more registers than that at any width.  PARTS = 2: two
+// groups of 4 wavefronts with the same 128 keys and every other (head, query tile) step each (see two_parts).
 // ------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void attn_dkv_plain_kernel(AttnArgs a) {
+template <int D, int PARTS>
+__global__ __launch_bounds__(PARTS * 256, PARTS) void attn_dkv_plain_kernel(AttnArgs a) {
     constexpr int KS = D / 16, CB = D / 32;
     constexpr int TILE = BT2 * D * 2, SLOT = 2 * TILE + 2 * BT2 * 4;   // Q tile, dO tile, lse[64], D[64]
     constexpr int COPIES = BT2 * D * 2 / 1024 / 4;                     // per wavefront and tile
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_all[];
     add_busy(a.cu_busy ? a.cu_busy + 2048 : nullptr, false);
 
     // grid: x = key/value head, y = position in the dispatch order of the key tiles (heaviest first), z = this workgroup's share
@@ -1083,7 +1147,9 @@ __global__ __launch_bounds__(256) void attn_dkv_plain_kernel(AttnArgs a) {
     const int group = g * group_heads + (blockIdx.z + 1) * group_heads / a.dkv_parts - h_first;
     const int k0 = (a.use_order ? a.order_k[blockIdx.y] : blockIdx.y) * BQ;
     // the wavefront's index as a scalar: what is derived from it (copy destinations, buffer descriptors) stays uniform
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
+    const int part = PARTS == 1 ? 0 : wv >> 2, wave = PARTS == 1 ? wv : wv & 3;
+    uint8_t *const smem = smem_all + part * DKV_PLAIN_LDS<D>;
     const int T = a.T;
     const bf16_t *qkv = (const bf16_t *)a.qkv;
     const bf16_t *dO = (const bf16_t *)a.d_o;
@@ -1139,7 +1205,7 @@ __global__ __launch_bounds__(256) void attn_dkv_plain_kernel(AttnArgs a) {
         uint8_t *stage_k = smem + 2 * SLOT + wave * 2 * ROWS32_BYTES<D>, *stage_v = stage_k + ROWS32_BYTES<D>;
         cp_kv.issue(rs_q, stage_k, k0 + wave * 32, ld, nq + g * dh);
         cp_kv.issue(rs_q, stage_v, k0 + wave * 32, ld, nq + nk + g * dh);
-        copy_tile(smem, h_first, qbeg);
+        if (part < n_steps) copy_tile(smem, h_first + part / tiles_per_head, qbeg + (part % tiles_per_head) * BT2);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -1148,17 +1214,17 @@ __global__ __launch_bounds__(256) void attn_dkv_plain_kernel(AttnArgs a) {
         }
     }
     int slot = 0;
-    for (int step = 0; step < n_steps; ++step, slot ^= 1) {
-        const int hh = step / tiles_per_head, qt = qbeg + (step % tiles_per_head) * BT2;
+    for (int step = part; step - part < n_steps; step += PARTS, slot ^= 1) {
+        const int qt = qbeg + (step % tiles_per_head) * BT2;
         const uint8_t *sQ = smem + slot * SLOT, *sdO = sQ + TILE;
         const float *sLse = reinterpret_cast<const float *>(sQ + 2 * TILE), *sD = sLse + BT2;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this step's tiles have landed
         lds_barrier();                                               // ... and everyone is done with the other slot
-        if (step + 1 < n_steps) {
-            const int nh2 = (step + 1) / tiles_per_head, nqt = qbeg + ((step + 1) % tiles_per_head) * BT2;
+        if (step + PARTS < n_steps) {
+            const int nh2 = (step + PARTS) / tiles_per_head, nqt = qbeg + ((step + PARTS) % tiles_per_head) * BT2;
             copy_tile(smem + (slot ^ 1) * SLOT, h_first + nh2, nqt);
         }
-        (void)hh;
+        if (PARTS == 2 && step >= n_steps) break;                    // the second group's last step of an odd number
         auto block = [&](auto B_) {
             constexpr int b = decltype(B_)::value;
             const int qb = qt + 32 * b;
@@ -1245,7 +1311,20 @@ __global__ __launch_bounds__(256) void attn_dkv_plain_kernel(AttnArgs a) {
     }
 done:
     lds_barrier();                                     // the tiles are done with: LDS now stages the output rows
-    store_dkv<D, CB>(a, smem, wave, half, g, k0 + wave * 32, key, valid, dk, dv);
+    uint8_t *stage = smem_all;
+    if constexpr (PARTS == 2) {
+        uint8_t *box = smem_all + wave * 2 * XCHG_BYTES<16 * CB>;
+        stage += 8 * XCHG_BYTES<16 * CB>;
+        if (part == 1) {
+            put_acc(box, dk);
+            put_acc(box + XCHG_BYTES<16 * CB>, dv);
+        }
+        lds_barrier();
+        if (part == 1) return;
+        merge_acc(box, dk, 1.f, 1.f);
+        merge_acc(box + XCHG_BYTES<16 * CB>, dv, 1.f, 1.f);
+    }
+    store_dkv<D, CB>(a, stage, wave, half, g, k0 + wave * 32, key, valid, dk, dv);
     add_busy(a.cu_busy ? a.cu_busy + 2048 : nullptr, true);
 }
 
@@ -1268,60 +1347,86 @@ bool four_waves(const AttnArgs &a) {
     return D <= 64 || tiles * a.nh < 512 || (a.q_steps > 0 && a.q_steps <= 14 * tiles);
 }
 
-template <int D, int KS, int CB, int W>
+// Two groups of four wavefronts per workgroup, each with every other 64-row step of the same 128 queries (keys) and their partial
+// results merged at the end: where 128 rows per workgroup do not even give every compute unit two workgroups, a workgroup's chain
+// of steps is what a launch takes, one wavefront per SIMD has nothing to hide its waits, and the halved chain pays for the merge.
+// With two workgroups per compute unit and more it is the other way round.  Forward / dQ + dK/dV in us, one -> two groups:
+// 16 heads of 64, 576 tokens 14 / 34 -> 12 / 29, 2304 in a long document (288 workgroups) 36 / 103 -> 28 / 76, 3500 (448) 52 / 152
+// -> 40 / 113; 16 of 80, 3500 42 / 113 -> 40 / 111; 32 of 128 (whose dK/dV kernel has no such form), 1031 (288) 25 / 62 -> 21 / 55,
+// 1500 (384) 31 / 78 -> 25 / 70; but 2304 (576) 33 / 98 -> 38 / 103 and 64 heads of 128, 1031 (576) 28 / 94 -> 30 / 94.
+bool two_parts(long workgroups) { return workgroups <= 512; }
+
+template <int D, int KS, int CB, int W, int PARTS>
 hipError_t launch_fwd(const AttnArgs &a, hipStream_t st) {
     static std::atomic<bool> configured{false};     // set once; concurrent first calls repeat the same idempotent set-up
-    const int smem = std::max(2 * 2 * BT2 * D * 2 + (W == 4 ? 0 : W * ROWS32_BYTES<D>), W * STAGE_BYTES<D>);
+    constexpr int XCHG = PARTS == 1 ? 0 : W * XCHG_BYTES<16 * CB + 2>;
+    const int smem = std::max(PARTS * 2 * 2 * BT2 * D * 2 + (W == 4 ? 0 : W * ROWS32_BYTES<D>), XCHG + W * STAGE_BYTES<D>);
     if (!configured.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_fwd_kernel<D, KS, CB, W>, smem);
+        hipError_t e = set_smem(attn_fwd_kernel<D, KS, CB, W, PARTS>, smem);
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
     }
-    attn_fwd_kernel<D, KS, CB, W><<<dim3(a.nh, ceil_div(a.T, FQ) * (FQ / (W * 32))), W * 64, smem, st>>>(a);
+    attn_fwd_kernel<D, KS, CB, W, PARTS><<<dim3(a.nh, ceil_div(a.T, FQ) * (FQ / (W * 32))), W * PARTS * 64, smem, st>>>(a);
     return hipGetLastError();
 }
-template <int D, int KS, int CB, int W>
+template <int D, int KS, int CB, int W, int PARTS>
 hipError_t launch_dq(const AttnArgs &a, hipStream_t st) {
     static std::atomic<bool> configured{false};
-    const int smem = std::max(DQ_LDS_BYTES<D, W>, W * STAGE_BYTES<D>);
+    constexpr int XCHG = PARTS == 1 ? 0 : W * XCHG_BYTES<16 * CB>;
+    const int smem = std::max(PARTS * DQ_LDS_BYTES<D, W>, XCHG + W * STAGE_BYTES<D>);
     if (!configured.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_dq_kernel<D, KS, CB, W>, smem);
+        hipError_t e = set_smem(attn_dq_kernel<D, KS, CB, W, PARTS>, smem);
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
     }
-    attn_dq_kernel<D, KS, CB, W><<<dim3(a.nh, ceil_div(a.T, FQ) * (FQ / (W * 32))), W * 64, smem, st>>>(a);
+    attn_dq_kernel<D, KS, CB, W, PARTS><<<dim3(a.nh, ceil_div(a.T, FQ) * (FQ / (W * 32))), W * PARTS * 64, smem, st>>>(a);
+    return hipGetLastError();
+}
+template <int D, int PARTS>
+hipError_t launch_dkv_plain(const AttnArgs &a, const dim3 &grid, hipStream_t st) {
+    static std::atomic<bool> configured{false};
+    static_assert(8 * XCHG_BYTES<D / 2> + 4 * STAGE32_BYTES<D> <= 2 * DKV_PLAIN_LDS<D> && 4 * STAGE32_BYTES<D> <= DKV_PLAIN_LDS<D>,
+                  "room for the exchange and the staged rows");
+    if (!configured.load(std::memory_order_acquire)) {
+        hipError_t e = set_smem(attn_dkv_plain_kernel<D, PARTS>, PARTS * DKV_PLAIN_LDS<D>);
+        if (e != hipSuccess) return e;
+        configured.store(true, std::memory_order_release);
+    }
+    attn_dkv_plain_kernel<D, PARTS><<<grid, PARTS * 256, PARTS * DKV_PLAIN_LDS<D>, st>>>(a);
     return hipGetLastError();
 }
 
 template <int D, int KS, int CB>
 hipError_t launch_fwd(const AttnArgs &a, hipStream_t st) {
+    if (two_parts((long)a.nh * ceil_div(a.T, 128))) return launch_fwd<D, KS, CB, 4, 2>(a, st);
     if constexpr (D > 64)
-        if (!four_waves<D>(a)) return launch_fwd<D, KS, CB, 8>(a, st);
-    return launch_fwd<D, KS, CB, 4>(a, st);
+        if (!four_waves<D>(a)) return launch_fwd<D, KS, CB, 8, 1>(a, st);
+    return launch_fwd<D, KS, CB, 4, 1>(a, st);
 }
 
 template <int D, int KS, int CB>
 hipError_t launch_bwd(const AttnArgs &a, hipStream_t st) {
-    static std::atomic<bool> configured{false};
-    constexpr bool PIPELINED = D > 64;                  // see attn_dkv_plain_kernel
-    constexpr int DKV_SLOT = 2 * BT2 * D * 2 + 2 * BT2 * 4;
-    static_assert(4 * STAGE32_BYTES<D> <= 2 * DKV_SLOT + 2 * DKV_STAGE_BYTES<D>, "room for the staged fp32 rows");
-    const int smem_dkv = PIPELINED ? 3 * DKV_SLOT + DKV_STAGE_BYTES<D> : 2 * DKV_SLOT + 2 * DKV_STAGE_BYTES<D>;
     hipError_t e;
-    if (!configured.load(std::memory_order_acquire)) {
-        if constexpr (PIPELINED) e = set_smem(attn_dkv_kernel<D, KS, CB>, smem_dkv);
-        else e = set_smem(attn_dkv_plain_kernel<D>, smem_dkv);
-        if (e != hipSuccess) return e;
-        configured.store(true, std::memory_order_release);
-    }
-    if (four_waves<D>(a)) e = launch_dq<D, KS, CB, 4>(a, st);
-    else if constexpr (D > 64) e = launch_dq<D, KS, CB, 8>(a, st);
+    if (two_parts((long)a.nh * ceil_div(a.T, 128))) e = launch_dq<D, KS, CB, 4, 2>(a, st);
+    else if (four_waves<D>(a)) e = launch_dq<D, KS, CB, 4, 1>(a, st);
+    else if constexpr (D > 64) e = launch_dq<D, KS, CB, 8, 1>(a, st);
     if (e != hipSuccess) return e;
     const dim3 grid(a.nkv, ceil_div(a.T, BQ), a.dkv_parts);
-    if constexpr (PIPELINED) attn_dkv_kernel<D, KS, CB><<<grid, 256, smem_dkv, st>>>(a);
-    else attn_dkv_plain_kernel<D><<<grid, 256, smem_dkv, st>>>(a);
+    if constexpr (D <= 64) {                            // the plain form (see attn_dkv_plain_kernel)
+        if (two_parts((long)grid.x * grid.y * grid.z)) e = launch_dkv_plain<D, 2>(a, grid, st);
+        else e = launch_dkv_plain<D, 1>(a, grid, st);
+    } else {
+        static std::atomic<bool> configured{false};
+        constexpr int DKV_SLOT = 2 * BT2 * D * 2 + 2 * BT2 * 4, smem_dkv = 3 * DKV_SLOT + DKV_STAGE_BYTES<D>;
+        static_assert(4 * STAGE32_BYTES<D> <= smem_dkv, "room for the staged fp32 rows");
+        if (!configured.load(std::memory_order_acquire)) {
+            if ((e = set_smem(attn_dkv_kernel<D, KS, CB>, smem_dkv)) != hipSuccess) return e;
+            configured.store(true, std::memory_order_release);
+        }
+        attn_dkv_kernel<D, KS, CB><<<grid, 256, smem_dkv, st>>>(a);
+    }
     if (a.dkv_parts > 1) dkv_reduce_kernel<<<ceil_div((long)a.T * 2 * a.nkv * (a.d / 8), 256), 256, 0, st>>>(a);
-    return hipGetLastError();
+    return e != hipSuccess ? e : hipGetLastError();
 }
 
 }  // namespace

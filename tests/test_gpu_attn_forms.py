@@ -1,5 +1,5 @@
-"""The two forms of the forward and dQ kernels for heads wider than 64 features: 128 queries per workgroup on short packs, 256 where
-many workgroups walk many keys, either side of the line and with ragged ends."""
+"""The forms of the attention kernels: 256 queries per workgroup where many workgroups walk many keys (heads wider than 64 features), 128
+on short packs, and there two groups of wavefronts that share the steps up to 512 workgroups; either side of the lines, ragged ends."""
 import numpy as np
 import pytest
 
@@ -20,3 +20,10 @@ def test_long_rows_many_heads(nh, nkv, d):
 def test_ends_of_128_query_workgroups(d, T):
     cut = T // 3
     attn_case(mm.BF16, 3, 3, d, np.array([0, cut, T], dtype=np.int32), np.array([0, 1], dtype=np.uint8), seed=52)
+
+
+# 1100 tokens: 9 tiles of 128; 57 heads make 513 workgroups, 56 make 504 (two groups of wavefronts, an even and an odd number of steps)
+@pytest.mark.parametrize("nh,nkv,d", [(57, 57, 64), (56, 56, 64), (56, 7, 64), (57, 19, 48), (56, 28, 80), (56, 56, 96), (56, 8, 128)])
+@pytest.mark.parametrize("cu,modes", [([0, 1, 66, 1100], [0, 1, 0]), ([0, 600, 728, 1100], [1, 0, 1])])
+def test_workgroups_of_two_groups(nh, nkv, d, cu, modes):
+    attn_case(mm.BF16, nh, nkv, d, np.array(cu, dtype=np.int32), np.array(modes, dtype=np.uint8), seed=53)
