@@ -175,15 +175,17 @@ int choose_tile(const GemmArgs *gs, int n, int n_cu, double &us) {
 // scratch, and a kernel that adds them up.  The smaller tile shapes fill the chip too, but at half or a quarter of the
 // arithmetic per byte on every K step; the cut pays for its scratch traffic and second launch once, so it wins where K is long.
 // The rule compares choose_tile's estimate with the same model for K / splits, plus the reduction (its launch and 0.345 us per
-// MB), and asks for 5 % as both are fits.  Measured with operands that come from HBM (larger than the memory-side cache holds
-// from call to call), tile shape -> cut: 1031 x 4096 x 22016 (the gate / up input gradient of a short pack) 233 -> 177 us in
-// three chunks, 300 x 4096 x 22016 154 -> 78 in eight, 1031 x 1280 x 22016 136 -> 70 in eight; at the rule's edge, 2304 x 1024 x
-// 11008, 69 -> 70.  Up to K = 8192 the tile shapes are ahead.
+// MB), and asks for 5 % as both are fits.  The tile shapes' constants hold for operands that the memory-side cache keeps (256 MB);
+// from HBM they take 1.2 to 1.6 times as long (the 256 x 256 chunks, each of which one XCD's L2 reads once, do not), so operands
+// of more than 96 MB, most of which are a large layer's weights, count against them with 1.2.  Measured with operands from
+// HBM, tile shape -> cut: 1031 x 4096 x 22016 (the gate / up input gradient of a short pack) 233 -> 177 us in three chunks, 1031 x
+// 4096 x 12288 (QKV) 128 -> 110, 366 x 4096 x 12288 86 -> 56 in eight, 1031 x 1280 x 22016 136 -> 70 in eight; at the rule's
+// edges 2304 x 1024 x 11008 69 -> 71 and 700 x 8192 x 13824 154 -> 157.  Up to K = 8192 the tile shapes are ahead.
 int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
     if (g.layout != GEMM_NN || g.bias || g.residual || !g.split_ws) return 1;
     const long tiles = (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE);
     const size_t plane = (size_t)g.M * g.N * 4;
-    best_us *= 0.95;
+    best_us *= (size_t)(g.M + g.N) * g.K * 2 > (96u << 20) ? 1.15 : 0.95;
     int best = 1;
     for (int s = 2; s <= 8 && s * tiles <= n_cu && s * 512 <= g.K && s * plane <= g.split_ws_bytes; ++s) {
         const double fill = (double)(s * tiles) / n_cu;
