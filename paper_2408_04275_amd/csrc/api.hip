@@ -44,7 +44,7 @@ struct BwdWs {
     void *d_m, *d_pre, *d_h, *d_y1, *d_o, *d_qkv;
     float *Dsum, *part_g, *part_b, *part_c, *part_din, *part_dres;      // partial sums of the second normalisation's backward pass and of fc1's bias
     float *part_g1, *part_b1, *part_c2;                                 // ... of the first normalisation's and of the QKV bias (all reduced at the end of the pass)
-    void *split_ws; size_t split_bytes;     // fp32 partial products of split weight-gradient GEMMs
+    void *split_ws; size_t split_bytes;     // fp32 partial products of GEMMs cut along K
     float *dkv_part; size_t dkv_part_bytes; // fp32 partial sums of dK and dV (grouped heads)
 };
 
@@ -136,8 +136,9 @@ void carve_ctx(Bump &b, const Dims &D, size_t T, Ctx &c) {
 }
 
 // What mmtrain_gemm_workspace_bytes answers: the scratch of a partly filled last round cut along K (gemm_mfma_tail_splits: never
-// more than 256 blocks of 256 x 256), and for few output tiles, which smaller tile shapes serve without scratch, the size
-// callers have been given for a cut of theirs.
+// more than 256 blocks of 256 x 256), and for few output tiles up to 256 tiles' worth of M x N partial products, which covers a
+// cut of an NN product (few_tile_splits: chunks * tiles <= compute units) and is what callers have been given for weight gradients,
+// which smaller tile shapes serve without scratch now.
 size_t gemm_scratch_bytes(size_t M, size_t N) {
     const size_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
     if (tiles > 128) return tiles % 256 && tiles % 256 <= 128 ? size_t(256) * 256 * 256 * 4 : 0;
