@@ -146,6 +146,8 @@ size_t gemm_scratch_bytes(size_t M, size_t N) {
     return s >= 2 ? s * M * N * 4 : 0;
 }
 
+// Every part is sized so that it never shrinks as T grows, also where the kernels need less of it for a longer pack (longer slabs,
+// fewer shares or chunks): a caller allocates once, for its longest pack, and the shorter ones have to fit.
 void carve_bwd(Bump &b, const Dims &D, size_t T, BwdWs &w) {
     w.d_m = b.take_elems(T * D.F, D.dtype);
     w.d_pre = b.take_elems(T * D.F1, D.dtype);
@@ -160,23 +162,24 @@ void carve_bwd(Bump &b, const Dims &D, size_t T, BwdWs &w) {
     w.part_din = enc ? b.take<float>((size_t)norm_bwd_blocks((int)T, D.H) * D.H) : nullptr;
     w.part_dres = enc ? b.take<float>((size_t)norm_bwd_blocks((int)T, D.H) * D.H) : nullptr;
     const int maxn = D.nqkv > D.F1 ? (D.nqkv > D.H ? D.nqkv : D.H) : (D.F1 > D.H ? D.F1 : D.H);
-    w.part_c = b.take<float>((size_t)colsum_slabs((int)T) * maxn);
+    const size_t slabs = colsum_slabs_max((int)T);
+    w.part_c = b.take<float>(slabs * maxn);
     w.part_g1 = b.take<float>((size_t)norm_bwd_blocks((int)T, D.H) * D.H);
     w.part_b1 = enc ? b.take<float>((size_t)norm_bwd_blocks((int)T, D.H) * D.H) : nullptr;
-    w.part_c2 = enc ? b.take<float>((size_t)colsum_slabs((int)T) * D.nqkv) : nullptr;
-    // scratch for the fp32 partial products of GEMMs that are cut along K (see gemm_scratch_bytes)
-    auto need = [](size_t M, size_t N) -> size_t { return gemm_scratch_bytes(M, N); };
+    w.part_c2 = enc ? b.take<float>(slabs * D.nqkv) : nullptr;
+    // scratch for the fp32 partial products of GEMMs that are cut along K: the four input gradients, the four weight gradients
     size_t sb = 0;
     if (D.dtype == DT_BF16) {
-        const size_t c[8] = {need(D.H, D.F), need(D.F1, D.H), need(D.H, D.nq), need(D.nqkv, D.H),
-                             need(T, D.F), need(T, D.H), need(T, D.nq), 0};
-        for (size_t v : c) sb = v > sb ? v : sb;
+        const long t = (long)T;
+        for (size_t v : {gemm_mfma_nn_scratch(t, D.F, D.H), gemm_mfma_nn_scratch(t, D.H, D.F1), gemm_mfma_nn_scratch(t, D.nq, D.H),
+                         gemm_mfma_nn_scratch(t, D.H, D.nqkv), gemm_mfma_tn_scratch(D.H, D.F, t), gemm_mfma_tn_scratch(D.F1, D.H, t),
+                         gemm_mfma_tn_scratch(D.H, D.nq, t), gemm_mfma_tn_scratch(D.nqkv, D.H, t)})
+            sb = v > sb ? v : sb;
     }
     w.split_bytes = sb;
     w.split_ws = sb ? (void *)b.take<float>(sb / 4) : nullptr;
-    const int parts = D.dtype == DT_BF16 && T ? attn_dkv_parts((int)T, D.nh, D.nkv, D.d) : 1;
-    w.dkv_part_bytes = parts > 1 ? parts * attn_dkv_part_bytes((int)T, D.nkv, D.d) : 0;
-    w.dkv_part = parts > 1 ? b.take<float>(w.dkv_part_bytes / 4) : nullptr;
+    w.dkv_part_bytes = D.dtype == DT_BF16 ? attn_dkv_room((int)T, D.nh, D.nkv, D.d) : 0;
+    w.dkv_part = w.dkv_part_bytes ? b.take<float>(w.dkv_part_bytes / 4) : nullptr;
 }
 
 hipError_t gemm(int dtype, const GemmArgs &g, hipStream_t st);

@@ -1447,12 +1447,21 @@ hipError_t attn_mfma_fwd(const AttnArgs &a, hipStream_t st) {
 // 204 -> 97 (4), 2047 260 -> 161 (4), 4096 411 -> 314 (2), 6000 625 -> 507 (2), where one and a half rounds become three; at 8192
 // tokens (512 workgroups as they are) two would gain 4 to 8 % for 134 MB of scratch, at 12000 nothing.  16 / 2 heads of 64, 2047
 // tokens: 199 -> 58 (8).
+static long longest_shared(long parts, int nkv, int d) {              // the longest pack whose groups are shared out over `parts` workgroups
+    const long tiles = d <= 64 ? 1536 / (parts * nkv) : (parts == 2 ? 384 : std::min(384l, 512 / parts)) / nkv;
+    return std::min(tiles * BQ, (long)(DKV_PART_BYTES_MAX / (parts * attn_dkv_part_bytes(1, nkv, d))));
+}
 int attn_dkv_parts(int T, int nh, int nkv, int d) {
-    const long group = nh / nkv, workgroups = (long)nkv * ceil_div(T, BQ), most = d <= 64 ? 1536 : workgroups <= 384 ? std::max(512l, 2 * workgroups) : 0;
     int parts = 1;
-    for (long p = 2; p <= group; ++p)
-        if (group % p == 0 && p * workgroups <= most && p * attn_dkv_part_bytes(T, nkv, d) <= DKV_PART_BYTES_MAX) parts = (int)p;
+    for (int p = 2; p <= nh / nkv; ++p)
+        if (nh / nkv % p == 0 && T <= longest_shared(p, nkv, d)) parts = p;
     return parts;
+}
+size_t attn_dkv_room(int T, int nh, int nkv, int d) {
+    size_t most = 0;
+    for (int p = 2; p <= nh / nkv; ++p)
+        if (nh / nkv % p == 0) most = std::max(most, p * attn_dkv_part_bytes((int)std::min((long)T, longest_shared(p, nkv, d)), nkv, d));
+    return most;
 }
 
 hipError_t attn_mfma_bwd(const AttnArgs &args, hipStream_t st) {

@@ -3,6 +3,7 @@
 // storage is fp32 or bf16.  Every kernel moves 16 bytes per lane per access and
 // touches each tensor once (rows are re-read from cache, not from HBM).
 #include "kernels.h"
+#include <algorithm>
 #include <atomic>
 
 namespace mmt {
@@ -696,6 +697,7 @@ hipError_t reduce_jobs(int dtype, const ReduceJob *jobs, int n, bool accumulate,
 // 15.5 at 4; 4111 x 5120 35.9 at 16, 29.8 at 8; 9536 x 4096 46.1 at 16, 48.3 at 8)
 int colsum_rows(int T) { return T > 6144 ? 16 : T > 3072 ? 8 : 4; }
 int colsum_slabs(int T) { return T > 0 ? ceil_div(T, colsum_rows(T)) : 1; }
+int colsum_slabs_max(int T) { return std::max({colsum_slabs(T), colsum_slabs(std::min(T, 3072)), colsum_slabs(std::min(T, 6144))}); }
 
 template <typename T>
 __global__ __launch_bounds__(256) void colsum_kernel(const T *__restrict__ in, int nrows, int N, int ld, int slab,

@@ -1,6 +1,7 @@
 // Host side of the bf16 GEMM (kernel: gemm_mfma.h): which tile shape, the K-cut of a gradient's partly filled last round, and
 // the 256 x 256 kernels.
 #include "gemm_mfma.h"
+#include <algorithm>
 #include <cmath>
 
 namespace mmt {
@@ -107,20 +108,49 @@ bool gemm_mfma_supported(const GemmArgs &g) {
 // one to begin with (fewer active compute units run at a higher clock), and the cut costs two extra launches.
 // Measured on the 22016 x 4096 x 8192 weight gradient (96 tiles in the last round, 2 chunks): 1.137 -> 1.100 ms; the
 // 8192 x 11008 x 4096 input gradient gains nothing, hence the bound on K.
+static int tail_chunks(long tiles, long K, int n_cu) {
+    const long rem = tiles % n_cu;
+    if (tiles < n_cu || rem == 0 || rem > n_cu / 2) return 1;
+    const long s = std::min({n_cu / rem, K / 512, 16l});
+    return s >= 2 && K * (s - 1) / s >= 4096 ? (int)s : 1;
+}
 int gemm_mfma_tail_splits(const GemmArgs &g, int n_cu, int &tail_tiles) {
     tail_tiles = 0;
     if (g.layout == GEMM_NT || !g.split_ws || g.bias || g.residual) return 1;
     const long tiles = (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE);
-    const long rem = tiles % n_cu;
-    if (tiles < n_cu || rem == 0 || rem > n_cu / 2) return 1;
-    long s = n_cu / rem;
-    s = s < g.K / 512 ? s : g.K / 512;
-    s = s < 16 ? s : 16;
-    const long fit = (long)(g.split_ws_bytes / ((size_t)rem * TILE * TILE * 4));
+    long s = tail_chunks(tiles, g.K, n_cu);
+    if (s < 2) return 1;
+    const long rem = tiles % n_cu, fit = (long)(g.split_ws_bytes / ((size_t)rem * TILE * TILE * 4));
     s = s < fit ? s : fit;
     if (s < 2 || (long)g.K * (s - 1) / s < 4096) return 1;
     tail_tiles = (int)rem;
     return (int)s;
+}
+
+// chunks that few_tile_splits may cut an input gradient into: no more tiles than compute units, 512 of K each
+constexpr int MAX_CHUNKS = 8;
+static int few_tile_chunks(long tiles, long K, int n_cu) { return (int)std::min({(long)MAX_CHUNKS, n_cu / tiles, K / 512}); }
+
+// Scratch with which neither cut is ever restricted, for an input gradient of at most M rows: the most that any row count up to M
+// uses, so that a caller's buffer for its longest pack serves every shorter one (the number of chunks falls as the rows grow).
+constexpr int WHOLE_CHIP = 256;                                       // compute units
+size_t gemm_mfma_nn_scratch(long M, long N, long K) {
+    const long tn = (N + TILE - 1) / TILE, tm = (M + TILE - 1) / TILE;
+    size_t most = 0;
+    for (long s = few_tile_chunks(tn, K, WHOLE_CHIP); s >= 2; --s)    // the most rows that s chunks are possible for
+        most = std::max(most, (size_t)s * std::min(M, WHOLE_CHIP / (s * tn) * TILE) * N * 4);
+    const long first = (WHOLE_CHIP + tn - 1) / tn;                    // the tile count modulo 256 repeats after 256 tile rows at most
+    for (long t = first; t <= tm && t < first + WHOLE_CHIP; ++t) {
+        const int s = tail_chunks(t * tn, K, WHOLE_CHIP);
+        if (s >= 2) most = std::max(most, (size_t)s * (t * tn % WHOLE_CHIP) * TILE * TILE * 4);
+    }
+    return most;
+}
+// The same for a weight gradient over at most K tokens (chunks grow with K)
+size_t gemm_mfma_tn_scratch(long M, long N, long K) {
+    const long tiles = (M + TILE - 1) / TILE * ((N + TILE - 1) / TILE);
+    const int s = tail_chunks(tiles, K, WHOLE_CHIP);
+    return s >= 2 ? (size_t)s * (tiles % WHOLE_CHIP) * TILE * TILE * 4 : 0;
 }
 
 // Weight-gradient products whose outputs have few tiles (at most 128: a narrow layer), run together: every tile of every
@@ -187,7 +217,7 @@ int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
     const size_t plane = (size_t)g.M * g.N * 4;
     best_us *= (size_t)(g.M + g.N) * g.K * 2 > (96u << 20) ? 1.15 : 0.95;
     int best = 1;
-    for (int s = 2; s <= 8 && s * tiles <= n_cu && s * 512 <= g.K && s * plane <= g.split_ws_bytes; ++s) {
+    for (int s = 2; s <= few_tile_chunks(tiles, g.K, n_cu) && s * plane <= g.split_ws_bytes; ++s) {
         const double fill = (double)(s * tiles) / n_cu;
         const double us = 3.4 + 4.13 + ceil_div(ceil_div(g.K, BK), s) * 0.958 * (1. + 0.276 * fill * fill) + 3.4 + 0.345e-6 * plane * (s + 0.5);
         if (us < best_us) { best = s; best_us = us; }

@@ -38,6 +38,10 @@ hipError_t gemm_f32_group(const GemmArgs *gs, int n, hipStream_t st);
 // gemm_mfma.hip: bf16 MFMA kernel.  `supported` checks alignment requirements.
 bool gemm_mfma_supported(const GemmArgs &g);
 hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st);
+// Scratch (GemmArgs::split_ws) with which no cut along K is restricted: input gradients of up to M rows (NN), weight gradients over
+// up to K tokens (TN).  Neither falls as that argument grows.
+size_t gemm_mfma_nn_scratch(long M, long N, long K);
+size_t gemm_mfma_tn_scratch(long M, long N, long K);
 // Weight gradients with few output tiles (gemm_mfma_few_tiles: transposed-A layout, no bias / residual, at most 128 tiles of
 // 256 x 256) computed together in one launch; up to 4, all with the same K and accumulate / c_f32.
 bool gemm_mfma_few_tiles(const GemmArgs &g);
@@ -98,10 +102,12 @@ hipError_t attn_mfma_fwd(const AttnArgs &a, hipStream_t st);
 hipError_t attn_mfma_bwd(const AttnArgs &a, hipStream_t st);
 
 // Backward, grouped heads: workgroups that share the query heads of a group (1: none), each with an fp32 partial result of
-// attn_dkv_part_bytes; parts * that never exceeds DKV_PART_BYTES_MAX.
+// attn_dkv_part_bytes; parts * that never exceeds DKV_PART_BYTES_MAX.  attn_dkv_room: the most that any pack of up to T tokens takes
+// (a longer pack has fewer shares).
 constexpr size_t DKV_PART_BYTES_MAX = size_t(96) << 20;
 inline size_t attn_dkv_part_bytes(int T, int nkv, int d) { return (size_t)T * 2 * nkv * d * 4; }
 int attn_dkv_parts(int T, int nh, int nkv, int d);
+size_t attn_dkv_room(int T, int nh, int nkv, int d);
 
 // elementwise.hip
 // Token bookkeeping of a pack: tok_seg, tok_info (see AttnArgs) and, if rope_cs is not null, the [T, d/2] rotary table.
@@ -129,6 +135,7 @@ hipError_t norm_bwd(int dtype, bool layernorm, const void *d_out, const void *x,
 hipError_t reduce_partials(int dtype, const float *part, int rows, int N, void *out, bool accumulate,
                            hipStream_t st);
 int colsum_slabs(int T);
+int colsum_slabs_max(int T);    // the most slabs that a pack of up to T tokens has (longer packs have longer slabs)
 // out[N] (+)= the sum of the rows of part[rows, N], for up to eight arrays of different shapes in one launch (null part or out: skipped)
 struct ReduceJob { const float *part; void *out; int rows, N; };
 hipError_t reduce_jobs(int dtype, const ReduceJob *jobs, int n, bool accumulate, hipStream_t st);
