@@ -155,7 +155,8 @@ MMTRAIN_API int mmtrain_layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_
                       void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /* Backward:  given dy[T,H] and the ctx of the matching forward call, writes dx[T,H]
- * and every non-NULL member of grads (grads itself may be NULL: input gradient only). */
+ * and every non-NULL member of grads (grads itself may be NULL: input gradient only).
+ * dx may be dy's buffer. */
 MMTRAIN_API int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch,
                       const mmtrain_layer_weights *weights, const void *x, const void *dy,
                       const void *ctx, void *dx, const mmtrain_layer_grads *grads, uint32_t flags,

@@ -275,7 +275,8 @@ hipError_t gemm(int dtype, const GemmArgs &g, hipStream_t st) {
 }
 
 // Weight-gradient GEMMs of a backward pass whose outputs have few tiles are not launched where they stand but
-// collected and run together at the end of the pass (gemm_mfma_group, gemm_f32_group): their operands all live until then.
+// collected and run together at the end of the pass (gemm_mfma_group, gemm_f32_group): their operands all live until then, except
+// dy where the caller lets dx overwrite it.
 struct DeferredWgrads {
     GemmArgs g[4];
     int n = 0;
@@ -415,7 +416,12 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     // ---- MLP block:  y = y1 + m . Wfc2^T (+ b_fc2)
     HIP_TRY(gemm(D.dtype, splittable(mk(GEMM_NN, T, D.F, D.H, dy, D.H, W->w_fc2, D.F, w.d_m, D.F), w.split_ws, w.split_bytes), st));
     DeferredWgrads later;
-    if (G.w_fc2) HIP_TRY(wgrad(D.dtype, splittable(f32out(mk(GEMM_TN, D.H, D.F, T, dy, D.H, c.m, D.F, G.w_fc2, D.F, nullptr, nullptr, accum), g32), w.split_ws, w.split_bytes), later, st));
+    const size_t act_bytes = (size_t)T * D.H * (D.dtype == DT_F32 ? 4 : 2);
+    const bool dy_lives = (uintptr_t)dx + act_bytes <= (uintptr_t)dy || (uintptr_t)dy + act_bytes <= (uintptr_t)dx;
+    if (G.w_fc2) {
+        const GemmArgs g = splittable(f32out(mk(GEMM_TN, D.H, D.F, T, dy, D.H, c.m, D.F, G.w_fc2, D.F, nullptr, nullptr, accum), g32), w.split_ws, w.split_bytes);
+        HIP_TRY(dy_lives ? wgrad(D.dtype, g, later, st) : gemm(D.dtype, g, st));
+    }
     // Partial sums (gain, bias and column-sum gradients) are reduced by ONE launch at the end of the pass: every array
     // has a buffer of its own in the workspace.
     ReduceJob jobs[8];
