@@ -825,4 +825,7 @@ int mmtrain_adam_step(const mmtrain_adam_desc *d, int64_t n, float *master, floa
     return MMTRAIN_OK;
 }
 
+// ---- for the tests: which form a call takes (host decisions only; not declared in mmtrain.h) -----------------------------
+MMTRAIN_API int mmtrain_route_adam(int64_t n, int32_t param_bytes) { return adam_streams((size_t)n, (size_t)param_bytes) ? 1 : 0; }
+
 }  // extern "C"

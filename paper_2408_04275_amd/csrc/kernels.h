@@ -156,6 +156,8 @@ struct AdamArgs {
     float lr, beta1, beta2, omb1, omb2, eps, weight_decay, grad_scale, inv_bias1, inv_bias2;
     int zero_grad;
 };
+// whether a shard of n elements is streamed (param_bytes: per element of the working copy, 0 without one)
+bool adam_streams(size_t n, size_t param_bytes);
 hipError_t adam_step(int param_dtype, size_t n, float *w, float *g, float *m, float *v, void *p, const AdamArgs &a,
                      hipStream_t st);
 

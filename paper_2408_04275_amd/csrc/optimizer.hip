@@ -7,6 +7,14 @@
 
 namespace mmt {
 
+// Streaming pays where the arrays do not fit the memory-side cache (256 MB) together.  us, plain -> streaming, on repeated
+// passes / after all inputs were written / after the gradient was / from HBM: 12.6 M elements with a bf16 copy (216 MiB)
+// 62 -> 65 / 63 -> 68 / 71 -> 65 / 92 -> 82, 16.8 M (288 MiB) 88 -> 85 / 85 -> 89 / 90 -> 84 / 119 -> 109, 21.0 M (360 MiB)
+// 135 -> 102 / 110 -> 108 / 117 -> 103 / 148 -> 127, 25.3 M 172 -> 124 / 144 -> 137 / 149 -> 124 / 174 -> 159, 41.9 M
+// 281 -> 202 / 255 -> 227 / 256 -> 213 / 278 -> 260.  With the gradient's load nontemporal too it was behind plain accesses
+// up to 33 M elements wherever an input was fresh (25.3 M: 152, 157).
+bool adam_streams(size_t n, size_t param_bytes) { return n * (16 + param_bytes) >= (size_t)360 << 20; }
+
 namespace {
 
 __device__ __forceinline__ void update(float &w, float g, float &m, float &v, const AdamArgs &a) {
@@ -27,7 +35,8 @@ __device__ __forceinline__ void store(T *p, V v) {
     else *reinterpret_cast<V *>(p) = v;
 }
 
-// QUADS groups of four elements per thread, all requested before the first is updated.  STREAM: nontemporal accesses.
+// QUADS groups of four elements per thread, all requested before the first is updated.  STREAM: nontemporal accesses, except for
+// the gradient's load: the backward pass has just written it, so the memory-side cache may still hold it.
 template <typename TP, bool STREAM, int QUADS>
 __global__ __launch_bounds__(256) void adam_kernel(size_t n, float *__restrict__ w, float *__restrict__ g,
                                                    float *__restrict__ m, float *__restrict__ v, TP *__restrict__ p,
@@ -38,7 +47,7 @@ __global__ __launch_bounds__(256) void adam_kernel(size_t n, float *__restrict__
     for (int k = 0; k < QUADS; ++k) {
         const size_t i = first + k * 1024;
         if (i + 4 > n) continue;
-        wv[k] = load<STREAM, f32x4>(w + i); gv[k] = load<STREAM, f32x4>(g + i);
+        wv[k] = load<STREAM, f32x4>(w + i); gv[k] = load<false, f32x4>(g + i);
         mv[k] = load<STREAM, f32x4>(m + i); vv[k] = load<STREAM, f32x4>(v + i);
     }
 #pragma unroll
@@ -73,10 +82,7 @@ __global__ __launch_bounds__(256) void adam_kernel(size_t n, float *__restrict__
 
 template <typename TP>
 hipError_t launch(size_t n, float *w, float *g, float *m, float *v, TP *p, const AdamArgs &a, hipStream_t st) {
-    // A shard far beyond the memory-side cache (256 MB) is streamed: nontemporal accesses, two groups per thread, 171 -> 158 us
-    // at 25.3 M elements (860 MB; a plain copy moves these bytes in 169 us).  A smaller one may still lie in the cache from the
-    // last step: plain accesses, 19.6 us against 27.9 at 4.2 M.
-    if (n >= (size_t)12 << 20) adam_kernel<TP, true, 2><<<(unsigned)((n + 2047) / 2048), 256, 0, st>>>(n, w, g, m, v, p, a);
+    if (adam_streams(n, p ? sizeof(TP) : 0)) adam_kernel<TP, true, 2><<<(unsigned)((n + 2047) / 2048), 256, 0, st>>>(n, w, g, m, v, p, a);
     else adam_kernel<TP, false, 1><<<(unsigned)((n + 1023) / 1024), 256, 0, st>>>(n, w, g, m, v, p, a);
     return hipGetLastError();
 }

@@ -1,4 +1,5 @@
-"""The optimizer step on a shard large enough for the streaming kernel, with a remainder, against the fp64 oracle."""
+"""The optimizer step on shards on both sides of the line from which it streams (360 MiB in all), with remainders, against the fp64
+oracle."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +11,7 @@ from paper_2408_04275_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [(12 << 20) + 1027, (12 << 20) + 2048])
+@pytest.mark.parametrize("n", [(12 << 20) + 1027, (12 << 20) + 2048, (20 << 20) + 1027, (20 << 20) + 2048])
 @pytest.mark.parametrize("param_dtype", [mm.BF16, mm.F32])
 def test_large_shard(n, param_dtype):
     rng = np.random.default_rng(n)
