@@ -826,6 +826,15 @@ int mmtrain_adam_step(const mmtrain_adam_desc *d, int64_t n, float *master, floa
 }
 
 // ---- for the tests: which form a call takes (host decisions only; not declared in mmtrain.h) -----------------------------
+MMTRAIN_API int mmtrain_route_gemm(int32_t layout, int32_t M, int32_t N, int32_t K, size_t workspace_bytes, int32_t n_cu, int32_t route[4]) {
+    GemmArgs g = mk(layout, M, N, K, nullptr, layout == GEMM_TN ? M : K, nullptr, layout == GEMM_NT ? K : N, nullptr, N);
+    if (!gemm_mfma_supported(g)) return MMTRAIN_ERR_UNSUPPORTED;
+    if (workspace_bytes) g = splittable(g, &g, workspace_bytes);             // (an address; nothing is written)
+    const GemmPlan p = gemm_mfma_plan(g, n_cu);
+    const int32_t r[4] = {p.tile_m, p.tile_n, p.tail_tiles, p.chunks};
+    for (int i = 0; i < 4; ++i) route[i] = r[i];
+    return MMTRAIN_OK;
+}
 MMTRAIN_API int mmtrain_route_adam(int64_t n, int32_t param_bytes) { return adam_streams((size_t)n, (size_t)param_bytes) ? 1 : 0; }
 
 }  // extern "C"

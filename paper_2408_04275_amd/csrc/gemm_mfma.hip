@@ -241,28 +241,41 @@ hipError_t gemm_mfma_group(const GemmArgs *gs, int n, hipStream_t st) {
     return launch_tn(choose_tile(gs, n, n_cu, us), p, n, st);
 }
 
-hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st) {
-    GemmP p = params(g);
-    int n_cu = 0, tail_tiles = 0;
-    hipError_t e = compute_units(n_cu);
-    if (e != hipSuccess) return e;
-    const int tail_s = gemm_mfma_tail_splits(g, n_cu, tail_tiles);
-    if (tail_tiles == 0) {
+GemmPlan gemm_mfma_plan(const GemmArgs &g, int n_cu) {
+    GemmPlan plan = {TILE_256, TILE, TILE, 0, 1, g.K};
+    int chunks = gemm_mfma_tail_splits(g, n_cu, plan.tail_tiles);
+    if (plan.tail_tiles == 0) {
         double us;
         const int shape = choose_tile(&g, 1, n_cu, us);
-        const int s = few_tile_splits(g, n_cu, us);
-        if (s > 1) {
-            p.k_chunk = ceil_div(ceil_div(g.K, s), BK) * BK;
-            p.splits = ceil_div(g.K, p.k_chunk);
-            p.C = (bf16_t *)g.split_ws; p.ldc = g.N; p.accumulate = 0; p.c_f32 = 1;
-            if ((e = launch_partials(g.layout, p, st)) != hipSuccess) return e;
-            sum_chunks_kernel<<<dim3(ceil_div(g.N, 2048), g.M < 4096 ? g.M : 4096), 256, 0, st>>>((const float *)g.split_ws, p.splits, g.M, g.N,
-                                                                                                   (bf16_t *)g.C, g.ldc, g.accumulate ? 1 : 0);
-            return hipGetLastError();
-        }
-        if (shape != TILE_256)
-            return g.layout == GEMM_NT ? launch_nt(shape, p, st) : g.layout == GEMM_NN ? launch_nn(shape, p, st) : launch_tn(shape, &p, 1, st);
+        chunks = few_tile_splits(g, n_cu, us);
+        if (chunks == 1) plan.shape = shape;
     }
+    for (const TileCost &t : COST_ROWS)
+        if (t.shape == plan.shape) { plan.tile_m = t.bm; plan.tile_n = t.bn; }
+    if (chunks > 1) {
+        plan.k_chunk = ceil_div(ceil_div(g.K, chunks), BK) * BK;
+        plan.chunks = ceil_div(g.K, plan.k_chunk);
+    }
+    return plan;
+}
+
+hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st) {
+    GemmP p = params(g);
+    int n_cu = 0;
+    hipError_t e = compute_units(n_cu);
+    if (e != hipSuccess) return e;
+    const GemmPlan plan = gemm_mfma_plan(g, n_cu);
+    const int tail_tiles = plan.tail_tiles;
+    if (plan.chunks > 1 && tail_tiles == 0) {
+        p.k_chunk = plan.k_chunk; p.splits = plan.chunks;
+        p.C = (bf16_t *)g.split_ws; p.ldc = g.N; p.accumulate = 0; p.c_f32 = 1;
+        if ((e = launch_partials(g.layout, p, st)) != hipSuccess) return e;
+        sum_chunks_kernel<<<dim3(ceil_div(g.N, 2048), g.M < 4096 ? g.M : 4096), 256, 0, st>>>((const float *)g.split_ws, p.splits, g.M, g.N,
+                                                                                               (bf16_t *)g.C, g.ldc, g.accumulate ? 1 : 0);
+        return hipGetLastError();
+    }
+    if (plan.shape != TILE_256)
+        return g.layout == GEMM_NT ? launch_nt(plan.shape, p, st) : g.layout == GEMM_NN ? launch_nn(plan.shape, p, st) : launch_tn(plan.shape, &p, 1, st);
     p.tile_count -= tail_tiles;                                       // the full rounds
     const bool add = p.residual || p.accumulate;
     if (g.c_f32) e = launch<false, false, false, true, Tile256>(p, st);
@@ -273,8 +286,7 @@ hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st) {
     GemmP t = params(g);
     t.C = (bf16_t *)g.split_ws; t.accumulate = 0; t.c_f32 = 1;
     t.tile_begin = p.tile_count; t.tile_count = tail_tiles; t.compact = 1;
-    t.k_chunk = ceil_div(ceil_div(g.K, tail_s), BK) * BK;
-    t.splits = ceil_div(g.K, t.k_chunk);
+    t.k_chunk = plan.k_chunk; t.splits = plan.chunks;
     e = launch_partials(g.layout, t, st);
     if (e != hipSuccess) return e;
     if (g.c_f32)

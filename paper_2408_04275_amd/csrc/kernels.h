@@ -38,6 +38,10 @@ hipError_t gemm_f32_group(const GemmArgs *gs, int n, hipStream_t st);
 // gemm_mfma.hip: bf16 MFMA kernel.  `supported` checks alignment requirements.
 bool gemm_mfma_supported(const GemmArgs &g);
 hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st);
+// How a product runs on n_cu compute units: tiles of tile_m x tile_n; all of it in `chunks` chunks of K (1: whole), or the last
+// tail_tiles tiles of the order in `chunks` chunks each.  Chunks are k_chunk long, the last one shorter.
+struct GemmPlan { int shape, tile_m, tile_n, tail_tiles, chunks, k_chunk; };
+GemmPlan gemm_mfma_plan(const GemmArgs &g, int n_cu);
 // Scratch (GemmArgs::split_ws) with which no cut along K is restricted: input gradients of up to M rows (NN), weight gradients over
 // up to K tokens (TN).  Neither falls as that argument grows.
 size_t gemm_mfma_nn_scratch(long M, long N, long K);

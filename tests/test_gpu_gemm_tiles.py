@@ -1,13 +1,15 @@
-"""Forward and input-gradient products in every tile shape the host can choose: sizes just past a tile edge, K with a remainder,
-K shorter than the look-ahead of the K loop and longer, with and without addends."""
+"""Products in every tile shape the host can choose and cut along K, each at sizes that do take that form (test_routes.py asks the
+library, also without a GPU): sizes just past a tile edge, K with a remainder, K shorter than the look-ahead of the K loop and longer, with and
+without addends."""
 import pytest
 
 from paper_2408_04275_amd import binding as mm
 from test_gpu_ops import gemm_case
+from util import gemm_route
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K) and the tile the rule in csrc/gemm_mfma.hip picks for it
+# (M, N, K) and the tile that the rule in csrc/gemm_mfma.hip picks for it
 SHAPES = [(9, 40, 24, "64x64"), (65, 136, 712, "64x64"), (129, 72, 256, "64x64"), (323, 2848, 8, "64x128"), (577, 2184, 1096, "64x128"),
           (593, 3328, 200, "128x128"), (705, 3208, 584, "128x128"), (1095, 3592, 136, "192x128"), (2703, 2184, 136, "256x128"),
           (2312, 3480, 72, "160x256"), (3880, 2576, 136, "192x256"), (3485, 3464, 328, "224x256")]
@@ -16,6 +18,7 @@ SHAPES = [(9, 40, 24, "64x64"), (65, 136, 712, "64x64"), (129, 72, 256, "64x64")
 @pytest.mark.parametrize("layout", [mm.GEMM_NT, mm.GEMM_NN])
 @pytest.mark.parametrize("M,N,K,tile", SHAPES)
 def test_gemm_tile_shape(layout, M, N, K, tile):
+    assert "%dx%d" % gemm_route(layout, M, N, K)[:2] == tile
     gemm_case(mm.BF16, layout, M, N, K, seed=21)
     gemm_case(mm.BF16, layout, M, N, K, bias=True, residual=True, accumulate=K > 500, seed=22)
 
@@ -27,13 +30,19 @@ WGRAD_SHAPES = [(8, 8, 1, "64x64"), (72, 136, 67, "64x64"), (520, 1032, 583, "64
 
 @pytest.mark.parametrize("M,N,K,tile", WGRAD_SHAPES)
 def test_weight_gradient_tile_shape(M, N, K, tile):
+    assert "%dx%d" % gemm_route(mm.GEMM_TN, M, N, K)[:2] == tile
     gemm_case(mm.BF16, mm.GEMM_TN, M, N, K, seed=23)
     gemm_case(mm.BF16, mm.GEMM_TN, M, N, K, accumulate=True, seed=24)
 
 
-# few tiles and a long K: with scratch an input gradient is cut along K (8, 5 and 7 chunks; K with a remainder, the last chunk shorter,
+# few tiles and a long K: with scratch an input gradient is cut along K (8, 7 and 5 chunks; K with a remainder, the last chunk shorter,
 # rows and columns past a tile edge); scratch for one chunk only leaves it whole
-@pytest.mark.parametrize("M,N,K,chunks", [(257, 4104, 25608, 8), (520, 4096, 22016, 5), (2304, 1032, 22024, 7), (257, 4104, 25608, 1)])
-def test_input_gradient_cut_along_k(M, N, K, chunks, monkeypatch):
-    monkeypatch.setattr(mm, "mmtrain_gemm_workspace_bytes", lambda layout, m, n: chunks * m * n * 4)
+CUTS = [(366, 4096, 12288, 8, 8), (257, 2056, 25608, 8, 8), (257, 4104, 25608, 8, 7), (520, 4096, 22016, 5, 5), (2304, 1032, 22024, 8, 5),
+        (257, 4104, 25608, 1, 1)]
+
+
+@pytest.mark.parametrize("M,N,K,room,chunks", CUTS)
+def test_input_gradient_cut_along_k(M, N, K, room, chunks, monkeypatch):
+    assert gemm_route(mm.GEMM_NN, M, N, K, room * M * N * 4)[2:] == (0, chunks)
+    monkeypatch.setattr(mm, "mmtrain_gemm_workspace_bytes", lambda layout, m, n: room * m * n * 4)
     gemm_case(mm.BF16, mm.GEMM_NN, M, N, K, accumulate=chunks == 5, seed=25, workspace=True)

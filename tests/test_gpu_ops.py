@@ -66,8 +66,8 @@ def test_gemm_bf16_many_tiles(layout):
     gemm_case(mm.BF16, layout, 2056, 2312, 328, seed=4)
 
 
-def test_gemm_bf16_few_tiles_cut_along_k():
-    # 4 output tiles, K = 4104: with scratch the weight-gradient layout is cut into K chunks (the last one ragged)
+def test_gemm_bf16_few_tiles_with_scratch():
+    # a weight gradient of 4 tiles of 256 x 256 and K = 4104, with the scratch its query grants (it runs in 64 x 64 tiles, uncut)
     assert mm.mmtrain_gemm_workspace_bytes(mm.GEMM_TN, 512, 392) > 0
     gemm_case(mm.BF16, mm.GEMM_TN, 512, 392, 4104, seed=5, workspace=True)
     gemm_case(mm.BF16, mm.GEMM_TN, 512, 392, 4104, accumulate=True, seed=6, workspace=True)

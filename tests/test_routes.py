@@ -2,7 +2,11 @@
 more scratch than the call has."""
 import ctypes as C
 
+import pytest
+
 from paper_2408_04275_amd import binding as mm
+from test_gpu_gemm_tiles import CUTS, SHAPES, WGRAD_SHAPES
+from util import gemm_route
 
 
 # the memory-side cache holds 256 MB; a shard whose arrays may still lie there from the pass before is not streamed
@@ -12,3 +16,43 @@ def test_optimizer_streams_only_what_cannot_be_cached():
     for n, param_bytes, streamed in [(4 << 20, 2, 0), (12 << 20, 2, 0), (16 << 20, 2, 0), ((20 << 20) - 1, 2, 0), (20 << 20, 2, 1),
                                      (18 << 20, 4, 1), (17 << 20, 4, 0), (20 << 20, 0, 0), (24 << 20, 0, 1), (1 << 30, 2, 1)]:
         assert route(n, param_bytes) == streamed, (n, param_bytes)
+
+
+# the sizes of the GPU parity tests take the forms that those tests name
+@pytest.mark.parametrize("layout", [mm.GEMM_NT, mm.GEMM_NN])
+@pytest.mark.parametrize("M,N,K,tile", SHAPES)
+def test_tile_shapes(layout, M, N, K, tile):
+    assert gemm_route(layout, M, N, K) == (*map(int, tile.split("x")), 0, 1)
+
+
+@pytest.mark.parametrize("M,N,K,tile", WGRAD_SHAPES)
+def test_weight_gradient_tile_shapes(M, N, K, tile):
+    assert gemm_route(mm.GEMM_TN, M, N, K) == (*map(int, tile.split("x")), 0, 1)
+
+
+def test_every_tile_shape_is_covered():
+    assert {s[3] for s in SHAPES} == {"64x64", "64x128", "128x128", "192x128", "256x128", "160x256", "192x256", "224x256"}
+    assert {s[3] for s in WGRAD_SHAPES} == {"64x64", "64x128", "128x128", "256x128"}
+
+
+@pytest.mark.parametrize("M,N,K,room,chunks", CUTS)
+def test_cuts_along_k(M, N, K, room, chunks):
+    assert gemm_route(mm.GEMM_NN, M, N, K, room * M * N * 4)[2:] == (0, chunks)
+    assert gemm_route(mm.GEMM_NN, M, N, K)[2:] == (0, 1)               # no scratch, no cut
+
+
+@pytest.mark.parametrize("layout", [mm.GEMM_NN, mm.GEMM_TN])
+def test_last_round_cut_along_k(layout):
+    # 288 tiles on 256 compute units: 32 of them in the last round, in 8 chunks (test_gpu_ops.py runs this product)
+    assert gemm_route(layout, 4360, 4040, 4872, mm.mmtrain_gemm_workspace_bytes(layout, 4360, 4040)) == (256, 256, 32, 8)
+
+
+@pytest.mark.parametrize("layout", [mm.GEMM_NT, mm.GEMM_NN, mm.GEMM_TN])
+def test_cuts_stay_within_their_scratch(layout):
+    for M in (8, 264, 520, 1032, 3000, 4360, 8192):
+        for N in (64, 1024, 1032, 4096, 11008):
+            for K in (8, 4096, 12288, 22016, 25608):
+                for room in (0, 256, M * N * 4, 3 * M * N * 4, 1 << 24, 1 << 40):
+                    tm, tn, tail, chunks = gemm_route(layout, M, N, K, room)
+                    assert chunks == 1 or chunks * (tail * 65536 if tail else M * N) * 4 <= room
+                    assert layout != mm.GEMM_NT or chunks == 1

@@ -1,4 +1,5 @@
 """Shared helpers of the GPU parity tests: run the oracle and the HIP path on the same seeded inputs."""
+import ctypes as C
 import os
 import sys
 import time
@@ -7,6 +8,7 @@ import numpy as np
 
 from oracle import bf16_storage
 from oracle import layer_oracle as orc
+from paper_2408_04275_amd import binding as mm
 from paper_2408_04275_amd import workloads as wl
 from paper_2408_04275_amd import parity
 
@@ -25,6 +27,15 @@ def say(msg):
             f.write(line + "\n")
     except OSError:
         pass
+
+
+def gemm_route(layout, M, N, K, workspace_bytes=0, compute_units=256):
+    """How a bf16 product runs: (tile rows, tile columns, tiles of the last round that are cut along K, chunks of K)."""
+    fn = mm.load_library().mmtrain_route_gemm
+    fn.argtypes = [C.c_int32] * 4 + [C.c_size_t, C.c_int32, C.POINTER(C.c_int32)]
+    route = (C.c_int32 * 4)()
+    assert fn(layout, M, N, K, workspace_bytes, compute_units, route) == mm.OK
+    return tuple(route)
 
 
 def oracle_run(shape, cu, modes, W, x, dy):
