@@ -252,20 +252,21 @@ typedef enum {
  * scratch for fp32 partial products.  With it, a bf16 NN or TN product without bias or
  * residual may be cut along K where that fills the chip better: the partly filled last
  * round of tiles of a large product, and all of an NN product with few tiles and a very
- * long K.  mmtrain_gemm_workspace_bytes() returns a size that allows the former (0 for NN with
- * few tiles: the latter takes chunks * M * N * 4 bytes where a caller has them, at most 8
- * chunks); a smaller workspace only restricts the cuts, and the result does not depend on
- * timing (the partial products are added in a fixed order). */
+ * long K.  mmtrain_gemm_workspace_bytes() returns a size that allows every such cut (for TN
+ * with few tiles, which is not cut, more than is used); a smaller workspace only restricts
+ * them, and the result does not depend on timing (the partial products are added in a fixed
+ * order). */
 MMTRAIN_API size_t mmtrain_gemm_workspace_bytes(int32_t layout, int32_t M, int32_t N);
 MMTRAIN_API int mmtrain_gemm(int32_t dtype, int32_t layout, int32_t M, int32_t N, int32_t K,
                  const void *A, int32_t lda, const void *B, int32_t ldb, void *C, int32_t ldc,
                  const void *bias, const void *residual, uint32_t flags,
                  void *workspace, size_t workspace_bytes, void *hip_stream);
 
-/* Bytes of workspace for the two attention operators below.  Beyond the per-token tables (the first
- * total_tokens * (12 + 4 n_heads) bytes or so, all that is required) it has room for the fp32 partial sums that
- * backward shares out when a group's query heads are worked off by several workgroups; with a smaller
- * workspace they are not. */
+/* Bytes of workspace for the two attention operators below.  Required are the per-token tables, for which
+ * total_tokens * (12 + 4 * n_heads) + 1024 bytes always suffice; less than the tables take is
+ * MMTRAIN_ERR_WORKSPACE.  Beyond them the answer has room for the fp32 partial sums that backward shares out when
+ * a group's query heads are worked off by several workgroups (at most 96 MiB; none are used where every query head
+ * has a key/value head of its own); with a smaller workspace they are not. */
 MMTRAIN_API size_t mmtrain_attn_workspace_bytes(int32_t total_tokens, int32_t n_segments, int32_t n_heads);
 
 /* Segment-masked attention forward over packed qkv[T, (nh + 2 nkv) d] (q heads | k heads |

@@ -135,17 +135,6 @@ void carve_ctx(Bump &b, const Dims &D, size_t T, Ctx &c) {
     c.m = b.take_elems(T * D.F, D.dtype);
 }
 
-// What mmtrain_gemm_workspace_bytes answers: the scratch of a partly filled last round cut along K (gemm_mfma_tail_splits: never
-// more than 256 blocks of 256 x 256), and for few output tiles up to 256 tiles' worth of M x N partial products, which covers a
-// cut of an NN product (few_tile_splits: chunks * tiles <= compute units) and is what callers have been given for weight gradients,
-// which smaller tile shapes serve without scratch now.
-size_t gemm_scratch_bytes(size_t M, size_t N) {
-    const size_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
-    if (tiles > 128) return tiles % 256 && tiles % 256 <= 128 ? size_t(256) * 256 * 256 * 4 : 0;
-    const size_t s = 256 / tiles < 32 ? 256 / tiles : 32;
-    return s >= 2 ? s * M * N * 4 : 0;
-}
-
 // Every part is sized so that it never shrinks as T grows, also where the kernels need less of it for a longer pack (longer slabs,
 // fewer shares or chunks): a caller allocates once, for its longest pack, and the shorter ones have to fit.
 void carve_bwd(Bump &b, const Dims &D, size_t T, BwdWs &w) {
@@ -638,8 +627,12 @@ int mmtrain_gemm(int32_t dtype, int32_t layout, int32_t M, int32_t N, int32_t K,
 size_t mmtrain_gemm_workspace_bytes(int32_t layout, int32_t M, int32_t N) {
     if (M <= 0 || N <= 0 || (layout != MMTRAIN_GEMM_NN && layout != MMTRAIN_GEMM_TN)) return 0;
     const size_t tiles = (((size_t)M + 255) / 256) * (((size_t)N + 255) / 256);
-    if (layout == MMTRAIN_GEMM_NN && tiles <= 128) return 0;       // only weight gradients are cut when tiles are few
-    return gemm_scratch_bytes((size_t)M, (size_t)N);
+    // a partly filled last round: never more than 256 blocks of 256 x 256
+    if (tiles > 128) return tiles % 256 && tiles % 256 <= 128 ? size_t(256) * 256 * 256 * 4 : 0;
+    // few tiles: an input gradient in as many chunks as its K, which is not known here, may allow; for a weight gradient, which is
+    // not cut, the size that callers have been given all along
+    const size_t most = layout == MMTRAIN_GEMM_NN ? 8 : 32, s = 256 / tiles < most ? 256 / tiles : most;
+    return s >= 2 ? s * (size_t)M * N * 4 : 0;
 }
 
 static size_t attn_scratch_bytes(int32_t total_tokens, int32_t n_heads) {

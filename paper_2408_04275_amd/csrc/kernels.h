@@ -19,7 +19,8 @@ struct GemmArgs {
     const void *residual;       // [M, ldc] or null
     bool accumulate;            // C += result
     bool c_f32 = false;         // C is fp32 whatever the operands' dtype (bias / residual are not combined with it)
-    // optional scratch for the fp32 partial products of a last round cut along K (NN and TN, bf16), 256-byte aligned
+    // optional scratch for the fp32 partial products of a last round cut along K (NN and TN, bf16) or of a whole product with
+    // few tiles (NN, bf16), 256-byte aligned
     void *split_ws = nullptr;
     size_t split_ws_bytes = 0;
     // measurement aid (matrix-core kernel only): when not null, device uint64[4]; the first workgroup stores the

@@ -35,14 +35,15 @@ def test_weight_gradient_tile_shape(M, N, K, tile):
     gemm_case(mm.BF16, mm.GEMM_TN, M, N, K, accumulate=True, seed=24)
 
 
-# few tiles and a long K: with scratch an input gradient is cut along K (8, 7 and 5 chunks; K with a remainder, the last chunk shorter,
-# rows and columns past a tile edge); scratch for one chunk only leaves it whole
-CUTS = [(366, 4096, 12288, 8, 8), (257, 2056, 25608, 8, 8), (257, 4104, 25608, 8, 7), (520, 4096, 22016, 5, 5), (2304, 1032, 22024, 8, 5),
-        (257, 4104, 25608, 1, 1)]
+# few tiles and a long K: with the scratch of its size query an input gradient is cut along K (8, 7 and 5 chunks; K with a remainder, the last chunk shorter,
+# rows and columns past a tile edge); scratch for fewer chunks allows no more than those, scratch for one leaves it whole
+CUTS = [(366, 4096, 12288, None, 8), (257, 2056, 25608, None, 8), (257, 4104, 25608, None, 7), (520, 4096, 22016, None, 5),
+        (2304, 1032, 22024, None, 5), (257, 4104, 25608, 5, 5), (257, 4104, 25608, 1, 1)]
 
 
 @pytest.mark.parametrize("M,N,K,room,chunks", CUTS)
 def test_input_gradient_cut_along_k(M, N, K, room, chunks, monkeypatch):
-    assert gemm_route(mm.GEMM_NN, M, N, K, room * M * N * 4)[2:] == (0, chunks)
-    monkeypatch.setattr(mm, "mmtrain_gemm_workspace_bytes", lambda layout, m, n: room * m * n * 4)
+    size = room * M * N * 4 if room else mm.mmtrain_gemm_workspace_bytes(mm.GEMM_NN, M, N)
+    assert gemm_route(mm.GEMM_NN, M, N, K, size)[2:] == (0, chunks)
+    monkeypatch.setattr(mm, "mmtrain_gemm_workspace_bytes", lambda layout, m, n: size)
     gemm_case(mm.BF16, mm.GEMM_NN, M, N, K, accumulate=chunks == 5, seed=25, workspace=True)

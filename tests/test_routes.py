@@ -37,7 +37,8 @@ def test_every_tile_shape_is_covered():
 
 @pytest.mark.parametrize("M,N,K,room,chunks", CUTS)
 def test_cuts_along_k(M, N, K, room, chunks):
-    assert gemm_route(mm.GEMM_NN, M, N, K, room * M * N * 4)[2:] == (0, chunks)
+    size = room * M * N * 4 if room else mm.mmtrain_gemm_workspace_bytes(mm.GEMM_NN, M, N)
+    assert gemm_route(mm.GEMM_NN, M, N, K, size)[2:] == (0, chunks)
     assert gemm_route(mm.GEMM_NN, M, N, K)[2:] == (0, 1)               # no scratch, no cut
 
 
@@ -56,3 +57,12 @@ def test_cuts_stay_within_their_scratch(layout):
                     tm, tn, tail, chunks = gemm_route(layout, M, N, K, room)
                     assert chunks == 1 or chunks * (tail * 65536 if tail else M * N) * 4 <= room
                     assert layout != mm.GEMM_NT or chunks == 1
+
+
+@pytest.mark.parametrize("layout", [mm.GEMM_NN, mm.GEMM_TN])
+def test_the_size_query_restricts_no_cut(layout):
+    for M in (8, 264, 368, 520, 1032, 2304, 3000, 4360, 8192):
+        for N in (64, 1024, 1032, 4096, 11008):
+            for K in (8, 4096, 12288, 22016, 25608):
+                size = mm.mmtrain_gemm_workspace_bytes(layout, M, N)
+                assert gemm_route(layout, M, N, K, size) == gemm_route(layout, M, N, K, 1 << 40)
