@@ -285,8 +285,9 @@ MMTRAIN_API int mmtrain_attn_bwd(const mmtrain_layer_desc *desc, const mmtrain_b
  * capture, tight serving or training loops, harnesses that forbid hipMalloc.  Same arguments, results and
  * kernels as mmtrain_attn_bwd without the workspace: the scratch (per-token segment tables, the per-head
  * row sums D that the dQ kernel hands to the dK/dV kernel, partial sums of dK and dV) is a fixed array of MMTRAIN_NOALLOC_SCRATCH_BYTES
- * inside the library, one copy on every GPU the library runs on, held until the process ends.  The call
- * allocates nothing and frees nothing, on the device or through any library.
+ * inside the library, one copy on every GPU on which this call is made: it arrives with the first such call, when
+ * the runtime loads the code it belongs to, and is held until the process ends.  Apart from that the call allocates
+ * nothing and frees nothing, on the device or through any library.
  *   Limits: total_tokens <= MMTRAIN_NOALLOC_MAX_TOKENS and total_tokens * n_heads <=
  *   MMTRAIN_NOALLOC_MAX_HEAD_TOKENS, else MMTRAIN_ERR_TOO_LARGE (checked on the host, nothing enqueued).
  *   All calls on one GPU share that GPU's array, which keeps the previous call's contents; no entry has to

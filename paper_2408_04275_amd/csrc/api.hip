@@ -150,9 +150,8 @@ void carve_bwd(Bump &b, const Dims &D, size_t T, BwdWs &w) {
     const bool enc = D.kind == MMTRAIN_ENCODER;            // bias gradients that the normalisation's backward kernel sums
     w.part_din = enc ? b.take<float>((size_t)norm_bwd_blocks((int)T, D.H) * D.H) : nullptr;
     w.part_dres = enc ? b.take<float>((size_t)norm_bwd_blocks((int)T, D.H) * D.H) : nullptr;
-    const int maxn = D.nqkv > D.F1 ? (D.nqkv > D.H ? D.nqkv : D.H) : (D.F1 > D.H ? D.F1 : D.H);
     const size_t slabs = colsum_slabs_max((int)T);
-    w.part_c = b.take<float>(slabs * maxn);
+    w.part_c = enc ? b.take<float>(slabs * D.F1) : nullptr;
     w.part_g1 = b.take<float>((size_t)norm_bwd_blocks((int)T, D.H) * D.H);
     w.part_b1 = enc ? b.take<float>((size_t)norm_bwd_blocks((int)T, D.H) * D.H) : nullptr;
     w.part_c2 = enc ? b.take<float>(slabs * D.nqkv) : nullptr;
@@ -202,18 +201,6 @@ AttnArgs mk_attn(const Dims &D, const mmtrain_batch *b, const Ctx &c) {
     a.tok_seg = c.tok_seg; a.tok_info = c.tok_info; a.qkv = c.qkv; a.ld_qkv = D.nqkv; a.o = c.o; a.lse = c.lse;
     attn_tile_order(b->cu_seqlens_host, b->seg_mask_host, b->mask_mode, b->n_segments, b->total_tokens, a);
     return a;
-}
-
-__global__ void fill_zero_kernel(uint32_t *p, size_t nwords) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nwords) p[i] = 0u;
-}
-hipError_t fill_zero(void *p, size_t elems, int dtype, hipStream_t st) {
-    if (!p || elems == 0) return hipSuccess;
-    const size_t bytes = elems * (dtype == DT_F32 ? 4 : 2);
-    const size_t words = bytes / 4;            // all parameter tensors have an even element count
-    fill_zero_kernel<<<ceil_div((long)words, 256), 256, 0, st>>>((uint32_t *)p, words);
-    return hipGetLastError();
 }
 
 #define HIP_TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return MMTRAIN_ERR_HIP; } while (0)

@@ -929,4 +929,17 @@ hipError_t gelu_bwd(int dtype, const void *d_a, const void *z, void *d_z, long n
     return hipGetLastError();
 }
 
+// ---- zeros (the gradients of an empty pack) --------------------------------------------
+__global__ void fill_zero_kernel(uint32_t *p, size_t nwords) {
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nwords) p[i] = 0u;
+}
+hipError_t fill_zero(void *p, size_t elems, int dtype, hipStream_t st) {
+    if (!p || elems == 0) return hipSuccess;
+    const size_t bytes = elems * (dtype == DT_F32 ? 4 : 2);
+    const size_t words = bytes / 4;            // all parameter tensors have an even element count
+    fill_zero_kernel<<<ceil_div((long)words, 256), 256, 0, st>>>((uint32_t *)p, words);
+    return hipGetLastError();
+}
+
 }  // namespace mmt

@@ -115,6 +115,7 @@ int attn_dkv_parts(int T, int nh, int nkv, int d);
 size_t attn_dkv_room(int T, int nh, int nkv, int d);
 
 // elementwise.hip
+hipError_t fill_zero(void *p, size_t elems, int dtype, hipStream_t st);
 // Token bookkeeping of a pack: tok_seg, tok_info (see AttnArgs) and, if rope_cs is not null, the [T, d/2] rotary table.
 struct TokenPrep {
     const int *cu;              // device [S+1]

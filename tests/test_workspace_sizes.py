@@ -29,3 +29,20 @@ def test_layer_sizes_never_fall_as_packs_grow(name):
             size = query(T)
             assert size >= last, (T, size, last)
             last = size
+
+
+def test_backward_workspace_holds_nothing_that_no_kernel_writes():
+    # what the backward pass of a 7B-shaped decoder layer keeps: the gradients of the activations, D, three arrays of partial sums of a
+    # gain gradient (1024 rows at most), and scratch for products cut along K (256 blocks of 256 x 256 at most); no bias, no column sums
+    kind, dtype, H, nh, nkv, d, F = SHAPES["decoder_7b"]
+    desc = mm.make_desc(*SHAPES["decoder_7b"])
+    for T in (64, 1024, 3072, 6144, 8192):
+        activations = 2 * T * (F + 2 * F + 2 * H + nh * d + (nh + 2 * nkv) * d)
+        bound = activations + 4 * T * nh + 3 * 4 * 1024 * H + 256 * 65536 * 4 + 16 * 256
+        assert mm.mmtrain_layer_workspace_bytes(desc, T, 4, 1) <= bound, T
+    # an encoder layer on a short pack: six arrays of partial sums, column sums in slabs of four rows, scratch for at most eight chunks
+    # of a 512 x 1024 input gradient
+    desc = mm.make_desc(*SHAPES["vit"])
+    T, H, F = 512, 1024, 4096
+    activations = 2 * T * (2 * F + 3 * H + 3 * H)
+    assert mm.mmtrain_layer_workspace_bytes(desc, T, 4, 1) <= activations + 4 * T * 16 + 6 * 4 * 512 * H + 4 * 128 * (F + 3 * H) + 24 * 256 + 8 * 4 * T * H
