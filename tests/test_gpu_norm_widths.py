@@ -21,10 +21,13 @@ def run(kind, dtype, H, T, seed):
     ref = oracle_run(shape, cu, modes, W, x, dy)
     floors = storage_floors(shape, cu, modes, W, x, dy, ref)
     # floor_err is the largest of n errors: near-Gaussian ones of standard deviation l2_err (relative to the tensor's rms) reach 5 of
-    # these with a probability of 6e-7 n, but one sample of the floor may be as low as 2.4 (the 128 elements of dnorm2_b at 3073
-    # tokens: 7.6e-3 at an l2_err of 3.1e-3, where ten seeds average 9.4e-3), so it does not bound another rounding by itself
-    for f in (floors or {}).values():
-        f["floor_err"] = max(f["floor_err"], 5. / 1.5 * f["l2_err"])
+    # these with a probability of 6e-7 n, but one sample of the floor may be as low as 2.4 on a small tensor (the 128 elements of
+    # dnorm2_b at 3073 tokens: 7.6e-3 at an l2_err of 3.1e-3, where ten seeds average 9.4e-3), so there it does not bound another
+    # rounding by itself.  From 4096 elements on the largest lies between 3.2 and 4.5 deviations, and 1.5 times that does.
+    for k, f in (floors or {}).items():
+        n = T * H if k in ("y", "dx") else W[k].size
+        if n < 4096:
+            f["floor_err"] = max(f["floor_err"], 5. / 1.5 * f["l2_err"])
     compare_layer(shape, gpu_run(shape, cu, modes, W, x, dy), ref, floors=floors)
 
 
