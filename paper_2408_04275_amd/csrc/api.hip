@@ -815,6 +815,9 @@ MMTRAIN_API int mmtrain_route_gemm(int32_t layout, int32_t M, int32_t N, int32_t
     for (int i = 0; i < 4; ++i) route[i] = r[i];
     return MMTRAIN_OK;
 }
+MMTRAIN_API int mmtrain_route_gemm_f32(int32_t layout, int32_t M, int32_t N, int32_t K) {      // 1: matrix instruction, 0: vector ALUs
+    return gemm_f32_supported(mk(layout, M, N, K, nullptr, layout == GEMM_TN ? M : K, nullptr, layout == GEMM_NT ? K : N, nullptr, N)) ? 1 : 0;
+}
 MMTRAIN_API int mmtrain_route_adam(int64_t n, int32_t param_bytes) { return adam_streams((size_t)n, (size_t)param_bytes) ? 1 : 0; }
 
 }  // extern "C"

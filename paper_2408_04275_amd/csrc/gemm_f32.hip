@@ -207,9 +207,13 @@ hipError_t launch(const GemmF32 &p, hipStream_t st) {
 }  // namespace
 
 // 16-byte accesses throughout: leading dimensions, N, and whatever index is contiguous in an operand multiples of 4, all
-// pointers 16-byte aligned, 32-bit byte offsets
+// pointers 16-byte aligned, 32-bit byte offsets.  A K of a few 16-deep blocks occupies only a few of a workgroup's wavefronts; where
+// there are tiles enough for the vector-ALU kernel to fill the chip too, that one is ahead up to K = 64 (NN) and 80 (TN), us there ->
+// here: NN 1352 x 3288 x 8 12.7 -> 17.0, 5652 x 3396 x 64 61 -> 69, x 72 ahead here; TN 772 x 2540 x 16 8.8 -> 15.2, 5504 x 1024 x 64 22 ->
+// 30, 5652 x 3396 x 80 75 -> 82, x 96 ahead here (NT 1456 x 2408 x 8 10.9 -> 11.2).
 bool gemm_f32_supported(const GemmArgs &g) {
     if (g.M <= 0 || g.N <= 0 || g.K <= 0) return false;
+    if (!few_tiles(g.M, g.N) && g.K < (g.layout == GEMM_TN ? 96 : g.layout == GEMM_NN ? 72 : 0)) return false;
     if ((g.lda | g.ldb | g.ldc | g.N) & 3) return false;
     const bool a_kc = g.layout != GEMM_TN, b_kc = g.layout == GEMM_NT;
     if ((a_kc || b_kc) && (g.K & 3)) return false;

@@ -468,14 +468,16 @@ void gemm_mfma_kernel(const ARG arg) {
             la.template copy_all<true>(smem + j * TS::A_BYTES, j * BK);
             lb.template copy_all<true>(smem + B0 + j * TS::B_BYTES, j * BK);
         }
-    } else {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * (RA + RB)) : "memory");     // A0 and B0 have landed
+    } else {                                                   // a short K: only the tiles it has, all of them waited for
 #pragma unroll
         for (int j = 0; j < AHEAD; ++j) {
+            if (j >= nk) continue;
             la.template copy_all<false>(smem + j * TS::A_BYTES, j * BK);
             lb.template copy_all<false>(smem + B0 + j * TS::B_BYTES, j * BK);
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * (RA + RB)) : "memory");         // A0 and B0 have landed
     lds_barrier();
     static_for(Frags{}, [&](auto F) { read_frag(S0{}, F, 0, B0, 0); });
 
@@ -553,8 +555,8 @@ void gemm_mfma_kernel(const ARG arg) {
     for (; kt < nk_fast; ++kt) step(std::integral_constant<int, 2>{}, kt);
     for (; kt < nk_copy; ++kt) step(std::integral_constant<int, 1>{}, kt);
     for (; kt < nk; ++kt) step(std::integral_constant<int, 0>{}, kt);
-    asm volatile("s_nop 15\n\ts_waitcnt vmcnt(0)" ::: "memory");   // the last MFMAs have written their accumulators;
-                                                                  // copies past the end of K (zero-filled) are done
+    asm volatile("s_nop 15\n\ts_waitcnt vmcnt(0)" ::: "memory");   // the last MFMAs have written their accumulators, and no copy is
+                                                                  // outstanding
     if constexpr (ASM_READS) {
         // the last slice's reads (never used) still target these registers: keep them reserved until they land
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

@@ -173,6 +173,7 @@ bool gemm_mfma_few_tiles(const GemmArgs &g) {
 // 22.6 -> 14.8 us on 2304 x 3072 x 1024 (256 x 128), 72.2 -> 65.6 us on 9536 x 1024 x 4096 (160 x 256), and 58.3 -> 25.8 us on
 // the 4096 x 1024 x 2880 weight gradient, which was cut along K before (128 x 128); products of whole rounds of large tiles stay
 // where they were.
+constexpr size_t FROM_HBM_BYTES = size_t(96) << 20;     // operands beyond this mostly come from HBM and not from the memory-side cache
 struct TileCost { int shape, bm, bn; double tile, step; };
 constexpr TileCost COST_ROWS[] = {                     // K-contiguous A
     {TILE_256, 256, 256, 4.13, 0.958}, {TILE_224, 224, 256, 2.92, 0.866}, {TILE_192, 192, 256, 2.19, 0.778},
@@ -186,17 +187,35 @@ template <int N>
 int choose_tile(const TileCost (&table)[N], double launch, double rounds_power, double load, const GemmArgs *gs, int n, int n_cu,
                 double &best_us) {
     int best = TILE_256;
+    size_t bytes = 0;
+    for (int i = 0; i < n; ++i) bytes += (size_t)(gs[i].M + gs[i].N) * gs[i].K * 2;
+    const bool from_hbm = bytes > FROM_HBM_BYTES;
     for (const TileCost &t : table) {
         long tiles = 0;
         for (int i = 0; i < n; ++i) tiles += (long)ceil_div(gs[i].M, t.bm) * ceil_div(gs[i].N, t.bn);
         const double share = (double)tiles / n_cu, fill = share < 1. ? share * share : 1.;
         const double us = launch + pow(ceil(share), rounds_power) * (t.tile + ceil_div(gs[0].K, BK) * t.step * (1. + load * fill));
-        // a smaller tile moves more bytes per product: only for a gain beyond the fit's error
-        if (t.shape == TILE_256 || us < best_us * (best == TILE_256 ? 0.98 : 1.)) { best = t.shape; best_us = us; }
+        // a smaller tile moves more bytes per product: only for a gain beyond the fit's error, and beyond what they cost more from HBM
+        // (operands of more than 96 MB: 1397 x 28672 x 5120 takes 336 us in 256 x 256 and 379 in 160 x 256, which the model puts 4 % ahead)
+        if (t.shape == TILE_256 || us < best_us * (best != TILE_256 ? 1. : from_hbm ? 0.95 : 0.98)) { best = t.shape; best_us = us; }
     }
     return best;
 }
+// A K of at most four steps lies below what the constants were fitted to, and there a tile's time is mostly that of its stores, which
+// the model lacks: 256 x 256 wherever its rounds are well filled.  Measured with the model's choice -> 256 x 256, us: forward and
+// input gradients 28360 x 7384 x 16 228 -> 175, 9504 x 4344 x 16 41 -> 33, 1000 x 28672 x 192 25.2 -> 22.1 (rounds 98, 95 and 88 % full),
+// but 6000 x 4096 x 128 18.8 -> 19.8 (75 %); weight gradients 4096 x 4096 x 64 12.6 -> 10.6, 28672 x 4096 x 64 64 -> 55, 4096 x 11008 x
+// 128 36.5 -> 30.6, 6144 x 2048 x 160 14.3 -> 13.3 (75 %).
+bool short_k_full_rounds(const GemmArgs *gs, int n, int n_cu) {
+    if (gs[0].K > 4 * BK) return false;
+    long tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += (long)ceil_div(gs[i].M, TILE) * ceil_div(gs[i].N, TILE);
+    const double filled = (double)tiles / ((double)ceil_div(tiles, n_cu) * n_cu);
+    return filled >= (gs[0].layout == GEMM_TN ? 0.75 : 0.8);
+}
 int choose_tile(const GemmArgs *gs, int n, int n_cu, double &us) {
+    us = 0.;
+    if (short_k_full_rounds(gs, n, n_cu)) return TILE_256;
     return gs[0].layout == GEMM_TN ? choose_tile(COST_WGRAD, 3.7, 1.079, 0.105, gs, n, n_cu, us)
                                    : choose_tile(COST_ROWS, 3.4, 1.042, 0.276, gs, n, n_cu, us);
 }
@@ -207,7 +226,8 @@ int choose_tile(const GemmArgs *gs, int n, int n_cu, double &us) {
 // The rule compares choose_tile's estimate with the same model for K / splits, plus the reduction (its launch and 0.345 us per
 // MB), and asks for 5 % as both are fits.  The tile shapes' constants hold for operands that the memory-side cache keeps (256 MB);
 // from HBM they take 1.2 to 1.6 times as long (the 256 x 256 chunks, each of which one XCD's L2 reads once, do not), so operands
-// of more than 96 MB, most of which are a large layer's weights, count against them with 1.2.  Measured with operands from
+// of more than 96 MB, most of which are a large layer's weights, count against them: their estimate then stands at 1.15 times itself
+// instead of 0.95.  Measured with operands from
 // HBM, tile shape -> cut: 1031 x 4096 x 22016 (the gate / up input gradient of a short pack) 233 -> 177 us in three chunks, 1031 x
 // 4096 x 12288 (QKV) 128 -> 110, 366 x 4096 x 12288 86 -> 56 in eight, 1031 x 1280 x 22016 136 -> 70 in eight; at the rule's
 // edges 2304 x 1024 x 11008 69 -> 71 and 700 x 8192 x 13824 154 -> 157.  Up to K = 8192 the tile shapes are ahead.
@@ -215,7 +235,7 @@ int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
     if (g.layout != GEMM_NN || g.bias || g.residual || !g.split_ws) return 1;
     const long tiles = (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE);
     const size_t plane = (size_t)g.M * g.N * 4;
-    best_us *= (size_t)(g.M + g.N) * g.K * 2 > (96u << 20) ? 1.15 : 0.95;
+    best_us *= (size_t)(g.M + g.N) * g.K * 2 > FROM_HBM_BYTES ? 1.15 : 0.95;
     int best = 1;
     for (int s = 2; s <= few_tile_chunks(tiles, g.K, n_cu) && s * plane <= g.split_ws_bytes; ++s) {
         const double fill = (double)(s * tiles) / n_cu;

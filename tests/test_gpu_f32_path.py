@@ -13,9 +13,9 @@ pytestmark = pytest.mark.gpu
 
 
 # one row past a 32 x 32 tile, K shorter than one wavefront's block, K with a remainder of 4 and of 12, 64 x 64 tiles with ragged
-# edges; widths that are no multiple of 4 take the vector-ALU kernel
+# edges; widths that are no multiple of 4, and a short K over many tiles (20; 92 too in a weight gradient), take the vector-ALU kernel
 @pytest.mark.parametrize("layout", [mm.GEMM_NT, mm.GEMM_NN, mm.GEMM_TN])
-@pytest.mark.parametrize("M,N,K", [(4, 4, 4), (36, 68, 20), (64, 32, 140), (100, 36, 1028), (1300, 1228, 92), (33, 30, 18)])
+@pytest.mark.parametrize("M,N,K", [(4, 4, 4), (36, 68, 20), (64, 32, 140), (100, 36, 1028), (1300, 1228, 92), (1300, 1228, 108), (1300, 1228, 20), (33, 30, 18)])
 def test_gemm_f32_tiles(layout, M, N, K):
     M = M if layout != mm.GEMM_TN else (M + 3) // 4 * 4
     gemm_case(mm.F32, layout, M, N, K, seed=31)

@@ -23,6 +23,15 @@ def test_gemm_tile_shape(layout, M, N, K, tile):
     gemm_case(mm.BF16, layout, M, N, K, bias=True, residual=True, accumulate=K > 500, seed=22)
 
 
+# a K of one to four steps: 256 x 256 tiles whose look-ahead is longer than K, several to a workgroup, ragged at every edge
+@pytest.mark.parametrize("layout,M,N,K", [(mm.GEMM_NT, 4200, 3464, 8), (mm.GEMM_NN, 4200, 3464, 64), (mm.GEMM_NT, 4200, 3464, 136),
+                                          (mm.GEMM_TN, 4104, 3464, 1), (mm.GEMM_TN, 4104, 3464, 65), (mm.GEMM_TN, 6152, 4040, 250)])
+def test_short_contractions(layout, M, N, K):
+    assert gemm_route(layout, M, N, K)[:2] == (256, 256)
+    gemm_case(mm.BF16, layout, M, N, K, seed=26)
+    gemm_case(mm.BF16, layout, M, N, K, residual=layout != mm.GEMM_TN, accumulate=True, seed=27)
+
+
 # weight gradients: one row or column of 8 past a tile edge, K (the tokens) with every kind of remainder
 WGRAD_SHAPES = [(8, 8, 1, "64x64"), (72, 136, 67, "64x64"), (520, 1032, 583, "64x64"), (1032, 2312, 321, "64x128"), (1544, 1288, 1411, "128x128"),
                 (2056, 1928, 1411, "256x128")]

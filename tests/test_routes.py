@@ -66,3 +66,28 @@ def test_the_size_query_restricts_no_cut(layout):
             for K in (8, 4096, 12288, 22016, 25608):
                 size = mm.mmtrain_gemm_workspace_bytes(layout, M, N)
                 assert gemm_route(layout, M, N, K, size) == gemm_route(layout, M, N, K, 1 << 40)
+
+
+# a K of up to four steps of 64: 256 x 256 where its rounds are well filled; the smaller tiles where they are not, and from K = 257 on
+def test_short_contractions():
+    for M, N, K in [(28672, 4096, 64), (4096, 4096, 16), (4096, 11008, 128), (22016, 4096, 256), (6144, 2048, 160)]:
+        assert gemm_route(mm.GEMM_TN, M, N, K) == (256, 256, 0, 1), (M, N, K)
+    for layout in (mm.GEMM_NT, mm.GEMM_NN):
+        for M, N, K in [(28360, 7384, 16), (9504, 4344, 16), (1000, 28672, 192), (1000, 28672, 256)]:
+            assert gemm_route(layout, M, N, K) == (256, 256, 0, 1), (M, N, K)
+        assert gemm_route(layout, 6000, 4096, 128)[:2] == (64, 128)     # 1.5 rounds of 256 x 256
+    assert gemm_route(mm.GEMM_TN, 1024, 4096, 64)[:2] == (64, 128)
+    assert gemm_route(mm.GEMM_NT, 1000, 28672, 264)[:2] != (256, 256)
+
+
+def test_operands_from_hbm_need_a_larger_gain():
+    assert gemm_route(mm.GEMM_NN, 1397, 28672, 5120)[:2] == (256, 256)  # 293 MB of weights, 4 % by the model; 13 % slower when measured
+    assert gemm_route(mm.GEMM_NN, 795, 28672, 4096)[:2] == (224, 256)   # 10 % by the model
+
+
+# fp32: short contractions over many tiles stay on the vector ALUs
+def test_fp32_short_contractions():
+    route = mm.load_library().mmtrain_route_gemm_f32
+    for layout, K, matrix in [(mm.GEMM_TN, 80, 0), (mm.GEMM_TN, 96, 1), (mm.GEMM_NN, 64, 0), (mm.GEMM_NN, 72, 1), (mm.GEMM_NT, 8, 1)]:
+        assert route(layout, 1352, 3288, K) == matrix, (layout, K)      # 1144 tiles of 64 x 64
+        assert route(layout, 640, 640, K) == 1                          # 100
