@@ -470,9 +470,9 @@ void gemm_mfma_kernel(const ARG arg) {
         }
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * (RA + RB)) : "memory");     // A0 and B0 have landed
     } else {                                                   // a short K: only the tiles it has, all of them waited for
-#pragma unroll
-        for (int j = 0; j < AHEAD; ++j) {
-            if (j >= nk) continue;
+        const int n = min(nk, AHEAD);
+#pragma unroll 1
+        for (int j = 0; j < n; ++j) {
             la.template copy_all<false>(smem + j * TS::A_BYTES, j * BK);
             lb.template copy_all<false>(smem + B0 + j * TS::B_BYTES, j * BK);
         }
