@@ -308,8 +308,11 @@ size_t mmtrain_layer_workspace_bytes(const mmtrain_layer_desc *desc, int32_t tot
     return ((b.off + 255) & ~size_t(255)) + 256;      // never 0 for a valid description
 }
 
-int mmtrain_layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch, const mmtrain_layer_weights *W,
-                      const void *x, void *y, void *ctx, void *workspace, size_t workspace_bytes, void *hip_stream) {
+// The forward pass.  Without `output` (y: NULL) it ends in front of the last product: ctx holds everything that the backward pass
+// reads by then, and a layer that is run again for its context alone (recomputation) has handed its output on the first time.
+// Four encoder layers of 2304 tokens: three products of 28 us out of 1785 us.
+static int layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch, const mmtrain_layer_weights *W,
+                     const void *x, void *y, bool output, void *ctx, void *workspace, size_t workspace_bytes, void *hip_stream) {
     Dims D;
     int rc = check_desc(desc, D);
     if (rc) return rc;
@@ -317,7 +320,7 @@ int mmtrain_layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     if ((rc = check_weights(D, W))) return rc;
     const int T = batch->total_tokens;
     if (T == 0) return MMTRAIN_OK;
-    if (!x || !y || !ctx || x == y || misaligned({x, y})) return MMTRAIN_ERR_INVALID_ARG;
+    if (!x || (output && !y) || !ctx || x == y || misaligned({x, y})) return MMTRAIN_ERR_INVALID_ARG;
     if (((uintptr_t)ctx | (uintptr_t)workspace) & 255) return MMTRAIN_ERR_INVALID_ARG;
     if (!workspace || workspace_bytes < mmtrain_layer_workspace_bytes(desc, T, batch->n_segments, 0))
         return MMTRAIN_ERR_WORKSPACE;
@@ -344,8 +347,13 @@ int mmtrain_layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.F1, D.H, c.h2, D.H, W->w_fc1, D.H, c.pre, D.F1, W->b_fc1), st));
     if (enc) HIP_TRY_TIMED(MMTRAIN_PROF_ACT_FWD, st, gelu_fwd(D.dtype, c.pre, c.m, (long)T * D.F, st));
     else HIP_TRY_TIMED(MMTRAIN_PROF_ACT_FWD, st, swiglu_fwd(D.dtype, c.pre, c.m, T, D.F, st));
-    HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.H, D.F, c.m, D.F, W->w_fc2, D.F, y, D.H, W->b_fc2, c.y1), st));
+    if (output) HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.H, D.F, c.m, D.F, W->w_fc2, D.F, y, D.H, W->b_fc2, c.y1), st));
     return MMTRAIN_OK;
+}
+
+int mmtrain_layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch, const mmtrain_layer_weights *W,
+                      const void *x, void *y, void *ctx, void *workspace, size_t workspace_bytes, void *hip_stream) {
+    return layer_fwd(desc, batch, W, x, y, true, ctx, workspace, workspace_bytes, hip_stream);
 }
 
 int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch, const mmtrain_layer_weights *W,
@@ -456,13 +464,13 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
 // ---- a stack of layers -------------------------------------------------------------
 // ctx: the inputs of layers 1 .. n-1 ([T, H] each), then the layer contexts: one per layer, or a single one with
 // MMTRAIN_STACK_RECOMPUTE.  Backward workspace: the layer's own, then two [T, H] buffers through which the
-// gradient travels down the stack, then (recomputation) one [T, H] buffer for the recomputed layer output.
+// gradient travels down the stack.
 namespace {
 struct StackPlan {
     size_t act, layer_ctx, layer_ws_fwd, layer_ws_bwd;
     bool recompute;
     size_t ctx_bytes(int n) const { return (size_t)(n - 1) * act + (recompute ? 1 : (size_t)n) * layer_ctx; }
-    size_t ws_bytes(bool bwd) const { return bwd ? layer_ws_bwd + 2 * act + (recompute ? act : 0) : layer_ws_fwd; }
+    size_t ws_bytes(bool bwd) const { return bwd ? layer_ws_bwd + 2 * act : layer_ws_fwd; }
 };
 int plan_stack(const mmtrain_layer_desc *desc, int n_layers, int T, int S, uint32_t flags, uint32_t allowed, StackPlan &p) {
     Dims D;
@@ -545,13 +553,12 @@ int mmtrain_stack_bwd(const mmtrain_layer_desc *desc, int32_t n_layers, const mm
     uint8_t *acts = (uint8_t *)ctx, *ctxs = acts + (size_t)(n_layers - 1) * p.act;
     uint8_t *ws = (uint8_t *)workspace;
     uint8_t *grad_buf[2] = {ws + p.layer_ws_bwd, ws + p.layer_ws_bwd + p.act};
-    uint8_t *y_again = ws + p.layer_ws_bwd + 2 * p.act;
     const void *g_in = dy;
     for (int l = n_layers - 1; l >= 0; --l) {
         const void *in = l == 0 ? x : acts + (size_t)(l - 1) * p.act;
         void *lctx = ctxs + (p.recompute ? 0 : (size_t)l * p.layer_ctx);
         if (p.recompute && l != n_layers - 1)
-            if ((rc = mmtrain_layer_fwd(desc, batch, &weights[l], in, y_again, lctx, workspace, p.layer_ws_bwd, hip_stream))) return rc;
+            if ((rc = layer_fwd(desc, batch, &weights[l], in, nullptr, false, lctx, workspace, p.layer_ws_bwd, hip_stream))) return rc;
         void *g_out = l == 0 ? dx : (void *)grad_buf[l & 1];
         if ((rc = mmtrain_layer_bwd(desc, batch, &weights[l], in, g_in, lctx, g_out, grads ? &grads[l] : nullptr, lflags,
                                     workspace, p.layer_ws_bwd, hip_stream))) return rc;
