@@ -1,0 +1,43 @@
+"""Weight gradients written and added as fp32 (bf16 operands), at the edges of their tiles: widths 16 past a tile,
+few and many tiles, and enough of them that workgroups take several in turn and every second one starts later.  The sums are the
+same whatever they are written as, so nothing here needs a tolerance: rounding the fp32 result gives the bf16 run's bits, and adding
+it to previous contents is one fp32 addition per element."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2408_04275_amd import binding as mm
+from paper_2408_04275_amd import workloads as wl
+from paper_2408_04275_amd.harness import LayerRunner, check
+
+pytestmark = pytest.mark.gpu
+
+# hidden, heads, head width, feed-forward width, tokens
+SHAPES = [(80, 1, 64, 144, 67), (272, 4, 64, 528, 300), (1296, 10, 128, 2576, 131), (2064, 16, 128, 8208, 70)]
+
+
+@pytest.mark.parametrize("H,nh,d,F,T", SHAPES)
+def test_added_to_previous_contents(H, nh, d, F, T):
+    shape = wl.LayerShape("f32g", wl.DECODER, wl.BF16, H, nh, nh, d, F, T)
+    cu, modes = np.array([0, 9, T], dtype=np.int32), np.zeros(2, dtype=np.uint8)
+    W = wl.make_weights(shape, 3, std=0.05)
+    x, dy = wl.make_activations(shape, T, 3)
+    runs = []
+    for f32 in (False, True):
+        r = LayerRunner(shape, W, cu, modes, grads_f32=f32)
+        r.set_inputs(x, dy)
+        check(r.forward(), "fwd")
+        check(r.backward(mm.BWD_WGRAD_F32 if f32 else 0), "bwd")
+        runs.append(r)
+    torch.cuda.synchronize()
+    once = {k: g.clone() for k, g in runs[1].g.items()}
+    for k, g in once.items():
+        assert torch.equal(g.bfloat16(), runs[0].g[k]), k
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    before = {k: torch.randn(g.shape, generator=gen, device="cuda") for k, g in once.items()}
+    for k, g in runs[1].g.items():
+        g.copy_(before[k])
+    check(runs[1].backward(mm.BWD_WGRAD_F32 | mm.BWD_ACCUMULATE_WGRAD), "bwd, added")
+    torch.cuda.synchronize()
+    for k, g in runs[1].g.items():
+        assert torch.equal(g, before[k] + once[k]), k
