@@ -26,9 +26,8 @@
 // then dK/dV with one KEY per lane, looping over the query tiles that can see the workgroup's
 // keys and over the query heads of the key/value head's group, so grouped-query gradients are
 // summed in registers and nothing needs atomics: results are deterministic.  The dK/dV kernel has two forms: for
-// heads wider than 64 features a software-pipelined one (one wavefront per SIMD, the next block's scores computed
-// under the current block's softmax, whole 64-query steps skipped per wavefront), for 64-wide heads a plain one
-// that leaves room for two workgroups per compute unit.
+// heads wider than 64 features one in which two wavefronts share the work on their keys (scores and softmax, products),
+// for 64-wide heads a plain one that leaves room for two workgroups per compute unit.
 //
 // Head dimensions: tiles in LDS are 64 or 128 features wide; a head of another width (a multiple of 16, e.g. 80) uses the
 // next wider ones with the missing features read as zero and never stored.  Template parameters: D the tiles' width, KS the
@@ -276,10 +275,9 @@ __device__ __forceinline__ void static_for(F &&f) {
 }
 typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
 
-// LDS reads of the dK/dV kernel's pipelined section, written as assembly together with their waits: the section
-// mixes them with the transposing reads, which the compiler's counting of outstanding LDS operations does not see
-// (its waits would come out stricter than needed and undo the look-ahead).  All of them are volatile, so they
-// are issued in source order, and LdsSched counts that order.
+// LDS reads of the dK/dV kernel, written as assembly together with their waits: the compiler makes reads wait for copies in flight
+// and does not count the transposing reads, so its waits come out stricter than needed.  All of them are volatile, so they are issued
+// in source order, and the kernel counts that order.
 template <int IMM, typename V>
 __device__ __forceinline__ void lds_read16(V &dst, uint32_t addr) {
     static_assert(sizeof(V) == 16 && IMM >= 0 && IMM < 65536, "ds_read_b128");
@@ -290,35 +288,6 @@ template <int ALLOWED, typename V>
 __device__ __forceinline__ void lds_wait(V &x) {
     asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(ALLOWED < 15 ? ALLOWED : 15));
 }
-// Issue order of the section: the log-sum-exps and the D values of the first four queries, PF score fragments;
-// then per softmax element e (a chunk): [the fragment of score MFMA e / PER_M + PF] [one transposing read]
-// [log-sum-exps and D values of the next four queries, every fourth element].
-template <int NM, int PER_M, int PF, int NR, int PER_R>
-struct LdsSched {
-    static constexpr bool has_frag(int e) { return e % PER_M == 0 && e / PER_M + PF < NM; }
-    static constexpr bool has_tr(int e) { return e % PER_R == 0 && e / PER_R < NR; }
-    static constexpr int in_chunk(int e) { return (has_frag(e) ? 1 : 0) + (has_tr(e) ? 1 : 0) + ((e & 3) == 0 && (e >> 2) < 3 ? 2 : 0); }
-    static constexpr int before(int e) {                 // operations issued before the waits of chunk e
-        int n = PF + 2;
-        for (int i = 0; i < e; ++i) n += in_chunk(i);
-        return n;
-    }
-    static constexpr int idx_frag(int j) { return j < PF ? 2 + j : before((j - PF) * PER_M); }
-    static constexpr int idx_d(int gq) {                 // the later of the two reads for queries 8 gq ..
-        return gq == 0 ? 1 : before(4 * (gq - 1)) + (has_frag(4 * (gq - 1)) ? 1 : 0) + (has_tr(4 * (gq - 1)) ? 1 : 0) + 1;
-    }
-    static constexpr int allowed_frag(int e) { return before(e) - 1 - idx_frag(e / PER_M); }
-    static constexpr int allowed_d(int e) { return before(e) - 1 - idx_d(e >> 2); }
-};
-// 128-wide head (16 score MFMAs, one per element, five fragments ahead, a transposing read per element): in front of
-// element 0 seven operations are out; fragment 0 was the third, the first D values the second of them
-static_assert(LdsSched<16, 1, 5, 16, 1>::before(0) == 7 && LdsSched<16, 1, 5, 16, 1>::allowed_frag(0) == 4 &&
-              LdsSched<16, 1, 5, 16, 1>::allowed_d(0) == 5, "issue order of the pipelined section, start");
-// element 0 adds a fragment, a transposing read and two reads for queries 8 .. 11; fragment 1 was the fourth operation
-static_assert(LdsSched<16, 1, 5, 16, 1>::before(1) == 11 && LdsSched<16, 1, 5, 16, 1>::allowed_frag(1) == 7 &&
-              LdsSched<16, 1, 5, 16, 1>::idx_d(1) == 10 && LdsSched<16, 1, 5, 16, 1>::allowed_d(4) == LdsSched<16, 1, 5, 16, 1>::before(4) - 11,
-              "issue order of the pipelined section, first element");
-
 // Inverse rotary embedding of a gradient held in accumulator layout (the backward pass of the rotation that
 // was applied to q and k before the attention): feature f < D/2 pairs with f + D/2, which sit in the same
 // lane and register index of accumulators c and c + CB/2.  cs = the (cos, sin) row of this lane's token.
@@ -350,7 +319,7 @@ constexpr int STAGE_BYTES = 32 * (2 * D + 16);
 template <int D>
 constexpr int ROWS32_BYTES = 32 * D * 2;              // 32 rows of one operand, staged in the tile layout
 template <int D>
-constexpr int DKV_STAGE_BYTES = 4 * ROWS32_BYTES<D>;  // the pipelined dK/dV kernel's K rows, behind its three slots
+constexpr int DKV_STAGE_BYTES = 4 * ROWS32_BYTES<D>;  // the rows of one operand of the plain dK/dV kernel's 4 wavefronts
 // the dQ kernel: first slot, then the Q and dO rows of 8 wavefronts (the second slot lies there later), or two slots, the second
 // of which holds the rows of one operand at a time of 4 wavefronts
 template <int D, int WAVES>
@@ -875,13 +844,26 @@ __global__ __launch_bounds__(WAVES * PARTS * 64, 2) void attn_fwd_kernel(AttnArg
 }
 
 // ------------------------------------------------------------------------------------------
-// backward: dK, dV.  One key per lane (4 wavefronts x 32 keys); loop over the query heads of the group and
-// over the 64-query tiles that can see the workgroup's keys.
+// backward: dK, dV for heads wider than 64 features.  32 keys belong to a pair of wavefronts on one SIMD: the first holds their K and
+// V rows and turns 32 queries at a time into P and dS (two score products of KS MFMAs and the softmax), the second holds dK and dV
+// and adds dO^T P and Q^T dS (4 CB MFMAs).  Neither fits a SIMD twice (the accumulators alone take 128 registers), but the two
+// halves do, and they need different units at the same time: while the first is in its softmax the second keeps the matrix core busy.
+// P and dS go through LDS, 4 KiB per block of 32 queries, in the layout in which both wavefronts hold them (lane by lane, no
+// conflicts), two buffers; the second wavefront works one block behind the first, with one barrier per block.  Q and dO tiles of 64
+// queries go round three slots: a tile is copied by the second wavefronts during the three blocks in front of its first use.
+// dQ + dK/dV in us, against one wavefront per 32 keys with the next block's scores under the exponentials of this one: 8192 tokens in
+// one long document, 32 heads of 128: 1666 -> 1600; in segments of 700 488 -> 468; 2047 tokens, 64 heads on 8, 191 -> 173; 1031
+// tokens 56.5 -> 52.2; 16 heads of 80, 4111 tokens 107.8 -> 99.8.
 // ------------------------------------------------------------------------------------------
+template <int D>
+constexpr int DKV_SLOT = 2 * BT2 * D * 2 + 2 * BT2 * 4;            // Q tile, dO tile, lse[64], D[64]
+constexpr int PDS_BYTES = 4 * 1024;                                // P and dS of one block of one pair
+template <int D>
+constexpr int DKV_PAIR_LDS = 3 * DKV_SLOT<D> + 2 * 4 * PDS_BYTES;
+
 template <int D, int KS, int CB>
-__global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
-    constexpr int TILE = BT2 * D * 2, SLOT = 2 * TILE + 2 * BT2 * 4;   // Q tile, dO tile, lse[64], D[64]
-    constexpr int COPIES = BT2 * D * 2 / 1024 / 4;                     // per wavefront and tile
+__global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
+    constexpr int TILE = BT2 * D * 2, SLOT = DKV_SLOT<D>, COPIES = BT2 * D * 2 / 1024 / 4;      // copies per second wavefront and tile
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     add_busy(a.cu_busy ? a.cu_busy + 2048 : nullptr, false);
 
@@ -892,7 +874,9 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
     const int group = g * group_heads + (blockIdx.z + 1) * group_heads / a.dkv_parts - h_first;
     const int k0 = (a.use_order ? a.order_k[blockIdx.y] : blockIdx.y) * BQ;
     // the wavefront's index as a scalar: what is derived from it (copy destinations, buffer descriptors) stays uniform
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, l32 = lane & 31;
+    const int pair = wv & 3;                            // wavefronts i and i + 4 of a workgroup share a SIMD
+    const bool first_of_pair = wv < 4;
     const int T = a.T;
     const bf16_t *qkv = (const bf16_t *)a.qkv;
     const bf16_t *dO = (const bf16_t *)a.d_o;
@@ -900,236 +884,208 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(AttnArgs a) {
     const int dh = a.d;                                 // head dimension in memory (<= D: LDS tiles and fragments are zero-padded to D)
     const int nq = a.nh * dh, nk = a.nkv * dh;
 
-    const int key = k0 + wave * 32 + l32;
+    const int key = k0 + pair * 32 + l32;
     const RowInfo me = key_range(a.tok_info, key, T);       // queries [lo, hi) see this key
     const bool valid = key < T;
-    const WaveBounds wb = wave_bounds(me, k0 + wave * 32, T);
+    const WaveBounds wb = wave_bounds(me, k0 + pair * 32, T);
     const int w_lo_min = wb.lo_min, w_lo_max = wb.lo_max, w_hi_max = wb.hi_max, w_hi_min = wb.hi_min;
     const RowInfo first = key_range(a.tok_info, k0, T), last = key_range(a.tok_info, min(k0 + BQ, T) - 1, T);
-    const int qbeg = first.lo, qend = last.hi;
-
-    bf16x8 kf[KS], vf[KS];                             // this wavefront's K and V rows as MFMA operands (filled below)
-    f32x16 dk[CB], dv[CB];
-#pragma unroll
-    for (int c = 0; c < CB; ++c) { dk[c] = zero16(); dv[c] = zero16(); }
-    const float sl2 = a.scale * LOG2E;
+    const int qbeg = first.lo, qend = last.hi;              // (never empty: a key sees itself)
 
     const __amdgpu_buffer_rsrc_t rs_q =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(qkv), 0, (int)(uint32_t)((size_t)T * ld * 2), 0x00020000);
+    // The (head, query tile) pairs form one sequence of steps, every step two blocks of 32 queries.
+    const int tiles_per_head = (qend - qbeg + BT2 - 1) / BT2, n_steps = group * tiles_per_head;
+    auto head_of = [&](int step) { return h_first + step / tiles_per_head; };
+    auto qt_of = [&](int step) { return qbeg + (step % tiles_per_head) * BT2; };
+    // whether any of the pair's keys is seen by queries qb .. qb + 31: both wavefronts skip the block otherwise
+    auto active = [&](int qb) { return qb < w_hi_max && qb + 32 > w_lo_min; };
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
+    const uint32_t box0 = lds0 + 3 * SLOT + pair * PDS_BYTES + lane * 16;        // this lane's part of the pair's first buffer
+
+    if (first_of_pair) {
+        bf16x8 kf[KS], vf[KS];                         // K and V rows as the MFMA's column operands
+        // copied into LDS the way tiles are (whole rows per instruction, rows beyond the pack and features beyond the head's width as
+        // zeros) and read back as fragments; loading them straight into the fragment layout takes 16 loads of 16 bytes per row.  The
+        // V rows stand in the third slot, which is first written behind the second barrier, the K rows where P and dS go later.
+        {
+            static_assert(4 * ROWS32_BYTES<D> <= SLOT && 4 * ROWS32_BYTES<D> <= 8 * PDS_BYTES, "room for the staged K and V rows");
+            RowCopier<D, ROWS32_BYTES<D> / 1024> cp_kv;
+            cp_kv.init(0, ld, dh);
+            uint8_t *stage_k = smem + 3 * SLOT + pair * ROWS32_BYTES<D>, *stage_v = smem + 2 * SLOT + pair * ROWS32_BYTES<D>;
+            cp_kv.issue(rs_q, stage_k, k0 + pair * 32, ld, nq + g * dh);
+            cp_kv.issue(rs_q, stage_v, k0 + pair * 32, ld, nq + nk + g * dh);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                kf[ks] = frag_k<D>(stage_k, l32, ks, half);
+                vf[ks] = frag_k<D>(stage_v, l32, ks, half);
+            }
+        }
+        const float sl2 = a.scale * LOG2E;
+        const unsigned span = (unsigned)(me.hi - me.lo);
+        // LDS addresses, shared by all blocks.  A fragment of the score MFMAs: row 32 b + l32 of a tile, 16-byte unit
+        // (2 ks + half) ^ swz_unit(row), and swz_unit(32 + l32) = swz_unit(l32) ^ 4, so block 1 finds slice ks where block 0
+        // finds slice ks ^ 2, 32 rows further on.
+        constexpr int KD = D / 16;                      // (the address of slice ks ^ 2 may lie beyond the slices in use)
+        uint32_t f0[KD];
+#pragma unroll
+        for (int k = 0; k < KD; ++k) f0[k] = lds0 + (l32 * (D / 8) + ((2 * k + half) ^ swz_unit<D>(l32))) * 16;
+        const uint32_t l0 = lds0 + 2 * TILE + half * 16;
+        uint32_t tile = 0;                              // LDS offset of the step's slot
+        // block b of the step whose first query is qt
+        auto block = [&](auto B_, int qt) {
+            constexpr int b = decltype(B_)::value;
+            const int qb = qt + 32 * b;
+            if (!active(qb)) return;
+            // LDS reads in the order they are issued: the score fragments (slice ks of Q, of dO), then the log-sum-exps and D values of
+            // the lane's four quads of queries.  AHEAD of them are out at any time; with the waits written out none of them is stricter.
+            constexpr int NF = 2 * KS, AHEAD = 8;
+            bf16x8 fr[NF];
+            f32x4 l4[4], d4[4];
+            auto issue = [&](auto I_) {
+                constexpr int i = decltype(I_)::value;
+                if constexpr (i < NF) lds_read16<(i & 1) * TILE + b * 64 * D>(fr[i], f0[(i >> 1) ^ (2 * b)] + tile);
+                else if constexpr (((i - NF) & 1) == 0) lds_read16<b * 128 + (i - NF) / 2 * 32>(l4[(i - NF) / 2], l0 + tile);
+                else lds_read16<b * 128 + (i - NF) / 2 * 32 + BT2 * 4>(d4[(i - NF) / 2], l0 + tile);
+            };
+            static_for<0, AHEAD>([&](auto I_) { issue(I_); });
+            f32x16 s = zero16(), dp = zero16();
+            static_for<0, NF>([&](auto J_) {
+                constexpr int j = decltype(J_)::value;
+                lds_wait<AHEAD - 1>(fr[j]);
+                if constexpr ((j & 1) == 0) s = MFMA(fr[j], kf[j >> 1], s);
+                else dp = MFMA(fr[j], vf[j >> 1], dp);
+                issue(std::integral_constant<int, j + AHEAD>{});
+            });
+            const bool inside = qb >= w_lo_max && qb + 32 <= w_hi_min;
+            const int rel = qb + 4 * half - me.lo;
+            uint32_t pp[8], dd[8];
+            // two copies of the loop, so that a block no key of which is masked pays nothing for the mask
+            auto softmax = [&](auto MASK_) {
+                static_for<0, 4>([&](auto Q_) {
+                    constexpr int gq = decltype(Q_)::value;
+                    lds_wait<6 - 2 * gq>(l4[gq]);
+                    lds_wait<6 - 2 * gq>(d4[gq]);
+                    float p[4], ds[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        p[e] = __builtin_amdgcn_exp2f(fmaf(s[4 * gq + e], sl2, -l4[gq][e] * LOG2E));
+                        if (decltype(MASK_)::value) p[e] = (unsigned)(rel + 8 * gq + e) < span ? p[e] : 0.f;
+                        ds[e] = p[e] * (dp[4 * gq + e] + d4[gq][e]);             // the D array holds -D
+                    }
+                    pp[2 * gq] = pack_bf16x2(p[0], p[1]); pp[2 * gq + 1] = pack_bf16x2(p[2], p[3]);
+                    dd[2 * gq] = pack_bf16x2(ds[0], ds[1]); dd[2 * gq + 1] = pack_bf16x2(ds[2], ds[3]);
+                });
+            };
+            if (inside) softmax(std::false_type{});
+            else softmax(std::true_type{});
+            auto *box = reinterpret_cast<__attribute__((address_space(3))) rawx4 *>((uintptr_t)(box0 + b * 4 * PDS_BYTES));
+            box[0] = rawx4{pp[0], pp[1], pp[2], pp[3]};
+            box[64] = rawx4{pp[4], pp[5], pp[6], pp[7]};
+            box[128] = rawx4{dd[0], dd[1], dd[2], dd[3]};
+            box[192] = rawx4{dd[4], dd[5], dd[6], dd[7]};
+        };
+        for (int step = 0; step < n_steps; ++step) {
+            const int qt = qt_of(step);
+            lds_barrier();
+            block(std::integral_constant<int, 0>{}, qt);
+            lds_barrier();
+            block(std::integral_constant<int, 1>{}, qt);
+            tile = tile == 2 * SLOT ? 0 : tile + SLOT;
+        }
+        lds_barrier();                                 // the last block's P and dS are there
+        lds_barrier();                                 // the tiles are done with
+        return;
+    }
+
+    // ---- the second wavefront of a pair
+    f32x16 dk[CB], dv[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) { dk[c] = zero16(); dv[c] = zero16(); }
     const __amdgpu_buffer_rsrc_t rs_do =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(dO), 0, (int)(uint32_t)((size_t)T * nq * 2), 0x00020000);
-    // every wavefront copies a quarter of the Q tile and of the dO tile; wavefronts 0 and 1 also fetch the
-    // 64 log-sum-exps and the 64 D values of the tile's queries (4 bytes per lane; queries >= T read as 0)
+    // each copies a quarter of the Q tile and of the dO tile; the first two also fetch the 64 log-sum-exps and the 64 D values of the
+    // tile's queries (4 bytes per lane; queries >= T read as 0)
     RowCopier<D, COPIES> cp_q, cp_do;
-    cp_q.init(wave * COPIES, ld, dh);
-    cp_do.init(wave * COPIES, nq, dh);
-    auto copy_tile = [&](uint8_t *slot, int head, int qt) {
-        cp_q.issue(rs_q, slot, qt, ld, head * dh);
-        cp_do.issue(rs_do, slot + TILE, qt, nq, head * dh);
-        if (wave < 2) {
-            const float *src = (wave == 0 ? a.lse : a.Dsum) + (long)head * T;
+    cp_q.init(pair * COPIES, ld, dh);
+    cp_do.init(pair * COPIES, nq, dh);
+    auto copy_q = [&](uint32_t slot, int step) { cp_q.issue(rs_q, smem + slot, qt_of(step), ld, head_of(step) * dh); };
+    auto copy_do = [&](uint32_t slot, int step) {
+        const int head = head_of(step), qt = qt_of(step);
+        cp_do.issue(rs_do, smem + slot + TILE, qt, nq, head * dh);
+        if (pair < 2) {
+            const float *src = (pair == 0 ? a.lse : a.Dsum) + (long)head * T;
             const __amdgpu_buffer_rsrc_t rs_f =
                 __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(src), 0, (int)(uint32_t)((size_t)T * 4), 0x00020000);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_f, (lds_void *)(slot + 2 * TILE + wave * BT2 * 4), 4,
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_f, (lds_void *)(smem + slot + 2 * TILE + pair * BT2 * 4), 4,
                                                      (int)((qt + lane) * 4), 0, 0, 0);
         }
     };
     TrReader<D> tr;
-    tr.init((uint32_t)(uintptr_t)(lds_void *)smem);
-
-    if (qbeg >= qend) goto done;      // no query sees these keys (cannot happen for a key of a segment: it sees itself)
-    {
-    // The (head, query tile) pairs form one sequence of steps, every step two blocks of 32 queries.  The blocks are
-    // software-pipelined: while the vector ALU turns the scores of a block into P and dS, the matrix core computes
-    // the scores of the block after it (one MFMA in front of every element of the softmax, so that neither unit
-    // waits for the other in this one-wavefront-per-SIMD kernel); the dV and dK products of the block follow.
-    // Three LDS slots: a step's second block reads the next step's tile for its look-ahead scores, so the copy of
-    // tile step + 2 is issued at the barrier in the middle of step `step`, into the slot tile step - 1 has left.
-    // A wavefront skips the steps none of whose queries sees any of its keys; the scores behind such a gap are
-    // computed on their own.
-    const int tiles_per_head = (qend - qbeg + BT2 - 1) / BT2, n_steps = group * tiles_per_head;
-    auto head_of = [&](int step) { return h_first + step / tiles_per_head; };
-    auto qt_of = [&](int step) { return qbeg + (step % tiles_per_head) * BT2; };
-    const unsigned span = (unsigned)(me.hi - me.lo);
-
-    // LDS addresses, shared by all blocks.  A fragment of the score MFMAs: row 32 bn + l32 of a tile, 16-byte unit
-    // (2 ks + half) ^ swz_unit(row), and swz_unit(32 + l32) = swz_unit(l32) ^ 4, so block 1 finds slice ks where block 0
-    // finds slice ks ^ 2, 32 rows further on.
-    constexpr int KD = D / 16;                          // (the address of slice ks ^ 2 may lie beyond the slices in use)
-    uint32_t f0[KD];
-#pragma unroll
-    for (int k = 0; k < KD; ++k)
-        f0[k] = (uint32_t)(uintptr_t)(lds_void *)smem + (l32 * (D / 8) + ((2 * k + half) ^ swz_unit<D>(l32))) * 16;
-    const uint32_t l0 = (uint32_t)(uintptr_t)(lds_void *)smem + 2 * TILE + half * 16;
-    uint32_t fcur[KD], fnxt[KD], trc[8], lcur = 0;    // ... of the current step's tile, of the next step's
-    int qt_cur = 0;
-    int mbase = 0;                                      // first query of this lane's quads minus the first that sees its key
-    f32x16 sc[2], dpc[2];                               // scores and dP of a step's two blocks
-
-    auto score_frag = [&](const uint32_t (&fa)[KD], auto BN_, auto J_) -> bf16x8 {
-        constexpr int bn = decltype(BN_)::value, j = decltype(J_)::value, ks = j >> 1;
-        return *(lds_bf16x8 *)(uintptr_t)(fa[ks ^ (2 * bn)] + ((j & 1) * TILE + bn * 64 * D));
-    };
-    auto issue_frag = [&](bf16x8 &dst, const uint32_t (&fa)[KD], auto BN_, auto J_) {
-        constexpr int bn = decltype(BN_)::value, j = decltype(J_)::value, ks = j >> 1;
-        lds_read16<(j & 1) * TILE + bn * 64 * D>(dst, fa[ks ^ (2 * bn)]);
-    };
-    // the scores of block 0 of the current tile, on their own
-    auto scores0 = [&]() {
-        static_for<0, 2 * KS>([&](auto J_) {
-            constexpr int j = decltype(J_)::value;
-            const bf16x8 f = score_frag(fcur, std::integral_constant<int, 0>{}, J_);
-            if constexpr (j == 0) mfma_v_first(sc[0], f, kf[0]);
-            else if constexpr (j == 1) mfma_v_first(dpc[0], f, vf[0]);
-            else if constexpr ((j & 1) == 0) mfma_v(sc[0], f, kf[j >> 1]);
-            else mfma_v(dpc[0], f, vf[j >> 1]);
-        });
-        mfma_results_settle();                         // the softmax reads them next
-    };
-    // block b of the current tile: softmax from (sc[b], dpc[b]) with the look-ahead scores of the block after it into
-    // (sc[b ^ 1], dpc[b ^ 1]), then dV += dO^T P and dK += Q^T dS
-    auto block = [&](auto B_) {
+    tr.init(lds0);
+    // block b (first query qb) of the tile at LDS offset `tile`
+    auto block = [&](auto B_, int qb, uint32_t tile) {
         constexpr int b = decltype(B_)::value;
-        constexpr int NM = 2 * KS, PER_M = 16 / NM, PF = NM > 8 ? 5 : 3;          // score MFMAs, softmax elements per MFMA, fragments in flight
-        constexpr int NR = 4 * CB, PER_R = 16 / NR;                  // transposing reads of the block's first 16 queries
-        const uint32_t (&fa)[KD] = b == 0 ? fcur : fnxt;
-        constexpr std::integral_constant<int, b ^ 1> BN{};
-        shortx4 o0[CB], o1[CB], q0f[CB], q1f[CB], o2[CB], o3[CB], q2f[CB], q3f[CB];
-        uint32_t pp[8], dd[8];
-        auto fused = [&](auto MASK_) {
-            constexpr bool MASK = decltype(MASK_)::value;
-            using Sched = LdsSched<NM, PER_M, PF, NR, PER_R>;
-            bf16x8 fr[NM];
-            f32x4 l4[4], d4[4];
-            lds_read16<b * 128>(l4[0], lcur);
-            lds_read16<b * 128 + BT2 * 4>(d4[0], lcur);
-            static_for<0, PF>([&](auto J_) { issue_frag(fr[decltype(J_)::value], fa, BN, J_); });
-            __builtin_amdgcn_sched_barrier(0);         // (the first reads stay in front of the elements' chunks)
-            float pprev = 0.f, dprev = 0.f;
-            static_for<0, 16>([&](auto E_) {
-                constexpr int e = decltype(E_)::value, gq = e >> 2, el = e & 3;
-                if constexpr (el == 0) { lds_wait<Sched::allowed_d(e)>(l4[gq]); lds_wait<Sched::allowed_d(e)>(d4[gq]); }
-                if constexpr (e % PER_M == 0 && e / PER_M < NM) {
-                    constexpr int j = e / PER_M;
-                    lds_wait<Sched::allowed_frag(e)>(fr[j]);
-                    // (the vector ALU reads these results no earlier than the next block's softmax, behind this block's
-                    // 4 CB dV / dK products; the two chains alternate, so no MFMA follows the one whose result it adds to)
-                    if constexpr (j == 0) mfma_v_first(sc[b ^ 1], fr[j], kf[0]);
-                    else if constexpr (j == 1) mfma_v_first(dpc[b ^ 1], fr[j], vf[0]);
-                    else if constexpr ((j & 1) == 0) mfma_v(sc[b ^ 1], fr[j], kf[j >> 1]);
-                    else mfma_v(dpc[b ^ 1], fr[j], vf[j >> 1]);
-                    if constexpr (j + PF < NM) issue_frag(fr[j + PF], fa, BN, std::integral_constant<int, j + PF>{});
-                }
-                if constexpr (Sched::has_tr(e)) {                    // read r: feature block r / 4; dO or Q; first or second quad
-                    constexpr int r = e / PER_R, c = r >> 2;
-                    if constexpr ((r & 3) == 0) o0[c] = TrReader<D>::template read_at<b, 0, c, 0, TILE>(trc);
-                    if constexpr ((r & 3) == 1) o1[c] = TrReader<D>::template read_at<b, 0, c, 1, TILE>(trc);
-                    if constexpr ((r & 3) == 2) q0f[c] = TrReader<D>::template read_at<b, 0, c, 0, 0>(trc);
-                    if constexpr ((r & 3) == 3) q1f[c] = TrReader<D>::template read_at<b, 0, c, 1, 0>(trc);
-                }
-                if constexpr (el == 0 && gq < 3) {
-                    lds_read16<b * 128 + (gq + 1) * 32>(l4[gq + 1], lcur);
-                    lds_read16<b * 128 + (gq + 1) * 32 + BT2 * 4>(d4[gq + 1], lcur);
-                }
-                const float lv = l4[gq][el], dvv = d4[gq][el];
-                float pv = __builtin_amdgcn_exp2f(fmaf(sc[b][e], sl2, -lv * LOG2E));
-                if (MASK) pv = (unsigned)(mbase + (32 * b + 8 * gq + el)) < span ? pv : 0.f;
-                const float dsv = pv * (dpc[b][e] + dvv);           // the D array holds -D
-                if constexpr (e & 1) { pp[e >> 1] = pack_bf16x2(pprev, pv); dd[e >> 1] = pack_bf16x2(dprev, dsv); }
-                else { pprev = pv; dprev = dsv; }
-                __builtin_amdgcn_sched_barrier(0);
-            });
+        if (!active(qb)) return;
+        // LDS reads in the order they are issued: P and dS, then groups of four transposing reads, group 4 m + c (m: 16 queries, c: 32
+        // features) for one dV and one dK MFMA; three groups are out in front of the first MFMA of each
+        constexpr int NG = 2 * CB;
+        bf16x8 pf[2], dsf[2];
+        shortx4 o[NG][2], q[NG][2];
+        const uint32_t box = box0 + b * 4 * PDS_BYTES;
+        uint32_t trc[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) trc[x] = tr.off[x] + tile;
+        lds_read16<0>(pf[0], box); lds_read16<2048>(dsf[0], box);
+        lds_read16<1024>(pf[1], box); lds_read16<3072>(dsf[1], box);
+        auto issue = [&](auto G_) {
+            constexpr int gi = decltype(G_)::value, m = gi / CB, c = gi % CB;
+            o[gi][0] = TrReader<D>::template read_at<b, m, c, 0, TILE>(trc); o[gi][1] = TrReader<D>::template read_at<b, m, c, 1, TILE>(trc);
+            q[gi][0] = TrReader<D>::template read_at<b, m, c, 0, 0>(trc); q[gi][1] = TrReader<D>::template read_at<b, m, c, 1, 0>(trc);
         };
-        if (qt_cur + 32 * b >= w_lo_max && qt_cur + 32 * b + 32 <= w_hi_min) fused(std::false_type{});
-        else fused(std::true_type{});
-        auto frag4 = [](const uint32_t *w) {
-            const uint4 v = make_uint4(w[0], w[1], w[2], w[3]);
-            return *reinterpret_cast<const bf16x8 *>(&v);
-        };
-        tr_wait<CB>(o0, o1, q0f, q1f);
-        static_for<0, CB>([&](auto C_) {                             // in flight during the next 2 CB MFMAs
-            constexpr int c = decltype(C_)::value;
-            o2[c] = TrReader<D>::template read_at<b, 1, c, 0, TILE>(trc); o3[c] = TrReader<D>::template read_at<b, 1, c, 1, TILE>(trc);
-            q2f[c] = TrReader<D>::template read_at<b, 1, c, 0, 0>(trc); q3f[c] = TrReader<D>::template read_at<b, 1, c, 1, 0>(trc);
+        static_for<0, 3>([&](auto G_) { issue(G_); });
+        static_for<0, NG>([&](auto G_) {
+            constexpr int gi = decltype(G_)::value, m = gi / CB, c = gi % CB, LEFT = NG - 1 - gi < 2 ? NG - 1 - gi : 2;
+            asm volatile("s_waitcnt lgkmcnt(%4)" : TR_WAIT2(o[gi]), TR_WAIT2(q[gi]) : "n"(4 * LEFT));
+            if constexpr (gi == 0) asm volatile("" : "+v"(pf[0]), "+v"(dsf[0]), "+v"(pf[1]), "+v"(dsf[1]));
+            dv[c] = MFMA(join(o[gi][0], o[gi][1]), pf[m], dv[c]);
+            dk[c] = MFMA(join(q[gi][0], q[gi][1]), dsf[m], dk[c]);
+            if constexpr (gi + 3 < NG) issue(std::integral_constant<int, gi + 3>{});
         });
-        {
-            const bf16x8 pf = frag4(pp), dsf = frag4(dd);
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                dv[c] = MFMA(join(o0[c], o1[c]), pf, dv[c]);
-                dk[c] = MFMA(join(q0f[c], q1f[c]), dsf, dk[c]);
-            }
-        }
-        tr_wait<CB>(o2, o3, q2f, q3f);
-        {
-            const bf16x8 pf = frag4(pp + 4), dsf = frag4(dd + 4);
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                dv[c] = MFMA(join(o2[c], o3[c]), pf, dv[c]);
-                dk[c] = MFMA(join(q2f[c], q3f[c]), dsf, dk[c]);
-            }
-        }
     };
-
-    // K and V rows of this wavefront's 32 keys: copied into LDS the way tiles are (whole rows per instruction, rows
-    // beyond the pack and features beyond the head's width as zeros) and read back as fragments; loading them
-    // straight into the fragment layout takes 16 loads of 16 bytes per row.  The V rows stand in the third slot, which
-    // the barrier below frees for the third tile, the K rows behind the slots.
-    {
-        constexpr int HALF_TILE = 32 * D * 2;
-        static_assert(4 * HALF_TILE <= SLOT && DKV_STAGE_BYTES<D> == 4 * HALF_TILE, "room for the staged K and V rows");
-        RowCopier<D, HALF_TILE / 1024> cp_kv;
-        cp_kv.init(0, ld, dh);
-        uint8_t *stage_k = smem + 3 * SLOT + wave * HALF_TILE, *stage_v = smem + 2 * SLOT + wave * HALF_TILE;
-        cp_kv.issue(rs_q, stage_k, k0 + wave * 32, ld, nq + g * dh);
-        cp_kv.issue(rs_q, stage_v, k0 + wave * 32, ld, nq + nk + g * dh);
-        copy_tile(smem, head_of(0), qt_of(0));
-        if (n_steps > 1) copy_tile(smem + SLOT, head_of(1), qt_of(1));
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            kf[ks] = frag_k<D>(stage_k, l32, ks, half);
-            vf[ks] = frag_k<D>(stage_v, l32, ks, half);
+    copy_q(0, 0); copy_do(0, 0);
+    if (n_steps > 1) { copy_q(SLOT, 1); copy_do(SLOT, 1); }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // Barrier 2 t stands in front of the first wavefront's block 0 of step t (tile t has landed, block 1 of step t - 1 is in its
+    // buffer), barrier 2 t + 1 in front of its block 1.  Behind the latter nobody reads tile t - 1 any more: its slot is tile t + 2's.
+    uint32_t tile = 0, before = 2 * SLOT;              // slots of tiles t and t - 1 (which is tile t + 2's)
+    for (int step = 0; step < n_steps; ++step) {
+        lds_barrier();
+        if (step > 0) {
+            if (step + 1 < n_steps) copy_do(tile == 2 * SLOT ? 0 : tile + SLOT, step + 1);
+            block(std::integral_constant<int, 1>{}, qt_of(step - 1) + 32, before);
         }
+        lds_barrier();
+        if (step + 2 < n_steps) copy_q(before, step + 2);
+        block(std::integral_constant<int, 0>{}, qt_of(step), tile);
+        // tile t + 1 has landed; the copies of Q for tile t + 2 may be in flight (memory operations retire in order)
+        if (step + 2 < n_steps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        before = tile;
+        tile = tile == 2 * SLOT ? 0 : tile + SLOT;
     }
     lds_barrier();
-    int slot = 0;
-    bool have0 = false;                                // block 0's scores of this step were computed by the step before
-    for (int step = 0; step < n_steps; ++step) {
-        const int qt = qt_of(step), nslot = slot == 2 ? 0 : slot + 1;
-        qt_cur = qt;
-        const bool more = step + 1 < n_steps;
-        const bool act = qt < w_hi_max && qt + BT2 > w_lo_min;
-        if (act) {
-#pragma unroll
-            for (int k = 0; k < KD; ++k) { fcur[k] = f0[k] + slot * SLOT; fnxt[k] = f0[k] + nslot * SLOT; }
-#pragma unroll
-            for (int x = 0; x < 8; ++x) trc[x] = tr.off[x] + slot * SLOT;
-            lcur = l0 + slot * SLOT;
-            mbase = qt + 4 * half - me.lo;
-            if (!have0) scores0();
-            block(std::integral_constant<int, 0>{});
-        }
-        if (more) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the next step's tile has landed
-            lds_barrier();                                           // ... for everyone, and tile step - 1 is no longer read
-            if (step + 2 < n_steps) copy_tile(smem + (nslot == 2 ? 0 : nslot + 1) * SLOT, head_of(step + 2), qt_of(step + 2));
-        }
-        if (act) block(std::integral_constant<int, 1>{});
-        have0 = act;
-        slot = nslot;
-    }
-    }
-done:
+    block(std::integral_constant<int, 1>{}, qt_of(n_steps - 1) + 32, before);
     lds_barrier();                                     // the tiles are done with: LDS now stages the output rows
-    store_dkv<D, CB>(a, smem, wave, half, g, k0 + wave * 32, key, valid, dk, dv);
-    add_busy(a.cu_busy ? a.cu_busy + 2048 : nullptr, true);
+    store_dkv<D, CB>(a, smem, pair, half, g, k0 + pair * 32, key, valid, dk, dv);
+    if (a.cu_busy && wv == 4 && lane == 0) atomicAdd(a.cu_busy + 2048 + (__smid() & 1023u), wall_clock64());
 }
 
 // ------------------------------------------------------------------------------------------
 // backward: dK, dV, the plain form: a block's scores, its softmax and its products one after the other, two LDS
 // slots.  Used for the 64-wide head, where it fits 256 registers, so that two workgroups share a compute unit
-// and overlap each other's phases; the pipelined kernel above needs more registers than that at any width.  PARTS = 2: two
+// and overlap each other's phases.  PARTS = 2: two
 // groups of 4 wavefronts with the same 128 keys and every other (head, query tile) step each (see two_parts).
 // ------------------------------------------------------------------------------------------
 template <int D, int PARTS>
@@ -1198,7 +1154,7 @@ __global__ __launch_bounds__(PARTS * 256, PARTS) void attn_dkv_plain_kernel(Attn
     {
     // the (head, query tile) pairs form one sequence; the copy of the next pair is in flight during this one
     const int tiles_per_head = (qend - qbeg + BT2 - 1) / BT2, n_steps = group * tiles_per_head;
-    // the K and V rows go through LDS as in the pipelined kernel, behind the two slots
+    // the K and V rows go through LDS as in the kernel above, behind the two slots
     {
         RowCopier<D, ROWS32_BYTES<D> / 1024> cp_kv;
         cp_kv.init(0, ld, dh);
@@ -1417,13 +1373,12 @@ hipError_t launch_bwd(const AttnArgs &a, hipStream_t st) {
         else e = launch_dkv_plain<D, 1>(a, grid, st);
     } else {
         static std::atomic<bool> configured{false};
-        constexpr int DKV_SLOT = 2 * BT2 * D * 2 + 2 * BT2 * 4, smem_dkv = 3 * DKV_SLOT + DKV_STAGE_BYTES<D>;
-        static_assert(4 * STAGE32_BYTES<D> <= smem_dkv, "room for the staged fp32 rows");
+        static_assert(4 * STAGE32_BYTES<D> <= DKV_PAIR_LDS<D>, "room for the staged fp32 rows");
         if (!configured.load(std::memory_order_acquire)) {
-            if ((e = set_smem(attn_dkv_kernel<D, KS, CB>, smem_dkv)) != hipSuccess) return e;
+            if ((e = set_smem(attn_dkv_kernel<D, KS, CB>, DKV_PAIR_LDS<D>)) != hipSuccess) return e;
             configured.store(true, std::memory_order_release);
         }
-        attn_dkv_kernel<D, KS, CB><<<grid, 256, smem_dkv, st>>>(a);
+        attn_dkv_kernel<D, KS, CB><<<grid, 512, DKV_PAIR_LDS<D>, st>>>(a);
     }
     if (a.dkv_parts > 1) dkv_reduce_kernel<<<ceil_div((long)a.T * 2 * a.nkv * (a.d / 8), 256), 256, 0, st>>>(a);
     return e != hipSuccess ? e : hipGetLastError();

@@ -154,7 +154,7 @@ def test_attention_padded_head_dim(nh, nkv, d):
 
 
 def test_attention_many_segment_boundaries_wide_head():
-    # 128-wide heads take the dK/dV kernel that looks one block ahead: segment boundaries inside key tiles make its
+    # 128-wide heads take the dK/dV kernel with two wavefronts per 32 keys: segment boundaries inside key tiles make its
     # wavefronts start and stop at different steps and restart per query head of the group (4 heads per K/V head);
     # segments shorter than one step, a bidirectional segment spanning several key tiles, a ragged end
     rng = np.random.default_rng(11)
