@@ -51,17 +51,16 @@ constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
 // Swizzle of the 16-byte units of a tile row in LDS: unit u of row `row` stands at position u ^ swz_unit<D>(row).
 // What it has to achieve was measured with a microbenchmark of LDS read patterns: a 16-byte-per-lane read is served
 // 16 lanes at a time, lanes 0-7 together with 24-31, 8-15 with 16-23 (and the same in the upper half), an 8-byte
-// transposing read one 16-lane group at a time, and a group runs at full rate when its lanes fall into distinct 16-byte
-// (8-byte) slots modulo 256 bytes.  With 128-byte rows (D = 64) the row's parity supplies one slot bit and a 3-bit
-// swizzle does; with 256-byte rows (D = 128) all four unit bits have to come from the swizzle: the fragment reads
-// (32 consecutive rows, one unit) need bit 3 to differ between rows 0-7 / 24-31 and 8-15 / 16-23, the transposing
-// reads (4 consecutive rows, two neighbouring units) need the row's lowest bit in a unit bit above bit 0.  The
-// 3-bit swizzle alone ran both at half rate there.
-__device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
+// transposing read 32 lanes at a time, lanes 0-31 and 32-63, each at full rate when its lanes fall into distinct slots modulo 256
+// bytes.  A fragment read covers 32 consecutive rows at one unit: rows 0-7 and 24-31 have to differ, and rows 8-23.  A transposing
+// read covers, with half a wavefront, four consecutive rows at four consecutive units (8 bytes a lane): the four rows have to differ in
+// the unit bits above the lowest two.  With 256-byte rows (D = 128) the row's two lowest bits go there and its next two below them;
+// with 128-byte rows (D = 64) the lowest bit is in the address as it is.  (With the lowest bit alone above, half of the lanes of a
+// transposing read were served at a time, and LDS was what the dK/dV kernel waited for.)
 template <int D>
 __device__ __forceinline__ int swz_unit(int row) {
-    if constexpr (D == 128) return ((row ^ (row >> 3) ^ ((row & 1) << 2)) & 7) | (((row >> 3) & 1) << 3);
-    else return swz(row);
+    if constexpr (D == 128) return (row & 2) << 2 | (row & 1) << 2 | (row >> 1 & 2) | (row >> 3 & 1);
+    else return (row & 2) << 1 | (row >> 1 & 2) | (row >> 3 & 1);
 }
 
 __device__ __forceinline__ bf16x8 pack8(const float *v) {
@@ -214,38 +213,32 @@ constexpr size_t MAX_TENSOR_BYTES = 0x7fff0000ull;      // what RowCopier's offs
 // Transposing reads.  Lane constants: 16-lane group gq = lane >> 4 forms the fragment rows (features)
 // 16 (gq & 1) .. + 15 for lane half h = gq >> 1; as a source, lane j = lane & 15 of the group supplies
 // the address of tile row 4 h + (j >> 2) (+ a multiple of 8), features 4 (j & 3) .. + 3 of the group's 16.
-// tr_off[X] holds that address for each value X of the compile-time part of the swizzled unit position.
+// off[2 C + SEC] holds that address for feature block C and the first or second 8 rows of 16, whose bit is in the swizzle.
 template <int D>
 struct TrReader {
-    uint32_t off[8];
+    static constexpr int N = D / 16;
+    uint32_t off[N];
     __device__ __forceinline__ void init(uint32_t lds_base) {
         const int lane = threadIdx.x & 63, gq = lane >> 4, j = lane & 15, qd = j & 3, t = j >> 2, h = gq >> 1;
-        // the lane's part of the swizzle of rows 4 h + t (+ a multiple of 8), low three unit bits
-        const int L = ((2 * (gq & 1) + (qd >> 1)) ^ swz_unit<D>(4 * h + t)) & 7;
+        const int L = (2 * (gq & 1) + (qd >> 1)) ^ swz_unit<D>(4 * h + t);
 #pragma unroll
-        for (int x = 0; x < 8; ++x) off[x] = lds_base + (4 * h + t) * 2 * D + (qd & 1) * 8 + ((x ^ L) << 4);
+        for (int x = 0; x < N; ++x) off[x] = lds_base + (4 * h + t) * 2 * D + (qd & 1) * 8 + ((L ^ (4 * (x >> 1)) ^ (x & 1)) << 4);
     }
     // half SEC (elements 4 SEC .. 4 SEC + 3) of the fragment of 32-row block B, MFMA M of the block, feature
     // block C of a tile at byte offset `tile` from lds_base: rows 32 B + 16 M + 8 SEC + 4 h + (0..3)
     template <int B, int M, int C, int SEC>
     __device__ __forceinline__ shortx4 read(uint32_t tile) const {
-        constexpr int CST = (4 * B + 2 * M + SEC) & 7, X = (4 * (C & 1)) ^ CST;
-        // unit bit 3 (features 64 ..): for 256-byte rows the swizzle flips it in every second group of 8 rows
-        constexpr int HI = D == 128 ? ((C >> 1) ^ (SEC & 1)) : (C >> 1);
-        constexpr int IMM = (32 * B + 16 * M + 8 * SEC) * 2 * D + HI * 128;
         shortx4 v;
-        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(off[X] + tile), "n"(IMM));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(off[2 * C + SEC] + tile), "n"((32 * B + 16 * M + 8 * SEC) * 2 * D));
         return v;
     }
-    // the same with the tile's offset already added to the eight addresses (base) and a constant offset on top
+    // the same with the tile's offset already added to the addresses (base) and a constant offset on top
     template <int B, int M, int C, int SEC, int EXTRA>
-    static __device__ __forceinline__ shortx4 read_at(const uint32_t (&base)[8]) {
-        constexpr int CST = (4 * B + 2 * M + SEC) & 7, X = (4 * (C & 1)) ^ CST;
-        constexpr int HI = D == 128 ? ((C >> 1) ^ (SEC & 1)) : (C >> 1);
-        constexpr int IMM = (32 * B + 16 * M + 8 * SEC) * 2 * D + HI * 128 + EXTRA;
+    static __device__ __forceinline__ shortx4 read_at(const uint32_t (&base)[N]) {
+        constexpr int IMM = (32 * B + 16 * M + 8 * SEC) * 2 * D + EXTRA;
         static_assert(IMM < 65536, "LDS offset field");
         shortx4 v;
-        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(base[X]), "n"(IMM));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(base[2 * C + SEC]), "n"(IMM));
         return v;
     }
 };
@@ -851,9 +844,11 @@ __global__ __launch_bounds__(WAVES * PARTS * 64, 2) void attn_fwd_kernel(AttnArg
 // P and dS go through LDS, 4 KiB per block of 32 queries, in the layout in which both wavefronts hold them (lane by lane, no
 // conflicts), two buffers; the second wavefront works one block behind the first, with one barrier per block.  Q and dO tiles of 64
 // queries go round three slots: a tile is copied by the second wavefronts during the three blocks in front of its first use.
-// dQ + dK/dV in us, against one wavefront per 32 keys with the next block's scores under the exponentials of this one: 8192 tokens in
-// one long document, 32 heads of 128: 1666 -> 1600; in segments of 700 488 -> 468; 2047 tokens, 64 heads on 8, 191 -> 173; 1031
-// tokens 56.5 -> 52.2; 16 heads of 80, 4111 tokens 107.8 -> 99.8.
+// What bounds it: the first wavefront, whose score MFMAs, exponentials and LDS reads (an MFMA needs a fragment, a product two) add up to
+// about 1.7 k cycles per block beside the second's products.  Computing the next block's scores under the exponentials, or giving dP and
+// dS to the second wavefront, moved that cost and did not lower it.  dQ + dK/dV in us, against one wavefront per 32 keys with the next
+// block's scores under the exponentials of this one: 8192 tokens in one long document, 32 heads of 128: 1623 -> 1534; in segments of
+// 700 470 -> 440; 2047 tokens, 64 heads on 8, 189 -> 170; 1031 tokens 56.7 -> 51.9; 16 heads of 80, 4111 tokens 108 -> 97.
 // ------------------------------------------------------------------------------------------
 template <int D>
 constexpr int DKV_SLOT = 2 * BT2 * D * 2 + 2 * BT2 * 4;            // Q tile, dO tile, lse[64], D[64]
@@ -895,9 +890,9 @@ __global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
     const __amdgpu_buffer_rsrc_t rs_q =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(qkv), 0, (int)(uint32_t)((size_t)T * ld * 2), 0x00020000);
     // The (head, query tile) pairs form one sequence of steps, every step two blocks of 32 queries.
-    const int tiles_per_head = (qend - qbeg + BT2 - 1) / BT2, n_steps = group * tiles_per_head;
-    auto head_of = [&](int step) { return h_first + step / tiles_per_head; };
-    auto qt_of = [&](int step) { return qbeg + (step % tiles_per_head) * BT2; };
+    const int n_steps = group * ((qend - qbeg + BT2 - 1) / BT2);
+    auto next_tile = [&](int qt) { return qt + BT2 >= qend ? qbeg : qt + BT2; };
+    auto next_slot = [](uint32_t tile) { return tile == 2 * SLOT ? 0u : tile + SLOT; };
     // whether any of the pair's keys is seen by queries qb .. qb + 31: both wavefronts skip the block otherwise
     auto active = [&](int qb) { return qb < w_hi_max && qb + 32 > w_lo_min; };
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
@@ -924,13 +919,11 @@ __global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
         }
         const float sl2 = a.scale * LOG2E;
         const unsigned span = (unsigned)(me.hi - me.lo);
-        // LDS addresses, shared by all blocks.  A fragment of the score MFMAs: row 32 b + l32 of a tile, 16-byte unit
-        // (2 ks + half) ^ swz_unit(row), and swz_unit(32 + l32) = swz_unit(l32) ^ 4, so block 1 finds slice ks where block 0
-        // finds slice ks ^ 2, 32 rows further on.
-        constexpr int KD = D / 16;                      // (the address of slice ks ^ 2 may lie beyond the slices in use)
-        uint32_t f0[KD];
+        // LDS addresses, shared by all blocks: row l32 of a tile's first 32, 16-byte unit 2 ks + half; the block's 32 rows are an
+        // immediate offset, as the swizzle does not see them
+        uint32_t f0[KS];
 #pragma unroll
-        for (int k = 0; k < KD; ++k) f0[k] = lds0 + (l32 * (D / 8) + ((2 * k + half) ^ swz_unit<D>(l32))) * 16;
+        for (int ks = 0; ks < KS; ++ks) f0[ks] = lds0 + (l32 * (D / 8) + ((2 * ks + half) ^ swz_unit<D>(l32))) * 16;
         const uint32_t l0 = lds0 + 2 * TILE + half * 16;
         uint32_t tile = 0;                              // LDS offset of the step's slot
         // block b of the step whose first query is qt
@@ -945,7 +938,7 @@ __global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
             f32x4 l4[4], d4[4];
             auto issue = [&](auto I_) {
                 constexpr int i = decltype(I_)::value;
-                if constexpr (i < NF) lds_read16<(i & 1) * TILE + b * 64 * D>(fr[i], f0[(i >> 1) ^ (2 * b)] + tile);
+                if constexpr (i < NF) lds_read16<(i & 1) * TILE + b * 64 * D>(fr[i], f0[i >> 1] + tile);
                 else if constexpr (((i - NF) & 1) == 0) lds_read16<b * 128 + (i - NF) / 2 * 32>(l4[(i - NF) / 2], l0 + tile);
                 else lds_read16<b * 128 + (i - NF) / 2 * 32 + BT2 * 4>(d4[(i - NF) / 2], l0 + tile);
             };
@@ -986,13 +979,14 @@ __global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
             box[128] = rawx4{dd[0], dd[1], dd[2], dd[3]};
             box[192] = rawx4{dd[4], dd[5], dd[6], dd[7]};
         };
+        int qt = qbeg;
         for (int step = 0; step < n_steps; ++step) {
-            const int qt = qt_of(step);
             lds_barrier();
             block(std::integral_constant<int, 0>{}, qt);
             lds_barrier();
             block(std::integral_constant<int, 1>{}, qt);
-            tile = tile == 2 * SLOT ? 0 : tile + SLOT;
+            tile = next_slot(tile);
+            qt = next_tile(qt);
         }
         lds_barrier();                                 // the last block's P and dS are there
         lds_barrier();                                 // the tiles are done with
@@ -1010,9 +1004,9 @@ __global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
     RowCopier<D, COPIES> cp_q, cp_do;
     cp_q.init(pair * COPIES, ld, dh);
     cp_do.init(pair * COPIES, nq, dh);
-    auto copy_q = [&](uint32_t slot, int step) { cp_q.issue(rs_q, smem + slot, qt_of(step), ld, head_of(step) * dh); };
-    auto copy_do = [&](uint32_t slot, int step) {
-        const int head = head_of(step), qt = qt_of(step);
+    // the tile of queries qt .. of `head`, its two halves one after the other
+    auto copy_q = [&](uint32_t slot, int head, int qt) { cp_q.issue(rs_q, smem + slot, qt, ld, head * dh); };
+    auto copy_do = [&](uint32_t slot, int head, int qt) {
         cp_do.issue(rs_do, smem + slot + TILE, qt, nq, head * dh);
         if (pair < 2) {
             const float *src = (pair == 0 ? a.lse : a.Dsum) + (long)head * T;
@@ -1034,9 +1028,9 @@ __global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
         bf16x8 pf[2], dsf[2];
         shortx4 o[NG][2], q[NG][2];
         const uint32_t box = box0 + b * 4 * PDS_BYTES;
-        uint32_t trc[8];
+        uint32_t trc[TrReader<D>::N];
 #pragma unroll
-        for (int x = 0; x < 8; ++x) trc[x] = tr.off[x] + tile;
+        for (int x = 0; x < TrReader<D>::N; ++x) trc[x] = tr.off[x] + tile;
         lds_read16<0>(pf[0], box); lds_read16<2048>(dsf[0], box);
         lds_read16<1024>(pf[1], box); lds_read16<3072>(dsf[1], box);
         auto issue = [&](auto G_) {
@@ -1054,29 +1048,39 @@ __global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
             if constexpr (gi + 3 < NG) issue(std::integral_constant<int, gi + 3>{});
         });
     };
-    copy_q(0, 0); copy_do(0, 0);
-    if (n_steps > 1) { copy_q(SLOT, 1); copy_do(SLOT, 1); }
+    int head = h_first, qt_copy = qbeg;                // of the tile that is copied next
+    auto copied = [&]() {
+        if (qt_copy + BT2 >= qend) ++head;
+        qt_copy = next_tile(qt_copy);
+    };
+    copy_q(0, head, qt_copy); copy_do(0, head, qt_copy);
+    copied();
+    if (n_steps > 1) { copy_q(SLOT, head, qt_copy); copy_do(SLOT, head, qt_copy); copied(); }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // Barrier 2 t stands in front of the first wavefront's block 0 of step t (tile t has landed, block 1 of step t - 1 is in its
-    // buffer), barrier 2 t + 1 in front of its block 1.  Behind the latter nobody reads tile t - 1 any more: its slot is tile t + 2's.
+    // buffer), barrier 2 t + 1 in front of its block 1.  Behind the latter nobody reads tile t - 1 any more: its slot is tile t + 2's,
+    // whose Q rows are requested there and whose dO rows behind the next barrier.
     uint32_t tile = 0, before = 2 * SLOT;              // slots of tiles t and t - 1 (which is tile t + 2's)
+    int qt_now = qbeg, qt_before = qbeg;
     for (int step = 0; step < n_steps; ++step) {
         lds_barrier();
         if (step > 0) {
-            if (step + 1 < n_steps) copy_do(tile == 2 * SLOT ? 0 : tile + SLOT, step + 1);
-            block(std::integral_constant<int, 1>{}, qt_of(step - 1) + 32, before);
+            if (step + 1 < n_steps) { copy_do(next_slot(tile), head, qt_copy); copied(); }
+            block(std::integral_constant<int, 1>{}, qt_before + 32, before);
         }
         lds_barrier();
-        if (step + 2 < n_steps) copy_q(before, step + 2);
-        block(std::integral_constant<int, 0>{}, qt_of(step), tile);
+        if (step + 2 < n_steps) copy_q(before, head, qt_copy);
+        block(std::integral_constant<int, 0>{}, qt_now, tile);
         // tile t + 1 has landed; the copies of Q for tile t + 2 may be in flight (memory operations retire in order)
         if (step + 2 < n_steps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         before = tile;
-        tile = tile == 2 * SLOT ? 0 : tile + SLOT;
+        tile = next_slot(tile);
+        qt_before = qt_now;
+        qt_now = next_tile(qt_now);
     }
     lds_barrier();
-    block(std::integral_constant<int, 1>{}, qt_of(n_steps - 1) + 32, before);
+    block(std::integral_constant<int, 1>{}, qt_before + 32, before);
     lds_barrier();                                     // the tiles are done with: LDS now stages the output rows
     store_dkv<D, CB>(a, smem, pair, half, g, k0 + pair * 32, key, valid, dk, dv);
     if (a.cu_busy && wv == 4 && lane == 0) atomicAdd(a.cu_busy + 2048 + (__smid() & 1023u), wall_clock64());
