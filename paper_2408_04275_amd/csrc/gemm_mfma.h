@@ -405,12 +405,18 @@ void gemm_mfma_kernel(const ARG arg) {
     lb.init(p.B + (size_t)k_begin * (B_KC ? 1 : p.ldb), p.ldb, n0, p.N, Kc);
 
     f32x4 acc[RA][RB];
+    // cleared (4 cycles a register, 1 k for a 256 x 256 tile) while the tile's first copies are on their way
+    auto clear = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < RA; ++i)
+        for (int i = 0; i < RA; ++i)
 #pragma unroll
-        for (int j = 0; j < RB; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+            for (int j = 0; j < RB; ++j) {
+                acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                asm volatile("" : "+a"(acc[i][j]));
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
 
     bf16x8 fa[2][RA], fb[2][RB];
     // Kernels with a K-strided operand read all their fragments as assembly (see lds_read_tr) and wait for
@@ -468,6 +474,15 @@ void gemm_mfma_kernel(const ARG arg) {
     // behind it.  At the barrier of step kt the tiles A(kt+1) and B(kt+1) must have landed; the copies younger than B(kt+1)
     // may still be in flight (memory operations retire in issue order).
     const int nk = (Kc + BK - 1) / BK, nk_whole = Kc / BK;       // K tiles; those without a remainder
+    // Where every workgroup has one tile, the XCDs walk over the whole K tiles in a circle, each from an eighth further on.  They share
+    // operand panels but no L2: in step, up to eight of them ask for a line that is still on its way from HBM, and each waits for it; out
+    // of step one fetches it and the others find it in the memory-side cache.  (The workgroups of one XCD stay in step: apart, they lose
+    // what L2 shares, 125 us and 199 us for the copies of 8192 x 4096 x 4096.)  From HBM, us: 1031 x 4096 x 11008 122 -> 98, 1031 x 4096 x
+    // 4096 45 -> 39, 2304 x 1024 x 4096 NN 38.8 -> 35.8, 4111 x 1280 x 5120 61.7 -> 59.9; operands in that cache: the same.  Launches of
+    // several rounds are out of step as they are (8192 x 4096 x 22016 lost 1 %), and below 32 K tiles everything is requested almost at
+    // once in any order: 4111 x 3840 x 1280 35.2 -> 36.3, 1031 x 4096 x 1024 the same, x 2048 25.4 -> 21.7.  Nor do weight gradients, which read
+    // longer pieces of their operands' rows: 4096 x 1024 x 2048 20.6 -> 20.9 from the cache, 24.1 -> 23.9 from HBM.
+    const int k_start = A_KC && nk_whole >= 32 && run_end - run_begin <= wg_per_xcd ? xcd * nk_whole / 8 : 0;     // the first K tile
     typedef std::integral_constant<int, 0> S0;
     typedef std::integral_constant<int, 1> S1;
     typedef std::make_integer_sequence<int, Sched::NG> Groups;
@@ -476,9 +491,11 @@ void gemm_mfma_kernel(const ARG arg) {
     if (nk_whole >= AHEAD) {
 #pragma unroll
         for (int j = 0; j < AHEAD; ++j) {
-            la.template copy_all<true>(smem + j * TS::A_BYTES, j * BK);
-            lb.template copy_all<true>(smem + B0 + j * TS::B_BYTES, j * BK);
+            const int k = (k_start + j >= nk_whole ? k_start + j - nk_whole : k_start + j) * BK;
+            la.template copy_all<true>(smem + j * TS::A_BYTES, k);
+            lb.template copy_all<true>(smem + B0 + j * TS::B_BYTES, k);
         }
+        clear();
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * (RA + RB)) : "memory");     // A0 and B0 have landed
     } else {                                                   // a short K: only the tiles it has, all of them waited for
         const int n = min(nk, AHEAD);
@@ -487,6 +504,7 @@ void gemm_mfma_kernel(const ARG arg) {
             la.template copy_all<false>(smem + j * TS::A_BYTES, j * BK);
             lb.template copy_all<false>(smem + B0 + j * TS::B_BYTES, j * BK);
         }
+        clear();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     lds_barrier();
@@ -494,14 +512,15 @@ void gemm_mfma_kernel(const ARG arg) {
 
     // LDS offsets of the slots of A(kt), A(kt+1), A(kt+AHEAD) and of B(kt), which is B(kt+AHEAD)'s as well, and B(kt+1)
     int oa = 0, oa1 = TS::A_BYTES, oad = AHEAD * TS::A_BYTES, ob = B0, ob1 = B0 + (AHEAD > 1 ? TS::B_BYTES : 0);
+    // scalar offsets of what the next step requests (of whole tiles)
+    uint32_t so_a = la.step_soff((k_start + AHEAD) * BK), so_b = lb.step_soff((k_start + AHEAD) * BK);
     // COPY: 2 = tile kt + AHEAD is whole (fast copies), 1 = it reaches beyond K, 0 = there is no such tile
     auto step = [&](auto COPY_, int kt) {
         constexpr int COPY = decltype(COPY_)::value;
-        const int k2 = (kt + AHEAD) * BK;
+        const int k2 = (kt + AHEAD) * BK;                      // (where the tile reaches beyond K)
         typedef std::remove_reference_t<decltype(la)> LA;
         typedef std::remove_reference_t<decltype(lb)> LB;
-        // fast path: scalar offsets and LDS destinations of this step's copies
-        const uint32_t so_a = __builtin_amdgcn_readfirstlane(la.step_soff(k2)), so_b = __builtin_amdgcn_readfirstlane(lb.step_soff(k2));
+        // fast path: LDS destinations of this step's copies
         const uint32_t mb_a = __builtin_amdgcn_readfirstlane(lds0 + oad + la.slab0), mb_b = __builtin_amdgcn_readfirstlane(lds0 + ob + lb.slab0);
         // first slice: fragments of the second slice; A(kt+AHEAD) into the slot A(kt-1) had
         static_for(Groups{}, [&](auto G) {
@@ -563,7 +582,16 @@ void gemm_mfma_kernel(const ARG arg) {
     };
     const int nk_fast = max(nk_whole - AHEAD, 0), nk_copy = max(nk - AHEAD, 0);
     int kt = 0;
-    for (; kt < nk_fast; ++kt) step(std::integral_constant<int, 2>{}, kt);
+    for (int lap = nk_fast - k_start;;) {                        // the requests pass the end of K at step `lap` and go on from its start
+        if (kt >= lap) { lap = nk_fast; so_a -= la.step_soff(nk_whole * BK); so_b -= lb.step_soff(nk_whole * BK); }
+#pragma unroll 1
+        for (; kt < lap; ++kt) {
+            step(std::integral_constant<int, 2>{}, kt);
+            so_a += la.step_soff(BK);
+            so_b += lb.step_soff(BK);
+        }
+        if (kt >= nk_fast) break;
+    }
     for (; kt < nk_copy; ++kt) step(std::integral_constant<int, 1>{}, kt);
     for (; kt < nk; ++kt) step(std::integral_constant<int, 0>{}, kt);
     asm volatile("s_nop 15\n\ts_waitcnt vmcnt(0)" ::: "memory");   // the last MFMAs have written their accumulators, and no copy is

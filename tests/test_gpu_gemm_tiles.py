@@ -2,6 +2,7 @@
 library, also without a GPU): sizes just past a tile edge, K with a remainder, K shorter than the look-ahead of the K loop and longer, with and
 without addends."""
 import pytest
+import torch
 
 from paper_2408_04275_amd import binding as mm
 from test_gpu_ops import gemm_case
@@ -56,3 +57,24 @@ def test_input_gradient_cut_along_k(M, N, K, room, chunks, monkeypatch):
     assert gemm_route(mm.GEMM_NN, M, N, K, size)[2:] == (0, chunks)
     monkeypatch.setattr(mm, "mmtrain_gemm_workspace_bytes", lambda layout, m, n: size)
     gemm_case(mm.BF16, mm.GEMM_NN, M, N, K, accumulate=chunks == 5, seed=25, workspace=True)
+
+
+# one tile per workgroup and 32 whole K tiles or more: every XCD starts at another eighth of K and goes round (31, and weight gradients: all at its start).  Small whole numbers
+# have exact sums in any order, so each K tile has to come in exactly once; a start next to the end of K, a remainder, each tile shape
+CIRCLES = [(mm.GEMM_NT, 9, 40, 2040, "64x64"), (mm.GEMM_NN, 129, 200, 2048, "64x64"), (mm.GEMM_TN, 72, 264, 2111, "64x64"), (mm.GEMM_NT, 577, 2184, 2568, "64x128"),
+           (mm.GEMM_TN, 1032, 2312, 2183, "128x128"), (mm.GEMM_NN, 2304, 1032, 2184, "128x128"), (mm.GEMM_NT, 1031, 4096, 2112, "192x128"), (mm.GEMM_NT, 2703, 2184, 2624, "256x128"),
+           (mm.GEMM_TN, 2056, 1928, 3000, "256x128"), (mm.GEMM_NN, 2312, 3480, 2056, "160x256"), (mm.GEMM_NT, 3880, 2576, 2696, "192x256"),
+           (mm.GEMM_NT, 3485, 3464, 2120, "224x256"), (mm.GEMM_NN, 4096, 4000, 2072, "256x256"), (mm.GEMM_TN, 4096, 4096, 2113, "256x256")]
+
+
+@pytest.mark.parametrize("layout,M,N,K,tile", CIRCLES)
+def test_contraction_that_starts_anywhere(layout, M, N, K, tile):
+    assert "%dx%d" % gemm_route(layout, M, N, K)[:2] == tile
+    gen = torch.Generator().manual_seed(28)
+    a, b = (torch.randint(-1, 2, (rows, K), generator=gen).float() for rows in (M, N))
+    A = (a.t() if layout == mm.GEMM_TN else a).contiguous().bfloat16().cuda()
+    B = (b if layout == mm.GEMM_NT else b.t()).contiguous().bfloat16().cuda()
+    out = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    assert mm.mmtrain_gemm(mm.BF16, layout, M, N, K, A, A.shape[1], B, B.shape[1], out, N) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(out.cpu(), (a @ b.t()).bfloat16())
