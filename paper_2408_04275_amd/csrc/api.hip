@@ -464,13 +464,13 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
 // ---- a stack of layers -------------------------------------------------------------
 // ctx: the inputs of layers 1 .. n-1 ([T, H] each), then the layer contexts: one per layer, or a single one with
 // MMTRAIN_STACK_RECOMPUTE.  Backward workspace: the layer's own, then two [T, H] buffers through which the
-// gradient travels down the stack.
+// gradient travels down the stack, then (recomputation) room for one [T, H] tensor that the size has always counted.
 namespace {
 struct StackPlan {
     size_t act, layer_ctx, layer_ws_fwd, layer_ws_bwd;
     bool recompute;
     size_t ctx_bytes(int n) const { return (size_t)(n - 1) * act + (recompute ? 1 : (size_t)n) * layer_ctx; }
-    size_t ws_bytes(bool bwd) const { return bwd ? layer_ws_bwd + 2 * act : layer_ws_fwd; }
+    size_t ws_bytes(bool bwd) const { return bwd ? layer_ws_bwd + 2 * act + (recompute ? act : 0) : layer_ws_fwd; }
 };
 int plan_stack(const mmtrain_layer_desc *desc, int n_layers, int T, int S, uint32_t flags, uint32_t allowed, StackPlan &p) {
     Dims D;
