@@ -266,20 +266,19 @@ __device__ __forceinline__ void static_for(F &&f) {
         static_for<I + 1, N>(f);
     }
 }
-typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
-
-// LDS reads of the dK/dV kernel, written as assembly together with their waits: the compiler makes reads wait for copies in flight
+// LDS read of the dK/dV kernel's first wavefronts.  A read written as assembly may only be waited for in one place of the program: where two
+// branches follow it, each with a wait of its own, the compiler copied the result in one of them in front of that branch's wait.
+template <typename V>
+__device__ __forceinline__ V lds_load(uint32_t addr) {
+    return *(volatile __attribute__((address_space(3))) const V *)(uintptr_t)addr;
+}
+// LDS reads of its second wavefronts, written as assembly together with their waits: the compiler makes reads wait for copies in flight
 // and does not count the transposing reads, so its waits come out stricter than needed.  All of them are volatile, so they are issued
 // in source order, and the kernel counts that order.
 template <int IMM, typename V>
 __device__ __forceinline__ void lds_read16(V &dst, uint32_t addr) {
     static_assert(sizeof(V) == 16 && IMM >= 0 && IMM < 65536, "ds_read_b128");
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(IMM));
-}
-// x is complete once at most ALLOWED LDS operations issued after its read are outstanding
-template <int ALLOWED, typename V>
-__device__ __forceinline__ void lds_wait(V &x) {
-    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(ALLOWED < 15 ? ALLOWED : 15));
 }
 // Inverse rotary embedding of a gradient held in accumulator layout (the backward pass of the rotation that
 // was applied to q and k before the attention): feature f < D/2 pairs with f + D/2, which sit in the same
@@ -932,24 +931,29 @@ __global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
             const int qb = qt + 32 * b;
             if (!active(qb)) return;
             // LDS reads in the order they are issued: the score fragments (slice ks of Q, of dO), then the log-sum-exps and D values of
-            // the lane's four quads of queries.  AHEAD of them are out at any time; with the waits written out none of them is stricter.
+            // the lane's four quads of queries.  AHEAD of them are out at any time; volatile keeps their order, the compiler writes the waits.
             constexpr int NF = 2 * KS, AHEAD = 8;
             bf16x8 fr[NF];
             f32x4 l4[4], d4[4];
+            uint32_t fa, la = l0 + tile;
+            asm volatile("" : "+v"(la));
             auto issue = [&](auto I_) {
                 constexpr int i = decltype(I_)::value;
-                if constexpr (i < NF) lds_read16<(i & 1) * TILE + b * 64 * D>(fr[i], f0[i >> 1] + tile);
-                else if constexpr (((i - NF) & 1) == 0) lds_read16<b * 128 + (i - NF) / 2 * 32>(l4[(i - NF) / 2], l0 + tile);
-                else lds_read16<b * 128 + (i - NF) / 2 * 32 + BT2 * 4>(d4[(i - NF) / 2], l0 + tile);
+                if constexpr (i < NF) {
+                    if constexpr ((i & 1) == 0) { fa = f0[i >> 1] + tile; asm volatile("" : "+v"(fa)); }      // (one address for both reads)
+                    fr[i] = lds_load<bf16x8>(fa + ((i & 1) * TILE + b * 64 * D));
+                } else if constexpr (((i - NF) & 1) == 0) l4[(i - NF) / 2] = lds_load<f32x4>(la + (b * 128 + (i - NF) / 2 * 32));
+                else d4[(i - NF) / 2] = lds_load<f32x4>(la + (b * 128 + (i - NF) / 2 * 32 + BT2 * 4));
             };
             static_for<0, AHEAD>([&](auto I_) { issue(I_); });
+            __builtin_amdgcn_sched_barrier(0);
             f32x16 s = zero16(), dp = zero16();
             static_for<0, NF>([&](auto J_) {
                 constexpr int j = decltype(J_)::value;
-                lds_wait<AHEAD - 1>(fr[j]);
                 if constexpr ((j & 1) == 0) s = MFMA(fr[j], kf[j >> 1], s);
                 else dp = MFMA(fr[j], vf[j >> 1], dp);
                 issue(std::integral_constant<int, j + AHEAD>{});
+                __builtin_amdgcn_sched_barrier(0);
             });
             const bool inside = qb >= w_lo_max && qb + 32 <= w_hi_min;
             const int rel = qb + 4 * half - me.lo;
@@ -958,8 +962,6 @@ __global__ __launch_bounds__(512, 2) void attn_dkv_kernel(AttnArgs a) {
             auto softmax = [&](auto MASK_) {
                 static_for<0, 4>([&](auto Q_) {
                     constexpr int gq = decltype(Q_)::value;
-                    lds_wait<6 - 2 * gq>(l4[gq]);
-                    lds_wait<6 - 2 * gq>(d4[gq]);
                     float p[4], ds[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
@@ -1208,7 +1210,7 @@ __global__ __launch_bounds__(PARTS * 256, PARTS) void attn_dkv_plain_kernel(Attn
                 q0f[0] = tr.template read<b, m, 0, 0>(tq); q1f[0] = tr.template read<b, m, 0, 1>(tq);
                 o0[1] = tr.template read<b, m, 1, 0>(tdo); o1[1] = tr.template read<b, m, 1, 1>(tdo);
                 q0f[1] = tr.template read<b, m, 1, 0>(tq); q1f[1] = tr.template read<b, m, 1, 1>(tq);
-                if (CB > 2) {
+                if constexpr (CB > 2) {
                     o0[2] = tr.template read<b, m, 2, 0>(tdo); o1[2] = tr.template read<b, m, 2, 1>(tdo);
                     q0f[2] = tr.template read<b, m, 2, 0>(tq); q1f[2] = tr.template read<b, m, 2, 1>(tq);
                     o0[3] = tr.template read<b, m, 3, 0>(tdo); o1[3] = tr.template read<b, m, 3, 1>(tdo);
