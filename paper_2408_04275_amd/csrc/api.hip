@@ -822,6 +822,12 @@ MMTRAIN_API int mmtrain_route_gemm(int32_t layout, int32_t M, int32_t N, int32_t
     for (int i = 0; i < 4; ++i) route[i] = r[i];
     return MMTRAIN_OK;
 }
+// a weight gradient [M, N] over K tokens with fp32 output: see gemm_mfma_late_start
+MMTRAIN_API int mmtrain_route_late_start(int32_t M, int32_t N, int32_t K, int32_t accumulate, int32_t n_cu) {
+    GemmArgs g = mk(GEMM_TN, M, N, K, nullptr, M, nullptr, N, nullptr, N);
+    g.c_f32 = true; g.accumulate = accumulate != 0;
+    return gemm_mfma_supported(g) ? gemm_mfma_late_start(g, n_cu) : -1;
+}
 MMTRAIN_API int mmtrain_route_gemm_f32(int32_t layout, int32_t M, int32_t N, int32_t K) {      // 1: matrix instruction, 0: vector ALUs
     return gemm_f32_supported(mk(layout, M, N, K, nullptr, layout == GEMM_TN ? M : K, nullptr, layout == GEMM_NT ? K : N, nullptr, N)) ? 1 : 0;
 }

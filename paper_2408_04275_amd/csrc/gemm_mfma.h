@@ -75,6 +75,7 @@ struct GemmP {
     // tiles) the partial product of chunk s of the launch's tile j is a dense block at C + (s * tile_count + j) * 65536
     // instead of a window of an M x N matrix.
     int tile_begin, tile_count, compact;
+    int late_start;            // units of 512 clocks that every second workgroup waits at its start
     unsigned long long *clock_probe;       // see GemmArgs
 };
 
@@ -378,15 +379,9 @@ void gemm_mfma_kernel(const ARG arg) {
             else b_rd[c][sl] = (sl * 32 + 8 * fq + (frow >> 2)) * B_PITCH + (frow & 3) * 8 + ((wn * RB + c) ^ (frow >> 2)) * 32;
         }
 
-    // Sums added to fp32 contents move 8 bytes per element: all compute units multiplying at once and then all at memory at once leave
-    // each idle half of the time.  Where a workgroup has two tiles and more, every second one starts later, by half a tile's time but
-    // no more than its memory phase takes.  Three rounds and more, 1031 tokens: 22016 x 4096 257 -> 248 us, 4096 x 11008 149 -> 140,
-    // 12288 x 4096 148 -> 136.
-    if constexpr (OUT_F32)
-        if ((q & 1) && first_problem(arg).accumulate && per >= 2 * wg_per_xcd) {
-            const int clocks = min((first_problem(arg).K + BK - 1) / BK * 1200 + 10000, 30000) * (RA * RB) / 64;
-            for (int i = 0; i < clocks / 512; ++i) __builtin_amdgcn_s_sleep(8);        // 512 clocks
-        }
+    if constexpr (OUT_F32)                                        // (see late_start)
+        if (q & 1)
+            for (int i = 0; i < first_problem(arg).late_start; ++i) __builtin_amdgcn_s_sleep(8);
 
     for (int logical = run_begin + q; logical < run_end; logical += wg_per_xcd) {
     int tm, tn, item;
@@ -753,6 +748,22 @@ void gemm_mfma_kernel(const ARG arg) {
     }
 }
 
+// Sums added to fp32 contents move 8 bytes per element: all compute units multiplying at once and then all at memory at once leave each
+// idle half of the time.  Where every workgroup has two tiles and more, every second one starts later, by half a tile's time but no more
+// than its memory phase takes.  The longer the K loop beside that phase, the less there is to hide and the more the workgroups drift out of
+// step by themselves.  Without -> with it, us, mean of two boxes: K = 1031: 8192 x 4096 (two rounds of 256 x 256 tiles) 125 -> 107, 12288 x 4096
+// (three) 147 -> 133, 28672 x 4096 (seven) 316 -> 294; K = 2048 160 -> 143, 203 -> 191, 451 -> 441; K = 4096 234 -> 223, 336 -> 330, 766 -> 763 and
+// 8192 x 12288 (six) 649 -> 648; but K = 6144 315 -> 312, 467 -> 472, 1104 -> 1100, 916 -> 922 and K = 8192 401 -> 404, 612 -> 616, 1432 -> 1433, 1179 -> 1196.
+// In 256 x 128 tiles, 6144 x 4096 (three): K = 1031 85 -> 81, 2048 119.7 -> 120.6, 4096 199 -> 200.  Every second workgroup, whichever have a tile more
+// than the others: to spare those gains where they are two of 32 (8448 x 4096 127 -> 116) and loses where they are 28 (11776 x 4096 132 -> 140).
+template <class TS>
+int late_start(int accumulate, int K, int items, int workgroups) {
+    constexpr int BLOCKS = TS::RA * TS::RB;
+    if (!accumulate || items / workgroups < 2 || K > (BLOCKS == 64 ? 4096 : 1536)) return 0;
+    const int clocks = (K + BK - 1) / BK * 1200 + 10000;
+    return (clocks < 30000 ? clocks : 30000) * BLOCKS / 64 / 512;
+}
+
 // compute units of the current device, rounded down to whole XCD octets (one persistent workgroup each)
 inline hipError_t compute_units(int &n) {
     static std::atomic<int> cached{0};
@@ -780,7 +791,7 @@ inline hipError_t allow_lds(std::atomic<bool> &configured, const void *kern, int
 }
 
 template <bool A_KC, bool B_KC, bool HAS_ADD, bool OUT_F32, class TS>
-hipError_t launch(const GemmP &p, hipStream_t st) {
+hipError_t launch(GemmP p, hipStream_t st) {
     static std::atomic<bool> configured{false};
     auto kern = gemm_mfma_kernel<A_KC, B_KC, HAS_ADD, OUT_F32, TS>;
     hipError_t e = allow_lds(configured, reinterpret_cast<const void *>(kern), TS::SMEM);
@@ -791,7 +802,9 @@ hipError_t launch(const GemmP &p, hipStream_t st) {
     if (e != hipSuccess) return e;
     const int items = p.tile_count * (OUT_F32 ? p.splits : 1), room = n_cu * TS::PER_CU;
     if (items <= 0) return hipSuccess;
-    kern<<<items < room ? items : room, 256, TS::SMEM, st>>>(p);
+    const int workgroups = items < room ? items : room;
+    p.late_start = OUT_F32 ? late_start<TS>(p.accumulate, p.K, items, workgroups) : 0;
+    kern<<<workgroups, 256, TS::SMEM, st>>>(p);
     return hipGetLastError();
 }
 

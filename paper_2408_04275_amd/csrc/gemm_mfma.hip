@@ -72,7 +72,7 @@ GemmP params(const GemmArgs &g) {
     p.tiles_m = ceil_div(g.M, TILE);
     p.tiles_n = ceil_div(g.N, TILE);
     p.splits = 1; p.k_chunk = g.K;
-    p.tile_begin = 0; p.tile_count = p.tiles_m * p.tiles_n; p.compact = 0;
+    p.tile_begin = 0; p.tile_count = p.tiles_m * p.tiles_n; p.compact = 0; p.late_start = 0;
     p.clock_probe = g.clock_probe;
     return p;
 }
@@ -278,6 +278,23 @@ GemmPlan gemm_mfma_plan(const GemmArgs &g, int n_cu) {
         plan.chunks = ceil_div(g.K, plan.k_chunk);
     }
     return plan;
+}
+
+int gemm_mfma_late_start(const GemmArgs &g, int n_cu) {
+    const GemmPlan plan = gemm_mfma_plan(g, n_cu);
+    const int items = ceil_div(g.M, plan.tile_m) * ceil_div(g.N, plan.tile_n) - plan.tail_tiles;
+    auto units = [&](auto TS_) {
+        typedef decltype(TS_) TS;
+        return late_start<TS>(g.accumulate, g.K, items, std::min(items, n_cu * TS::PER_CU));
+    };
+    if (!g.c_f32) return 0;
+    switch (plan.shape) {
+        case TILE_256x128: return units(Tile256x128{});
+        case TILE_128: return units(Tile128{});
+        case TILE_64x128: return units(Tile64x128{});
+        case TILE_64: return units(Tile64{});
+        default: return units(Tile256{});
+    }
 }
 
 hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st) {

@@ -6,7 +6,7 @@ namespace gemm_detail {
 namespace {
 
 template <bool HAS_ADD, bool OUT_F32, class TS>
-hipError_t launch_group(const GemmGroup &g, hipStream_t st) {
+hipError_t launch_group(GemmGroup &g, hipStream_t st) {
     static std::atomic<bool> configured{false};
     auto kern = gemm_mfma_kernel<false, false, HAS_ADD, OUT_F32, TS, GemmGroup>;
     hipError_t e = allow_lds(configured, reinterpret_cast<const void *>(kern), TS::SMEM);
@@ -16,7 +16,9 @@ hipError_t launch_group(const GemmGroup &g, hipStream_t st) {
     if (e != hipSuccess) return e;
     const int items = g.first[MAX_GROUP], room = n_cu * TS::PER_CU;
     if (items <= 0) return hipSuccess;
-    kern<<<items < room ? items : room, 256, TS::SMEM, st>>>(g);
+    const int workgroups = items < room ? items : room;
+    g.p[0].late_start = OUT_F32 ? late_start<TS>(g.p[0].accumulate, g.p[0].K, items, workgroups) : 0;
+    kern<<<workgroups, 256, TS::SMEM, st>>>(g);
     return hipGetLastError();
 }
 

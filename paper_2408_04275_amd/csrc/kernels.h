@@ -43,6 +43,8 @@ hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st);
 // tail_tiles tiles of the order in `chunks` chunks each.  Chunks are k_chunk long, the last one shorter.
 struct GemmPlan { int shape, tile_m, tile_n, tail_tiles, chunks, k_chunk; };
 GemmPlan gemm_mfma_plan(const GemmArgs &g, int n_cu);
+// units of 512 clocks by which every second workgroup of a weight gradient with fp32 output starts later on n_cu compute units
+int gemm_mfma_late_start(const GemmArgs &g, int n_cu);
 // Scratch (GemmArgs::split_ws) with which no cut along K is restricted: input gradients of up to M rows (NN), weight gradients over
 // up to K tokens (TN).  Neither falls as that argument grows.
 size_t gemm_mfma_nn_scratch(long M, long N, long K);

@@ -91,3 +91,16 @@ def test_fp32_short_contractions():
     for layout, K, matrix in [(mm.GEMM_TN, 80, 0), (mm.GEMM_TN, 96, 1), (mm.GEMM_NN, 64, 0), (mm.GEMM_NN, 72, 1), (mm.GEMM_NT, 8, 1)]:
         assert route(layout, 1352, 3288, K) == matrix, (layout, K)      # 1144 tiles of 64 x 64
         assert route(layout, 640, 640, K) == 1                          # 100
+
+
+# Weight gradients added to fp32 contents: every second workgroup starts later only where the launch has two rounds of tiles and more and few
+# enough tokens to gain by it.  (M, N, tokens): whether
+@pytest.mark.parametrize("M,N,K,late", [(8192, 4096, 300, True), (12288, 4096, 1031, True), (28672, 4096, 2048, True), (8192, 4096, 4096, True), (22016, 4096, 4096, True),
+                                        (6144, 4096, 1031, True), (6144, 4096, 2048, False), (4096, 4096, 1031, False), (8192, 4096, 4097, False),
+                                        (22016, 4096, 8192, False), (8192, 12288, 6144, False), (8192, 8192, 200000, False)])
+def test_late_start_of_fp32_gradients(M, N, K, late):
+    route = mm.load_library().mmtrain_route_late_start
+    route.argtypes = [C.c_int32] * 5
+    units = route(M, N, K, 1, 256)
+    assert (0 < units <= 30000 // 512) if late else units == 0
+    assert route(M, N, K, 0, 256) == 0                                 # nothing is read: nothing to hide
