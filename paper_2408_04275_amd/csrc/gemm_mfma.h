@@ -607,29 +607,30 @@ void gemm_mfma_kernel(const ARG arg) {
         // L2 half filled: 29 % more bytes written).  A wavefront's LDS instructions execute in order, so neither the read-back of a
         // block nor the writes of the next one into the same place wait for what stands in front of them; the compiler is only kept
         // from reordering them.  The previous contents are fetched a row block ahead of their use, in front of the stores in between:
-        // memory operations retire in order, and a load behind a store returns only when that store has been acknowledged.  Lanes
-        // outside the matrix carry an offset that the descriptor's bounds check turns into nothing, without a branch.  22016 x 4096,
-        // 1031 tokens added to fp32 gradients: 308 -> 257 us, 300 tokens 223 -> 172 (in 32-row chunks whose loads stood behind stores).
-        float *const out = reinterpret_cast<float *>(p.C) +
+        // memory operations retire in order, and a load behind a store returns only when that store has been acknowledged.  Every row
+        // block has a descriptor of its own, so that 32-bit offsets reach rows of up to 2^26 elements; lanes outside the matrix carry an
+        // offset that the descriptor's bounds check turns into nothing, without a branch.  22016 x 4096, 1031 tokens added to fp32 gradients: 308 -> 257 us, 300 tokens 223 -> 172 (in 32-row chunks whose loads stood behind stores).
+        const uint32_t pitch = p.compact ? 256u : (uint32_t)p.ldc;
+        const int wm0 = __builtin_amdgcn_readfirstlane(wm) * 16 * RA;         // first row of this wavefront
+        float *const out = reinterpret_cast<float *>(p.C) + (size_t)wm0 * pitch +
                            (p.compact ? (size_t)(chunk * p.tile_count + tl) << 16 : (size_t)chunk * p.M * p.ldc + (size_t)m0 * p.ldc + n0);
-        const __amdgpu_buffer_rsrc_t rs_out = make_rsrc(out, OOB);
-        const uint32_t row_bytes = (p.compact ? 256u : (uint32_t)p.ldc) * 4u;
         constexpr int UNITS = 4 * RB, RPP = 64 / UNITS, PASSES = 16 / RPP, DEPTH = 2;       // 16-byte units per row, rows per pass
         const int er = lane / UNITS, eu = lane % UNITS;
-        const int row0 = wm * 16 * RA + er, col0 = wn * 16 * RB + eu * 4, rows = p.M - m0;
+        const int col0 = wn * 16 * RB + eu * 4, rows = p.M - m0 - wm0;
         const uint32_t col_bytes = n0 + col0 < p.N ? (uint32_t)col0 * 4u : OOB;
         uint8_t *stg = smem + wave * (16 * 16 * RB * 4);
         // unit u of staged row r is kept at unit u ^ turn(r): the 16 rows that a write covers fall into distinct 16-byte slots
         auto turn = [](int r) { return RB == 2 ? ((r >> 2) & 1) | ((r & 3) << 1) : r & 15; };
         rawx4 prev[DEPTH][PASSES];
+        auto block = [&](int i) { return make_rsrc(out + (size_t)(16 * i) * pitch, OOB); };
         auto offset = [&](int i, int pass) {
-            const int r = row0 + 16 * i + RPP * pass;
-            return (int)(r < rows && col_bytes != OOB ? (uint32_t)r * row_bytes + col_bytes : OOB);
+            const int r = RPP * pass + er;
+            return (int)(16 * i + r < rows && col_bytes != OOB ? (uint32_t)r * pitch * 4u + col_bytes : OOB);
         };
         auto fetch = [&](auto I_) {
             constexpr int i = decltype(I_)::value;
 #pragma unroll
-            for (int pass = 0; pass < PASSES; ++pass) prev[i % DEPTH][pass] = __builtin_amdgcn_raw_buffer_load_b128(rs_out, offset(i, pass), 0, 0);
+            for (int pass = 0; pass < PASSES; ++pass) prev[i % DEPTH][pass] = __builtin_amdgcn_raw_buffer_load_b128(block(i), offset(i, pass), 0, 0);
         };
         auto finish = [&](auto ADD_) {
             constexpr bool ADD = decltype(ADD_)::value;
@@ -652,7 +653,7 @@ void gemm_mfma_kernel(const ARG arg) {
 #pragma unroll
                 for (int pass = 0; pass < PASSES; ++pass) {
                     if constexpr (ADD) v[pass] += *reinterpret_cast<const f32x4 *>(&prev[i % DEPTH][pass]);
-                    __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const rawx4 *>(&v[pass]), rs_out, offset(i, pass), 0, STREAMING);
+                    __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const rawx4 *>(&v[pass]), block(i), offset(i, pass), 0, STREAMING);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             });

@@ -88,7 +88,7 @@ hipError_t launch_partials(int layout, const GemmP &p, hipStream_t st) {
 bool gemm_mfma_supported(const GemmArgs &g) {
     if (g.M <= 0 || g.N <= 0 || g.K <= 0) return false;
     if (g.c_f32 && (g.layout != GEMM_TN || g.bias || g.residual)) return false;   // fp32 output: weight gradients only
-    if (g.c_f32 && g.ldc > 1 << 21) return false;                                 // a tile's rows of it are addressed with 32-bit byte offsets
+    if (g.c_f32 && g.ldc > 1 << 26) return false;                                 // 16 rows of it are addressed with 32-bit byte offsets
     if ((g.lda | g.ldb | g.ldc | g.N) & 7) return false;
     const bool a_kc = g.layout != GEMM_TN, b_kc = g.layout == GEMM_NT;
     if ((a_kc || b_kc) && (g.K & 7)) return false;

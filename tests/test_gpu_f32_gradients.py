@@ -41,3 +41,27 @@ def test_added_to_previous_contents(H, nh, d, F, T):
     torch.cuda.synchronize()
     for k, g in runs[1].g.items():
         assert torch.equal(g, before[k] + once[k]), k
+
+
+def test_rows_of_more_than_2_21_elements():
+    # the gradient of the second feed-forward weight: rows of 8 MiB, two tiles of them, ragged in both directions
+    H, nh, d, F, T = 272, 4, 64, (1 << 21) + 16, 8
+    desc = mm.make_desc(mm.DECODER, mm.BF16, H, nh, nh, d, F)
+    batch = mm.PackedBatch.on_device(np.array([0, T], dtype=np.int32), np.zeros(1, dtype=np.uint8))
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16)  # noqa: E731
+    w = {"norm1_w": rand(H), "w_qkv": rand(3 * nh * d, H) * 0.05, "w_o": rand(H, nh * d) * 0.05, "norm2_w": rand(H),
+         "w_fc1": rand(2 * F, H) * 0.05, "w_fc2": rand(H, F) * 0.001}
+    x, dy = rand(T, H), rand(T, H)
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    nbytes = max(mm.mmtrain_layer_workspace_bytes(desc, T, 1, b) for b in (0, 1))
+    ws, ctx = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (nbytes, mm.mmtrain_layer_ctx_bytes(desc, T)))
+    weights = mm.make_weights(w)
+    check(mm.mmtrain_layer_fwd(desc, batch, weights, x, y, ctx, ws, nbytes), "fwd")
+    before = torch.randn((H, F), generator=gen, device="cuda")
+    g = [torch.empty((H, F), dtype=torch.bfloat16, device="cuda"), torch.empty_like(before), before.clone()]
+    for out, flags in zip(g, (0, mm.BWD_WGRAD_F32, mm.BWD_WGRAD_F32 | mm.BWD_ACCUMULATE_WGRAD)):
+        check(mm.mmtrain_layer_bwd(desc, batch, weights, x, dy, ctx, dx, mm.make_grads({"w_fc2": out}), flags, ws, nbytes), "bwd")
+    torch.cuda.synchronize()
+    assert g[1].abs().max() > 0 and torch.equal(g[1].bfloat16(), g[0])
+    assert torch.equal(g[2], before + g[1])

@@ -104,3 +104,11 @@ def test_late_start_of_fp32_gradients(M, N, K, late):
     units = route(M, N, K, 1, 256)
     assert (0 < units <= 30000 // 512) if late else units == 0
     assert route(M, N, K, 0, 256) == 0                                 # nothing is read: nothing to hide
+
+
+# fp32 gradients of any width that the operands can have (the feed-forward width of test_gpu_f32_gradients.py's widest layer among them)
+@pytest.mark.parametrize("N", [(1 << 21) + 16, (1 << 22) + 8, (1 << 23) - 65536])
+def test_wide_fp32_gradients_stay_on_the_matrix_cores(N):
+    route = mm.load_library().mmtrain_route_late_start
+    route.argtypes = [C.c_int32] * 5
+    assert route(272, N, 1, 1, 256) >= 0
