@@ -14,9 +14,11 @@ pytestmark = pytest.mark.gpu
 
 # hidden, heads, head width, feed-forward width, tokens
 SHAPES = [(80, 1, 64, 144, 67), (272, 4, 64, 528, 300), (1296, 10, 128, 2576, 131), (2064, 16, 128, 8208, 70)]
+# the same with more tokens than the K loop looks ahead, and the tiles that the gradients of the two feed-forward weights take
+LONGER = [(2064, 4, 128, 5520, 777, "256x128", "256x256"), (2064, 16, 128, 8208, 450, "256x256", "256x128")]
 
 
-@pytest.mark.parametrize("H,nh,d,F,T", SHAPES)
+@pytest.mark.parametrize("H,nh,d,F,T", SHAPES + [s[:5] for s in LONGER])
 def test_added_to_previous_contents(H, nh, d, F, T):
     shape = wl.LayerShape("f32g", wl.DECODER, wl.BF16, H, nh, nh, d, F, T)
     cu, modes = np.array([0, 9, T], dtype=np.int32), np.zeros(2, dtype=np.uint8)

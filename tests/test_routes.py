@@ -5,6 +5,7 @@ import ctypes as C
 import pytest
 
 from paper_2408_04275_amd import binding as mm
+from test_gpu_f32_gradients import LONGER
 from test_gpu_gemm_tiles import CUTS, SHAPES, WGRAD_SHAPES
 from util import gemm_route
 
@@ -112,3 +113,10 @@ def test_wide_fp32_gradients_stay_on_the_matrix_cores(N):
     route = mm.load_library().mmtrain_route_late_start
     route.argtypes = [C.c_int32] * 5
     assert route(272, N, 1, 1, 256) >= 0
+
+
+@pytest.mark.parametrize("H,nh,d,F,T,tile1,tile2", LONGER)
+def test_tiles_of_fp32_gradients(H, nh, d, F, T, tile1, tile2):
+    for (M, N), tile in (((2 * F, H), tile1), ((H, F), tile2)):
+        assert gemm_route(mm.GEMM_TN, M, N, T) == (*map(int, tile.split("x")), 0, 1)
+        assert ((M + 255) // 256) * ((N + 255) // 256) > 128                 # a launch of its own, not one of a group
