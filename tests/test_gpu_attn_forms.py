@@ -29,10 +29,11 @@ def test_workgroups_of_two_groups(nh, nkv, d, cu, modes):
     attn_case(mm.BF16, nh, nkv, d, np.array(cu, dtype=np.int32), np.array(modes, dtype=np.uint8), seed=53)
 
 
-# dK/dV with two wavefronts per 32 keys: 1, 2, 3, 4 and 7 tiles of 64 queries (three slots, one block behind) over one and three heads of a
-# group; a first segment of 33 tokens makes wavefronts skip single blocks of 32
-@pytest.mark.parametrize("nh,d", [(1, 128), (3, 128), (3, 80), (1, 96)])
+# dK/dV with two wavefronts per 32 keys: 1, 2, 3, 4 and 7 tiles of 64 queries per head (three slots, one block behind); a first segment of
+# 33 tokens makes wavefronts skip single blocks of 32.  One head, or three and four of a group: one per workgroup, and all of them in one
+# workgroup, which then changes head every 1 to 7 tiles while its copies are two tiles ahead
+@pytest.mark.parametrize("nh,d,share_heads", [(1, 128, True), (3, 128, True), (3, 80, True), (1, 96, True), (3, 128, False), (4, 128, False), (3, 80, False), (4, 96, False)])
 @pytest.mark.parametrize("T", [59, 123, 187, 251, 443])
-def test_key_gradients_of_few_steps(nh, d, T):
-    attn_case(mm.BF16, nh, 1, d, np.array([0, T], dtype=np.int32), np.array([1], dtype=np.uint8), seed=54)
-    attn_case(mm.BF16, nh, 1, d, np.array([0, 33, T], dtype=np.int32), np.array([0, 0], dtype=np.uint8), seed=55)
+def test_key_gradients_of_few_steps(nh, d, share_heads, T):
+    attn_case(mm.BF16, nh, 1, d, np.array([0, T], dtype=np.int32), np.array([1], dtype=np.uint8), seed=54, share_heads=share_heads)
+    attn_case(mm.BF16, nh, 1, d, np.array([0, 33, T], dtype=np.int32), np.array([0, 0], dtype=np.uint8), seed=55, share_heads=share_heads)

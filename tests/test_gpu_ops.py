@@ -88,7 +88,9 @@ def test_gemm_f32(layout, M, N, K):
     gemm_case(mm.F32, layout, M, N, K, bias=True, residual=True, accumulate=(K == 33))
 
 
-def attn_case(dtype, nh, nkv, d, cu, modes, seed=0, std=1.0):
+def attn_case(dtype, nh, nkv, d, cu, modes, seed=0, std=1.0, share_heads=True):
+    """share_heads=False: scratch for the per-token tables only, so that the dK/dV kernels' workgroups walk over all query heads of a
+    group instead of sharing them out."""
     rng = np.random.default_rng(seed)
     T = int(cu[-1])
     nq, nk = nh * d, nkv * d
@@ -101,7 +103,7 @@ def attn_case(dtype, nh, nkv, d, cu, modes, seed=0, std=1.0):
     o_ref, lse_ref = orc.attention_fwd(q, k, v, cu, modes, scale)
     desc = mm.make_desc(mm.DECODER, dtype, 64, nh, nkv, d, 64)
     batch = mm.PackedBatch.on_device(cu, modes)
-    wsb = mm.mmtrain_attn_workspace_bytes(T, len(cu) - 1, nh)
+    wsb = mm.mmtrain_attn_workspace_bytes(T, len(cu) - 1, nh) if share_heads else T * (12 + 4 * nh) + 1024
     ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
     dqkv = to_device(qkv, dtype)
     o = torch.zeros((T, nq), dtype=torch_dtype(dtype), device="cuda")
@@ -153,16 +155,17 @@ def test_attention_padded_head_dim(nh, nkv, d):
     attn_case(mm.BF16, nh, nkv, d, RAGGED_CU, RAGGED_MODES, std=1.0, seed=7)
 
 
-def test_attention_many_segment_boundaries_wide_head():
+@pytest.mark.parametrize("share_heads", [True, False])
+def test_attention_many_segment_boundaries_wide_head(share_heads):
     # 128-wide heads take the dK/dV kernel with two wavefronts per 32 keys: segment boundaries inside key tiles make its
-    # wavefronts start and stop at different steps and restart per query head of the group (4 heads per K/V head);
-    # segments shorter than one step, a bidirectional segment spanning several key tiles, a ragged end
+    # wavefronts start and stop at different steps, and restart per query head of the group (4 heads per K/V head) where they are not shared
+    # out; segments shorter than one step, a bidirectional segment spanning several key tiles, a ragged end
     rng = np.random.default_rng(11)
     lens = [3, 61, 130, 7, 320, 64, 1, 65, 511, 40, 200, 129]
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     modes = rng.integers(0, 2, len(lens)).astype(np.uint8)
     modes[4], modes[8] = 1, 0                                   # the 320-token one bidirectional, the 511-token one causal
-    attn_case(mm.BF16, 8, 2, 128, cu, modes, std=1.0, seed=12)
+    attn_case(mm.BF16, 8, 2, 128, cu, modes, std=1.0, seed=12, share_heads=share_heads)
 
 
 def test_attention_more_tiles_than_the_order_tables_hold():
