@@ -52,6 +52,11 @@
  * measurement aids (mmtrain_profile_*) are process-wide and not thread-safe;
  * mmtrain_attn_bwd_noalloc shares one scratch array per device.
  *
+ * Sums.  A call repeats bit for bit with the same arguments, sizes and scratch.  The order in which a bf16 product
+ * adds up its K terms (in fp32) depends on the product's size and, where every workgroup has one tile, also on the
+ * tile that an output lies in: equal rows of an operand need not give equal bits in different places of a result, and
+ * a row's last bits may change with the number of rows beside it.
+ *
  * Errors.  Every call returns an mmtrain_status (0 = OK, negative = error).
  * Argument and segment validation happens before any HIP call; on such an error
  * nothing has been enqueued.  The library never throws and never aborts.

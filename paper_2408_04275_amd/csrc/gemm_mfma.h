@@ -487,7 +487,9 @@ void gemm_mfma_kernel(const ARG arg) {
     // operand panels but no L2: in step, up to eight of them ask for a line that is still on its way from HBM, and each waits for it; out
     // of step one fetches it and the others find it in the memory-side cache.  (The workgroups of one XCD stay in step: apart, they lose
     // what L2 shares, 125 us and 199 us for the copies of 8192 x 4096 x 4096.)  From HBM, us: 1031 x 4096 x 11008 122 -> 98, 1031 x 4096 x
-    // 4096 45 -> 39, 2304 x 1024 x 4096 NN 38.8 -> 35.8, 4111 x 1280 x 5120 61.7 -> 59.9; operands in that cache: the same.  Launches of
+    // 4096 45 -> 39, 2304 x 1024 x 4096 NN 38.8 -> 35.8, 4111 x 1280 x 5120 61.7 -> 59.9; 120 products of random sizes: 2 % less in 64 x 64
+    // tiles, 6 % in 64 x 128 and 128 x 128.  Operands in that cache: the same, but 1 % more (0.2 us) in 64 x 64 tiles (46 x 2048 x 5120 NN 17.5 ->
+    // 17.8); whole layers' weights come from HBM.  An element's sum then depends in its order on the tile that it lies in.  Launches of
     // several rounds are out of step as they are (8192 x 4096 x 22016 lost 1 %), and below 32 K tiles everything is requested almost at
     // once in any order: 4111 x 3840 x 1280 35.2 -> 36.3, 1031 x 4096 x 1024 the same, x 2048 25.4 -> 21.7.  Nor do weight gradients, which read
     // longer pieces of their operands' rows: 4096 x 1024 x 2048 20.6 -> 20.9 from the cache, 24.1 -> 23.9 from HBM.
