@@ -843,11 +843,13 @@ __global__ __launch_bounds__(WAVES * PARTS * 64, 2) void attn_fwd_kernel(AttnArg
 // P and dS go through LDS, 4 KiB per block of 32 queries, in the layout in which both wavefronts hold them (lane by lane, no
 // conflicts), two buffers; the second wavefront works one block behind the first, with one barrier per block.  Q and dO tiles of 64
 // queries go round three slots: a tile is copied by the second wavefronts during the three blocks in front of its first use.
-// What bounds it: the first wavefront, whose score MFMAs, exponentials and LDS reads (an MFMA needs a fragment, a product two) add up to
-// about 1.7 k cycles per block beside the second's products.  Computing the next block's scores under the exponentials, or giving dP and
-// dS to the second wavefront, moved that cost and did not lower it.  dQ + dK/dV in us, against one wavefront per 32 keys with the next
-// block's scores under the exponentials of this one: 8192 tokens in one long document, 32 heads of 128: 1623 -> 1534; in segments of
-// 700 470 -> 440; 2047 tokens, 64 heads on 8, 189 -> 170; 1031 tokens 56.7 -> 51.9; 16 heads of 80, 4111 tokens 108 -> 97.
+// What bounds it: issue slots and power.  A block of 32 queries takes 1.62 k cycles (all keys visible), at about 1.7 GHz.  Left out one at a
+// time: the second wavefront's work 1.52 k (and 2.0 GHz: a quarter of the time), the exponentials 1.50 k, the score fragments' reads 1.59 k, the
+// transposing reads 1.61 k; nothing that is left gives much by itself.  Computing the next block's scores under the exponentials, or giving dP
+// and dS to the second wavefront, moved cost and did not lower it.  dQ + dK/dV in us, against one wavefront per 32 keys with the next block's
+// scores under the exponentials of this one and transposing reads at half rate: 32 heads of 128, 8192 tokens in one long document 1616 -> 1502; in
+// bidirectional segments of 700 471 -> 411; 1031 tokens in four segments 45.8 -> 40.9; 64 heads on 8, 2047 tokens 334 -> 299; 16 heads of 80, 4111
+// bidirectional tokens in twelve segments 78.7 -> 69.6.
 // ------------------------------------------------------------------------------------------
 template <int D>
 constexpr int DKV_SLOT = 2 * BT2 * D * 2 + 2 * BT2 * 4;            // Q tile, dO tile, lse[64], D[64]
@@ -1404,10 +1406,10 @@ hipError_t attn_mfma_fwd(const AttnArgs &a, hipStream_t st) {
 // units, each with a chain of up to 96 steps.  Shared out, each writes fp32 partial sums (dkv_reduce_kernel adds them in order),
 // which costs 16 bytes per key, head and feature pair.  Only divisors of the group, so that the shares are equal (8 heads over 3
 // workgroups: 8 % slower than over 2), and as many as give two workgroups per compute unit, one at a time (128-wide heads), or
-// six, two at a time.  dQ + dK/dV in us, 64 / 8 heads of 128, before -> after: 500 tokens 151 -> 61 (8 workgroups per group), 1031
-// 204 -> 97 (4), 2047 260 -> 161 (4), 4096 411 -> 314 (2), 6000 625 -> 507 (2), where one and a half rounds become three; at 8192
-// tokens (512 workgroups as they are) two would gain 4 to 8 % for 134 MB of scratch, at 12000 nothing.  16 / 2 heads of 64, 2047
-// tokens: 199 -> 58 (8).
+// six, two at a time.  dQ + dK/dV in us, 64 / 8 heads of 128, one causal segment, without -> with: 500 tokens 116 -> 53 (8 workgroups per
+// group), 1031 232 -> 109 (4), 2047 460 -> 301 (4), 4096 1127 -> 906 (2), 6000 2053 -> 1952 (2), where one and a half rounds become three; at 8192
+// tokens (512 workgroups as they are) two would gain 4 to 8 % for 134 MB of scratch, at 12000 nothing (these two with one wavefront per 32
+// keys).  32 / 8 heads, 2047 tokens: 247 -> 175.  16 / 2 heads of 64, 2047 tokens: 294 -> 80 (8).
 static long longest_shared(long parts, int nkv, int d) {              // the longest pack whose groups are shared out over `parts` workgroups
     const long tiles = d <= 64 ? 1536 / (parts * nkv) : (parts == 2 ? 384 : std::min(384l, 512 / parts)) / nkv;
     return std::min(tiles * BQ, (long)(DKV_PART_BYTES_MAX / (parts * attn_dkv_part_bytes(1, nkv, d))));

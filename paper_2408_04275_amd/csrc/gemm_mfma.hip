@@ -169,8 +169,9 @@ bool gemm_mfma_few_tiles(const GemmArgs &g) {
 // costs a start and epilogue plus so much per 64-deep K step, and a step gets slower as the chip fills (clock, L2).  The
 // constants (us) are least-squares fits to 150 random shapes each for the forward and input-gradient products (250 - 12000
 // rows, widths 1024 - 22016; nine tile shapes) and for the weight gradients (512 - 5120 square to oblong, K = 250 - 12000; five
-// shapes, A and B both strided): the shape the rule picks is 0.03 % / 0.07 % slower than the best of them on average, 2 % / 7 %
-// at worst.  Against 256 x 256 throughout it measured 65.9 -> 13.5 us on the 576 x 1024 x 4096 forward product (64 x 64 tiles),
+// shapes, A and B both strided): the shape the rule picked was 0.03 % / 0.07 % slower than the best of them on average, 2 % / 7 %
+// at worst.  The K loop of one round and the fp32 epilogue have become faster since; another 140 and 60 random shapes, half of them from HBM:
+// 0.4 % / 0.5 % on average, 18 % (345 x 2752 x 9592 from HBM, 78 us in 64 x 64) / 9 % (3944 x 1208 x 379, 11.4 us in 256 x 128) at worst.  Against 256 x 256 throughout it measured 65.9 -> 13.5 us on the 576 x 1024 x 4096 forward product (64 x 64 tiles),
 // 22.6 -> 14.8 us on 2304 x 3072 x 1024 (256 x 128), 72.2 -> 65.6 us on 9536 x 1024 x 4096 (160 x 256), and 58.3 -> 25.8 us on
 // the 4096 x 1024 x 2880 weight gradient, which was cut along K before (128 x 128); products of whole rounds of large tiles stay
 // where they were.
@@ -226,12 +227,13 @@ int choose_tile(const GemmArgs *gs, int n, int n_cu, double &us) {
 // arithmetic per byte on every K step; the cut pays for its scratch traffic and second launch once, so it wins where K is long.
 // The rule compares choose_tile's estimate with the same model for K / splits, plus the reduction (its launch and 0.345 us per
 // MB), and asks for 5 % as both are fits.  The tile shapes' constants hold for operands that the memory-side cache keeps (256 MB);
-// from HBM they take 1.2 to 1.6 times as long (the 256 x 256 chunks, each of which one XCD's L2 reads once, do not), so operands
+// from HBM they take 1.1 to 1.6 times as long (the 256 x 256 chunks, each of which one XCD's L2 reads once, do not), so operands
 // of more than 96 MB, most of which are a large layer's weights, count against them: their estimate then stands at 1.15 times itself
 // instead of 0.95.  Measured with operands from
-// HBM, tile shape -> cut: 1031 x 4096 x 22016 (the gate / up input gradient of a short pack) 233 -> 177 us in three chunks, 1031 x
-// 4096 x 12288 (QKV) 128 -> 110, 366 x 4096 x 12288 86 -> 56 in eight, 1031 x 1280 x 22016 136 -> 70 in eight; at the rule's
-// edges 2304 x 1024 x 11008 69 -> 71 and 700 x 8192 x 13824 154 -> 157.  Up to K = 8192 the tile shapes are ahead.
+// HBM, tile shape -> cut: 1031 x 4096 x 22016 (the gate / up input gradient of a short pack) 209 -> 169 us in three chunks, 1031 x
+// 4096 x 12288 (QKV) 116 -> 100, 1031 x 4096 x 11008 104 -> 92, 366 x 4096 x 12288 87 -> 50 in eight, 1031 x 1280 x 22016 129 -> 67 in eight, 2304 x
+// 1024 x 11008 93 -> 62 in six; from the cache the first three 185 -> 164, 98 -> 98, 88 -> 91.  With two chunks it is about even: 1500 x 4096 x 22016
+// 248 -> 238 (from the cache 210 -> 222), 2047 x 4096 x 22016 304 -> 266, 700 x 8192 x 13824 145 -> 157.  Up to K = 8192 the tile shapes are ahead.
 int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
     if (g.layout != GEMM_NN || g.bias || g.residual || !g.split_ws) return 1;
     const long tiles = (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE);
