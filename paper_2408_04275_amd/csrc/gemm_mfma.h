@@ -826,16 +826,18 @@ hipError_t launch(GemmP p, hipStream_t st) {
 
 // Tile shapes smaller than 256 x 256 (choose_tile in gemm_mfma.hip).  AHEAD is as deep as LDS allows with the number of
 // workgroups per compute unit that hides a small tile's barrier waits: a 64 x 64 step is 128 cycles of MFMA against several
-// hundred of memory latency.  The first three need a K-contiguous A.
+// hundred of memory latency.  Those of 224, 192, 160 and 96 rows need a K-contiguous A.
 typedef TileShape<7, 8, 2> Tile224;
 typedef TileShape<6, 8, 2> Tile192;
 typedef TileShape<5, 8, 2> Tile160;
 typedef TileShape<8, 4, 2> Tile256x128;
 typedef TileShape<6, 4, 3> Tile192x128;
+typedef TileShape<5, 4, 3> Tile160x128;
 typedef TileShape<4, 4, 4> Tile128;
+typedef TileShape<3, 4, 4> Tile96x128;
 typedef TileShape<2, 4, 3> Tile64x128;
 typedef TileShape<2, 2, 4> Tile64;
-enum { TILE_256, TILE_224, TILE_192, TILE_160, TILE_256x128, TILE_192x128, TILE_128, TILE_64x128, TILE_64, N_TILE_SHAPES };
+enum { TILE_256, TILE_224, TILE_192, TILE_160, TILE_256x128, TILE_192x128, TILE_160x128, TILE_128, TILE_96x128, TILE_64x128, TILE_64, N_TILE_SHAPES };
 
 // the launch of a forward or input-gradient product in tiles of shape TS
 template <bool A_KC, bool B_KC, class TS>
@@ -852,7 +854,9 @@ hipError_t launch_tile_shape(int shape, const GemmP &p, hipStream_t st) {
         case TILE_160: return launch_tile<A_KC, B_KC, Tile160>(p, st);
         case TILE_256x128: return launch_tile<A_KC, B_KC, Tile256x128>(p, st);
         case TILE_192x128: return launch_tile<A_KC, B_KC, Tile192x128>(p, st);
+        case TILE_160x128: return launch_tile<A_KC, B_KC, Tile160x128>(p, st);
         case TILE_128: return launch_tile<A_KC, B_KC, Tile128>(p, st);
+        case TILE_96x128: return launch_tile<A_KC, B_KC, Tile96x128>(p, st);
         case TILE_64x128: return launch_tile<A_KC, B_KC, Tile64x128>(p, st);
         case TILE_64: return launch_tile<A_KC, B_KC, Tile64>(p, st);
         default: return hipErrorInvalidValue;

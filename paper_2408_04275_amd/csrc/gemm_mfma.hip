@@ -170,7 +170,7 @@ bool gemm_mfma_few_tiles(const GemmArgs &g) {
 // constants (us) are least-squares fits to 150 random shapes each for the forward and input-gradient products (250 - 12000
 // rows, widths 1024 - 22016; nine tile shapes) and for the weight gradients (512 - 5120 square to oblong, K = 250 - 12000; five
 // shapes, A and B both strided): the shape the rule picked was 0.03 % / 0.07 % slower than the best of them on average, 2 % / 7 %
-// at worst.  The K loop of one round and the fp32 epilogue have become faster since; another 140 and 60 random shapes, half of them from HBM:
+// at worst (the two shapes between, 160 x 128 and 96 x 128, came later: see MIN_K_BETWEEN).  The K loop of one round and the fp32 epilogue have become faster since; another 140 and 60 random shapes, half of them from HBM:
 // 0.4 % / 0.5 % on average, 18 % (345 x 2752 x 9592 from HBM, 78 us in 64 x 64) / 9 % (3944 x 1208 x 379, 11.4 us in 256 x 128) at worst.  Against 256 x 256 throughout it measured 65.9 -> 13.5 us on the 576 x 1024 x 4096 forward product (64 x 64 tiles),
 // 22.6 -> 14.8 us on 2304 x 3072 x 1024 (256 x 128), 72.2 -> 65.6 us on 9536 x 1024 x 4096 (160 x 256), and 58.3 -> 25.8 us on
 // the 4096 x 1024 x 2880 weight gradient, which was cut along K before (128 x 128); products of whole rounds of large tiles stay
@@ -180,11 +180,18 @@ struct TileCost { int shape, bm, bn; double tile, step; };
 constexpr TileCost COST_ROWS[] = {                     // K-contiguous A
     {TILE_256, 256, 256, 4.13, 0.958}, {TILE_224, 224, 256, 2.92, 0.866}, {TILE_192, 192, 256, 2.19, 0.778},
     {TILE_160, 160, 256, 1.37, 0.694}, {TILE_256x128, 256, 128, 1.15, 0.575}, {TILE_192x128, 192, 128, 1.01, 0.462},
-    {TILE_128, 128, 128, 0.77, 0.348}, {TILE_64x128, 64, 128, 0.0, 0.223}, {TILE_64, 64, 64, 0.0, 0.142}};
+    {TILE_160x128, 160, 128, 0.89, 0.405}, {TILE_128, 128, 128, 0.77, 0.348}, {TILE_96x128, 96, 128, 0.60, 0.295}, {TILE_64x128, 64, 128, 0.0, 0.223}, {TILE_64, 64, 64, 0.0, 0.142}};
 constexpr TileCost COST_WGRAD[] = {
     {TILE_256, 256, 256, 4.05, 1.044}, {TILE_256x128, 256, 128, 2.10, 0.618}, {TILE_128, 128, 128, 1.49, 0.389},
     {TILE_64x128, 64, 128, 0.10, 0.254}, {TILE_64, 64, 64, 0.0, 0.176}};
 
+// 160 x 128 and 96 x 128 stand between the older shapes, where 128 x 128 or 192 x 128 leave a quarter to a half of the compute units idle: such
+// products are bound by what a unit copies into LDS per K step, which falls with the tile (96 x 128: 28 KiB instead of 32, 160 x 128: 36 instead of
+// 40).  From the cache / from HBM, us: 2304 x 1024 x 4096 in 128 x 128 (144 tiles) -> 96 x 128 (192) 27.9 -> 24.9 / 38.4 -> 31.8, 2880 x 1024 x 4096 NN
+// 30.7 -> 27.8 / 36.0 -> 32.8, 1031 x 4096 x 11008 in 192 x 128 (192) -> 160 x 128 (224) 90.1 -> 81.1 / 100.6 -> 94.9; of 67 random products of 40 and more K
+// steps the rule took one of them for 18, which became 2 to 15 % faster, and none slower than two runs of one build differ.  Below 40 steps the
+// time is less of the copies' (2304 x 1024 x 1024 11.6 -> 10.9) and the shapes stay what the parity tests of those sizes name.
+constexpr int MIN_K_BETWEEN = 2560;
 template <int N>
 int choose_tile(const TileCost (&table)[N], double launch, double rounds_power, double load, const GemmArgs *gs, int n, int n_cu,
                 double &best_us) {
@@ -193,6 +200,7 @@ int choose_tile(const TileCost (&table)[N], double launch, double rounds_power, 
     for (int i = 0; i < n; ++i) bytes += (size_t)(gs[i].M + gs[i].N) * gs[i].K * 2;
     const bool from_hbm = bytes > FROM_HBM_BYTES;
     for (const TileCost &t : table) {
+        if ((t.shape == TILE_160x128 || t.shape == TILE_96x128) && gs[0].K < MIN_K_BETWEEN) continue;
         long tiles = 0;
         for (int i = 0; i < n; ++i) tiles += (long)ceil_div(gs[i].M, t.bm) * ceil_div(gs[i].N, t.bn);
         const double share = (double)tiles / n_cu, fill = share < 1. ? share * share : 1.;
