@@ -316,6 +316,9 @@ constexpr int DKV_STAGE_BYTES = 4 * ROWS32_BYTES<D>;  // the rows of one operand
 // of which holds the rows of one operand at a time of 4 wavefronts
 template <int D, int WAVES>
 constexpr int DQ_LDS_BYTES = WAVES == 8 ? 2 * BT2 * D * 2 + 8 * 2 * ROWS32_BYTES<D> : 2 * 2 * BT2 * D * 2;
+// the forward kernel: two slots of a K and a V tile; with 8 wavefronts their Q rows (of 4: in the second slot) and the first 32 K rows
+template <int D, int WAVES>
+constexpr int FWD_LDS_BYTES = 2 * 2 * BT2 * D * 2 + (WAVES == 8 ? 9 * ROWS32_BYTES<D> : 0);
 // the plain dK/dV kernel: two slots of a Q tile, a dO tile and their log-sum-exps and D values, and the K and V rows of 4 wavefronts
 template <int D>
 constexpr int DKV_PLAIN_LDS = 2 * (2 * BT2 * D * 2 + 2 * BT2 * 4) + 2 * DKV_STAGE_BYTES<D>;
@@ -647,20 +650,39 @@ __device__ __forceinline__ float sum_across_halves(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 // The forward kernel's running maximum is lazy: the reference the exponentials are taken against moves only when a
-// step's maximum exceeds it by more than 2^LAZY_LOG2 (in units of the exponent), so the output accumulators are rescaled
-// a few times per query instead of at almost every step; exponentials stay below 2^LAZY_LOG2, far inside fp32 and bf16 range.
+// block's maximum exceeds it by more than 2^LAZY_LOG2 (in units of the exponent), so the output accumulators are rescaled
+// a few times per query instead of at almost every block; exponentials stay below 2^LAZY_LOG2, far inside fp32 and bf16 range.
+// From the first block to the second it moves by any amount: the exponential of the maximum is 1 and has no rounding error, and of 64
+// keys the first reference is more often the row's maximum than of 32 (l2 error of the output, 1100 causal tokens of 64 heads: 2.051e-3; lazy
+// there too 2.079e-3; the maximum over 64 keys at once 2.058e-3).
 constexpr float LAZY_LOG2 = 8.f;
+
+// LDS reads of items lo .. hi - 1 of a forward block of KS items with one read each and NI - KS with two
+template <int KS, int NI>
+constexpr int lds_ops(int lo, int hi) {
+    int n = 0;
+    for (int x = lo; x < hi && x < NI; ++x) n += x < KS ? 1 : 2;
+    return n;
+}
 
 // ------------------------------------------------------------------------------------------
 // forward.  WAVES wavefronts x 32 queries per workgroup, two wavefronts per SIMD either way (so that one can run its
 // softmax on the vector ALUs while the other occupies the matrix core): 8 wavefronts = 256 queries, one workgroup per
 // compute unit (every K / V tile is fetched once for 256 queries), or 4 wavefronts = 128 queries, two workgroups per
 // compute unit (see four_waves).  PARTS = 2: two groups of 4 wavefronts with the same 128 queries, the keys of every other step and
-// LDS slots each (see two_parts).  The keys are walked 64 at a time through
-// two LDS slots of {K tile, V tile}, both copied global -> LDS directly in their memory order (wavefronts 4..7 copy K,
-// 0..3 copy V).  O^T = V^T . P^T takes V^T from the row-major tile by the transposing LDS read, the same scheme as
-// dQ^T = K^T . dS^T above.  One barrier per step: after it every wavefront has finished the previous step, so the slot
-// that step used may be refilled.
+// LDS slots each (see two_parts).  The keys are walked 64 at a time through two LDS slots of {K tile, V tile}, both copied global -> LDS
+// directly in their memory order (wavefronts 4..7 copy K, 0..3 copy V).  O^T = V^T . P^T takes V^T from the row-major tile by the
+// transposing LDS read, the same scheme as dQ^T = K^T . dS^T above.  One barrier per step: after it every wavefront has finished the
+// previous step, so the slot that step used may be refilled.
+// LOOK_AHEAD: with eight wavefronts each works one block of 32 keys ahead: the scores of the next block are multiplied between the
+// exponentials of the current one, neither of which needs the other, and a K tile therefore stands one block further on than its V tile.
+// Taken one after the other, a block's scores, maxima, exponentials and products wait for each other and for their LDS reads, and two
+// wavefronts per SIMD overlap only part of that (an issue benchmark of the same mix: 980 cycles per block for one wavefront, 620 in turn).
+// What bounds it: LDS reads (half of its cycles) and MFMAs together, the barrier (the ramp behind it and the wavefront that comes last), and
+// power: a tenth fewer cycles come with 4 % less clock.  128 keys per step, reads 3, 5 or 6 items ahead change nothing.  us without ->
+// with it: 32 heads of 128, 8192 tokens in one long document 490 -> 446, in spans 138 -> 128.  Four wavefronts, whose workgroups walk
+// fewer steps, run the longer program from a cold instruction cache and lose as much there as they gain: alone, 2047 tokens of 64 heads on 8 48.4 ->
+// 46.5, but in a row of other kernels the same, one image of 576 patches through a layer 63.5 -> 64.4.
 // ------------------------------------------------------------------------------------------
 template <int D, int KS, int CB, int WAVES, int PARTS>
 __global__ __launch_bounds__(WAVES * PARTS * 64, 2) void attn_fwd_kernel(AttnArgs a) {
@@ -668,6 +690,7 @@ __global__ __launch_bounds__(WAVES * PARTS * 64, 2) void attn_fwd_kernel(AttnArg
     constexpr int FQW = WAVES * 32;                                // queries per workgroup
     constexpr int TILE = BT2 * D * 2, SLOT = 2 * TILE;             // K tile, then V tile
     constexpr int COPIES = BT2 * D * 2 / 1024 / 4;                 // per wavefront and tile (four wavefronts copy a tile)
+    constexpr bool LOOK_AHEAD = WAVES == 8;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_all[];
     const int head = blockIdx.x, g = head / (a.nh / a.nkv);
     // the dispatch order is kept per FQ-query tile; the workgroups of one tile (two, with four wavefronts each) follow each other
@@ -697,20 +720,21 @@ __global__ __launch_bounds__(WAVES * PARTS * 64, 2) void attn_fwd_kernel(AttnArg
     f32x16 oacc[CB];
 #pragma unroll
     for (int c = 0; c < CB; ++c) oacc[c] = zero16();
-    float m_run = -INFINITY, l_run = 0.f;
+    // the reference of the exponentials (raw score), the same in the exponent's units, the row sum
+    float m_run = -INFINITY, msc = 0.f, l_run = 0.f;
     const float sl2 = a.scale * LOG2E;
 
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(qkv), 0, (int)(uint32_t)((size_t)T * ld * 2), 0x00020000);
-    // eight wavefronts: 4..7 copy the K tile, 0..3 the V tile; four wavefronts: each copies its quarter of both
+    // eight wavefronts: 4..7 copy the K tile, 0..3 the V tile; four wavefronts: each copies its quarter of both.  With the look ahead a
+    // step's K tile stands one block of 32 keys further on than its V tile, and the first block's K rows have a place of their own
     RowCopier<D, COPIES> cp;
     cp.init((wave & 3) * COPIES, ld, dh);
     auto copy_kv = [&](uint8_t *slot, int kt) {
-        if (WAVES == 4 || wave >= 4) cp.issue(rs, slot, kt, ld, nq + g * dh);
+        if (WAVES == 4 || wave >= 4) cp.issue(rs, slot, kt + (LOOK_AHEAD ? 32 : 0), ld, nq + g * dh);
         if (WAVES == 4 || wave < 4) cp.issue(rs, slot + TILE, kt, ld, nq + nk + g * dh);
     };
-    TrReader<D> tr;
-    tr.init((uint32_t)(uintptr_t)(lds_void *)smem);
+    constexpr int K_FIRST = 2 * SLOT + WAVES * ROWS32_BYTES<D>;
 
     // The Q rows go through LDS like the dQ kernel's Q, dO and O rows (see there): behind the two slots, or, with four
     // wavefronts (whose Q rows fill a slot exactly), in the second slot, which is first written after the first barrier.
@@ -719,94 +743,237 @@ __global__ __launch_bounds__(WAVES * PARTS * 64, 2) void attn_fwd_kernel(AttnArg
         cp_q.init(0, ld, dh);
         uint8_t *st_q = smem + (WAVES == 4 ? SLOT : 2 * SLOT) + wave * ROWS32_BYTES<D>;
         cp_q.issue(rs, st_q, q0 + wave * 32, ld, head * dh);
+        if (LOOK_AHEAD && (wave == 4 || wave == 5)) cp.issue(rs, smem + K_FIRST, kbeg, ld, nq + g * dh);
         if (part == 0 || kbeg + BT2 < kend) copy_kv(smem, kbeg + part * BT2);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[ks] = frag_k<D>(st_q, l32, ks, half);
     }
-    int slot = 0;
-    for (int kt = kbeg + part * BT2; kt - part * BT2 < kend; kt += PARTS * BT2, slot ^= 1) {
-        const uint8_t *sK = smem + slot * SLOT;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this step's tiles have landed
-        lds_barrier();                                               // ... and everyone is done with the other slot
-        if (kt + PARTS * BT2 < kend) copy_kv(smem + (slot ^ 1) * SLOT, kt + PARTS * BT2);
-        bool act[2];
+    TrReader<D> tr;
+    tr.init((uint32_t)(uintptr_t)(lds_void *)smem);
+    if constexpr (LOOK_AHEAD) {
+        // LDS addresses in the first slot: K rows l32, 16-byte unit 2 ks + half; the V tile's transposing reads
+        uint32_t kadr[KS];
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) act[b] = (kt + 32 * b < w_hi_max) && (kt + 32 * b + 32 > w_lo_min);
-        if (!(act[0] || act[1])) continue;
-        f32x16 s[2];
+        for (int ks = 0; ks < KS; ++ks) kadr[ks] = lds0 + (l32 * (D / 8) + ((2 * ks + half) ^ swz_unit<D>(l32))) * 16;
+        const unsigned span = (unsigned)(me.hi - me.lo);
+        f32x16 s[2];                                       // scores of the blocks of either parity
+        uint32_t pp[8];
+        // element i of a block: its exponential, the row sum, packed in pairs.  Register i  <->  key kb + 8 (i >> 2) + 4 half + (i & 3)
+        auto element = [&](auto I_, const f32x16 &cur, float &keep) {
+            constexpr int i = decltype(I_)::value;
+            const float p = __builtin_amdgcn_exp2f(fmaf(cur[i], sl2, -msc));
+            l_run += p;
+            asm volatile("" : "+v"(l_run));               // (here, between the MFMAs: the compiler would collect the additions behind them)
+            if constexpr (i & 1) pp[i >> 1] = pack_bf16x2(keep, p);
+            else keep = p;
+        };
+        auto p_frag = [&](auto M_) {
+            constexpr int m = decltype(M_)::value;
+            const rawx4 w = {pp[4 * m], pp[4 * m + 1], pp[4 * m + 2], pp[4 * m + 3]};
+            return *reinterpret_cast<const bf16x8 *>(&w);
+        };
+        auto mask = [&](f32x16 &x, int kb) {
+            const int rel = kb + 4 * half - me.lo;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            s[b] = zero16();
-            if (act[b]) {
+            for (int i = 0; i < 16; ++i) x[i] = (unsigned)(rel + 8 * (i >> 2) + (i & 3)) < span ? x[i] : -INFINITY;
+        };
+        auto max16 = [&](const f32x16 &x) {
+            float mx = x[0];
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) s[b] = MFMA(frag_k<D>(sK, 32 * b + l32, ks, half), qf[ks], s[b]);
-            }
-        }
-        // online softmax on the raw scores (the scale is folded into the exponent);
-        // register i of block b  <->  key kt + 32 b + 8 (i >> 2) + 4 half + (i & 3)
-        float mx = -INFINITY;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            if (!act[b]) continue;
-            const int kb = kt + 32 * b;
-            if (!(kb >= w_lo_max && kb + 32 <= w_hi_min)) {            // some lane needs masking
-                const unsigned span = (unsigned)(me.hi - me.lo);
-                const int rel = kb + 4 * half - me.lo;
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    s[b][i] = (unsigned)(rel + 8 * (i >> 2) + (i & 3)) < span ? s[b][i] : -INFINITY;
-            }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[b][i]);
-        }
-        mx = max_across_halves(mx);
-        // move the reference only where the step's maximum is more than 2^LAZY_LOG2 above it (always from -inf)
-        const bool need = (mx - m_run) * sl2 > LAZY_LOG2;
-        if (__builtin_amdgcn_ballot_w64(need) != 0) {
+            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, x[i]);
+            return mx;
+        };
+        float m_limit = -INFINITY;                         // the maximum that moves the reference
+        const float lazy = LAZY_LOG2 / sl2;
+        // move the reference only where a block's maximum (of this lane's keys, or of its other half's) is more than 2^LAZY_LOG2 above it;
+        // STRICT (a wavefront's first block): the next one moves it by any amount
+        auto follow = [&](float mx, auto STRICT_) {
+            if (__builtin_amdgcn_ballot_w64(mx > m_limit) == 0) return;
+            mx = max_across_halves(mx);
+            const bool need = mx > m_limit;
             const float corr = need ? __builtin_amdgcn_exp2f((m_run - mx) * sl2) : 1.f;
             m_run = need ? mx : m_run;
+            m_limit = decltype(STRICT_)::value ? m_run : m_run + lazy;
+            msc = m_run == -INFINITY ? 0.f : m_run * sl2;
             l_run *= corr;
 #pragma unroll
             for (int c = 0; c < CB; ++c)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) oacc[c][i] *= corr;
-        }
-        const float msc = m_run == -INFINITY ? 0.f : m_run * sl2;
-        const uint32_t tv = slot * SLOT + TILE;
-        auto block = [&](auto B_) {
-            constexpr int b = decltype(B_)::value;
-            if (!act[b]) return;
-            // V^T fragments of this block: [MFMA m][feature block c], two halves each; in flight during the exponentials
-            shortx4 t0[4], t1[4], t2[4], t3[4];
-            t0[0] = tr.template read<b, 0, 0, 0>(tv); t1[0] = tr.template read<b, 0, 0, 1>(tv);
-            t2[0] = tr.template read<b, 1, 0, 0>(tv); t3[0] = tr.template read<b, 1, 0, 1>(tv);
-            t0[1] = tr.template read<b, 0, 1, 0>(tv); t1[1] = tr.template read<b, 0, 1, 1>(tv);
-            t2[1] = tr.template read<b, 1, 1, 0>(tv); t3[1] = tr.template read<b, 1, 1, 1>(tv);
-            if constexpr (CB > 2) {
-                t0[2] = tr.template read<b, 0, 2, 0>(tv); t1[2] = tr.template read<b, 0, 2, 1>(tv);
-                t2[2] = tr.template read<b, 1, 2, 0>(tv); t3[2] = tr.template read<b, 1, 2, 1>(tv);
-            }
-            if constexpr (CB > 3) {
-                t0[3] = tr.template read<b, 0, 3, 0>(tv); t1[3] = tr.template read<b, 0, 3, 1>(tv);
-                t2[3] = tr.template read<b, 1, 3, 0>(tv); t3[3] = tr.template read<b, 1, 3, 1>(tv);
-            }
-            float p[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                p[i] = __builtin_amdgcn_exp2f(fmaf(s[b][i], sl2, -msc));
-                l_run += p[i];
-            }
-            tr_wait<CB>(t0, t1, t2, t3);
-            const bf16x8 p0 = pack8(p), p1 = pack8(p + 8);
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                oacc[c] = MFMA(join(t0[c], t1[c]), p0, oacc[c]);
-                oacc[c] = MFMA(join(t2[c], t3[c]), p1, oacc[c]);
-            }
         };
-        block(std::integral_constant<int, 0>{});
-        block(std::integral_constant<int, 1>{});
+        // Block b of a step, whose scores are in s[b]: its exponentials and products with V, and the scores of the block behind it (keys
+        // nb ..), whose MFMAs have nothing to do with the exponentials and stand between them.  Items 0 .. KS - 1 are the score MFMAs, the
+        // others those with V (16 keys m, 32 features c); each needs one LDS read (K: 16 bytes, V: two transposing ones), issued AHEAD
+        // items in front of it.
+        auto block = [&](auto SLOT_, auto B_, int nb) {
+            constexpr int b = decltype(B_)::value, NI = KS + 2 * CB, AHEAD = 4, AT = decltype(SLOT_)::value * SLOT;
+            const f32x16 &cur = s[b];
+            f32x16 &nxt = s[b ^ 1];
+            bf16x8 fr[KS];
+            shortx4 v0[2 * CB], v1[2 * CB];
+            auto issue = [&](auto X_) {
+                constexpr int x = decltype(X_)::value;
+                if constexpr (x < KS) lds_read16<AT + b * 64 * D>(fr[x], kadr[x]);
+                else if constexpr (x < NI) {
+                    constexpr int m = (x - KS) / CB, c = (x - KS) % CB;
+                    v0[x - KS] = TrReader<D>::template read_at<b, m, c, 0, AT + TILE>(tr.off);
+                    v1[x - KS] = TrReader<D>::template read_at<b, m, c, 1, AT + TILE>(tr.off);
+                }
+            };
+            float keep = 0.f, mx = -INFINITY;
+            static_for<0, AHEAD>([&](auto X_) { issue(X_); });
+            __builtin_amdgcn_sched_barrier(0);
+            // two elements while the first reads are on their way, the others spread over the items in front of the second 16 keys' products
+            constexpr int E0 = 2, SPAN = KS + CB;
+            static_for<0, E0>([&](auto I_) { element(I_, cur, keep); });
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<0, NI>([&](auto X_) {
+                constexpr int x = decltype(X_)::value;
+                constexpr int behind = lds_ops<KS, NI>(x + 1, x + AHEAD);       // reads issued behind item x's
+                if constexpr (x < KS) {
+                    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[x]) : "n"(behind));
+                    if constexpr (x == 0) nxt = MFMA(fr[x], qf[x], zero16());
+                    else nxt = MFMA(fr[x], qf[x], nxt);
+                } else {
+                    constexpr int m = (x - KS) / CB, c = (x - KS) % CB;
+                    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(v0[x - KS]), "+v"(v1[x - KS]) : "n"(behind));
+                    oacc[c] = MFMA(join(v0[x - KS], v1[x - KS]), p_frag(std::integral_constant<int, m>{}), oacc[c]);
+                }
+                issue(std::integral_constant<int, x + AHEAD>{});
+                constexpr int lo = x < SPAN ? E0 + (16 - E0) * x / SPAN : 16, hi = x + 1 < SPAN ? E0 + (16 - E0) * (x + 1) / SPAN : 16;
+                static_for<lo, hi>([&](auto I_) { element(I_, cur, keep); });
+                if constexpr (x > KS) {
+                    constexpr int d0 = 16 * (x - KS - 1) / (2 * CB - 1), d1 = 16 * (x - KS) / (2 * CB - 1);
+                    static_for<d0, d1>([&](auto I_) { mx = fmaxf(mx, nxt[decltype(I_)::value]); });
+                    asm volatile("" : "+v"(mx));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if (!(nb >= w_lo_max && nb + 32 <= w_hi_min)) {
+                mask(nxt, nb);
+                mx = max16(nxt);
+            }
+            follow(mx, std::false_type{});
+        };
+        auto active = [&](int kb) { return kb < w_hi_max && kb + 32 > w_lo_min; };
+        // The first block that has keys for this wavefront, numbered from kbeg on: its scores are computed one block earlier, by
+        // themselves.  (Its blocks follow one another: both bounds of the ranges are non-decreasing.)
+        const int lead = max(w_lo_min - kbeg, 0), lead_steps = lead / BT2, lead_rest = lead % BT2;
+        const int n_first = 2 * lead_steps + (lead_rest < 32 ? 0 : lead_rest < 64 ? 1 : 2);
+        const int kb_first = kbeg + (n_first >> 1) * BT2 + (n_first & 1) * 32;
+        const int kt_head = active(kb_first) ? (n_first == 0 ? kbeg : kbeg + ((n_first - 1) >> 1) * BT2) : -1;
+        // one step, its tiles in the given slot: written out per slot, so that every LDS address is a lane's constant and an immediate offset
+        auto step = [&](auto SLOT_, int kt) {
+            constexpr int slot = decltype(SLOT_)::value;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this step's tiles have landed
+            lds_barrier();                                               // ... and everyone is done with the other slot
+            if (kt == kt_head) {
+                const uint32_t at = n_first == 0 ? K_FIRST : slot * SLOT + ((n_first - 1) & 1) * 64 * D;
+                f32x16 x = zero16();
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) x = MFMA(lds_load<bf16x8>(kadr[ks] + at), qf[ks], x);
+                if (!(kb_first >= w_lo_max && kb_first + 32 <= w_hi_min)) mask(x, kb_first);
+                if (n_first & 1) s[1] = x;
+                else s[0] = x;
+                follow(max16(x), std::true_type{});
+            }
+            if (active(kt)) block(SLOT_, std::integral_constant<int, 0>{}, kt + 32);
+            // (behind the first block: right behind the barrier all wavefronts would wait for each other at the copies)
+            if (kt + BT2 < kend) copy_kv(smem + (slot ^ 1) * SLOT, kt + BT2);
+            if (active(kt + 32)) block(SLOT_, std::integral_constant<int, 1>{}, kt + BT2);
+        };
+        for (int kt = kbeg; kt < kend; kt += 2 * BT2) {
+            step(std::integral_constant<int, 0>{}, kt);
+            if (kt + BT2 >= kend) break;
+            step(std::integral_constant<int, 1>{}, kt + BT2);
+        }
+    } else {
+        int slot = 0;
+        for (int kt = kbeg + part * BT2; kt - part * BT2 < kend; kt += PARTS * BT2, slot ^= 1) {
+            const uint8_t *sK = smem + slot * SLOT;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this step's tiles have landed
+            lds_barrier();                                               // ... and everyone is done with the other slot
+            if (kt + PARTS * BT2 < kend) copy_kv(smem + (slot ^ 1) * SLOT, kt + PARTS * BT2);
+            bool act[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) act[b] = (kt + 32 * b < w_hi_max) && (kt + 32 * b + 32 > w_lo_min);
+            if (!(act[0] || act[1])) continue;
+            f32x16 s[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                s[b] = zero16();
+                if (act[b]) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) s[b] = MFMA(frag_k<D>(sK, 32 * b + l32, ks, half), qf[ks], s[b]);
+                }
+            }
+            // online softmax on the raw scores (the scale is folded into the exponent);
+            // register i of block b  <->  key kt + 32 b + 8 (i >> 2) + 4 half + (i & 3)
+            float mx = -INFINITY;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                if (!act[b]) continue;
+                const int kb = kt + 32 * b;
+                if (!(kb >= w_lo_max && kb + 32 <= w_hi_min)) {            // some lane needs masking
+                    const unsigned span = (unsigned)(me.hi - me.lo);
+                    const int rel = kb + 4 * half - me.lo;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        s[b][i] = (unsigned)(rel + 8 * (i >> 2) + (i & 3)) < span ? s[b][i] : -INFINITY;
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[b][i]);
+            }
+            mx = max_across_halves(mx);
+            // move the reference only where the step's maximum is more than 2^LAZY_LOG2 above it (always from -inf)
+            const bool need = (mx - m_run) * sl2 > LAZY_LOG2;
+            if (__builtin_amdgcn_ballot_w64(need) != 0) {
+                const float corr = need ? __builtin_amdgcn_exp2f((m_run - mx) * sl2) : 1.f;
+                m_run = need ? mx : m_run;
+                l_run *= corr;
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) oacc[c][i] *= corr;
+            }
+            msc = m_run == -INFINITY ? 0.f : m_run * sl2;
+            const uint32_t tv = slot * SLOT + TILE;
+            auto block = [&](auto B_) {
+                constexpr int b = decltype(B_)::value;
+                if (!act[b]) return;
+                // V^T fragments of this block: [MFMA m][feature block c], two halves each; in flight during the exponentials
+                shortx4 t0[4], t1[4], t2[4], t3[4];
+                t0[0] = tr.template read<b, 0, 0, 0>(tv); t1[0] = tr.template read<b, 0, 0, 1>(tv);
+                t2[0] = tr.template read<b, 1, 0, 0>(tv); t3[0] = tr.template read<b, 1, 0, 1>(tv);
+                t0[1] = tr.template read<b, 0, 1, 0>(tv); t1[1] = tr.template read<b, 0, 1, 1>(tv);
+                t2[1] = tr.template read<b, 1, 1, 0>(tv); t3[1] = tr.template read<b, 1, 1, 1>(tv);
+                if constexpr (CB > 2) {
+                    t0[2] = tr.template read<b, 0, 2, 0>(tv); t1[2] = tr.template read<b, 0, 2, 1>(tv);
+                    t2[2] = tr.template read<b, 1, 2, 0>(tv); t3[2] = tr.template read<b, 1, 2, 1>(tv);
+                }
+                if constexpr (CB > 3) {
+                    t0[3] = tr.template read<b, 0, 3, 0>(tv); t1[3] = tr.template read<b, 0, 3, 1>(tv);
+                    t2[3] = tr.template read<b, 1, 3, 0>(tv); t3[3] = tr.template read<b, 1, 3, 1>(tv);
+                }
+                float p[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    p[i] = __builtin_amdgcn_exp2f(fmaf(s[b][i], sl2, -msc));
+                    l_run += p[i];
+                }
+                tr_wait<CB>(t0, t1, t2, t3);
+                const bf16x8 p0 = pack8(p), p1 = pack8(p + 8);
+#pragma unroll
+                for (int c = 0; c < CB; ++c) {
+                    oacc[c] = MFMA(join(t0[c], t1[c]), p0, oacc[c]);
+                    oacc[c] = MFMA(join(t2[c], t3[c]), p1, oacc[c]);
+                }
+            };
+            block(std::integral_constant<int, 0>{});
+            block(std::integral_constant<int, 1>{});
+        }
     }
 
     lds_barrier();                                     // the tiles are done with: LDS now stages the output rows
@@ -1324,7 +1491,7 @@ template <int D, int KS, int CB, int W, int PARTS>
 hipError_t launch_fwd(const AttnArgs &a, hipStream_t st) {
     static std::atomic<bool> configured{false};     // set once; concurrent first calls repeat the same idempotent set-up
     constexpr int XCHG = PARTS == 1 ? 0 : W * XCHG_BYTES<16 * CB + 2>;
-    const int smem = std::max(PARTS * 2 * 2 * BT2 * D * 2 + (W == 4 ? 0 : W * ROWS32_BYTES<D>), XCHG + W * STAGE_BYTES<D>);
+    const int smem = std::max(PARTS * FWD_LDS_BYTES<D, W>, XCHG + W * STAGE_BYTES<D>);
     if (!configured.load(std::memory_order_acquire)) {
         hipError_t e = set_smem(attn_fwd_kernel<D, KS, CB, W, PARTS>, smem);
         if (e != hipSuccess) return e;
