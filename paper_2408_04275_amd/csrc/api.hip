@@ -669,8 +669,9 @@ static int attn_common(const mmtrain_layer_desc *desc, const mmtrain_batch *batc
     if (workspace_bytes > scratch) { a.dkv_part = reinterpret_cast<float *>((uint8_t *)workspace + scratch); a.dkv_part_bytes = workspace_bytes - scratch; }
     a.cu_busy = g_attn_busy;
     attn_tile_order(batch->cu_seqlens_host, batch->seg_mask_host, batch->mask_mode, batch->n_segments, T, a);
-    HIP_TRY(prep_tokens({batch->cu_seqlens_dev, batch->seg_mask_dev, batch->mask_mode, batch->n_segments, T, tok_seg, tok_info, D.d, 0.f,
-                         nullptr}, st));
+    if (D.dtype == DT_BF16 && batch->n_segments <= ATTN_LANE_SEGMENTS) a.tok_info = nullptr;      // the kernels look into cu themselves
+    else HIP_TRY(prep_tokens({batch->cu_seqlens_dev, batch->seg_mask_dev, batch->mask_mode, batch->n_segments, T, tok_seg, tok_info, D.d, 0.f,
+                              nullptr}, st));
     return MMTRAIN_OK;
 }
 

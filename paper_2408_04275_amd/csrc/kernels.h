@@ -57,6 +57,7 @@ hipError_t gemm_mfma_group(const GemmArgs *gs, int n, hipStream_t st);
 // Segment bookkeeping produced by prep_tokens():
 //   tok_seg[t]  = index of the segment that holds token t
 //   tok_info[t] = {start of that segment, end of that segment with bit 30 set if it is bidirectional}
+constexpr int ATTN_LANE_SEGMENTS = 64;      // one per lane of a wavefront
 struct AttnArgs {
     int T, S, nh, nkv, d;
     float scale;
@@ -70,7 +71,8 @@ struct AttnArgs {
     const void *d_o;            // bwd: [T, nh*d]
     void *d_qkv;                // bwd: [T, ld_qkv]
     float *Dsum;                // bwd scratch: [nh, T]; D = rowsum(dO * O) per query and head (the matrix-core kernels keep -D there)
-    // MFMA path: tok_info[t] = {segment start, segment end | (bidirectional ? 1 << 30 : 0)}
+    // MFMA path: tok_info[t] = {segment start, segment end | (bidirectional ? 1 << 30 : 0)}; may be null for a pack of at most
+    // ATTN_LANE_SEGMENTS segments (cu and modes are read instead)
     const int2 *tok_info;
     // MFMA path, backward: when not null, the [T, d/2] (cos, sin) table of the rotary embedding; dQ and dK are
     // then rotated back in the kernels' epilogues (otherwise the caller does it afterwards)
