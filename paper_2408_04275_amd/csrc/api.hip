@@ -440,12 +440,15 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     // the matrix-core kernels rotate dQ, dK back themselves
     const bool fused_unrotate = !enc && (D.dtype == DT_BF16 ? D.d == 64 || D.d == 128 : attn_f32_supported(a));
     if (fused_unrotate) a.rope_cs = c.rope_cs;
+    const bool fused_colsum = enc && G.b_qkv && D.dtype == DT_BF16 && D.d <= COLSUM_HEAD;      // (an encoder has one query head per key/value head)
+    if (fused_colsum) a.colsum = w.part_c2;
     {
         ProfScope ps(MMTRAIN_PROF_ATTN_BWD, st);
         HIP_TRY(attn_bwd(D.dtype, a, st));
     }
     if (!enc && !fused_unrotate) HIP_TRY_TIMED(MMTRAIN_PROF_ROPE, st, rope_inplace(D.dtype, w.d_qkv, D.nqkv, T, D.nh + D.nkv, D.d, c.rope_cs, true, st));
-    if (enc && G.b_qkv) {
+    if (fused_colsum) reduce_later(w.part_c2, G.b_qkv, ceil_div(T, 32), D.nqkv);
+    else if (enc && G.b_qkv) {
         HIP_TRY(colsum_partials(D.dtype, w.d_qkv, T, D.nqkv, D.nqkv, w.part_c2, st));
         reduce_later(w.part_c2, G.b_qkv, ns, D.nqkv);
     }

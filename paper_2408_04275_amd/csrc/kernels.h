@@ -57,6 +57,7 @@ hipError_t gemm_mfma_group(const GemmArgs *gs, int n, hipStream_t st);
 // Segment bookkeeping produced by prep_tokens():
 //   tok_seg[t]  = index of the segment that holds token t
 //   tok_info[t] = {start of that segment, end of that segment with bit 30 set if it is bidirectional}
+constexpr int COLSUM_HEAD = 96;
 constexpr int ATTN_LANE_SEGMENTS = 64;      // one per lane of a wavefront
 struct AttnArgs {
     int T, S, nh, nkv, d;
@@ -79,6 +80,9 @@ struct AttnArgs {
     const float2 *rope_cs;
     // MFMA path, backward, grouped heads: scratch for fp32 partial sums of dK and dV (may be null), [parts][T][2 nkv d]
     float *dkv_part; size_t dkv_part_bytes;
+    // MFMA path, backward, heads of up to COLSUM_HEAD features, one query head per key/value head: when not null, receives the column sums of d_qkv over every 32 tokens,
+    // [ceil(T / 32)][ld_qkv] fp32 (the gradient of the bias that qkv has)
+    float *colsum;
     int dkv_parts;              // workgroups that share a group's query heads; set by attn_mfma_bwd
     // MFMA path: dispatch order of the query tiles (256 queries: forward, dQ) and of the key tiles (128
     // keys: dK/dV), heaviest first; use_order = 0 means index order (more tiles than the tables hold)
