@@ -2,6 +2,7 @@
 // carving of ctx / workspace, and the launch sequence of one layer forward / backward.
 #include "../../include/mmtrain.h"
 #include "kernels.h"
+#include "reduce.h"
 #include <cmath>
 #include <initializer_list>
 #include <mutex>
@@ -264,10 +265,17 @@ hipError_t wgrad(int dtype, const GemmArgs &g, DeferredWgrads &later, hipStream_
     }
     return gemm(dtype, g, st);
 }
-hipError_t run_deferred(int dtype, const DeferredWgrads &later, hipStream_t st) {
-    if (later.n == 0) return hipSuccess;
+// ... together with the sums of partial results of type `gdt` that the pass has collected, in the same launch where that has room for them
+hipError_t run_deferred(int dtype, const DeferredWgrads &later, int gdt, const ReduceJob *jobs, int n_jobs, bool accumulate, hipStream_t st) {
+    ReduceJobSet set;
+    const bool together = later.n > 0 && dtype == DT_BF16 && reduce_job_set(jobs, n_jobs, accumulate, set) &&
+                          gemm_mfma_group_has_room(later.g, later.n);
+    if (!together) {
+        const hipError_t e = reduce_jobs(gdt, jobs, n_jobs, accumulate, st);
+        if (e != hipSuccess || later.n == 0) return e;
+    }
     ProfScope ps(MMTRAIN_PROF_GEMM_TN, st);
-    return dtype == DT_BF16 ? gemm_mfma_group(later.g, later.n, st) : gemm_f32_group(later.g, later.n, st);
+    return dtype == DT_BF16 ? gemm_mfma_group(later.g, later.n, together ? &set : nullptr, st) : gemm_f32_group(later.g, later.n, st);
 }
 
 }  // namespace
@@ -459,8 +467,7 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
                      G.norm1_w ? w.part_g1 : nullptr, (enc && G.norm1_b) ? w.part_b1 : nullptr, nullptr, nullptr, T, D.H, st));
     reduce_later(w.part_g1, G.norm1_w, nb, D.H);
     if (enc) reduce_later(w.part_b1, G.norm1_b, nb, D.H);
-    HIP_TRY(reduce_jobs(gdt, jobs, n_jobs, accum, st));
-    HIP_TRY(run_deferred(D.dtype, later, st));
+    HIP_TRY(run_deferred(D.dtype, later, gdt, jobs, n_jobs, accum, st));
     return MMTRAIN_OK;
 }
 

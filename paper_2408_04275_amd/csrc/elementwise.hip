@@ -3,6 +3,7 @@
 // storage is fp32 or bf16.  Every kernel moves 16 bytes per lane per access and
 // touches each tensor once (rows are re-read from cache, not from HBM).
 #include "kernels.h"
+#include "reduce.h"
 #include <algorithm>
 #include <atomic>
 
@@ -622,72 +623,40 @@ hipError_t reduce_partials(int dtype, const float *part, int rows, int N, void *
     return hipGetLastError();
 }
 
-// Up to eight reductions of different shapes in one launch (blockIdx.y picks the job): everything a backward pass leaves
-// behind as partial sums -- gain and bias gradients of both normalisations, the bias gradients of the four linears --
-// is added up by one kernel at the end of the pass instead of by one launch where each array is produced.
-struct ReduceJobSet { const float *part[8]; void *out[8]; int rows[8]; int N[8]; };
+// one launch for a set of reductions (see reduce.h)
 template <typename T>
-__global__ __launch_bounds__(256) void reduce_jobs_kernel(ReduceJobSet set, bool accumulate) {
+__global__ __launch_bounds__(256) void reduce_jobs_kernel(ReduceJobSet set) {
     __shared__ float red[32][36];
-    const int N = set.N[blockIdx.y], rows = set.rows[blockIdx.y];
-    if (blockIdx.x * 32 >= N) return;                                 // the grid is as wide as the widest job
-    const float *part = set.part[blockIdx.y];
-    T *out = (T *)set.out[blockIdx.y];
-    const int cl = threadIdx.x & 7, rl = threadIdx.x >> 3;
-    const int c = blockIdx.x * 32 + cl * 4;
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
-    if (c < N) {
-        // eight rows in flight per thread: a thread's rows are 32 apart, and one load at a time leaves the kernel waiting
-        // on memory latency (8 arrays of a few megabytes took 20 us)
-        f32x4 t[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) t[u] = s;
-        int r = rl;
-        for (; r + 7 * 32 < rows; r += 256) {
-            const float *q = part + (size_t)r * N + c;
-            f32x4 v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4 *>(q + (size_t)(32 * u) * N);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] += v[u];
-        }
-        for (; r < rows; r += 32) t[0] += *reinterpret_cast<const f32x4 *>(part + (size_t)r * N + c);
-        s = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    reduce_unit<T>(set, blockIdx.x, red);
+}
+
+bool reduce_job_set(const ReduceJob *jobs, int n, bool accumulate, ReduceJobSet &set) {
+    set = {};
+    set.accumulate = accumulate ? 1 : 0;
+    int m = 0;
+    for (int i = 0; i < n && m < 8; ++i) {
+        if (!jobs[i].part || !jobs[i].out || jobs[i].N <= 0) continue;
+        if (jobs[i].N % 4) return false;
+        set.part[m] = jobs[i].part; set.out[m] = jobs[i].out; set.rows[m] = jobs[i].rows; set.N[m] = jobs[i].N;
+        set.units[m + 1] = set.units[m] + ceil_div(jobs[i].N, 32);
+        ++m;
     }
-    *reinterpret_cast<f32x4 *>(&red[rl][cl * 4]) = s;
-    __syncthreads();
-    const int oc = blockIdx.x * 32 + threadIdx.x;
-    if (threadIdx.x < 32 && oc < N) {
-        float t = 0.f;
-#pragma unroll
-        for (int i = 0; i < 32; ++i) t += red[i][threadIdx.x];
-        if (accumulate) t += Elem<T>::load(out + oc);
-        Elem<T>::store(out + oc, t);
-    }
+    for (int i = m + 1; i <= 8; ++i) set.units[i] = set.units[m];
+    return m > 0;
 }
 
 hipError_t reduce_jobs(int dtype, const ReduceJob *jobs, int n, bool accumulate, hipStream_t st) {
-    ReduceJobSet set = {};
-    int m = 0, widest = 0;
-    bool quads = true;
-    for (int i = 0; i < n && m < 8; ++i) {
-        if (!jobs[i].part || !jobs[i].out || jobs[i].N <= 0) continue;
-        set.part[m] = jobs[i].part; set.out[m] = jobs[i].out; set.rows[m] = jobs[i].rows; set.N[m] = jobs[i].N;
-        widest = jobs[i].N > widest ? jobs[i].N : widest;
-        quads = quads && jobs[i].N % 4 == 0;
-        ++m;
-    }
-    if (m == 0) return hipSuccess;
-    if (!quads) {                                  // the vector form needs whole quads: one launch each
-        for (int i = 0; i < m; ++i) {
-            hipError_t e = reduce_partials(dtype, set.part[i], set.rows[i], set.N[i], set.out[i], accumulate, st);
+    ReduceJobSet set;
+    if (!reduce_job_set(jobs, n, accumulate, set)) {               // the vector form needs whole quads: one launch each
+        for (int i = 0; i < n; ++i) {
+            if (!jobs[i].part || !jobs[i].out || jobs[i].N <= 0) continue;
+            hipError_t e = reduce_partials(dtype, jobs[i].part, jobs[i].rows, jobs[i].N, jobs[i].out, accumulate, st);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
     }
-    dim3 grid(ceil_div(widest, 32), m);
-    if (dtype == DT_F32) reduce_jobs_kernel<float><<<grid, 256, 0, st>>>(set, accumulate);
-    else reduce_jobs_kernel<bf16_t><<<grid, 256, 0, st>>>(set, accumulate);
+    if (dtype == DT_F32) reduce_jobs_kernel<float><<<set.units[8], 256, 0, st>>>(set);
+    else reduce_jobs_kernel<bf16_t><<<set.units[8], 256, 0, st>>>(set);
     return hipGetLastError();
 }
 

@@ -33,6 +33,7 @@
 // tile-rows so that concurrently resident tiles share A and B panels.
 #pragma once
 #include "kernels.h"
+#include "reduce.h"
 #include <atomic>
 #include <utility>
 #include <type_traits>
@@ -86,10 +87,15 @@ struct GemmGroup {
     GemmP p[MAX_GROUP];
     int first[MAX_GROUP + 1];
     int n;
+    // Sums that ride along: the workgroups behind the first `workgroups` add these up, on compute units that have no tile (any more)
+    int workgroups;
+    ReduceJobSet reduce;
 };
 // what the kernel needs from its argument, for one product or a group
 __device__ __forceinline__ const GemmP &first_problem(const GemmP &a) { return a; }
 __device__ __forceinline__ const GemmP &first_problem(const GemmGroup &a) { return a.p[0]; }
+__device__ __forceinline__ int gemm_workgroups(const GemmP &) { return gridDim.x; }
+__device__ __forceinline__ int gemm_workgroups(const GemmGroup &a) { return a.workgroups; }
 __device__ __forceinline__ int work_items(const GemmP &a, bool split) { return a.tile_count * (split ? a.splits : 1); }
 __device__ __forceinline__ int work_items(const GemmGroup &a, bool) { return a.first[MAX_GROUP]; }
 // work item `logical` of the launch -> its problem and its index among that problem's items
@@ -353,6 +359,17 @@ void gemm_mfma_kernel(const ARG arg) {
     const unsigned long long *const probe_ = first_problem(arg).clock_probe;
     unsigned long long *const clock_probe = const_cast<unsigned long long *>(probe_);
 
+    if constexpr (std::is_same<ARG, GemmGroup>::value) {
+        const int workgroups = arg.workgroups;
+        if ((int)blockIdx.x >= workgroups) {
+            typedef typename std::conditional<OUT_F32, float, bf16_t>::type T;
+            for (int unit = blockIdx.x - workgroups; unit < arg.reduce.units[8]; unit += gridDim.x - workgroups) {
+                reduce_unit<T>(arg.reduce, unit, reinterpret_cast<float (*)[36]>(smem));
+                __syncthreads();
+            }
+            return;
+        }
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     if (clock_probe && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -367,7 +384,7 @@ void gemm_mfma_kernel(const ARG arg) {
     const int per = ntiles >> 3, rem = ntiles & 7;
     const int run_begin = xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per;
     const int run_end = run_begin + per + (xcd < rem ? 1 : 0);
-    const int wg_per_xcd = (gridDim.x - xcd + 7) >> 3;
+    const int wg_per_xcd = (gemm_workgroups(arg) - xcd + 7) >> 3;
 
     // fragment addressing (v_mfma_f32_16x16x32_bf16: lane l holds row l & 15, k = 8 (l >> 4) .. + 7 of a
     // 16-row, 32-deep fragment).  K-contiguous tile: row block i, slice s -> row 16 i + (l & 15), unit
@@ -866,7 +883,8 @@ hipError_t launch_tile_shape(int shape, const GemmP &p, hipStream_t st) {
 hipError_t launch_nt(int shape, const GemmP &p, hipStream_t st);
 hipError_t launch_nn(int shape, const GemmP &p, hipStream_t st);
 // gemm_mfma_tn.hip: up to MAX_GROUP weight gradients in one launch, all in the same tile shape (a single one: n = 1)
-hipError_t launch_tn(int shape, const GemmP *p, int n, hipStream_t st);
+// reduce: when not null, sums to be added up by the same launch
+hipError_t launch_tn(int shape, const GemmP *p, int n, const ReduceJobSet *reduce, hipStream_t st);
 
 }  // namespace gemm_detail
 }  // namespace mmt

@@ -5,6 +5,9 @@ namespace mmt {
 namespace gemm_detail {
 namespace {
 
+// workgroups that add up sums riding along (64 units of 32 columns at a time: 8 arrays of an encoder layer take 416 of them, 2 to 3 us each)
+constexpr int REDUCE_WORKGROUPS = 64;
+
 template <bool HAS_ADD, bool OUT_F32, class TS>
 hipError_t launch_group(GemmGroup &g, hipStream_t st) {
     static std::atomic<bool> configured{false};
@@ -17,14 +20,18 @@ hipError_t launch_group(GemmGroup &g, hipStream_t st) {
     const int items = g.first[MAX_GROUP], room = n_cu * TS::PER_CU;
     if (items <= 0) return hipSuccess;
     const int workgroups = items < room ? items : room;
+    g.workgroups = workgroups;
+    const int sums = g.reduce.units[8] < REDUCE_WORKGROUPS ? g.reduce.units[8] : REDUCE_WORKGROUPS;
+    static_assert(TS::SMEM >= REDUCE_LDS, "room for a reduction");
     g.p[0].late_start = OUT_F32 ? late_start<TS>(g.p[0].accumulate, g.p[0].K, items, workgroups) : 0;
-    kern<<<workgroups, 256, TS::SMEM, st>>>(g);
+    kern<<<workgroups + sums, 256, TS::SMEM, st>>>(g);
     return hipGetLastError();
 }
 
 template <class TS>
-hipError_t launch_shape(const GemmP *p, int n, hipStream_t st) {
+hipError_t launch_shape(const GemmP *p, int n, const ReduceJobSet *reduce, hipStream_t st) {
     GemmGroup g = {};
+    if (reduce) g.reduce = *reduce;
     int total = 0;
     for (int i = 0; i < MAX_GROUP; ++i) {
         g.first[i] = total;
@@ -41,13 +48,13 @@ hipError_t launch_shape(const GemmP *p, int n, hipStream_t st) {
 
 }  // namespace
 
-hipError_t launch_tn(int shape, const GemmP *p, int n, hipStream_t st) {
+hipError_t launch_tn(int shape, const GemmP *p, int n, const ReduceJobSet *reduce, hipStream_t st) {
     switch (shape) {
-        case TILE_256: return launch_shape<Tile256>(p, n, st);
-        case TILE_256x128: return launch_shape<Tile256x128>(p, n, st);
-        case TILE_128: return launch_shape<Tile128>(p, n, st);
-        case TILE_64x128: return launch_shape<Tile64x128>(p, n, st);
-        case TILE_64: return launch_shape<Tile64>(p, n, st);
+        case TILE_256: return launch_shape<Tile256>(p, n, reduce, st);
+        case TILE_256x128: return launch_shape<Tile256x128>(p, n, reduce, st);
+        case TILE_128: return launch_shape<Tile128>(p, n, reduce, st);
+        case TILE_64x128: return launch_shape<Tile64x128>(p, n, reduce, st);
+        case TILE_64: return launch_shape<Tile64>(p, n, reduce, st);
         default: return hipErrorInvalidValue;
     }
 }

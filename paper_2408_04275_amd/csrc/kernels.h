@@ -52,7 +52,10 @@ size_t gemm_mfma_tn_scratch(long M, long N, long K);
 // Weight gradients with few output tiles (gemm_mfma_few_tiles: transposed-A layout, no bias / residual, at most 128 tiles of
 // 256 x 256) computed together in one launch; up to 4, all with the same K and accumulate / c_f32.
 bool gemm_mfma_few_tiles(const GemmArgs &g);
-hipError_t gemm_mfma_group(const GemmArgs *gs, int n, hipStream_t st);
+// reduce: when not null, sums (reduce.h) that the same launch adds up, to outputs of the gradients' type; worth it where the launch has room.
+struct ReduceJobSet;
+bool gemm_mfma_group_has_room(const GemmArgs *gs, int n);
+hipError_t gemm_mfma_group(const GemmArgs *gs, int n, const ReduceJobSet *reduce, hipStream_t st);
 
 // Segment bookkeeping produced by prep_tokens():
 //   tok_seg[t]  = index of the segment that holds token t
