@@ -268,14 +268,14 @@ hipError_t wgrad(int dtype, const GemmArgs &g, DeferredWgrads &later, hipStream_
 // ... together with the sums of partial results of type `gdt` that the pass has collected, in the same launch where that has room for them
 hipError_t run_deferred(int dtype, const DeferredWgrads &later, int gdt, const ReduceJob *jobs, int n_jobs, bool accumulate, hipStream_t st) {
     ReduceJobSet set;
-    const bool together = later.n > 0 && dtype == DT_BF16 && reduce_job_set(jobs, n_jobs, accumulate, set) &&
-                          gemm_mfma_group_has_room(later.g, later.n);
+    const bool together = later.n > 0 && reduce_job_set(jobs, n_jobs, accumulate, set) &&
+                          (dtype == DT_F32 || gemm_mfma_group_has_room(later.g, later.n));
     if (!together) {
         const hipError_t e = reduce_jobs(gdt, jobs, n_jobs, accumulate, st);
         if (e != hipSuccess || later.n == 0) return e;
     }
     ProfScope ps(MMTRAIN_PROF_GEMM_TN, st);
-    return dtype == DT_BF16 ? gemm_mfma_group(later.g, later.n, together ? &set : nullptr, st) : gemm_f32_group(later.g, later.n, st);
+    return dtype == DT_BF16 ? gemm_mfma_group(later.g, later.n, together ? &set : nullptr, st) : gemm_f32_group(later.g, later.n, together ? &set : nullptr, st);
 }
 
 }  // namespace
@@ -342,8 +342,11 @@ static int layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch,
                             D.d, D.rope_base, c.rope_cs};
     // attention block
     HIP_TRY_TIMED(MMTRAIN_PROF_NORM_FWD, st, norm_fwd(D.dtype, enc, x, W->norm1_w, W->norm1_b, c.h1, c.mean1, c.rstd1, T, D.H, D.eps, &prep, st));
-    HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.nqkv, D.H, c.h1, D.H, W->w_qkv, D.H, c.qkv, D.nqkv, W->b_qkv), st));
-    if (!enc) HIP_TRY_TIMED(MMTRAIN_PROF_ROPE, st, rope_inplace(D.dtype, c.qkv, D.nqkv, T, D.nh + D.nkv, D.d, c.rope_cs, false, st));
+    const GemmArgs qkv = mk(GEMM_NT, T, D.nqkv, D.H, c.h1, D.H, W->w_qkv, D.H, c.qkv, D.nqkv, W->b_qkv);
+    const bool rotates = !enc && D.dtype == DT_F32 && gemm_f32_rope_supported(qkv, D.d);
+    if (rotates) HIP_TRY_TIMED(MMTRAIN_PROF_GEMM_NT, st, gemm_f32_rope(qkv, D.d, D.nh + D.nkv, c.rope_cs, st));
+    else HIP_TRY(gemm(D.dtype, qkv, st));
+    if (!enc && !rotates) HIP_TRY_TIMED(MMTRAIN_PROF_ROPE, st, rope_inplace(D.dtype, c.qkv, D.nqkv, T, D.nh + D.nkv, D.d, c.rope_cs, false, st));
     AttnArgs a = mk_attn(D, batch, c);
     {
         ProfScope ps(MMTRAIN_PROF_ATTN_FWD, st);
@@ -352,9 +355,12 @@ static int layer_fwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch,
     HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.H, D.nq, c.o, D.nq, W->w_o, D.nq, c.y1, D.H, W->b_o, x), st));
     // MLP block
     HIP_TRY_TIMED(MMTRAIN_PROF_NORM_FWD, st, norm_fwd(D.dtype, enc, c.y1, W->norm2_w, W->norm2_b, c.h2, c.mean2, c.rstd2, T, D.H, D.eps, nullptr, st));
-    HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.F1, D.H, c.h2, D.H, W->w_fc1, D.H, c.pre, D.F1, W->b_fc1), st));
+    const GemmArgs fc1 = mk(GEMM_NT, T, D.F1, D.H, c.h2, D.H, W->w_fc1, D.H, c.pre, D.F1, W->b_fc1);
+    const bool activates = !enc && D.dtype == DT_F32 && gemm_f32_swiglu_supported(fc1);
+    if (activates) HIP_TRY_TIMED(MMTRAIN_PROF_GEMM_NT, st, gemm_f32_swiglu(fc1, c.m, st));
+    else HIP_TRY(gemm(D.dtype, fc1, st));
     if (enc) HIP_TRY_TIMED(MMTRAIN_PROF_ACT_FWD, st, gelu_fwd(D.dtype, c.pre, c.m, (long)T * D.F, st));
-    else HIP_TRY_TIMED(MMTRAIN_PROF_ACT_FWD, st, swiglu_fwd(D.dtype, c.pre, c.m, T, D.F, st));
+    else if (!activates) HIP_TRY_TIMED(MMTRAIN_PROF_ACT_FWD, st, swiglu_fwd(D.dtype, c.pre, c.m, T, D.F, st));
     if (output) HIP_TRY(gemm(D.dtype, mk(GEMM_NT, T, D.H, D.F, c.m, D.F, W->w_fc2, D.F, y, D.H, W->b_fc2, c.y1), st));
     return MMTRAIN_OK;
 }
@@ -406,7 +412,10 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
     const int nb = norm_bwd_blocks(T, D.H), ns = colsum_slabs(T);
 
     // ---- MLP block:  y = y1 + m . Wfc2^T (+ b_fc2)
-    HIP_TRY(gemm(D.dtype, splittable(mk(GEMM_NN, T, D.F, D.H, dy, D.H, W->w_fc2, D.F, w.d_m, D.F), w.split_ws, w.split_bytes), st));
+    const GemmArgs to_pre = mk(GEMM_NN, T, D.F, D.H, dy, D.H, W->w_fc2, D.F, w.d_pre, D.F1);
+    const bool activates = !enc && D.dtype == DT_F32 && gemm_f32_swiglu_bwd_supported(to_pre);
+    if (activates) HIP_TRY_TIMED(MMTRAIN_PROF_GEMM_NN, st, gemm_f32_swiglu_bwd(to_pre, c.pre, st));
+    else HIP_TRY(gemm(D.dtype, splittable(mk(GEMM_NN, T, D.F, D.H, dy, D.H, W->w_fc2, D.F, w.d_m, D.F), w.split_ws, w.split_bytes), st));
     DeferredWgrads later;
     const size_t act_bytes = (size_t)T * D.H * (D.dtype == DT_F32 ? 4 : 2);
     const bool dy_lives = (uintptr_t)dx + act_bytes <= (uintptr_t)dy || (uintptr_t)dy + act_bytes <= (uintptr_t)dx;
@@ -425,7 +434,7 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
         HIP_TRY_TIMED(MMTRAIN_PROF_ACT_BWD, st, gelu_bwd_colsum(D.dtype, w.d_m, c.pre, w.d_pre, T, D.F1, w.part_c, st));
         reduce_later(w.part_c, G.b_fc1, ns, D.F1);
     } else if (enc) HIP_TRY_TIMED(MMTRAIN_PROF_ACT_BWD, st, gelu_bwd(D.dtype, w.d_m, c.pre, w.d_pre, (long)T * D.F, st));
-    else HIP_TRY_TIMED(MMTRAIN_PROF_ACT_BWD, st, swiglu_bwd(D.dtype, w.d_m, c.pre, w.d_pre, T, D.F, st));
+    else if (!activates) HIP_TRY_TIMED(MMTRAIN_PROF_ACT_BWD, st, swiglu_bwd(D.dtype, w.d_m, c.pre, w.d_pre, T, D.F, st));
     HIP_TRY(gemm(D.dtype, splittable(mk(GEMM_NN, T, D.H, D.F1, w.d_pre, D.F1, W->w_fc1, D.H, w.d_h, D.H), w.split_ws, w.split_bytes), st));
     if (G.w_fc1) HIP_TRY(wgrad(D.dtype, splittable(f32out(mk(GEMM_TN, D.F1, D.H, T, w.d_pre, D.F1, c.h2, D.H, G.w_fc1, D.H, nullptr, nullptr, accum), g32), w.split_ws, w.split_bytes), later, st));
     // d_y1 = dy + norm2_bwd(d_h2); the same kernel sums the columns of dy (b_fc2's gradient) and of d_y1 (b_o's)

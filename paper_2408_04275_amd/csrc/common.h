@@ -48,6 +48,18 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// 1 / (1 + exp(-x)) with the hardware exponential and reciprocal (each within an fp32 rounding or two; the library's
+// expf and the IEEE division take some twenty instructions more per element)
+__device__ __forceinline__ float sigmoid_fast(float x) {
+    return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(x * -1.4426950408889634f));
+}
+// Gradient of silu(gate) up:  d_gate = d * up * s * (1 + gate * (1 - s)),  d_up = d * gate * s,  s = sigmoid(gate).  The library forms on
+// purpose: with sigmoid_fast the kernel over bf16 rows runs 6 % slower (141 -> 150 us).
+__device__ __forceinline__ float2 swiglu_gradient(float d, float gate, float up) {
+    const float s = 1.f / (1.f + expf(-gate));
+    return {d * up * s * (1.f + gate * (1.f - s)), d * gate * s};
+}
+
 // Sum over a workgroup of NW waves; `red` is NW floats of LDS.  Result on every thread.
 template <int NW>
 __device__ __forceinline__ float block_sum(float v, float *red) {

@@ -627,7 +627,7 @@ hipError_t reduce_partials(int dtype, const float *part, int rows, int N, void *
 template <typename T>
 __global__ __launch_bounds__(256) void reduce_jobs_kernel(ReduceJobSet set) {
     __shared__ float red[32][36];
-    reduce_unit<T>(set, blockIdx.x, red);
+    reduce_unit<T>(set, blockIdx.x, red, threadIdx.x);
 }
 
 bool reduce_job_set(const ReduceJob *jobs, int n, bool accumulate, ReduceJobSet &set) {
@@ -741,11 +741,6 @@ hipError_t rope_inplace(int dtype, void *qkv, int ld, int T, int n_rot_heads, in
 
 // ---- SwiGLU --------------------------------------------------------------------------
 // gu[T, 2F] = [gate | up];  m = gate * sigmoid(gate) * up.
-// 1 / (1 + exp(-x)) with the hardware exponential and reciprocal (each within an fp32 rounding or two; the library's
-// expf and the IEEE division take some twenty instructions more per element)
-__device__ __forceinline__ float sigmoid_fast(float x) {
-    return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(x * -1.4426950408889634f));
-}
 template <typename T>
 __global__ __launch_bounds__(256) void swiglu_fwd_kernel(const T *__restrict__ gu, T *__restrict__ m, long nchunks, int F) {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
@@ -761,7 +756,6 @@ __global__ __launch_bounds__(256) void swiglu_fwd_kernel(const T *__restrict__ g
     store8_stream(m + t * F + c, g);
 }
 
-// d_gate = d_m * up * s * (1 + gate * (1 - s)),  d_up = d_m * gate * s,  s = sigmoid(gate).
 template <typename T>
 __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const T *__restrict__ d_m, const T *__restrict__ gu,
                                                          T *__restrict__ d_gu, long nchunks, int F) {
@@ -776,10 +770,9 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const T *__restrict__ d
     load8_stream(d_m + t * F + c, dm);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const float s = 1.f / (1.f + expf(-g[j]));      // the library forms on purpose: with sigmoid_fast this kernel runs 6 % slower (141 -> 150 us)
-        const float dg = dm[j] * u[j] * s * (1.f + g[j] * (1.f - s));
-        u[j] = dm[j] * g[j] * s;
-        g[j] = dg;
+        const float2 d = swiglu_gradient(dm[j], g[j], u[j]);
+        g[j] = d.x;
+        u[j] = d.y;
     }
     store8_stream(d_gu + t * 2 * F + c, g);
     store8_stream(d_gu + t * 2 * F + F + c, u);

@@ -15,6 +15,7 @@
 //     (fragments) x (l & 15) + f, which only the epilogue has to know.
 // Rows and k outside the matrix read as zero (the buffer descriptor's bounds check).
 #include "kernels.h"
+#include "reduce.h"
 
 namespace mmt {
 
@@ -27,7 +28,19 @@ struct GemmF32 {
     float *C; int ldc;
     const float *bias, *residual;
     int accumulate;
+    // what an epilogue other than PLAIN needs
+    float *extra;              // SWIGLU: [M, pair], silu(gate) up
+    const float *gu;           // SWIGLU_BWD: [M, 2 N], gate and up side by side
+    const float2 *cs;          // ROPE: [M, pair], cosine and sine
+    int pair;                  // SWIGLU, ROPE: distance of the two columns that belong together
+    int rotated;               // ROPE: heads that are rotated; those behind them are stored as they are
 };
+// Elementwise work on a product that its epilogue does, instead of a launch behind it (2.5 to 4 us each; with the sums that ride along below, a decoder
+// layer of 256 features and 512 tokens, forward and backward: 125.3 -> 116.0 us):
+//   SWIGLU      C = [gate | up], and silu(gate) up next to it.  A tile takes half of its columns from the gate and the same ones from up.
+//   ROPE        the rotary embedding of heads of 2 pair features; a tile's columns are `half a tile` of a head's first half and their partners.
+//   SWIGLU_BWD  the product is the gradient of silu(gate) up and is not stored: C = [d_gate | d_up], 2 N wide.
+enum { PLAIN, SWIGLU, ROPE, SWIGLU_BWD };
 
 constexpr uint32_t OOB = 0xfffffff0u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, size_t bytes) {
@@ -40,7 +53,8 @@ struct Operand {
     __amdgpu_buffer_rsrc_t rs;
     uint32_t off[KC ? TB : 4], step;
     int kq, K;
-    __device__ __forceinline__ void init(const float *X, int ld, int row0, int nrows, int K_) {
+    // fragments TB / 2 .. of a K-contiguous operand: rows from row0 + second on
+    __device__ __forceinline__ void init(const float *X, int ld, int row0, int nrows, int K_, int second = 8 * TB) {
         const int r = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
         K = K_;
         kq = 4 * q;
@@ -48,7 +62,7 @@ struct Operand {
             rs = rsrc(X, ((size_t)(nrows - 1) * ld + K_) * 4);
             step = 64;
 #pragma unroll
-            for (int f = 0; f < TB; ++f) off[f] = (uint32_t)(((size_t)(row0 + 16 * f + r) * ld + kq) * 4);
+            for (int f = 0; f < TB; ++f) off[f] = (uint32_t)(((size_t)(row0 + (f < TB / 2 ? 0 : second) + 16 * (f % (TB / 2)) + r) * ld + kq) * 4);
         } else {
             rs = rsrc(X, ((size_t)(K_ - 1) * ld + nrows) * 4);
             step = (uint32_t)ld * 64u;
@@ -85,15 +99,18 @@ struct Operand {
 };
 
 // AHEAD: K blocks of a wavefront in flight while one is multiplied
-template <int TB, int NW, int AHEAD, bool A_KC, bool B_KC>
+template <int TB, int NW, int AHEAD, bool A_KC, bool B_KC, int EPI = PLAIN>
 __device__ __forceinline__ void gemm_f32_tile(const GemmF32 &p, int n0, int m0) {
     constexpr int TILE = 16 * TB, PITCH = TILE + 4;
+    constexpr bool PAIRED = EPI == SWIGLU || EPI == ROPE;
+    constexpr int WIDTH = PAIRED ? TILE / 2 : TILE;             // columns that the epilogue walks over
+    static_assert(!PAIRED || B_KC, "pairs are rows of a K-contiguous B");
     __shared__ __attribute__((aligned(16))) float red[NW / 2][TILE][PITCH];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, q = lane >> 4;
     Operand<TB, A_KC> la;
     Operand<TB, B_KC> lb;
     la.init(p.A, p.lda, m0, p.M, p.K);
-    lb.init(p.B, p.ldb, n0, p.N, p.K);
+    lb.init(p.B, p.ldb, n0, p.N, p.K, PAIRED ? p.pair : 8 * TB);
 
     f32x4 acc[TB][TB];
 #pragma unroll
@@ -119,6 +136,21 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32 &p, int n0, int m0) 
                         acc[fa][fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[s][fb][j], a[s][fa][j], acc[fa][fb], 0, 0, 0);
             la.load(kb + NW * (s + AHEAD), a[s]);
             lb.load(kb + NW * (s + AHEAD), b[s]);
+        }
+    }
+
+    // what the epilogue reads besides the product, requested in front of the sum over the wavefronts
+    constexpr int ITEMS = (TILE * WIDTH + 256 * NW - 1) / (256 * NW);
+    f32x4 in[EPI == SWIGLU_BWD || EPI == ROPE ? ITEMS : 1][2];
+    if constexpr (EPI == SWIGLU_BWD || EPI == ROPE) {
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const int c = threadIdx.x + 64 * NW * i, row = c / (WIDTH / 4), m = m0 + row, n = n0 + c % (WIDTH / 4) * 4;
+            in[i][0] = in[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (row >= TILE || m >= p.M || n >= p.N) continue;
+            const float *at = EPI == ROPE ? reinterpret_cast<const float *>(p.cs + (size_t)m * p.pair + n % (2 * p.pair)) : p.gu + (size_t)m * 2 * p.N + n;
+            in[i][0] = *reinterpret_cast<const f32x4 *>(at);
+            in[i][1] = *reinterpret_cast<const f32x4 *>(at + (EPI == ROPE ? 4 : p.N));
         }
     }
 
@@ -157,31 +189,75 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32 &p, int n0, int m0) 
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < (TILE * TILE + 256 * NW - 1) / (256 * NW); ++i) {
-        const int c = threadIdx.x + 64 * NW * i, row = c / (TILE / 4), col = c % (TILE / 4) * 4;
+    for (int i = 0; i < ITEMS; ++i) {
+        const int c = threadIdx.x + 64 * NW * i, row = c / (WIDTH / 4), col = c % (WIDTH / 4) * 4;
         const int m = m0 + row, n = n0 + col;
-        if (row >= TILE || m >= p.M || n >= p.N) continue;        // N is a multiple of 4
-        f32x4 v = *reinterpret_cast<const f32x4 *>(&red[0][row][col]) + *reinterpret_cast<const f32x4 *>(&red[1][row][col]);
+        if (row >= TILE || m >= p.M || n >= (EPI == SWIGLU ? p.pair : p.N)) continue;        // N is a multiple of 4
+        auto sum = [&](int at) { return *reinterpret_cast<const f32x4 *>(&red[0][row][at]) + *reinterpret_cast<const f32x4 *>(&red[1][row][at]); };
+        f32x4 v = sum(col);
         const size_t o = (size_t)m * p.ldc + n;
-        if (p.bias) v += *reinterpret_cast<const f32x4 *>(p.bias + n);
-        if (p.residual) v += *reinterpret_cast<const f32x4 *>(p.residual + o);
-        if (p.accumulate) v += *reinterpret_cast<const f32x4 *>(p.C + o);
-        *reinterpret_cast<f32x4 *>(p.C + o) = v;
+        if constexpr (EPI == PLAIN) {
+            if (p.bias) v += *reinterpret_cast<const f32x4 *>(p.bias + n);
+            if (p.residual) v += *reinterpret_cast<const f32x4 *>(p.residual + o);
+            if (p.accumulate) v += *reinterpret_cast<const f32x4 *>(p.C + o);
+            *reinterpret_cast<f32x4 *>(p.C + o) = v;
+        } else if constexpr (EPI == SWIGLU_BWD) {
+            f32x4 dg, du;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float2 d = swiglu_gradient(v[e], in[i][0][e], in[i][1][e]);
+                dg[e] = d.x;
+                du[e] = d.y;
+            }
+            *reinterpret_cast<f32x4 *>(p.C + o) = dg;
+            *reinterpret_cast<f32x4 *>(p.C + o + p.N) = du;
+        } else {
+            f32x4 w = sum(col + TILE / 2);
+            if constexpr (EPI == SWIGLU) {
+                f32x4 x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = v[e] * sigmoid_fast(v[e]) * w[e];
+                *reinterpret_cast<f32x4 *>(p.extra + (size_t)m * p.pair + n) = x;
+            } else if (n0 < p.rotated * 2 * p.pair) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float co = in[i][e >> 1][2 * (e & 1)], si = in[i][e >> 1][2 * (e & 1) + 1], lo = v[e], hi = w[e];
+                    v[e] = lo * co - hi * si;
+                    w[e] = hi * co + lo * si;
+                }
+            }
+            *reinterpret_cast<f32x4 *>(p.C + o) = v;
+            *reinterpret_cast<f32x4 *>(p.C + o + p.pair) = w;
+        }
     }
 }
 
-template <int TB, int NW, int AHEAD, bool A_KC, bool B_KC>
+template <int TB, int NW, int AHEAD, bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmF32 p) {
-    gemm_f32_tile<TB, NW, AHEAD, A_KC, B_KC>(p, blockIdx.x * 16 * TB, blockIdx.y * 16 * TB);
+    int n0 = blockIdx.x * 16 * TB;
+    if constexpr (EPI == SWIGLU) n0 /= 2;
+    if constexpr (EPI == ROPE) {                       // pair / (half a tile) tiles per head
+        const int per_head = p.pair / (8 * TB), head = blockIdx.x / per_head;
+        n0 = head * 2 * p.pair + (blockIdx.x - head * per_head) * 8 * TB;
+    }
+    gemm_f32_tile<TB, NW, AHEAD, A_KC, B_KC, EPI>(p, n0, blockIdx.y * 16 * TB);
 }
 
-// Several weight gradients in one launch: problem i has the workgroups [first[i], first[i + 1]), row by row of tiles.
+// Several weight gradients in one launch: problem i has the workgroups [first[i], first[i + 1]), row by row of tiles.  Those behind the last one's
+// add up sums that ride along, two units each: in a launch of their own these took 3.9 us at the end of a pass.
 constexpr int MAX_GROUP = 4;
 struct GroupF32 {
     GemmF32 p[MAX_GROUP];
     int first[MAX_GROUP + 1];
+    ReduceJobSet reduce;
 };
 __global__ __launch_bounds__(512) void gemm_f32_group_kernel(GroupF32 g) {
+    if ((int)blockIdx.x >= g.first[MAX_GROUP]) {
+        __shared__ float sums[2][32][36];
+        const int half = threadIdx.x >> 8;             // (a unit behind the last one has no columns)
+        reduce_unit<float>(g.reduce, 2 * (blockIdx.x - g.first[MAX_GROUP]) + half, sums[half], threadIdx.x & 255);
+        return;
+    }
     int i = 0;
 #pragma unroll
     for (int j = 1; j < MAX_GROUP; ++j) i += (int)blockIdx.x >= g.first[j] ? 1 : 0;
@@ -193,14 +269,14 @@ __global__ __launch_bounds__(512) void gemm_f32_group_kernel(GroupF32 g) {
 
 bool few_tiles(int M, int N) { return (long)ceil_div(M, 64) * ceil_div(N, 64) < 384; }
 
-template <bool A_KC, bool B_KC>
+template <bool A_KC, bool B_KC, int EPI = PLAIN>
 hipError_t launch(const GemmF32 &p, hipStream_t st) {
     // 64 x 64 tiles read half the operand bytes; they pay once there are enough of them (2048^3: 233 -> 150 us; 1024 x 2560 x
     // 512, 640 tiles: 43.5 -> 37.9; at 264 tiles both take 20 us; 512 x 256 x 688, 32 tiles: 7.0 -> 19.2)
     if (!few_tiles(p.M, p.N))
-        gemm_f32_kernel<4, 4, 2, A_KC, B_KC><<<dim3(ceil_div(p.N, 64), ceil_div(p.M, 64)), 256, 0, st>>>(p);
+        gemm_f32_kernel<4, 4, 2, A_KC, B_KC, EPI><<<dim3(ceil_div(p.N, 64), ceil_div(p.M, 64)), 256, 0, st>>>(p);
     else
-        gemm_f32_kernel<2, 8, 2, A_KC, B_KC><<<dim3(ceil_div(p.N, 32), ceil_div(p.M, 32)), 512, 0, st>>>(p);
+        gemm_f32_kernel<2, 8, 2, A_KC, B_KC, EPI><<<dim3(ceil_div(p.N, 32), ceil_div(p.M, 32)), 512, 0, st>>>(p);
     return hipGetLastError();
 }
 
@@ -226,13 +302,13 @@ bool gemm_f32_supported(const GemmArgs &g) {
 
 static GemmF32 params(const GemmArgs &g) {
     return {g.M, g.N, g.K, (const float *)g.A, g.lda, (const float *)g.B, g.ldb, (float *)g.C, g.ldc,
-            (const float *)g.bias, (const float *)g.residual, g.accumulate ? 1 : 0};
+            (const float *)g.bias, (const float *)g.residual, g.accumulate ? 1 : 0, nullptr, nullptr, nullptr, 0, 0};
 }
 
 bool gemm_f32_few_tiles(const GemmArgs &g) { return g.layout == GEMM_TN && gemm_f32_supported(g) && few_tiles(g.M, g.N); }
 
 // The weight gradients of a small layer together: 64 to 344 tiles each on the 512-token layer, 7.1 + 9.6 + 7.0 + 7.1 us one by one.
-hipError_t gemm_f32_group(const GemmArgs *gs, int n, hipStream_t st) {
+hipError_t gemm_f32_group(const GemmArgs *gs, int n, const ReduceJobSet *reduce, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     if (n > MAX_GROUP) return hipErrorInvalidValue;
     GroupF32 grp = {};
@@ -245,8 +321,33 @@ hipError_t gemm_f32_group(const GemmArgs *gs, int n, hipStream_t st) {
         total += ceil_div(gs[i].M, 32) * ceil_div(gs[i].N, 32);
     }
     grp.first[MAX_GROUP] = total;
-    gemm_f32_group_kernel<<<total, 512, 0, st>>>(grp);
+    if (reduce) grp.reduce = *reduce;
+    gemm_f32_group_kernel<<<total + ceil_div(grp.reduce.units[8], 2), 512, 0, st>>>(grp);
     return hipGetLastError();
+}
+
+static bool product_alone(const GemmArgs &g) { return !g.bias && !g.residual && !g.accumulate && gemm_f32_supported(g); }
+
+bool gemm_f32_swiglu_supported(const GemmArgs &g) { return g.layout == GEMM_NT && g.N % 8 == 0 && g.ldc == g.N && product_alone(g); }
+hipError_t gemm_f32_swiglu(const GemmArgs &g, void *m, hipStream_t st) {
+    GemmF32 p = params(g);
+    p.extra = (float *)m; p.pair = g.N / 2;
+    return launch<true, true, SWIGLU>(p, st);
+}
+
+// (heads of whole tiles, whichever size of tile is taken)
+bool gemm_f32_rope_supported(const GemmArgs &g, int d) { return g.layout == GEMM_NT && d % 64 == 0 && g.N % d == 0 && product_alone(g); }
+hipError_t gemm_f32_rope(const GemmArgs &g, int d, int rotated, const float2 *cs, hipStream_t st) {
+    GemmF32 p = params(g);
+    p.cs = cs; p.pair = d / 2; p.rotated = rotated;
+    return launch<true, true, ROPE>(p, st);
+}
+
+bool gemm_f32_swiglu_bwd_supported(const GemmArgs &g) { return g.layout == GEMM_NN && g.ldc == 2 * g.N && product_alone(g); }
+hipError_t gemm_f32_swiglu_bwd(const GemmArgs &g, const void *gu, hipStream_t st) {
+    GemmF32 p = params(g);
+    p.gu = (const float *)gu;
+    return launch<true, false, SWIGLU_BWD>(p, st);
 }
 
 hipError_t gemm_f32(const GemmArgs &g, hipStream_t st) {

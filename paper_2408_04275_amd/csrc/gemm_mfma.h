@@ -364,7 +364,7 @@ void gemm_mfma_kernel(const ARG arg) {
         if ((int)blockIdx.x >= workgroups) {
             typedef typename std::conditional<OUT_F32, float, bf16_t>::type T;
             for (int unit = blockIdx.x - workgroups; unit < arg.reduce.units[8]; unit += gridDim.x - workgroups) {
-                reduce_unit<T>(arg.reduce, unit, reinterpret_cast<float (*)[36]>(smem));
+                reduce_unit<T>(arg.reduce, unit, reinterpret_cast<float (*)[36]>(smem), threadIdx.x);
                 __syncthreads();
             }
             return;

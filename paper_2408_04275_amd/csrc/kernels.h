@@ -35,7 +35,18 @@ bool gemm_f32_supported(const GemmArgs &g);
 hipError_t gemm_f32(const GemmArgs &g, hipStream_t st);
 // ... weight gradients with few tiles of 64 x 64 (below 384), up to 4 in one launch
 bool gemm_f32_few_tiles(const GemmArgs &g);
-hipError_t gemm_f32_group(const GemmArgs *gs, int n, hipStream_t st);
+struct ReduceJobSet;
+// reduce: when not null, sums (reduce.h) that the same launch adds up, to fp32 outputs
+hipError_t gemm_f32_group(const GemmArgs *gs, int n, const ReduceJobSet *reduce, hipStream_t st);
+// ... products whose epilogue does the elementwise work behind them.  C = [gate | up], m [M, N / 2] = silu(gate) up
+bool gemm_f32_swiglu_supported(const GemmArgs &g);
+hipError_t gemm_f32_swiglu(const GemmArgs &g, void *m, hipStream_t st);
+// C's first `rotated` heads of d columns get the rotary embedding (cs: [M, d / 2])
+bool gemm_f32_rope_supported(const GemmArgs &g, int d);
+hipError_t gemm_f32_rope(const GemmArgs &g, int d, int rotated, const float2 *cs, hipStream_t st);
+// the product is the gradient of silu(gate) up with gu = [gate | up]: C = [d_gate | d_up], leading dimension 2 N
+bool gemm_f32_swiglu_bwd_supported(const GemmArgs &g);
+hipError_t gemm_f32_swiglu_bwd(const GemmArgs &g, const void *gu, hipStream_t st);
 // gemm_mfma.hip: bf16 MFMA kernel.  `supported` checks alignment requirements.
 bool gemm_mfma_supported(const GemmArgs &g);
 hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st);
@@ -53,7 +64,6 @@ size_t gemm_mfma_tn_scratch(long M, long N, long K);
 // 256 x 256) computed together in one launch; up to 4, all with the same K and accumulate / c_f32.
 bool gemm_mfma_few_tiles(const GemmArgs &g);
 // reduce: when not null, sums (reduce.h) that the same launch adds up, to outputs of the gradients' type; worth it where the launch has room.
-struct ReduceJobSet;
 bool gemm_mfma_group_has_room(const GemmArgs *gs, int n);
 hipError_t gemm_mfma_group(const GemmArgs *gs, int n, const ReduceJobSet *reduce, hipStream_t st);
 

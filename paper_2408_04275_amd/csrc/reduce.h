@@ -17,16 +17,16 @@ struct ReduceJobSet {
 bool reduce_job_set(const ReduceJob *jobs, int n, bool accumulate, ReduceJobSet &set);
 
 constexpr int REDUCE_LDS = 32 * 36 * 4;
-// one unit, by 256 threads; red: REDUCE_LDS bytes
+// one unit, by 256 threads of a workgroup (tid); red: REDUCE_LDS bytes; has a barrier
 template <typename T>
-__device__ __forceinline__ void reduce_unit(const ReduceJobSet &set, int unit, float (*red)[36]) {
+__device__ __forceinline__ void reduce_unit(const ReduceJobSet &set, int unit, float (*red)[36], int tid) {
     int j = 0;
 #pragma unroll
     for (int i = 1; i < 8; ++i) j += unit >= set.units[i];
     const int N = set.N[j], rows = set.rows[j], c0 = (unit - set.units[j]) * 32;
     const float *part = set.part[j];
     T *out = (T *)set.out[j];
-    const int cl = threadIdx.x & 7, rl = threadIdx.x >> 3;
+    const int cl = tid & 7, rl = tid >> 3;
     const int c = c0 + cl * 4;
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
     if (c < N) {
@@ -49,11 +49,11 @@ __device__ __forceinline__ void reduce_unit(const ReduceJobSet &set, int unit, f
     }
     *reinterpret_cast<f32x4 *>(&red[rl][cl * 4]) = s;
     __syncthreads();
-    const int oc = c0 + threadIdx.x;
-    if (threadIdx.x < 32 && oc < N) {
+    const int oc = c0 + tid;
+    if (tid < 32 && oc < N) {
         float t = 0.f;
 #pragma unroll
-        for (int i = 0; i < 32; ++i) t += red[i][threadIdx.x];
+        for (int i = 0; i < 32; ++i) t += red[i][tid];
         if (set.accumulate) t += Elem<T>::load(out + oc);
         Elem<T>::store(out + oc, t);
     }
