@@ -435,12 +435,21 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
         reduce_later(w.part_c, G.b_fc1, ns, D.F1);
     } else if (enc) HIP_TRY_TIMED(MMTRAIN_PROF_ACT_BWD, st, gelu_bwd(D.dtype, w.d_m, c.pre, w.d_pre, (long)T * D.F, st));
     else if (!activates) HIP_TRY_TIMED(MMTRAIN_PROF_ACT_BWD, st, swiglu_bwd(D.dtype, w.d_m, c.pre, w.d_pre, T, D.F, st));
-    HIP_TRY(gemm(D.dtype, splittable(mk(GEMM_NN, T, D.H, D.F1, w.d_pre, D.F1, W->w_fc1, D.H, w.d_h, D.H), w.split_ws, w.split_bytes), st));
-    if (G.w_fc1) HIP_TRY(wgrad(D.dtype, splittable(f32out(mk(GEMM_TN, D.F1, D.H, T, w.d_pre, D.F1, c.h2, D.H, G.w_fc1, D.H, nullptr, nullptr, accum), g32), w.split_ws, w.split_bytes), later, st));
+    // A gradient that is cut along K as a whole stays in its parts, in the scratch, where the normalisation behind it adds them up: that runs in front of
+    // the weight gradient then, which may use the same scratch.
+    NormParts parts = {(const float *)w.split_ws, 0};
+    int *const chunks = norm_bwd_adds_parts(D.dtype, enc, D.H) ? &parts.n : nullptr;
+    auto in_parts = [&](GemmArgs g) { g = splittable(g, w.split_ws, w.split_bytes); g.chunks = chunks; return g; };
+    HIP_TRY(gemm(D.dtype, in_parts(mk(GEMM_NN, T, D.H, D.F1, w.d_pre, D.F1, W->w_fc1, D.H, w.d_h, D.H)), st));
     // d_y1 = dy + norm2_bwd(d_h2); the same kernel sums the columns of dy (b_fc2's gradient) and of d_y1 (b_o's)
-    HIP_TRY_TIMED(MMTRAIN_PROF_NORM_BWD, st, norm_bwd(D.dtype, enc, w.d_h, c.y1, W->norm2_w, c.mean2, c.rstd2, dy, w.d_y1,
-                     G.norm2_w ? w.part_g : nullptr, (enc && G.norm2_b) ? w.part_b : nullptr,
-                     (enc && G.b_o) ? w.part_din : nullptr, (enc && G.b_fc2) ? w.part_dres : nullptr, T, D.H, st));
+    auto norm2 = [&]() {
+        ProfScope ps(MMTRAIN_PROF_NORM_BWD, st);
+        return norm_bwd(D.dtype, enc, w.d_h, c.y1, W->norm2_w, c.mean2, c.rstd2, dy, w.d_y1, G.norm2_w ? w.part_g : nullptr,
+                        (enc && G.norm2_b) ? w.part_b : nullptr, (enc && G.b_o) ? w.part_din : nullptr, (enc && G.b_fc2) ? w.part_dres : nullptr, T, D.H, parts, st);
+    };
+    if (parts.n) HIP_TRY(norm2());
+    if (G.w_fc1) HIP_TRY(wgrad(D.dtype, splittable(f32out(mk(GEMM_TN, D.F1, D.H, T, w.d_pre, D.F1, c.h2, D.H, G.w_fc1, D.H, nullptr, nullptr, accum), g32), w.split_ws, w.split_bytes), later, st));
+    if (!parts.n) HIP_TRY(norm2());
     reduce_later(w.part_g, G.norm2_w, nb, D.H);
     if (enc) {
         reduce_later(w.part_b, G.norm2_b, nb, D.H);
@@ -469,11 +478,17 @@ int mmtrain_layer_bwd(const mmtrain_layer_desc *desc, const mmtrain_batch *batch
         HIP_TRY(colsum_partials(D.dtype, w.d_qkv, T, D.nqkv, D.nqkv, w.part_c2, st));
         reduce_later(w.part_c2, G.b_qkv, ns, D.nqkv);
     }
-    HIP_TRY(gemm(D.dtype, splittable(mk(GEMM_NN, T, D.H, D.nqkv, w.d_qkv, D.nqkv, W->w_qkv, D.H, w.d_h, D.H), w.split_ws, w.split_bytes), st));
-    if (G.w_qkv) HIP_TRY(wgrad(D.dtype, splittable(f32out(mk(GEMM_TN, D.nqkv, D.H, T, w.d_qkv, D.nqkv, c.h1, D.H, G.w_qkv, D.H, nullptr, nullptr, accum), g32), w.split_ws, w.split_bytes), later, st));
+    parts.n = 0;
+    HIP_TRY(gemm(D.dtype, in_parts(mk(GEMM_NN, T, D.H, D.nqkv, w.d_qkv, D.nqkv, W->w_qkv, D.H, w.d_h, D.H)), st));
     // dx = d_y1 + norm1_bwd(d_h1)
-    HIP_TRY_TIMED(MMTRAIN_PROF_NORM_BWD, st, norm_bwd(D.dtype, enc, w.d_h, x, W->norm1_w, c.mean1, c.rstd1, w.d_y1, dx,
-                     G.norm1_w ? w.part_g1 : nullptr, (enc && G.norm1_b) ? w.part_b1 : nullptr, nullptr, nullptr, T, D.H, st));
+    auto norm1 = [&]() {
+        ProfScope ps(MMTRAIN_PROF_NORM_BWD, st);
+        return norm_bwd(D.dtype, enc, w.d_h, x, W->norm1_w, c.mean1, c.rstd1, w.d_y1, dx, G.norm1_w ? w.part_g1 : nullptr,
+                        (enc && G.norm1_b) ? w.part_b1 : nullptr, nullptr, nullptr, T, D.H, parts, st);
+    };
+    if (parts.n) HIP_TRY(norm1());
+    if (G.w_qkv) HIP_TRY(wgrad(D.dtype, splittable(f32out(mk(GEMM_TN, D.nqkv, D.H, T, w.d_qkv, D.nqkv, c.h1, D.H, G.w_qkv, D.H, nullptr, nullptr, accum), g32), w.split_ws, w.split_bytes), later, st));
+    if (!parts.n) HIP_TRY(norm1());
     reduce_later(w.part_g1, G.norm1_w, nb, D.H);
     if (enc) reduce_later(w.part_b1, G.norm1_b, nb, D.H);
     HIP_TRY(run_deferred(D.dtype, later, gdt, jobs, n_jobs, accum, st));

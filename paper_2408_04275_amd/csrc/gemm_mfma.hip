@@ -334,6 +334,7 @@ hipError_t gemm_mfma(const GemmArgs &g, hipStream_t st) {
         p.k_chunk = plan.k_chunk; p.splits = plan.chunks;
         p.C = (bf16_t *)g.split_ws; p.ldc = g.N; p.accumulate = 0; p.c_f32 = 1;
         if ((e = launch_partials(g.layout, p, st)) != hipSuccess) return e;
+        if (g.chunks) { *g.chunks = p.splits; return hipSuccess; }
         sum_chunks_kernel<<<dim3(ceil_div(g.N, 2048), g.M < 4096 ? g.M : 4096), 256, 0, st>>>((const float *)g.split_ws, p.splits, g.M, g.N,
                                                                                                (bf16_t *)g.C, g.ldc, g.accumulate ? 1 : 0);
         return hipGetLastError();

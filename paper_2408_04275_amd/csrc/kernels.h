@@ -23,6 +23,9 @@ struct GemmArgs {
     // few tiles (NN, bf16), 256-byte aligned
     void *split_ws = nullptr;
     size_t split_ws_bytes = 0;
+    // when not null and the product is cut as a whole (bf16 NN): its partial products [*chunks][M][N] are left in split_ws for the caller to
+    // add up, and C is not written.  Otherwise left alone.
+    int *chunks = nullptr;
     // measurement aid (matrix-core kernel only): when not null, device uint64[4]; the first workgroup stores the
     // shader-clock counter and the constant 100 MHz counter at its start ([0], [1]) and at its end ([2], [3])
     unsigned long long *clock_probe = nullptr;
@@ -155,9 +158,12 @@ hipError_t norm_fwd(int dtype, bool layernorm, const void *x, const void *g, con
 // d_in = norm_bwd(d_out) + d_res;  gain/bias gradient partial sums go to part_g/part_b, the column sums of d_in
 // and of d_res to part_din / part_dres ([norm_bwd_blocks(T, H), H] fp32 each; null = skip).
 int norm_bwd_blocks(int T, int H);
+// A d_out that is still in fp32 parts [n_parts][T][H] (see GemmArgs::chunks), which the kernel adds up itself, comes as `parts` (n_parts: 0 if it is not).
+bool norm_bwd_adds_parts(int dtype, bool layernorm, int H);
+struct NormParts { const float *p = nullptr; int n = 0; };
 hipError_t norm_bwd(int dtype, bool layernorm, const void *d_out, const void *x, const void *g,
                     const float *mean, const float *rstd, const void *d_res, void *d_in,
-                    float *part_g, float *part_b, float *part_din, float *part_dres, int T, int H, hipStream_t st);
+                    float *part_g, float *part_b, float *part_din, float *part_dres, int T, int H, NormParts parts, hipStream_t st);
 // out[c] (+)= sum_r part[r, c]
 hipError_t reduce_partials(int dtype, const float *part, int rows, int N, void *out, bool accumulate,
                            hipStream_t st);
