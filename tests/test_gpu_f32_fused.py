@@ -4,9 +4,11 @@ import numpy as np
 import pytest
 
 from oracle import layer_oracle as orc
+from paper_2408_04275_amd import binding as mm
 from paper_2408_04275_amd import parity
 from paper_2408_04275_amd import workloads as wl
 from paper_2408_04275_amd.harness import LayerRunner
+from test_gpu_ops import attn_case
 
 pytestmark = pytest.mark.gpu
 
@@ -34,3 +36,8 @@ def test_f32_layers_with_fused_launches(kind, H, nh, nkv, d, F, lens):
     parity.check("dx", gdx, dx, wl.F32)
     for k in G:
         parity.check("d" + k, gG[k], G[k], wl.F32)
+
+
+# dQ and dK/dV rows of workgroups together beyond what one grid holds
+def test_f32_attention_with_many_heads():
+    attn_case(mm.F32, 40000, 40000, 64, np.array([0, 5, 9], dtype=np.int32), np.array([0, 1], dtype=np.uint8), seed=34)
