@@ -257,10 +257,16 @@ int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
 }
 
 // Sums ride along where the launch leaves compute units without a tile: no full round, or a last one that is at most three quarters full.
-// On 192 tiles for 256 units (a 1024-wide encoder layer, 9536 tokens) the launch of their own took 12 us, on 600 (1280 wide, 4111) 16.
+// On 192 tiles for 256 units (a 1024-wide encoder layer, 9536 tokens) the launch of their own took 12 us, on 600 (1280 wide, 4111) 16.  Outputs of more than one round
+// of 256 x 256 tiles (1280 wide: 300) take more, smaller tiles over few tokens and have no such gap: 500, 900, 2000 tokens alone -> along 240 -> 254, 330 -> 345,
+// 465 -> 471; 2100 490 -> 489.  Of less than one (1024 wide: 192): 300, 900, 2000 tokens 154.9 -> 151.2, 223 -> 218, 332 -> 322.
+constexpr int MIN_K_WITH_SUMS = 2048;
 bool gemm_mfma_group_has_room(const GemmArgs *gs, int n) {
     int n_cu = 0;
     if (n <= 0 || compute_units(n_cu) != hipSuccess) return false;
+    long large = 0;
+    for (int i = 0; i < n; ++i) large += (long)ceil_div(gs[i].M, TILE) * ceil_div(gs[i].N, TILE);
+    if (large >= n_cu && gs[0].K < MIN_K_WITH_SUMS) return false;
     double us;
     const int shape = choose_tile(gs, n, n_cu, us);
     for (const TileCost &t : COST_WGRAD)
