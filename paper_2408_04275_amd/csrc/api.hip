@@ -866,6 +866,8 @@ MMTRAIN_API int mmtrain_route_late_start(int32_t M, int32_t N, int32_t K, int32_
 MMTRAIN_API int mmtrain_route_gemm_f32(int32_t layout, int32_t M, int32_t N, int32_t K) {      // 1: matrix instruction, 0: vector ALUs
     return gemm_f32_supported(mk(layout, M, N, K, nullptr, layout == GEMM_TN ? M : K, nullptr, layout == GEMM_NT ? K : N, nullptr, N)) ? 1 : 0;
 }
+// 1: the normalisation's backward kernel adds up an input gradient that is cut along K
+MMTRAIN_API int mmtrain_route_norm_parts(int32_t dtype, int32_t layernorm, int32_t hidden) { return norm_bwd_adds_parts(dtype, layernorm != 0, hidden) ? 1 : 0; }
 MMTRAIN_API int mmtrain_route_adam(int64_t n, int32_t param_bytes) { return adam_streams((size_t)n, (size_t)param_bytes) ? 1 : 0; }
 
 }  // extern "C"

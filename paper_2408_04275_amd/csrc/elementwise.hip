@@ -342,9 +342,9 @@ int norm_bwd_blocks(int T, int H) {
     return all < grid ? (all > 0 ? all : 1) : grid;
 }
 
-// SPLIT: d_out comes as the fp32 partial products of the input gradient in front, cut along K, and is added up here, in order, instead of by a kernel
-// that writes it and this one that reads it back: 1031 rows of 4096 in three parts, 14.2 + 11.6 -> 21.1 us.  (Few rows, about one per workgroup:
-// the parts are not requested a row ahead.)
+// SPLIT: d_out comes as the fp32 partial products of the input gradient in front, cut along K, and is added up here, in order, instead
+// of by a kernel that writes it and this one that reads it back: 1031 rows of 4096 in three parts, 14.2 + 11.6 -> 21.1 us.  The parts
+// are not requested a row ahead (up to 1024 rows a workgroup has one, up to 2047 two).
 template <typename T, bool LN, int NORM_BWD_MAXC, bool COLS, bool SPLIT = false>
 __global__ __launch_bounds__(256) void norm_bwd_kernel(const T *__restrict__ d_out, const T *__restrict__ x,
                                                        const T *__restrict__ g, const float *__restrict__ mean,
@@ -561,8 +561,13 @@ __global__ __launch_bounds__(256) void norm_bwd_wave_kernel(const T *__restrict_
     if constexpr (COLS) { flush(ad, part_din); flush(ae, part_dres); }
 }
 
-// (a decoder's: an encoder's input gradients have too short a K to be cut as a whole)
-bool norm_bwd_adds_parts(int dtype, bool layernorm, int H) { return dtype == DT_BF16 && !layernorm && H > NORM_BWD_WAVE_H && H <= 256 * 8 * NORM_BWD_MAXC; }
+// Built for RMSNorm rows of more than NORM_BWD_WAVE_H and at most SPLIT_MAX_H columns; in front of other normalisations the parts are
+// summed by a kernel of their own.  Backward of a frozen decoder layer, apart -> together, us: 4096 wide, 300, 700, 1031, 1400, 2047 tokens
+// 244.4 -> 242.1, 363.3 -> 357.4, 474.4 -> 468.3, 636.3 -> 633.4, 807.8 -> 795.9; 2048 wide (ffn 11008), 300, 1400 154.2 -> 151.2,
+// 355.6 -> 350.7.  Wider rows take four column chunks per thread, which leaves registers for one wavefront per SIMD (232 -> 352), and lose:
+// 5120 wide, 300, 1031 tokens 327.4 -> 330.8, 676.0 -> 681.7; 6144, 300 387.1 -> 390.3; 8192, 300 684.1 -> 688.4.
+constexpr int SPLIT_MAX_H = 4096;
+bool norm_bwd_adds_parts(int dtype, bool layernorm, int H) { return dtype == DT_BF16 && !layernorm && H > NORM_BWD_WAVE_H && H <= SPLIT_MAX_H; }
 
 hipError_t norm_bwd(int dtype, bool layernorm, const void *d_out, const void *x, const void *g,
                     const float *mean, const float *rstd, const void *d_res, void *d_in, float *part_g,
@@ -578,8 +583,7 @@ hipError_t norm_bwd(int dtype, bool layernorm, const void *d_out, const void *x,
                 nullptr, (const bf16_t *)x, (const bf16_t *)g, mean, rstd, (const bf16_t *)d_res, (bf16_t *)d_in, part_g, part_b, nullptr, nullptr, T, H, parts);
         };
         if (H <= 2048) launch(std::integral_constant<int, 1>{});
-        else if (H <= 4096) launch(std::integral_constant<int, 2>{});
-        else launch(std::integral_constant<int, 4>{});
+        else launch(std::integral_constant<int, 2>{});
         return hipGetLastError();
     }
 #define L2(TT, LNV, MC, CV) norm_bwd_kernel<TT, LNV, MC, CV><<<grid, 256, 0, st>>>((const TT *)d_out, (const TT *)x, (const TT *)g, mean, rstd, (const TT *)d_res, (TT *)d_in, part_g, part_b, part_din, part_dres, T, H, parts)

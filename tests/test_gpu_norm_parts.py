@@ -1,5 +1,6 @@
 """Decoder layers of short packs: the input gradient in front of the second normalisation is cut along K as a whole, and the normalisation's backward
-kernel adds up its parts.  One and several rows per workgroup, every row width the kernel is built for, whole and partly filled batches of parts."""
+kernel adds up its parts, in rows of up to 4096; wider ones (4112) keep a kernel that sums them.  One and several rows per workgroup, both widths
+the kernel is built for, whole and partly filled batches of parts."""
 import numpy as np
 import pytest
 

@@ -120,3 +120,12 @@ def test_tiles_of_fp32_gradients(H, nh, d, F, T, tile1, tile2):
     for (M, N), tile in (((2 * F, H), tile1), ((H, F), tile2)):
         assert gemm_route(mm.GEMM_TN, M, N, T) == (*map(int, tile.split("x")), 0, 1)
         assert ((M + 255) // 256) * ((N + 255) // 256) > 128                 # a launch of its own, not one of a group
+
+
+# parts of an input gradient are added up by the normalisation's backward kernel where that is faster than a kernel of their own
+def test_widths_whose_normalisation_adds_parts():
+    for dtype in (mm.F32, mm.BF16):
+        for layernorm in (0, 1):
+            for H in (256, 1024, 1040, 2048, 4096, 4112, 5120, 8192):
+                adds = mm.load_library().mmtrain_route_norm_parts(dtype, layernorm, H)
+                assert adds == (dtype == mm.BF16 and not layernorm and 1024 < H <= 4096), (dtype, layernorm, H)
