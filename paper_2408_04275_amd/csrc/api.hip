@@ -868,6 +868,7 @@ MMTRAIN_API int mmtrain_route_gemm_f32(int32_t layout, int32_t M, int32_t N, int
 }
 // 1: the normalisation's backward kernel adds up an input gradient that is cut along K
 MMTRAIN_API int mmtrain_route_norm_parts(int32_t dtype, int32_t layernorm, int32_t hidden) { return norm_bwd_adds_parts(dtype, layernorm != 0, hidden) ? 1 : 0; }
+MMTRAIN_API int mmtrain_route_attn_f32_bwd(int32_t T, int32_t nh, int32_t nkv, int32_t d) { return attn_f32_bwd_launches(T, nh, nkv, d); }
 MMTRAIN_API int mmtrain_route_adam(int64_t n, int32_t param_bytes) { return adam_streams((size_t)n, (size_t)param_bytes) ? 1 : 0; }
 
 }  // extern "C"

@@ -235,8 +235,8 @@ __device__ __forceinline__ float row_dots(const Tensor<D> &O, int row0, const f3
     return row_sum(d);
 }
 
-// dQ_i = scale * sum_j dS_ij k_j,  dS_ij = P_ij (dO_i . v_j - D_i),  P_ij = exp(s_ij - lse_i)
-template <int D, int NW>
+// dQ_i = scale * sum_j dS_ij k_j,  dS_ij = P_ij (dO_i . v_j - D_i),  P_ij = exp(s_ij - lse_i).  KEEP_D: D goes to a.Dsum as well
+template <int D, int NW, bool KEEP_D>
 __device__ __forceinline__ void dq_rows(const AttnArgs &a, Partials<D, NW> &part, int h) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = threadIdx.x & 15;
     const int q0 = blockIdx.x * 16, g = h / (a.nh / a.nkv), T = a.T, nq = a.nh * D, nk = a.nkv * D;
@@ -251,6 +251,7 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, Partials<D, NW> &part
     for (int i = 0; i < D / 16; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float Di = row_dots<D>(O, q0, gf);
     const float lse = q0 + r < T ? a.lse[(size_t)h * T + q0 + r] : 0.f;
+    if (KEEP_D && threadIdx.x < 16 && q0 + r < T) a.Dsum[(size_t)h * T + q0 + r] = Di;
     for (int k0 = kbeg + 16 * wave; k0 < kend; k0 += 16 * NW) {
         f32x4 kf[D / 16], vf[D / 16], kc[4][D / 64];
         K.pieces(k0, kf);
@@ -268,8 +269,9 @@ __device__ __forceinline__ void dq_rows(const AttnArgs &a, Partials<D, NW> &part
     part.store((float *)a.d_qkv + h * D, a.ld_qkv, q0, T, a.scale, a.rope_cs);
 }
 
-// dK_j = scale * sum_{h in group} sum_i dS_ij q_i,   dV_j = sum_{h in group} sum_i P_ij dO_i
-template <int D, int NW>
+// dK_j = scale * sum_{h in group} sum_i dS_ij q_i,   dV_j = sum_{h in group} sum_i P_ij dO_i.  KEPT_D: D is in a.Dsum; otherwise it is
+// formed again for every block of keys, to the same bits
+template <int D, int NW, bool KEPT_D>
 __device__ __forceinline__ void dkv_rows(const AttnArgs &a, Partials<D, NW> &part, int g) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = threadIdx.x & 15, q4 = ((threadIdx.x & 48) >> 4) * 4;
     const int k0 = blockIdx.x * 16, group = a.nh / a.nkv, T = a.T, nq = a.nh * D, nk = a.nkv * D;
@@ -293,9 +295,14 @@ __device__ __forceinline__ void dkv_rows(const AttnArgs &a, Partials<D, NW> &par
         f32x4 lse, Ds, p, ds;
 #pragma unroll
         for (int e = 0; e < 4; ++e) lse[e] = a.lse[(size_t)h * T + min(q0 + q4 + e, T - 1)];
-        const float d = row_dots<D>(O, q0, gf);
+        if constexpr (KEPT_D) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) Ds[e] = __shfl(d, q4 + e, 64);
+            for (int e = 0; e < 4; ++e) Ds[e] = a.Dsum[(size_t)h * T + min(q0 + q4 + e, T - 1)];
+        } else {
+            const float d = row_dots<D>(O, q0, gf);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Ds[e] = __shfl(d, q4 + e, 64);
+        }
         const uint32_t seen = seen_bits(me, q0);
         const f32x4 s = dot_rows<D>(qf, kf) * a.scale, dp = dot_rows<D>(gf, vf);
 #pragma unroll
@@ -317,15 +324,25 @@ __device__ __forceinline__ void dkv_rows(const AttnArgs &a, Partials<D, NW> &par
     part.store(out + nq + nk + g * D, a.ld_qkv, k0, T, 1.f, nullptr);
 }
 
-// Both in one launch, the dK/dV workgroups (longer with grouped heads) first: each alone leaves half of the compute units of a small pack idle (128
-// workgroups at 512 tokens and 4 heads), and D from the rows at hand costs dK/dV one more read and spares it the wait for dQ.  There 8.6 + 8.5 -> 10.6 us, the
-// layer forward and backward 115.3 -> 109.6.  Rows first .. of the nkv + nh rows of workgroups (a grid holds 65535).
+// Both in one launch, the dK/dV workgroups (longer with grouped heads) first; see one_launch.  Rows first .. of the nkv + nh rows of
+// workgroups (a grid holds 65535).
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_f32_bwd_kernel(AttnArgs a, int first) {
     __shared__ __attribute__((aligned(16))) Partials<D, NW> part;
     const int y = first + blockIdx.y;
-    if (y < a.nkv) dkv_rows<D, NW>(a, part, y);
-    else dq_rows<D, NW>(a, part, y - a.nkv);
+    if (y < a.nkv) dkv_rows<D, NW, false>(a, part, y);
+    else dq_rows<D, NW, false>(a, part, y - a.nkv);
+}
+// ... or one after the other
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(AttnArgs a) {
+    __shared__ __attribute__((aligned(16))) Partials<D, NW> part;
+    dq_rows<D, NW, true>(a, part, blockIdx.y);
+}
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(AttnArgs a) {
+    __shared__ __attribute__((aligned(16))) Partials<D, NW> part;
+    dkv_rows<D, NW, true>(a, part, blockIdx.y);
 }
 
 }  // namespace
@@ -344,10 +361,27 @@ hipError_t attn_f32_fwd(const AttnArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
+// One launch where dK/dV alone leaves the chip part empty: dQ fills it, and D from the rows at hand costs dK/dV one more read and spares it
+// the wait for dQ (512 tokens and 4 heads of 64 in four segments, 128 workgroups: 18.1 -> 11.2 us).  With more workgroups of 64-wide heads that
+// read is work on a full chip.  One launch against two, mean over 3 to 21 packs of one to eight segments each (dK/dV workgroups: ratio): 192: 0.88,
+// 256: 0.96, 320: 0.87, 384: 0.90, 448: 0.97, 512: 1.05, 640: 0.99, 768: 1.01, 1024: 1.09; 16 heads, 8192 tokens in one segment 6547 us against 5679.
+// Single packs scatter around these: of 273 the rule is 8 % faster on average than two launches, and seven are 2.5 % or more slower, 16 heads on 4 over
+// 1019 tokens in eight segments (48.4 -> 55.9 us) the most.
+// 128-wide heads, four wavefronts per workgroup, gain at every length (32 heads, 96 tokens 27.2 -> 22.8 us, 8192 38629 -> 36478).
+constexpr long ONE_LAUNCH_WORKGROUPS = 448;
+static bool one_launch(int T, int nkv, int d) { return d != 64 || (long)ceil_div(T, 16) * nkv <= ONE_LAUNCH_WORKGROUPS; }
+int attn_f32_bwd_launches(int T, int nh, int nkv, int d) { return one_launch(T, nkv, d) ? ceil_div(nkv + nh, 65535) : 2; }
+
 hipError_t attn_f32_bwd(const AttnArgs &a, hipStream_t st) {
     if (a.T == 0) return hipSuccess;
+    const int blocks = ceil_div(a.T, 16);
+    if (!one_launch(a.T, a.nkv, a.d)) {
+        attn_f32_dq_kernel<64, 8><<<dim3(blocks, a.nh), 512, 0, st>>>(a);
+        attn_f32_dkv_kernel<64, 8><<<dim3(blocks, a.nkv), 512, 0, st>>>(a);
+        return hipGetLastError();
+    }
     for (int first = 0, rows; (rows = a.nkv + a.nh - first) > 0; first += 65535) {
-        const dim3 grid(ceil_div(a.T, 16), rows < 65535 ? rows : 65535);
+        const dim3 grid(blocks, rows < 65535 ? rows : 65535);
         if (a.d == 64) attn_f32_bwd_kernel<64, 8><<<grid, 512, 0, st>>>(a, first);
         else attn_f32_bwd_kernel<128, 4><<<grid, 256, 0, st>>>(a, first);
     }

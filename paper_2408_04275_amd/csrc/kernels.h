@@ -87,7 +87,8 @@ struct AttnArgs {
     float *lse;                 // [nh, T]
     const void *d_o;            // bwd: [T, nh*d]
     void *d_qkv;                // bwd: [T, ld_qkv]
-    float *Dsum;                // bwd scratch: [nh, T]; D = rowsum(dO * O) per query and head (the matrix-core kernels keep -D there)
+    float *Dsum;                // bwd scratch: [nh, T]; D = rowsum(dO * O) per query and head (the bf16 kernels keep -D there; the fp32 matrix kernels write and
+                                // read it where dQ and dK/dV are two launches)
     // MFMA path: tok_info[t] = {segment start, segment end | (bidirectional ? 1 << 30 : 0)}; may be null for a pack of at most
     // ATTN_LANE_SEGMENTS segments (cu and modes are read instead)
     const int2 *tok_info;
@@ -126,6 +127,7 @@ hipError_t attn_simple_bwd(const AttnArgs &a, hipStream_t st);
 bool attn_f32_supported(const AttnArgs &a);
 hipError_t attn_f32_fwd(const AttnArgs &a, hipStream_t st);
 hipError_t attn_f32_bwd(const AttnArgs &a, hipStream_t st);
+int attn_f32_bwd_launches(int T, int nh, int nkv, int d);
 // attn_mfma.hip: bf16 storage, matrix cores
 hipError_t attn_mfma_fwd(const AttnArgs &a, hipStream_t st);
 hipError_t attn_mfma_bwd(const AttnArgs &a, hipStream_t st);

@@ -38,6 +38,17 @@ def test_f32_layers_with_fused_launches(kind, H, nh, nkv, d, F, lens):
         parity.check("d" + k, gG[k], G[k], wl.F32)
 
 
-# dQ and dK/dV rows of workgroups together beyond what one grid holds
+# many workgroups of 64-wide heads: a dQ and a dK/dV launch
 def test_f32_attention_with_many_heads():
     attn_case(mm.F32, 40000, 40000, 64, np.array([0, 5, 9], dtype=np.int32), np.array([0, 1], dtype=np.uint8), seed=34)
+
+
+# dQ and dK/dV rows of workgroups together beyond what one grid holds
+def test_f32_attention_backward_beyond_one_grid():
+    attn_case(mm.F32, 40000, 40000, 128, np.array([0, 1, 2], dtype=np.int32), np.array([0, 1], dtype=np.uint8), seed=36)
+
+
+# one launch for both and one each, at the line between them (448 workgroups of dK/dV) and past it, grouped heads too
+@pytest.mark.parametrize("nh,nkv,T", [(32, 32, 224), (32, 32, 225), (28, 14, 512), (28, 14, 513), (4, 1, 97)])
+def test_f32_attention_backward_together_and_apart(nh, nkv, T):
+    attn_case(mm.F32, nh, nkv, 64, np.array([0, T // 3, T // 3 + 1, T], dtype=np.int32), np.array([0, 1, 0], dtype=np.uint8), seed=35)

@@ -129,3 +129,11 @@ def test_widths_whose_normalisation_adds_parts():
             for H in (256, 1024, 1040, 2048, 4096, 4112, 5120, 8192):
                 adds = mm.load_library().mmtrain_route_norm_parts(dtype, layernorm, H)
                 assert adds == (dtype == mm.BF16 and not layernorm and 1024 < H <= 4096), (dtype, layernorm, H)
+
+
+# dQ and dK/dV of fp32 attention run together only where dK/dV of 64-wide heads leaves the chip part empty; a grid holds 65535 rows
+def test_launches_of_f32_attention_backward():
+    route = mm.load_library().mmtrain_route_attn_f32_bwd
+    for T, nh, nkv, d, launches in [(512, 4, 4, 64, 1), (1792, 4, 4, 64, 1), (1793, 4, 4, 64, 2), (224, 32, 32, 64, 1), (225, 32, 32, 64, 2),
+                                    (8192, 4, 1, 64, 2), (8192, 32, 32, 128, 1), (9, 40000, 40000, 64, 2), (2, 40000, 40000, 128, 2)]:
+        assert route(T, nh, nkv, d) == launches, (T, nh, nkv, d)
