@@ -269,7 +269,7 @@ hipError_t wgrad(int dtype, const GemmArgs &g, DeferredWgrads &later, hipStream_
 hipError_t run_deferred(int dtype, const DeferredWgrads &later, int gdt, const ReduceJob *jobs, int n_jobs, bool accumulate, hipStream_t st) {
     ReduceJobSet set;
     const bool together = later.n > 0 && reduce_job_set(jobs, n_jobs, accumulate, set) &&
-                          (dtype == DT_F32 || gemm_mfma_group_has_room(later.g, later.n));
+                          (dtype == DT_F32 || gemm_mfma_group_has_room(later.g, later.n, set));
     if (!together) {
         const hipError_t e = reduce_jobs(gdt, jobs, n_jobs, accumulate, st);
         if (e != hipSuccess || later.n == 0) return e;
@@ -869,6 +869,16 @@ MMTRAIN_API int mmtrain_route_gemm_f32(int32_t layout, int32_t M, int32_t N, int
 // 1: the normalisation's backward kernel adds up an input gradient that is cut along K
 MMTRAIN_API int mmtrain_route_norm_parts(int32_t dtype, int32_t layernorm, int32_t hidden) { return norm_bwd_adds_parts(dtype, layernorm != 0, hidden) ? 1 : 0; }
 MMTRAIN_API int mmtrain_route_attn_f32_bwd(int32_t T, int32_t nh, int32_t nkv, int32_t d) { return attn_f32_bwd_launches(T, nh, nkv, d); }
+// 1: the sums of n_jobs arrays (job: rows, columns each) ride along with the weight gradients of n products (mn: M, N each) over K tokens
+MMTRAIN_API int mmtrain_route_sums_along(int32_t n, const int32_t *mn, int32_t K, int32_t n_jobs, const int32_t *job, int32_t n_cu) {
+    GemmArgs g[4];
+    ReduceJob jobs[8];
+    ReduceJobSet set;
+    if (n > 4 || n_jobs > 8) return MMTRAIN_ERR_INVALID_ARG;
+    for (int i = 0; i < n; ++i) g[i] = mk(GEMM_TN, mn[2 * i], mn[2 * i + 1], K, nullptr, mn[2 * i], nullptr, mn[2 * i + 1], nullptr, mn[2 * i + 1]);
+    for (int i = 0; i < n_jobs; ++i) jobs[i] = {reinterpret_cast<const float *>(job), &set, job[2 * i], job[2 * i + 1]};      // (addresses; nothing is read)
+    return reduce_job_set(jobs, n_jobs, false, set) && gemm_mfma_group_has_room(g, n, set, n_cu) ? 1 : 0;
+}
 MMTRAIN_API int mmtrain_route_adam(int64_t n, int32_t param_bytes) { return adam_streams((size_t)n, (size_t)param_bytes) ? 1 : 0; }
 
 }  // extern "C"

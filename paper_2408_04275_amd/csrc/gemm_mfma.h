@@ -83,6 +83,8 @@ struct GemmP {
 // Several products of one layout and epilogue in one launch (the weight gradients of a narrow layer, each with too few
 // tiles to fill the chip): the work items of problem i are [first[i], first[i + 1]); first[i] for i >= n is the total.
 constexpr int MAX_GROUP = 4;
+// workgroups that add up sums riding along, a unit of 32 columns at a time (8 arrays of a 1024-wide encoder layer: 416 units)
+constexpr int GROUP_SUM_WORKGROUPS = 64;
 struct GemmGroup {
     GemmP p[MAX_GROUP];
     int first[MAX_GROUP + 1];

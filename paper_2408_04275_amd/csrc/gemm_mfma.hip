@@ -192,19 +192,26 @@ constexpr TileCost COST_WGRAD[] = {
 // steps the rule took one of them for 18, which became 2 to 15 % faster, and none slower than two runs of one build differ.  Below 40 steps the
 // time is less of the copies' (2304 x 1024 x 1024 11.6 -> 10.9) and the shapes stay what the parity tests of those sizes name.
 constexpr int MIN_K_BETWEEN = 2560;
+struct LaunchCost { double launch, rounds_power, load; };
+constexpr LaunchCost LAUNCH_ROWS = {3.4, 1.042, 0.276}, LAUNCH_WGRAD = {3.7, 1.079, 0.105};
+long tiles_of(const TileCost &t, const GemmArgs *gs, int n) {
+    long tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += (long)ceil_div(gs[i].M, t.bm) * ceil_div(gs[i].N, t.bn);
+    return tiles;
+}
+double tiles_us(const TileCost &t, const LaunchCost &c, long tiles, int K, int n_cu) {
+    const double share = (double)tiles / n_cu, fill = share < 1. ? share * share : 1.;
+    return c.launch + pow(ceil(share), c.rounds_power) * (t.tile + ceil_div(K, BK) * t.step * (1. + c.load * fill));
+}
 template <int N>
-int choose_tile(const TileCost (&table)[N], double launch, double rounds_power, double load, const GemmArgs *gs, int n, int n_cu,
-                double &best_us) {
+int choose_tile(const TileCost (&table)[N], const LaunchCost &cost, const GemmArgs *gs, int n, int n_cu, double &best_us) {
     int best = TILE_256;
     size_t bytes = 0;
     for (int i = 0; i < n; ++i) bytes += (size_t)(gs[i].M + gs[i].N) * gs[i].K * 2;
     const bool from_hbm = bytes > FROM_HBM_BYTES;
     for (const TileCost &t : table) {
         if ((t.shape == TILE_160x128 || t.shape == TILE_96x128) && gs[0].K < MIN_K_BETWEEN) continue;
-        long tiles = 0;
-        for (int i = 0; i < n; ++i) tiles += (long)ceil_div(gs[i].M, t.bm) * ceil_div(gs[i].N, t.bn);
-        const double share = (double)tiles / n_cu, fill = share < 1. ? share * share : 1.;
-        const double us = launch + pow(ceil(share), rounds_power) * (t.tile + ceil_div(gs[0].K, BK) * t.step * (1. + load * fill));
+        const double us = tiles_us(t, cost, tiles_of(t, gs, n), gs[0].K, n_cu);
         // a smaller tile moves more bytes per product: only for a gain beyond the fit's error, and beyond what they cost more from HBM
         // (operands of more than 96 MB: 1397 x 28672 x 5120 takes 336 us in 256 x 256 and 379 in 160 x 256, which the model puts 4 % ahead)
         if (t.shape == TILE_256 || us < best_us * (best != TILE_256 ? 1. : from_hbm ? 0.95 : 0.98)) { best = t.shape; best_us = us; }
@@ -226,8 +233,7 @@ bool short_k_full_rounds(const GemmArgs *gs, int n, int n_cu) {
 int choose_tile(const GemmArgs *gs, int n, int n_cu, double &us) {
     us = 0.;
     if (short_k_full_rounds(gs, n, n_cu)) return TILE_256;
-    return gs[0].layout == GEMM_TN ? choose_tile(COST_WGRAD, 3.7, 1.079, 0.105, gs, n, n_cu, us)
-                                   : choose_tile(COST_ROWS, 3.4, 1.042, 0.276, gs, n, n_cu, us);
+    return gs[0].layout == GEMM_TN ? choose_tile(COST_WGRAD, LAUNCH_WGRAD, gs, n, n_cu, us) : choose_tile(COST_ROWS, LAUNCH_ROWS, gs, n, n_cu, us);
 }
 
 // An input gradient (NN) with few tiles and a very long K, cut along K as a whole: `splits` chunks of 256 x 256 tiles through
@@ -256,27 +262,31 @@ int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
     return best;
 }
 
-// Sums ride along where the launch leaves compute units without a tile: no full round, or a last one that is at most three quarters full.
-// On 192 tiles for 256 units (a 1024-wide encoder layer, 9536 tokens) the launch of their own took 12 us, on 600 (1280 wide, 4111) 16.  Outputs of more than one round
-// of 256 x 256 tiles (1280 wide: 300) take more, smaller tiles over few tokens and have no such gap: 500, 900, 2000 tokens alone -> along 240 -> 254, 330 -> 345,
-// 465 -> 471; 2100 490 -> 489.  Of less than one (1024 wide: 192): 300, 900, 2000 tokens 154.9 -> 151.2, 223 -> 218, 332 -> 322.
-constexpr int MIN_K_WITH_SUMS = 2048;
-bool gemm_mfma_group_has_room(const GemmArgs *gs, int n) {
-    int n_cu = 0;
-    if (n <= 0 || compute_units(n_cu) != hipSuccess) return false;
-    long large = 0;
-    for (int i = 0; i < n; ++i) large += (long)ceil_div(gs[i].M, TILE) * ceil_div(gs[i].N, TILE);
-    if (large >= n_cu && gs[0].K < MIN_K_WITH_SUMS) return false;
-    double us;
+// Sums ride along where the launch leaves compute units without a tile, no full round or a last one that is at most three quarters full,
+// and where they are done about when that round is.  The few workgroups that add them up take longer than a launch of their own would: a
+// unit of 32 columns about 2 us of latency and 5 ns per row.  What they spare is that launch and its run, 8 us together (measured: 2 to 20).
+// Backward pass of an encoder layer, alone -> along, us: 512 wide, 300 and 3000 tokens 76.4 -> 74.2, 153.7 -> 146.0; 1024 wide, 900 and 9536
+// 139.6 -> 134.1, 627 -> 619; 1280 wide (600 tiles in 2.34 rounds), 900, 2304 and 6000 202 -> 221, 314 -> 317, 664 -> 651; 1408 and 1536 wide, whose
+// feed-forward gradients do not take part, 300, 900, 1500 and 2304 tokens 144 -> 155, 238.5 -> 252, 306 -> 308, 410 -> 399.  In those, and in 512, 1536 and 2048
+// wide decoder layers, 64 to 9536 tokens, nothing that rides along by this rule was slower than alone by more than two runs of one build differ.
+constexpr double SUM_UNIT_US = 2., SUM_ROW_US = 0.005, SUMS_LAUNCH_US = 8.;
+bool gemm_mfma_group_has_room(const GemmArgs *gs, int n, const ReduceJobSet &sums, int n_cu) {
+    if (n <= 0) return false;
+    double us, sum_us = 0.;
     const int shape = choose_tile(gs, n, n_cu, us);
+    for (int j = 0; j < 8; ++j) sum_us += (sums.units[j + 1] - sums.units[j]) * (SUM_UNIT_US + SUM_ROW_US * sums.rows[j]);
+    sum_us /= std::max(1, std::min(sums.units[8], GROUP_SUM_WORKGROUPS));
     for (const TileCost &t : COST_WGRAD)
         if (t.shape == shape) {
-            long tiles = 0;
-            for (int i = 0; i < n; ++i) tiles += (long)ceil_div(gs[i].M, t.bm) * ceil_div(gs[i].N, t.bn);
-            const long last = tiles % n_cu;
-            return last > 0 && 4 * last <= 3 * n_cu;
+            const long tiles = tiles_of(t, gs, n), last = tiles % n_cu;
+            return last > 0 && 4 * last <= 3 * n_cu &&
+                   sum_us <= tiles_us(t, LAUNCH_WGRAD, tiles, gs[0].K, n_cu) / ceil_div(tiles, n_cu) + SUMS_LAUNCH_US;
         }
     return false;
+}
+bool gemm_mfma_group_has_room(const GemmArgs *gs, int n, const ReduceJobSet &sums) {
+    int n_cu = 0;
+    return compute_units(n_cu) == hipSuccess && gemm_mfma_group_has_room(gs, n, sums, n_cu);
 }
 hipError_t gemm_mfma_group(const GemmArgs *gs, int n, const ReduceJobSet *reduce, hipStream_t st) {
     if (n <= 0) return hipSuccess;

@@ -5,9 +5,6 @@ namespace mmt {
 namespace gemm_detail {
 namespace {
 
-// workgroups that add up sums riding along (64 units of 32 columns at a time: 8 arrays of an encoder layer take 416 of them, 2 to 3 us each)
-constexpr int REDUCE_WORKGROUPS = 64;
-
 template <bool HAS_ADD, bool OUT_F32, class TS>
 hipError_t launch_group(GemmGroup &g, hipStream_t st) {
     static std::atomic<bool> configured{false};
@@ -21,7 +18,7 @@ hipError_t launch_group(GemmGroup &g, hipStream_t st) {
     if (items <= 0) return hipSuccess;
     const int workgroups = items < room ? items : room;
     g.workgroups = workgroups;
-    const int sums = g.reduce.units[8] < REDUCE_WORKGROUPS ? g.reduce.units[8] : REDUCE_WORKGROUPS;
+    const int sums = g.reduce.units[8] < GROUP_SUM_WORKGROUPS ? g.reduce.units[8] : GROUP_SUM_WORKGROUPS;
     static_assert(TS::SMEM >= REDUCE_LDS, "room for a reduction");
     g.p[0].late_start = OUT_F32 ? late_start<TS>(g.p[0].accumulate, g.p[0].K, items, workgroups) : 0;
     kern<<<workgroups + sums, 256, TS::SMEM, st>>>(g);

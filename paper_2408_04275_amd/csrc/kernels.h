@@ -67,7 +67,8 @@ size_t gemm_mfma_tn_scratch(long M, long N, long K);
 // 256 x 256) computed together in one launch; up to 4, all with the same K and accumulate / c_f32.
 bool gemm_mfma_few_tiles(const GemmArgs &g);
 // reduce: when not null, sums (reduce.h) that the same launch adds up, to outputs of the gradients' type; worth it where the launch has room.
-bool gemm_mfma_group_has_room(const GemmArgs *gs, int n);
+bool gemm_mfma_group_has_room(const GemmArgs *gs, int n, const ReduceJobSet &sums);
+bool gemm_mfma_group_has_room(const GemmArgs *gs, int n, const ReduceJobSet &sums, int n_cu);
 hipError_t gemm_mfma_group(const GemmArgs *gs, int n, const ReduceJobSet *reduce, hipStream_t st);
 
 // Segment bookkeeping produced by prep_tokens():

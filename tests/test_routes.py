@@ -137,3 +137,25 @@ def test_launches_of_f32_attention_backward():
     for T, nh, nkv, d, launches in [(512, 4, 4, 64, 1), (1792, 4, 4, 64, 1), (1793, 4, 4, 64, 2), (224, 32, 32, 64, 1), (225, 32, 32, 64, 2),
                                     (8192, 4, 1, 64, 2), (8192, 32, 32, 128, 1), (9, 40000, 40000, 64, 2), (2, 40000, 40000, 128, 2)]:
         assert route(T, nh, nkv, d) == launches, (T, nh, nkv, d)
+
+
+def _encoder_sums(H, heads, d, F, T):
+    """Weight gradients of a bf16 encoder layer that are computed together, and the partial sums at the end of its backward pass."""
+    ceil = lambda a, b: -(-a // b)  # noqa: E731
+    nq = heads * d
+    products = [(m, n) for m, n in ((H, F), (F, H), (H, nq), (3 * nq, H)) if ceil(m, 256) * ceil(n, 256) <= 128]
+    norm = min(ceil(T, 4), 512) if H <= 1024 else min(T, 1024)
+    jobs = [(norm, H)] * 6 + [(ceil(T, 4 if T <= 3072 else 8 if T <= 6144 else 16), F), (ceil(T, 32), 3 * nq)]
+    return products, jobs
+
+
+# sums ride along only where they are done about when the products are: either side, as measured (us alone and along at the rule)
+@pytest.mark.parametrize("H,heads,d,F,T,along", [
+    (512, 8, 64, 2048, 300, 1), (512, 8, 64, 2048, 9536, 1), (768, 12, 64, 3072, 900, 0), (1024, 16, 64, 4096, 64, 1), (1024, 16, 64, 4096, 256, 1),
+    (1024, 16, 64, 4096, 300, 1), (1024, 16, 64, 4096, 9536, 1), (1280, 16, 80, 5120, 900, 0), (1280, 16, 80, 5120, 2304, 0), (1280, 16, 80, 5120, 4111, 1),
+    (1408, 16, 96, 6144, 300, 0), (1408, 16, 96, 6144, 900, 0), (1408, 16, 96, 6144, 2304, 1), (1536, 24, 64, 6144, 300, 0),
+    (1536, 24, 64, 6144, 1500, 0), (1536, 24, 64, 6144, 4111, 1)])
+def test_sums_ride_along_where_there_is_time(H, heads, d, F, T, along):
+    products, jobs = _encoder_sums(H, heads, d, F, T)
+    flat = lambda pairs: (C.c_int32 * (2 * len(pairs)))(*[v for p in pairs for v in p])  # noqa: E731
+    assert mm.load_library().mmtrain_route_sums_along(len(products), flat(products), T, len(jobs), flat(jobs), 256) == along
