@@ -189,9 +189,15 @@ constexpr TileCost COST_WGRAD[] = {
 // products are bound by what a unit copies into LDS per K step, which falls with the tile (96 x 128: 28 KiB instead of 32, 160 x 128: 36 instead of
 // 40).  From the cache / from HBM, us: 2304 x 1024 x 4096 in 128 x 128 (144 tiles) -> 96 x 128 (192) 27.9 -> 24.9 / 38.4 -> 31.8, 2880 x 1024 x 4096 NN
 // 30.7 -> 27.8 / 36.0 -> 32.8, 1031 x 4096 x 11008 in 192 x 128 (192) -> 160 x 128 (224) 90.1 -> 81.1 / 100.6 -> 94.9; of 67 random products of 40 and more K
-// steps the rule took one of them for 18, which became 2 to 15 % faster, and none slower than two runs of one build differ.  Below 40 steps the
-// time is less of the copies' (2304 x 1024 x 1024 11.6 -> 10.9) and the shapes stay what the parity tests of those sizes name.
+// steps the rule took one of them for 18, which became 2 to 15 % faster, and none slower than two runs of one build differ.  Another 330 of 40 steps
+// and more: from the cache 7 % faster on average, seven of them 2 % and more slower; from HBM 6 %, but with as many tiles as before, of fewer rows,
+// 7 % slower (284 x 7368 x 10048 in 174 tiles of 128 x 128 -> 96 x 128 74 -> 88 us, 442 x 8248 x 7616 in 195 of 192 x 128 -> 160 x 128 16 %), with up to
+// 15 % more 2 % slower, 15 to 30 % more 5 % faster, beyond 12 %.  So operands that come from HBM need 15 % more tiles, or a full round of them
+// (600 x 8192 x 8192 82 -> 79 us).
+// Below 40 steps, 60 products of 6 to 39: 7 % faster from the cache and 6 % from HBM on average, between 2 % slower (384 deep) and 13 % faster, with few rows
+// from HBM up to 13 % slower.  Those keep the older shapes, which the tests of short contractions name.
 constexpr int MIN_K_BETWEEN = 2560;
+constexpr double MIN_MORE_BETWEEN = 1.15;
 struct LaunchCost { double launch, rounds_power, load; };
 constexpr LaunchCost LAUNCH_ROWS = {3.4, 1.042, 0.276}, LAUNCH_WGRAD = {3.7, 1.079, 0.105};
 long tiles_of(const TileCost &t, const GemmArgs *gs, int n) {
@@ -203,18 +209,30 @@ double tiles_us(const TileCost &t, const LaunchCost &c, long tiles, int K, int n
     const double share = (double)tiles / n_cu, fill = share < 1. ? share * share : 1.;
     return c.launch + pow(ceil(share), c.rounds_power) * (t.tile + ceil_div(K, BK) * t.step * (1. + c.load * fill));
 }
+// older_us: the estimate without the two shapes between
 template <int N>
-int choose_tile(const TileCost (&table)[N], const LaunchCost &cost, const GemmArgs *gs, int n, int n_cu, double &best_us) {
+int choose_tile(const TileCost (&table)[N], const LaunchCost &cost, const GemmArgs *gs, int n, int n_cu, double &best_us, double &older_us) {
     int best = TILE_256;
+    long older_tiles = 0;
     size_t bytes = 0;
     for (int i = 0; i < n; ++i) bytes += (size_t)(gs[i].M + gs[i].N) * gs[i].K * 2;
     const bool from_hbm = bytes > FROM_HBM_BYTES;
-    for (const TileCost &t : table) {
-        if ((t.shape == TILE_160x128 || t.shape == TILE_96x128) && gs[0].K < MIN_K_BETWEEN) continue;
-        const double us = tiles_us(t, cost, tiles_of(t, gs, n), gs[0].K, n_cu);
-        // a smaller tile moves more bytes per product: only for a gain beyond the fit's error, and beyond what they cost more from HBM
-        // (operands of more than 96 MB: 1397 x 28672 x 5120 takes 336 us in 256 x 256 and 379 in 160 x 256, which the model puts 4 % ahead)
-        if (t.shape == TILE_256 || us < best_us * (best != TILE_256 ? 1. : from_hbm ? 0.95 : 0.98)) { best = t.shape; best_us = us; }
+    for (const bool between : {false, true}) {
+        if (between && gs[0].K < MIN_K_BETWEEN) break;
+        for (const TileCost &t : table) {
+            if ((t.shape == TILE_160x128 || t.shape == TILE_96x128) != between) continue;
+            const long tiles = tiles_of(t, gs, n);
+            if (between && from_hbm && tiles % n_cu && tiles < MIN_MORE_BETWEEN * older_tiles) continue;
+            const double us = tiles_us(t, cost, tiles, gs[0].K, n_cu);
+            // a smaller tile moves more bytes per product: only for a gain beyond the fit's error, and beyond what they cost more from HBM
+            // (operands of more than 96 MB: 1397 x 28672 x 5120 takes 336 us in 256 x 256 and 379 in 160 x 256, which the model puts 4 % ahead)
+            if (t.shape == TILE_256 || us < best_us * (best != TILE_256 ? 1. : from_hbm ? 0.95 : 0.98)) {
+                best = t.shape;
+                best_us = us;
+                if (!between) older_tiles = tiles;
+            }
+        }
+        if (!between) older_us = best_us;
     }
     return best;
 }
@@ -230,10 +248,14 @@ bool short_k_full_rounds(const GemmArgs *gs, int n, int n_cu) {
     const double filled = (double)tiles / ((double)ceil_div(tiles, n_cu) * n_cu);
     return filled >= (gs[0].layout == GEMM_TN ? 0.75 : 0.8);
 }
-int choose_tile(const GemmArgs *gs, int n, int n_cu, double &us) {
-    us = 0.;
+int choose_tile(const GemmArgs *gs, int n, int n_cu, double &us, double &older_us) {
+    us = older_us = 0.;
     if (short_k_full_rounds(gs, n, n_cu)) return TILE_256;
-    return gs[0].layout == GEMM_TN ? choose_tile(COST_WGRAD, LAUNCH_WGRAD, gs, n, n_cu, us) : choose_tile(COST_ROWS, LAUNCH_ROWS, gs, n, n_cu, us);
+    return gs[0].layout == GEMM_TN ? choose_tile(COST_WGRAD, LAUNCH_WGRAD, gs, n, n_cu, us, older_us) : choose_tile(COST_ROWS, LAUNCH_ROWS, gs, n, n_cu, us, older_us);
+}
+int choose_tile(const GemmArgs *gs, int n, int n_cu) {
+    double us, older_us;
+    return choose_tile(gs, n, n_cu, us, older_us);
 }
 
 // An input gradient (NN) with few tiles and a very long K, cut along K as a whole: `splits` chunks of 256 x 256 tiles through
@@ -248,6 +270,10 @@ int choose_tile(const GemmArgs *gs, int n, int n_cu, double &us) {
 // 4096 x 12288 (QKV) 116 -> 100, 1031 x 4096 x 11008 104 -> 92, 366 x 4096 x 12288 87 -> 50 in eight, 1031 x 1280 x 22016 129 -> 67 in eight, 2304 x
 // 1024 x 11008 93 -> 62 in six; from the cache the first three 185 -> 164, 98 -> 98, 88 -> 91.  With two chunks it is about even: 1500 x 4096 x 22016
 // 248 -> 238 (from the cache 210 -> 222), 2047 x 4096 x 22016 304 -> 266, 700 x 8192 x 13824 145 -> 157.  Up to K = 8192 the tile shapes are ahead.
+// The estimate compared with leaves 160 x 128 and 96 x 128 out (gemm_mfma_plan): these fall furthest behind it from HBM.  Cut -> tile, from the
+// cache / from HBM: 1031 x 2048 x 11008 in six 57 -> 59 / 59 -> 82, 1984 x 1280 x 14336 72 -> 83 / 77 -> 108, 576 x 5120 x 11264 in four 74 -> 68 / 77 -> 101,
+// 1088 x 4096 x 9728 in three 85 -> 80 / 88 -> 98.  A cut in two is weighed against them: 640 x 8192 x 13824 154 -> 124 / 154 -> 139, 576 x 8192 x 27648
+// 286 -> 259 / 288 -> 263.
 int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
     if (g.layout != GEMM_NN || g.bias || g.residual || !g.split_ws) return 1;
     const long tiles = (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE);
@@ -272,8 +298,8 @@ int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
 constexpr double SUM_UNIT_US = 2., SUM_ROW_US = 0.005, SUMS_LAUNCH_US = 8.;
 bool gemm_mfma_group_has_room(const GemmArgs *gs, int n, const ReduceJobSet &sums, int n_cu) {
     if (n <= 0) return false;
-    double us, sum_us = 0.;
-    const int shape = choose_tile(gs, n, n_cu, us);
+    double sum_us = 0.;
+    const int shape = choose_tile(gs, n, n_cu);
     for (int j = 0; j < 8; ++j) sum_us += (sums.units[j + 1] - sums.units[j]) * (SUM_UNIT_US + SUM_ROW_US * sums.rows[j]);
     sum_us /= std::max(1, std::min(sums.units[8], GROUP_SUM_WORKGROUPS));
     for (const TileCost &t : COST_WGRAD)
@@ -300,17 +326,17 @@ hipError_t gemm_mfma_group(const GemmArgs *gs, int n, const ReduceJobSet *reduce
     int n_cu = 0;
     hipError_t e = compute_units(n_cu);
     if (e != hipSuccess) return e;
-    double us;
-    return launch_tn(choose_tile(gs, n, n_cu, us), p, n, reduce, st);
+    return launch_tn(choose_tile(gs, n, n_cu), p, n, reduce, st);
 }
 
 GemmPlan gemm_mfma_plan(const GemmArgs &g, int n_cu) {
     GemmPlan plan = {TILE_256, TILE, TILE, 0, 1, g.K};
     int chunks = gemm_mfma_tail_splits(g, n_cu, plan.tail_tiles);
     if (plan.tail_tiles == 0) {
-        double us;
-        const int shape = choose_tile(&g, 1, n_cu, us);
-        chunks = few_tile_splits(g, n_cu, us);
+        double us, older_us;
+        const int shape = choose_tile(&g, 1, n_cu, us, older_us);
+        chunks = few_tile_splits(g, n_cu, older_us);
+        if (chunks == 2) chunks = few_tile_splits(g, n_cu, us);
         if (chunks == 1) plan.shape = shape;
     }
     for (const TileCost &t : COST_ROWS)

@@ -159,3 +159,20 @@ def test_sums_ride_along_where_there_is_time(H, heads, d, F, T, along):
     products, jobs = _encoder_sums(H, heads, d, F, T)
     flat = lambda pairs: (C.c_int32 * (2 * len(pairs)))(*[v for p in pairs for v in p])  # noqa: E731
     assert mm.load_library().mmtrain_route_sums_along(len(products), flat(products), T, len(jobs), flat(jobs), 256) == along
+
+
+# long input gradients: cut in three and more, which beats the tiles of 96 and 160 rows where they would fit too, but not in two, which does not
+@pytest.mark.parametrize("M,N,K,route", [
+    (1031, 2048, 11008, (256, 256, 0, 6)), (1984, 1280, 14336, (256, 256, 0, 6)), (576, 5120, 11264, (256, 256, 0, 4)), (1088, 4096, 9728, (256, 256, 0, 3)),
+    (768, 3072, 12800, (256, 256, 0, 7)), (640, 8192, 13824, (160, 128, 0, 1)), (576, 8192, 27648, (160, 128, 0, 1)), (2304, 1024, 4096, (96, 128, 0, 1))])
+def test_cuts_against_the_tiles_between(M, N, K, route):
+    assert gemm_route(mm.GEMM_NN, M, N, K, 1 << 40) == route
+
+
+# operands beyond 96 MB: these tiles need 15 % more of them than the older shapes, or a full round
+@pytest.mark.parametrize("layout", [mm.GEMM_NT, mm.GEMM_NN])
+@pytest.mark.parametrize("M,N,K,tile", [
+    (284, 7368, 10048, "128x128"), (442, 8248, 7616, "192x128"), (300, 12288, 4096, "192x128"), (600, 8192, 8192, "160x128"), (520, 4096, 11008, "96x128"),
+    (1031, 4096, 11008, "160x128"), (300, 11008, 4096, "160x128")])
+def test_tiles_between_from_hbm(layout, M, N, K, tile):
+    assert "%dx%d" % gemm_route(layout, M, N, K)[:2] == tile
