@@ -362,21 +362,25 @@ __device__ __forceinline__ void store_rows(uint8_t *stage, const f32x16 (&acc)[C
             *reinterpret_cast<uint2 *>(stage + l32 * RS + (32 * c + 8 * gq + 4 * half) * 2) = w;
         }
     const int r0 = lane / LPR, cb = (lane % LPR) * 16;
-    float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    uint4 v[32 / RPI];                                 // read and stored without a branch in between: callers without sums paid up to 3 % for one
 #pragma unroll
     for (int i = 0; i < 32 / RPI; ++i) {
         const int r = i * RPI + r0;
-        const uint4 v = *reinterpret_cast<const uint4 *>(stage + r * RS + cb);
-        if (r < rows_valid && cb / 2 < dh) {
-            *reinterpret_cast<uint4 *>(dst + (long)r * ld + cb / 2) = v;
-            if (SUMS && colsum) {
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { sum[2 * e] += __uint_as_float(w[e] << 16); sum[2 * e + 1] += __uint_as_float(w[e] & 0xffff0000u); }
-            }
-        }
+        v[i] = *reinterpret_cast<const uint4 *>(stage + r * RS + cb);
+        if (r < rows_valid && cb / 2 < dh) *reinterpret_cast<uint4 *>(dst + (long)r * ld + cb / 2) = v[i];
     }
     if (SUMS && colsum) {
+        float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 32 / RPI; ++i) {
+            const bool valid = i * RPI + r0 < rows_valid;
+            const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                sum[2 * e] += valid ? __uint_as_float(w[e] << 16) : 0.f;
+                sum[2 * e + 1] += valid ? __uint_as_float(w[e] & 0xffff0000u) : 0.f;
+            }
+        }
 #pragma unroll
         for (int o = LPR; o < 64; o *= 2)
 #pragma unroll
