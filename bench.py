@@ -142,7 +142,8 @@ def hbm_kernel_bytes(shape, T):
     rope_cols = (shape.n_heads + shape.n_kv_heads) * shape.head_dim
     return {
         "norm_fwd": 2 * (2 * A + 2 * T * 4),                                 # two launches: read x, write h, statistics
-        "norm_bwd": 2 * (4 * A + 2 * T * 4),                                 # two launches: read d_out, x, d_res, write d_in
+        # two launches: read d_out, x, d_res, write d_in (at least: decoders on short packs may read d_out in fp32 parts)
+        "norm_bwd": 2 * (4 * A + 2 * T * 4),
         "rope": 0 if enc else 2 * T * rope_cols * e + T * shape.head_dim * 4,   # q and k in place + the (cos, sin) table
         "act_fwd": T * (F1 + F) * e,                                         # read the pre-activation, write m
         "act_bwd": T * (F + 2 * F1) * e,                                     # read d_m and the pre-activation, write its gradient

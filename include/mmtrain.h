@@ -211,6 +211,12 @@ MMTRAIN_API const char *mmtrain_status_string(int status);
  * Process-wide, not thread-safe; event objects are created on demand and
  * reused.  Used by the benchmark to obtain per-kernel launch durations inside
  * the timed region.
+ * A class counts launches, and work that another class's launch does counts
+ * there: on fp32 decoders rotation, SwiGLU and its gradient are mostly part of the
+ * products (ROPE, ACT_FWD and ACT_BWD then report nothing); GEMM_TN holds the gain and
+ * bias gradients' sums where they are added up by the launch of the weight
+ * gradients; NORM_BWD of short packs the sum over an input gradient's parts,
+ * where that is cut along K (fp32 parts are then read instead of the gradient).
  * ------------------------------------------------------------------------ */
 typedef enum {
     MMTRAIN_PROF_GEMM_NT = 0, MMTRAIN_PROF_GEMM_NN = 1, MMTRAIN_PROF_GEMM_TN = 2,

@@ -362,12 +362,12 @@ hipError_t attn_f32_fwd(const AttnArgs &a, hipStream_t st) {
 }
 
 // One launch where dK/dV alone leaves the chip part empty: dQ fills it, and D from the rows at hand costs dK/dV one more read and spares it
-// the wait for dQ (512 tokens and 4 heads of 64 in four segments, 128 workgroups: 18.1 -> 11.2 us).  With more workgroups of 64-wide heads that
-// read is work on a full chip.  One launch against two, mean over 3 to 21 packs of one to eight segments each (dK/dV workgroups: ratio): 192: 0.88,
-// 256: 0.96, 320: 0.87, 384: 0.90, 448: 0.97, 512: 1.05, 640: 0.99, 768: 1.01, 1024: 1.09; 16 heads, 8192 tokens in one segment 6547 us against 5679.
-// Single packs scatter around these: of 273 the rule is 8 % faster on average than two launches, and seven are 2.5 % or more slower, 16 heads on 4 over
-// 1019 tokens in eight segments (48.4 -> 55.9 us) the most.
-// 128-wide heads, four wavefronts per workgroup, gain at every length (32 heads, 96 tokens 27.2 -> 22.8 us, 8192 38629 -> 36478).
+// the wait for dQ (512 tokens and 4 heads of 64 in four segments, 128 workgroups: 18.1 -> 11.2 us).  With more workgroups of 64-wide heads
+// that read is work on a full chip.  One launch against two, mean over 3 to 21 packs of one to eight segments each (dK/dV workgroups:
+// ratio): 192: 0.88, 256: 0.96, 320: 0.87, 384: 0.90, 448: 0.97, 512: 1.05, 640: 0.99, 768: 1.01, 1024: 1.09; 16 heads, 8192 tokens in one
+// segment 6547 us against 5679. Single packs scatter around these: of 273 the rule is 8 % faster on average than two launches, and seven
+// are 2.5 % or more slower, 16 heads on 4 over 1019 tokens in eight segments (48.4 -> 55.9 us) the most. 128-wide heads, four wavefronts
+// per workgroup, gain at every length (32 heads, 96 tokens 27.2 -> 22.8 us, 8192 38629 -> 36478).
 constexpr long ONE_LAUNCH_WORKGROUPS = 448;
 static bool one_launch(int T, int nkv, int d) { return d != 64 || (long)ceil_div(T, 16) * nkv <= ONE_LAUNCH_WORKGROUPS; }
 int attn_f32_bwd_launches(int T, int nh, int nkv, int d) { return one_launch(T, nkv, d) ? ceil_div(nkv + nh, 65535) : 2; }

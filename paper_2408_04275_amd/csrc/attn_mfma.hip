@@ -203,7 +203,9 @@ typedef __attribute__((ext_vector_type(8))) short shortx8;
 // (first + i) of a tile covering its rows (first + i) * 512 / D ...  What depends on the lane is computed once
 // (init); a copy then costs one addition.  Rows at or beyond the end of the tensor read as zero (the descriptor's
 // bounds check), and so do the columns from row_elems on (a head narrower than the tile): their lanes carry an
-// offset of 2 GiB, which no tensor reaches (the launchers check), and the sum with the tile's offset cannot wrap.
+// offset of 2 GiB, which no tensor reaches (the launchers check), and the sum with the offset of a tile that starts in front of the
+// tensor's end cannot wrap.  The forward kernel's K tile may start up to 31 rows behind it: with rows of over 1024 elements and a tensor just under
+// 2 GiB those columns wrap around to its first rows, which exist, and the scores of such keys are masked.
 template <int D, int N>
 struct RowCopier {
     static constexpr int UPR = D / 8, ROWS_PER_COPY = 1024 / (2 * D);

@@ -563,9 +563,9 @@ __global__ __launch_bounds__(256) void norm_bwd_wave_kernel(const T *__restrict_
 
 // Built for RMSNorm rows of more than NORM_BWD_WAVE_H and at most SPLIT_MAX_H columns; in front of other normalisations the parts are
 // summed by a kernel of their own.  Backward of a frozen decoder layer, apart -> together, us: 4096 wide, 300, 700, 1031, 1400, 2047 tokens
-// 244.4 -> 242.1, 363.3 -> 357.4, 474.4 -> 468.3, 636.3 -> 633.4, 807.8 -> 795.9; 2048 wide (ffn 11008), 300, 1400 154.2 -> 151.2,
-// 355.6 -> 350.7.  Wider rows take four column chunks per thread, which leaves registers for one wavefront per SIMD (232 -> 352), and lose:
-// 5120 wide, 300, 1031 tokens 327.4 -> 330.8, 676.0 -> 681.7; 6144, 300 387.1 -> 390.3; 8192, 300 684.1 -> 688.4.
+// 244.4 -> 242.1, 363.3 -> 357.4, 474.4 -> 468.3, 636.3 -> 633.4, 807.8 -> 795.9; 2048 wide (ffn 11008), 300, 1400 154.2 -> 151.2, 355.6 ->
+// 350.7.  Wider rows take four column chunks per thread, which leaves registers for one wavefront per SIMD (232 -> 352), and lose: 5120
+// wide, 300, 1031 tokens 327.4 -> 330.8, 676.0 -> 681.7; 6144, 300 387.1 -> 390.3; 8192, 300 684.1 -> 688.4.
 constexpr int SPLIT_MAX_H = 4096;
 bool norm_bwd_adds_parts(int dtype, bool layernorm, int H) { return dtype == DT_BF16 && !layernorm && H > NORM_BWD_WAVE_H && H <= SPLIT_MAX_H; }
 

@@ -638,13 +638,14 @@ void gemm_mfma_kernel(const ARG arg) {
 
     if constexpr (OUT_F32) {
         // ---- fp32 epilogue (never together with bias or residual): one row block of 16 rows at a time through this wavefront's own
-        // staging area, so that loads and stores cover whole rows of 64 RB bytes and whole cache lines (64-byte pieces straight from the accumulators leave the
-        // L2 half filled: 29 % more bytes written).  A wavefront's LDS instructions execute in order, so neither the read-back of a
-        // block nor the writes of the next one into the same place wait for what stands in front of them; the compiler is only kept
-        // from reordering them.  The previous contents are fetched a row block ahead of their use, in front of the stores in between:
-        // memory operations retire in order, and a load behind a store returns only when that store has been acknowledged.  Every row
-        // block has a descriptor of its own, so that 32-bit offsets reach rows of up to 2^26 elements; lanes outside the matrix carry an
-        // offset that the descriptor's bounds check turns into nothing, without a branch.  22016 x 4096, 1031 tokens added to fp32 gradients: 308 -> 257 us, 300 tokens 223 -> 172 (in 32-row chunks whose loads stood behind stores).
+        // staging area, so that loads and stores cover whole rows of 64 RB bytes and whole cache lines (64-byte pieces straight from the
+        // accumulators leave the L2 half filled: 29 % more bytes written).  A wavefront's LDS instructions execute in order, so neither the
+        // read-back of a block nor the writes of the next one into the same place wait for what stands in front of them; the compiler is
+        // only kept from reordering them.  The previous contents are fetched a row block ahead of their use, in front of the stores in
+        // between: memory operations retire in order, and a load behind a store returns only when that store has been acknowledged.  Every
+        // row block has a descriptor of its own, so that 32-bit offsets reach rows of up to 2^26 elements; lanes outside the matrix carry
+        // an offset that the descriptor's bounds check turns into nothing, without a branch.  22016 x 4096, 1031 tokens added to fp32
+        // gradients: 308 -> 257 us, 300 tokens 223 -> 172 (in 32-row chunks whose loads stood behind stores).
         const uint32_t pitch = p.compact ? 256u : (uint32_t)p.ldc;
         const int wm0 = __builtin_amdgcn_readfirstlane(wm) * 16 * RA;         // first row of this wavefront
         float *const out = reinterpret_cast<float *>(p.C) + (size_t)wm0 * pitch +

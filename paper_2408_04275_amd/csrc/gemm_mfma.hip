@@ -162,40 +162,41 @@ bool gemm_mfma_few_tiles(const GemmArgs &g) {
            (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE) <= 128;
 }
 
-// Tile shape of a product, or of a group of products of one layout and contraction.  The 256 x 256 tile does the most
-// arithmetic per byte fetched, but a product with few of them leaves most compute units idle (one image of 576 patches through
-// a 1024 x 1024 linear: 12 tiles) and one with a few more than a whole number of rounds runs a nearly empty last one.  The rule
-// is the time each shape needs: every compute unit works off ceil(tiles / compute units) tiles one after the other, a tile
-// costs a start and epilogue plus so much per 64-deep K step, and a step gets slower as the chip fills (clock, L2).  The
-// constants (us) are least-squares fits to 150 random shapes each for the forward and input-gradient products (250 - 12000
-// rows, widths 1024 - 22016; nine tile shapes) and for the weight gradients (512 - 5120 square to oblong, K = 250 - 12000; five
-// shapes, A and B both strided): the shape the rule picked was 0.03 % / 0.07 % slower than the best of them on average, 2 % / 7 %
-// at worst (the two shapes between, 160 x 128 and 96 x 128, came later: see MIN_K_BETWEEN).  The K loop of one round and the fp32 epilogue have become faster since; another 140 and 60 random shapes, half of them from HBM:
-// 0.4 % / 0.5 % on average, 18 % (345 x 2752 x 9592 from HBM, 78 us in 64 x 64) / 9 % (3944 x 1208 x 379, 11.4 us in 256 x 128) at worst.  Against 256 x 256 throughout it measured 65.9 -> 13.5 us on the 576 x 1024 x 4096 forward product (64 x 64 tiles),
-// 22.6 -> 14.8 us on 2304 x 3072 x 1024 (256 x 128), 72.2 -> 65.6 us on 9536 x 1024 x 4096 (160 x 256), and 58.3 -> 25.8 us on
-// the 4096 x 1024 x 2880 weight gradient, which was cut along K before (128 x 128); products of whole rounds of large tiles stay
-// where they were.
+// Tile shape of a product, or of a group of products of one layout and contraction.  The 256 x 256 tile does the most arithmetic per byte
+// fetched, but a product with few of them leaves most compute units idle (one image of 576 patches through a 1024 x 1024 linear: 12 tiles)
+// and one with a few more than a whole number of rounds runs a nearly empty last one.  The rule is the time each shape needs: every compute
+// unit works off ceil(tiles / compute units) tiles one after the other, a tile costs a start and epilogue plus so much per 64-deep K step,
+// and a step gets slower as the chip fills (clock, L2).  The constants (us) are least-squares fits to 150 random shapes each for the
+// forward and input-gradient products (250 - 12000 rows, widths 1024 - 22016; nine tile shapes) and for the weight gradients (512 - 5120
+// square to oblong, K = 250 - 12000; five shapes, A and B both strided): the shape the rule picked was 0.03 % / 0.07 % slower than the best
+// of them on average, 2 % / 7 % at worst (the two shapes between, 160 x 128 and 96 x 128, came later: see MIN_K_BETWEEN).  The K loop of
+// one round and the fp32 epilogue have become faster since; another 140 and 60 random shapes, half of them from HBM: 0.4 % / 0.5 % on
+// average, 18 % (345 x 2752 x 9592 from HBM, 78 us in 64 x 64) / 9 % (3944 x 1208 x 379, 11.4 us in 256 x 128) at worst.  Against 256 x 256
+// throughout it measured 65.9 -> 13.5 us on the 576 x 1024 x 4096 forward product (64 x 64 tiles), 22.6 -> 14.8 us on 2304 x 3072 x 1024
+// (256 x 128), 72.2 -> 65.6 us on 9536 x 1024 x 4096 (160 x 256), and 58.3 -> 25.8 us on the 4096 x 1024 x 2880 weight gradient, which was
+// cut along K before (128 x 128); products of whole rounds of large tiles stay where they were.
 constexpr size_t FROM_HBM_BYTES = size_t(96) << 20;     // operands beyond this mostly come from HBM and not from the memory-side cache
 struct TileCost { int shape, bm, bn; double tile, step; };
 constexpr TileCost COST_ROWS[] = {                     // K-contiguous A
     {TILE_256, 256, 256, 4.13, 0.958}, {TILE_224, 224, 256, 2.92, 0.866}, {TILE_192, 192, 256, 2.19, 0.778},
     {TILE_160, 160, 256, 1.37, 0.694}, {TILE_256x128, 256, 128, 1.15, 0.575}, {TILE_192x128, 192, 128, 1.01, 0.462},
-    {TILE_160x128, 160, 128, 0.89, 0.405}, {TILE_128, 128, 128, 0.77, 0.348}, {TILE_96x128, 96, 128, 0.60, 0.295}, {TILE_64x128, 64, 128, 0.0, 0.223}, {TILE_64, 64, 64, 0.0, 0.142}};
+    {TILE_160x128, 160, 128, 0.89, 0.405}, {TILE_128, 128, 128, 0.77, 0.348}, {TILE_96x128, 96, 128, 0.60, 0.295},
+    {TILE_64x128, 64, 128, 0.0, 0.223}, {TILE_64, 64, 64, 0.0, 0.142}};
 constexpr TileCost COST_WGRAD[] = {
     {TILE_256, 256, 256, 4.05, 1.044}, {TILE_256x128, 256, 128, 2.10, 0.618}, {TILE_128, 128, 128, 1.49, 0.389},
     {TILE_64x128, 64, 128, 0.10, 0.254}, {TILE_64, 64, 64, 0.0, 0.176}};
 
-// 160 x 128 and 96 x 128 stand between the older shapes, where 128 x 128 or 192 x 128 leave a quarter to a half of the compute units idle: such
-// products are bound by what a unit copies into LDS per K step, which falls with the tile (96 x 128: 28 KiB instead of 32, 160 x 128: 36 instead of
-// 40).  From the cache / from HBM, us: 2304 x 1024 x 4096 in 128 x 128 (144 tiles) -> 96 x 128 (192) 27.9 -> 24.9 / 38.4 -> 31.8, 2880 x 1024 x 4096 NN
-// 30.7 -> 27.8 / 36.0 -> 32.8, 1031 x 4096 x 11008 in 192 x 128 (192) -> 160 x 128 (224) 90.1 -> 81.1 / 100.6 -> 94.9; of 67 random products of 40 and more K
-// steps the rule took one of them for 18, which became 2 to 15 % faster, and none slower than two runs of one build differ.  Another 330 of 40 steps
-// and more: from the cache 7 % faster on average, seven of them 2 % and more slower; from HBM 6 %, but with as many tiles as before, of fewer rows,
-// 7 % slower (284 x 7368 x 10048 in 174 tiles of 128 x 128 -> 96 x 128 74 -> 88 us, 442 x 8248 x 7616 in 195 of 192 x 128 -> 160 x 128 16 %), with up to
-// 15 % more 2 % slower, 15 to 30 % more 5 % faster, beyond 12 %.  So operands that come from HBM need 15 % more tiles, or a full round of them
-// (600 x 8192 x 8192 82 -> 79 us).
-// Below 40 steps, 60 products of 6 to 39: 7 % faster from the cache and 6 % from HBM on average, between 2 % slower (384 deep) and 13 % faster, with few rows
-// from HBM up to 13 % slower.  Those keep the older shapes, which the tests of short contractions name.
+// 160 x 128 and 96 x 128 stand between the older shapes, where 128 x 128 or 192 x 128 leave a quarter to a half of the compute units idle:
+// such products are bound by what a unit copies into LDS per K step, which falls with the tile (96 x 128: 28 KiB instead of 32, 160 x 128:
+// 36 instead of 40).  From the cache / from HBM, us: 2304 x 1024 x 4096 in 128 x 128 (144 tiles) -> 96 x 128 (192) 27.9 -> 24.9 / 38.4 ->
+// 31.8, 2880 x 1024 x 4096 NN 30.7 -> 27.8 / 36.0 -> 32.8, 1031 x 4096 x 11008 in 192 x 128 (192) -> 160 x 128 (224) 90.1 -> 81.1 / 100.6
+// -> 94.9; of 67 random products of 40 and more K steps the rule took one of them for 18, which became 2 to 15 % faster, and none slower
+// than two runs of one build differ.  Another 330 of 40 steps and more: from the cache 7 % faster on average, seven of them 2 % and more
+// slower; from HBM 6 %, but with as many tiles as before, of fewer rows, 7 % slower (284 x 7368 x 10048 in 174 tiles of 128 x 128 -> 96 x
+// 128 74 -> 88 us, 442 x 8248 x 7616 in 195 of 192 x 128 -> 160 x 128 16 %), with up to 15 % more 2 % slower, 15 to 30 % more 5 % faster,
+// beyond 12 %.  So operands that come from HBM need 15 % more tiles, or a full round of them (600 x 8192 x 8192 82 -> 79 us). Below 40
+// steps, 60 products of 6 to 39: 7 % faster from the cache and 6 % from HBM on average, between 2 % slower (384 deep) and 13 % faster, with
+// few rows from HBM up to 13 % slower.  Those keep the older shapes, which the tests of short contractions name.
 constexpr int MIN_K_BETWEEN = 2560;
 constexpr double MIN_MORE_BETWEEN = 1.15;
 struct LaunchCost { double launch, rounds_power, load; };
@@ -258,22 +259,21 @@ int choose_tile(const GemmArgs *gs, int n, int n_cu) {
     return choose_tile(gs, n, n_cu, us, older_us);
 }
 
-// An input gradient (NN) with few tiles and a very long K, cut along K as a whole: `splits` chunks of 256 x 256 tiles through
-// scratch, and a kernel that adds them up.  The smaller tile shapes fill the chip too, but at half or a quarter of the
-// arithmetic per byte on every K step; the cut pays for its scratch traffic and second launch once, so it wins where K is long.
-// The rule compares choose_tile's estimate with the same model for K / splits, plus the reduction (its launch and 0.345 us per
-// MB), and asks for 5 % as both are fits.  The tile shapes' constants hold for operands that the memory-side cache keeps (256 MB);
-// from HBM they take 1.1 to 1.6 times as long (the 256 x 256 chunks, each of which one XCD's L2 reads once, do not), so operands
-// of more than 96 MB, most of which are a large layer's weights, count against them: their estimate then stands at 1.15 times itself
-// instead of 0.95.  Measured with operands from
-// HBM, tile shape -> cut: 1031 x 4096 x 22016 (the gate / up input gradient of a short pack) 209 -> 169 us in three chunks, 1031 x
-// 4096 x 12288 (QKV) 116 -> 100, 1031 x 4096 x 11008 104 -> 92, 366 x 4096 x 12288 87 -> 50 in eight, 1031 x 1280 x 22016 129 -> 67 in eight, 2304 x
-// 1024 x 11008 93 -> 62 in six; from the cache the first three 185 -> 164, 98 -> 98, 88 -> 91.  With two chunks it is about even: 1500 x 4096 x 22016
-// 248 -> 238 (from the cache 210 -> 222), 2047 x 4096 x 22016 304 -> 266, 700 x 8192 x 13824 145 -> 157.  Up to K = 8192 the tile shapes are ahead.
-// The estimate compared with leaves 160 x 128 and 96 x 128 out (gemm_mfma_plan): these fall furthest behind it from HBM.  Cut -> tile, from the
-// cache / from HBM: 1031 x 2048 x 11008 in six 57 -> 59 / 59 -> 82, 1984 x 1280 x 14336 72 -> 83 / 77 -> 108, 576 x 5120 x 11264 in four 74 -> 68 / 77 -> 101,
-// 1088 x 4096 x 9728 in three 85 -> 80 / 88 -> 98.  A cut in two is weighed against them: 640 x 8192 x 13824 154 -> 124 / 154 -> 139, 576 x 8192 x 27648
-// 286 -> 259 / 288 -> 263.
+// An input gradient (NN) with few tiles and a very long K, cut along K as a whole: `splits` chunks of 256 x 256 tiles through scratch, and
+// a kernel that adds them up.  The smaller tile shapes fill the chip too, but at half or a quarter of the arithmetic per byte on every K
+// step; the cut pays for its scratch traffic and second launch once, so it wins where K is long. The rule compares choose_tile's estimate
+// with the same model for K / splits, plus the reduction (its launch and 0.345 us per MB), and asks for 5 % as both are fits.  The tile
+// shapes' constants hold for operands that the memory-side cache keeps (256 MB); from HBM they take 1.1 to 1.6 times as long (the 256 x 256
+// chunks, each of which one XCD's L2 reads once, do not), so operands of more than 96 MB, most of which are a large layer's weights, count
+// against them: their estimate then stands at 1.15 times itself instead of 0.95.  Measured with operands from HBM, tile shape -> cut: 1031
+// x 4096 x 22016 (the gate / up input gradient of a short pack) 209 -> 169 us in three chunks, 1031 x 4096 x 12288 (QKV) 116 -> 100, 1031 x
+// 4096 x 11008 104 -> 92, 366 x 4096 x 12288 87 -> 50 in eight, 1031 x 1280 x 22016 129 -> 67 in eight, 2304 x 1024 x 11008 93 -> 62 in
+// six; from the cache the first three 185 -> 164, 98 -> 98, 88 -> 91.  With two chunks it is about even: 1500 x 4096 x 22016 248 -> 238
+// (from the cache 210 -> 222), 2047 x 4096 x 22016 304 -> 266, 700 x 8192 x 13824 145 -> 157.  Up to K = 8192 the tile shapes are ahead.
+// The estimate compared with leaves 160 x 128 and 96 x 128 out (gemm_mfma_plan): these fall furthest behind it from HBM.  Cut -> tile, from
+// the cache / from HBM: 1031 x 2048 x 11008 in six 57 -> 59 / 59 -> 82, 1984 x 1280 x 14336 72 -> 83 / 77 -> 108, 576 x 5120 x 11264 in
+// four 74 -> 68 / 77 -> 101, 1088 x 4096 x 9728 in three 85 -> 80 / 88 -> 98.  A cut in two is weighed against them: 640 x 8192 x 13824 154
+// -> 124 / 154 -> 139, 576 x 8192 x 27648 286 -> 259 / 288 -> 263.
 int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
     if (g.layout != GEMM_NN || g.bias || g.residual || !g.split_ws) return 1;
     const long tiles = (long)ceil_div(g.M, TILE) * ceil_div(g.N, TILE);
@@ -290,11 +290,12 @@ int few_tile_splits(const GemmArgs &g, int n_cu, double best_us) {
 
 // Sums ride along where the launch leaves compute units without a tile, no full round or a last one that is at most three quarters full,
 // and where they are done about when that round is.  The few workgroups that add them up take longer than a launch of their own would: a
-// unit of 32 columns about 2 us of latency and 5 ns per row.  What they spare is that launch and its run, 8 us together (measured: 2 to 20).
-// Backward pass of an encoder layer, alone -> along, us: 512 wide, 300 and 3000 tokens 76.4 -> 74.2, 153.7 -> 146.0; 1024 wide, 900 and 9536
-// 139.6 -> 134.1, 627 -> 619; 1280 wide (600 tiles in 2.34 rounds), 900, 2304 and 6000 202 -> 221, 314 -> 317, 664 -> 651; 1408 and 1536 wide, whose
-// feed-forward gradients do not take part, 300, 900, 1500 and 2304 tokens 144 -> 155, 238.5 -> 252, 306 -> 308, 410 -> 399.  In those, and in 512, 1536 and 2048
-// wide decoder layers, 64 to 9536 tokens, nothing that rides along by this rule was slower than alone by more than two runs of one build differ.
+// unit of 32 columns about 2 us of latency and 5 ns per row.  What they spare is that launch and its run, 8 us together (measured: 2 to
+// 20). Backward pass of an encoder layer, alone -> along, us: 512 wide, 300 and 3000 tokens 76.4 -> 74.2, 153.7 -> 146.0; 1024 wide, 900
+// and 9536 139.6 -> 134.1, 627 -> 619; 1280 wide (600 tiles in 2.34 rounds), 900, 2304 and 6000 202 -> 221, 314 -> 317, 664 -> 651; 1408
+// and 1536 wide, whose feed-forward gradients do not take part, 300, 900, 1500 and 2304 tokens 144 -> 155, 238.5 -> 252, 306 -> 308, 410 ->
+// 399.  In those, and in 512, 1536 and 2048 wide decoder layers, 64 to 9536 tokens, nothing that rides along by this rule was slower than
+// alone by more than two runs of one build differ.
 constexpr double SUM_UNIT_US = 2., SUM_ROW_US = 0.005, SUMS_LAUNCH_US = 8.;
 bool gemm_mfma_group_has_room(const GemmArgs *gs, int n, const ReduceJobSet &sums, int n_cu) {
     if (n <= 0) return false;

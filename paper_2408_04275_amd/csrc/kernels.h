@@ -98,8 +98,8 @@ struct AttnArgs {
     const float2 *rope_cs;
     // MFMA path, backward, grouped heads: scratch for fp32 partial sums of dK and dV (may be null), [parts][T][2 nkv d]
     float *dkv_part; size_t dkv_part_bytes;
-    // MFMA path, backward, heads of up to COLSUM_HEAD features, one query head per key/value head: when not null, receives the column sums of d_qkv over every 32 tokens,
-    // [ceil(T / 32)][ld_qkv] fp32 (the gradient of the bias that qkv has)
+    // MFMA path, backward, heads of up to COLSUM_HEAD features, one query head per key/value head: when not null, receives the column sums
+    // of d_qkv over every 32 tokens, [ceil(T / 32)][ld_qkv] fp32 (the gradient of the bias that qkv has)
     float *colsum;
     int dkv_parts;              // workgroups that share a group's query heads; set by attn_mfma_bwd
     // MFMA path: dispatch order of the query tiles (256 queries: forward, dQ) and of the key tiles (128

@@ -40,7 +40,7 @@ def test_backward_workspace_holds_nothing_that_no_kernel_writes():
         activations = 2 * T * (F + 2 * F + 2 * H + nh * d + (nh + 2 * nkv) * d)
         bound = activations + 4 * T * nh + 3 * 4 * 1024 * H + 256 * 65536 * 4 + 16 * 256
         assert mm.mmtrain_layer_workspace_bytes(desc, T, 4, 1) <= bound, T
-    # an encoder layer on a short pack: six arrays of partial sums, column sums in slabs of four rows, scratch for at most eight chunks
+    # an encoder layer on a short pack: six arrays of partial sums, column sums in slabs of four rows (QKV's as wider heads need them), scratch for at most eight chunks
     # of a 512 x 1024 input gradient
     desc = mm.make_desc(*SHAPES["vit"])
     T, H, F = 512, 1024, 4096
