@@ -194,11 +194,13 @@ constexpr TileCost COST_WGRAD[] = {
 // than two runs of one build differ.  Another 330 of 40 steps and more: from the cache 7 % faster on average, seven of them 2 % and more
 // slower; from HBM 6 %, but with as many tiles as before, of fewer rows, 7 % slower (284 x 7368 x 10048 in 174 tiles of 128 x 128 -> 96 x
 // 128 74 -> 88 us, 442 x 8248 x 7616 in 195 of 192 x 128 -> 160 x 128 16 %), with up to 15 % more 2 % slower, 15 to 30 % more 5 % faster,
-// beyond 12 %.  So operands that come from HBM need 15 % more tiles, or a full round of them (600 x 8192 x 8192 82 -> 79 us). Below 40
-// steps, 60 products of 6 to 39: 7 % faster from the cache and 6 % from HBM on average, between 2 % slower (384 deep) and 13 % faster, with
-// few rows from HBM up to 13 % slower.  Those keep the older shapes, which the tests of short contractions name.
+// beyond 12 %; six and seven row tiles instead of five and six, below 700 rows, 1 % slower (520 x 4096 x 14336 92 -> 98 us) where those of
+// longer ones gain.  So operands that come from HBM need 15 % more tiles, 22 % up to 1024 rows, or a full round of them (600 x 8192 x 8192
+// 82 -> 79 us).  Below 40 steps, 60 products of 6 to 39: 7 % faster from the cache and 6 % from HBM on average, between 2 % slower (384
+// deep) and 13 % faster, with few rows from HBM up to 13 % slower.  Those keep the older shapes, which the tests of short contractions
+// name.
 constexpr int MIN_K_BETWEEN = 2560;
-constexpr double MIN_MORE_BETWEEN = 1.15;
+constexpr double MIN_MORE_BETWEEN = 1.15, MIN_MORE_FEW_ROWS = 1.22;
 struct LaunchCost { double launch, rounds_power, load; };
 constexpr LaunchCost LAUNCH_ROWS = {3.4, 1.042, 0.276}, LAUNCH_WGRAD = {3.7, 1.079, 0.105};
 long tiles_of(const TileCost &t, const GemmArgs *gs, int n) {
@@ -223,7 +225,7 @@ int choose_tile(const TileCost (&table)[N], const LaunchCost &cost, const GemmAr
         for (const TileCost &t : table) {
             if ((t.shape == TILE_160x128 || t.shape == TILE_96x128) != between) continue;
             const long tiles = tiles_of(t, gs, n);
-            if (between && from_hbm && tiles % n_cu && tiles < MIN_MORE_BETWEEN * older_tiles) continue;
+            if (between && from_hbm && tiles % n_cu && tiles < (gs[0].M < 1024 ? MIN_MORE_FEW_ROWS : MIN_MORE_BETWEEN) * older_tiles) continue;
             const double us = tiles_us(t, cost, tiles, gs[0].K, n_cu);
             // a smaller tile moves more bytes per product: only for a gain beyond the fit's error, and beyond what they cost more from HBM
             // (operands of more than 96 MB: 1397 x 28672 x 5120 takes 336 us in 256 x 256 and 379 in 160 x 256, which the model puts 4 % ahead)
